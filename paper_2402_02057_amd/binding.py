@@ -1,10 +1,16 @@
-"""Thin ctypes binding of the C-ABI HIP library (include/la.h): argument marshalling only.
+"""Thin binding of the C-ABI HIP library (include/la.h): argument marshalling only.
 
 Every step of the hot path runs in the library's kernels.  There is no fallback: if the
 library has not been built (python -m paper_2402_02057_amd.buildlib, or
 __graft_entry__.build()) loading fails loudly.
+
+The calls of a decoding step are marshalled by an extension module (csrc/la_binding.cpp): an entry
+point is called once per layer and step, and checking its tensors in Python took longer than the
+shorter launches take on the GPU.  The functions below document the arguments and hand them on;
+queries and testing hooks, and whoever wants the C functions themselves (load()), go through ctypes.
 """
 import ctypes
+import importlib
 import os
 
 import torch
@@ -16,6 +22,8 @@ LA_OK = 0
 LA_EINVAL, LA_EUNSUPPORTED, LA_ENOMEM, LA_EHIP = -1, -2, -3, -4
 _lib = None
 
+
+# (the C structures below are for callers of load())
 
 class StepDesc(ctypes.Structure):
     """la_step_desc of include/la.h."""
@@ -127,6 +135,25 @@ def load():
     return lib
 
 
+class _Native:
+    """The extension module, opened on the first call into it."""
+
+    def __getattr__(self, name):
+        load()
+        try:
+            module = importlib.import_module("._la_native", __package__)
+        except ImportError as e:
+            raise RuntimeError("the extension module _la_native is not built or does not load (%s); run "
+                               "__graft_entry__.build()" % e) from e
+        module.set_error_class(LaError)
+        for key in dir(module):
+            setattr(self, key, getattr(module, key))
+        return getattr(module, name)
+
+
+_native = _Native()
+
+
 EXPORTS = ("la_step_rope", "la_step_attention", "la_step_attention_noalloc", "la_step_attention_fp8kv", "la_step_attention_rope", "la_step_attention_cap", "la_kv_commit", "la_kv_commit_rope", "la_step_attention_paged", "la_kv_commit_paged", "la_kv_commit_batch", "la_step_attention_rows", "la_step_attention_batch", "la_step_attention_batch_paged", "la_verify", "la_verify_step", "la_verify_step_batch", "la_verify_sample", "la_verify_sample_batch", "la_step_attention_workspace_bytes", "la_step_attention_kernel", "la_shutdown", "la_select_workspace", "la_debug_override", "la_probe_stream_read", "la_probe_mfma",
            "la_last_error", "la_version")
 
@@ -134,25 +161,6 @@ EXPORTS = ("la_step_rope", "la_step_attention", "la_step_attention_noalloc", "la
 def _check(rc):
     if rc != LA_OK:
         raise LaError(rc, load().la_last_error().decode())
-
-
-def _ptr(x, dtype, shape, name, allow_empty_null=False):
-    """Device pointer of a contiguous CUDA tensor of the expected dtype and shape."""
-    if x is None:
-        if allow_empty_null:
-            return None
-        raise ValueError("%s is None" % name)
-    if not isinstance(x, torch.Tensor):
-        raise TypeError("%s must be a torch.Tensor" % name)
-    if not x.is_cuda:
-        raise ValueError("%s must live on the GPU" % name)
-    if x.dtype != dtype:
-        raise ValueError("%s must be %s, got %s" % (name, dtype, x.dtype))
-    if tuple(x.shape) != tuple(shape):
-        raise ValueError("%s must have shape %s, got %s" % (name, tuple(shape), tuple(x.shape)))
-    if not x.is_contiguous():
-        raise ValueError("%s must be contiguous" % name)
-    return x.data_ptr() if x.numel() else None
 
 
 def _stream(stream):
@@ -166,34 +174,15 @@ def _stream(stream):
 def la_step_attention(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim,
                       out, stream=None):
     """out[T, heads, head_dim] (bf16) <- lookahead-step attention; asynchronous on `stream`."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    rc = load().la_step_attention(
-        _ptr(q, bf, (T, heads, head_dim), "q"),
-        _ptr(k_cache, bf, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True),
-        _ptr(v_cache, bf, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True),
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out, stream)
     return out
 
 
 def la_step_attention_noalloc(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim,
                               out, stream=None):
     """la_step_attention through the entry point that allocates nothing (fixed scratch block)."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    rc = load().la_step_attention_noalloc(
-        _ptr(q, bf, (T, heads, head_dim), "q"),
-        _ptr(k_cache, bf, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True),
-        _ptr(v_cache, bf, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True),
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_noalloc(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out,
+                                   stream)
     return out
 
 
@@ -201,19 +190,8 @@ def la_step_attention_fp8kv(q, k_cache, v_cache, step_k, step_v, k_scale, v_scal
                             head_dim, out, stream=None):
     """The step over a cache of 8-bit floats (uint8 codes, cache and step rows) with one fp32 scale per
     KV head for the keys and one for the values; q and out are bf16.  Asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf, u8 = torch.bfloat16, torch.uint8
-    rc = load().la_step_attention_fp8kv(
-        _ptr(q, bf, (T, heads, head_dim), "q"),
-        _ptr(k_cache, u8, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True),
-        _ptr(v_cache, u8, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True),
-        _ptr(step_k, u8, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, u8, (T, kv_heads, head_dim), "step_v"),
-        _ptr(k_scale, torch.float32, (kv_heads,), "k_scale"),
-        _ptr(v_scale, torch.float32, (kv_heads,), "v_scale"),
-        P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_fp8kv(q, k_cache, v_cache, step_k, step_v, k_scale, v_scale, P, W, N, G, heads, kv_heads,
+                                 head_dim, out, stream)
     return out
 
 
@@ -221,33 +199,14 @@ def la_step_attention_cap(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads
                           stream=None):
     """la_step_attention over caches [kv_heads, capacity, head_dim] whose first P rows per head are
     the prefix (capacity is read from the tensors); asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    capacity = int(k_cache.shape[1])
-    rc = load().la_step_attention_cap(
-        _ptr(q, bf, (T, heads, head_dim), "q"),
-        _ptr(k_cache, bf, (kv_heads, capacity, head_dim), "k_cache"),
-        _ptr(v_cache, bf, (kv_heads, capacity, head_dim), "v_cache"), capacity,
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_cap(q, k_cache, v_cache, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out, stream)
     return out
 
 
 def la_step_rope(q, step_k, cos, sin, P, W, N, G, heads, kv_heads, head_dim, interleaved=False, stream=None):
     """Rotate q [T, heads, d] and step_k [T, kv_heads, d] (bf16, in place) by the step's positions with
     the fp32 tables cos, sin [max_pos, d/2]; asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    max_pos = int(cos.shape[0])
-    rc = load().la_step_rope(
-        _ptr(q, torch.bfloat16, (T, heads, head_dim), "q", allow_empty_null=True),   # None: the keys alone
-        _ptr(step_k, torch.bfloat16, (T, kv_heads, head_dim), "step_k"),
-        _ptr(cos, torch.float32, (max_pos, head_dim // 2), "cos"),
-        _ptr(sin, torch.float32, (max_pos, head_dim // 2), "sin"),
-        max_pos, P, W, N, G, heads, kv_heads, head_dim, 1 if interleaved else 0, _stream(stream))
-    _check(rc)
+    _native.step_rope(q, step_k, cos, sin, P, W, N, G, heads, kv_heads, head_dim, interleaved, stream)
 
 
 def la_step_attention_rope(q, k_cache, v_cache, step_k, step_v, cos, sin, P, W, N, G, heads, kv_heads, head_dim, out,
@@ -256,204 +215,71 @@ def la_step_attention_rope(q, k_cache, v_cache, step_k, step_v, cos, sin, P, W, 
     step_k must be rotated already, e.g. by la_step_rope(None, step_k, ...); True: step_k comes
     unrotated too and the kernel turns the step keys it stages (append with la_kv_commit_rope then);
     asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    max_pos = int(cos.shape[0])
-    rc = load().la_step_attention_rope(
-        _ptr(q, bf, (T, heads, head_dim), "q"),
-        _ptr(k_cache, bf, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True),
-        _ptr(v_cache, bf, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True),
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        _ptr(cos, torch.float32, (max_pos, head_dim // 2), "cos"),
-        _ptr(sin, torch.float32, (max_pos, head_dim // 2), "sin"),
-        max_pos, 1 if interleaved else 0, 1 if rotate_keys else 0, P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_rope(q, k_cache, v_cache, step_k, step_v, cos, sin, P, W, N, G, heads, kv_heads, head_dim,
+                                out, interleaved, rotate_keys, stream)
     return out
 
 
 def la_kv_commit(k_cache, v_cache, step_k, step_v, P, W, N, G, kv_heads, head_dim, best, n_out, stream=None):
     """Append the rows of the tokens la_verify_step accepted (device-side best, n_out) to the caches
     [kv_heads, capacity, head_dim] at row P; asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    capacity = int(k_cache.shape[1])
-    rc = load().la_kv_commit(
-        _ptr(k_cache, bf, (kv_heads, capacity, head_dim), "k_cache"),
-        _ptr(v_cache, bf, (kv_heads, capacity, head_dim), "v_cache"), capacity,
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, kv_heads, head_dim,
-        _ptr(best, torch.int32, (1,), "best"), _ptr(n_out, torch.int32, (1,), "n_out"), _stream(stream))
-    _check(rc)
+    _native.kv_commit(k_cache, v_cache, step_k, step_v, P, W, N, G, kv_heads, head_dim, best, n_out, stream)
 
 
 def la_kv_commit_rope(k_cache, v_cache, step_k, step_v, cos, sin, P, W, N, G, kv_heads, head_dim, best, n_out,
                       interleaved=False, stream=None):
     """la_kv_commit for unrotated step keys: the appended key rows are turned by their cache positions
     (tables as for la_step_rope); asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    capacity = int(k_cache.shape[1])
-    max_pos = int(cos.shape[0])
-    rc = load().la_kv_commit_rope(
-        _ptr(k_cache, bf, (kv_heads, capacity, head_dim), "k_cache"),
-        _ptr(v_cache, bf, (kv_heads, capacity, head_dim), "v_cache"), capacity,
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        _ptr(cos, torch.float32, (max_pos, head_dim // 2), "cos"),
-        _ptr(sin, torch.float32, (max_pos, head_dim // 2), "sin"),
-        max_pos, 1 if interleaved else 0, P, W, N, G, kv_heads, head_dim,
-        _ptr(best, torch.int32, (1,), "best"), _ptr(n_out, torch.int32, (1,), "n_out"), _stream(stream))
-    _check(rc)
+    _native.kv_commit_rope(k_cache, v_cache, step_k, step_v, cos, sin, P, W, N, G, kv_heads, head_dim, best, n_out,
+                           interleaved, stream)
 
 
 def la_step_attention_batch(seqs, W, N, G, heads, kv_heads, head_dim, stream=None):
     """Several steps in one launch.  `seqs` is a list of dicts with q, k_cache, v_cache, step_k,
     step_v, out (tensors as for la_step_attention) and P; asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    descs = (StepDesc * len(seqs))()
-    for d, x in zip(descs, seqs):
-        P = int(x["P"])
-        d.q = _ptr(x["q"], bf, (T, heads, head_dim), "q")
-        d.k_cache = _ptr(x["k_cache"], bf, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True)
-        d.v_cache = _ptr(x["v_cache"], bf, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True)
-        d.step_k = _ptr(x["step_k"], bf, (T, kv_heads, head_dim), "step_k")
-        d.step_v = _ptr(x["step_v"], bf, (T, kv_heads, head_dim), "step_v")
-        d.out = _ptr(x["out"], bf, (T, heads, head_dim), "out")
-        d.P, d.reserved = P, 0
-    _check(load().la_step_attention_batch(ctypes.cast(descs, ctypes.c_void_p), len(seqs), W, N, G, heads, kv_heads,
-                                          head_dim, _stream(stream)))
+    _native.step_attention_batch(seqs, W, N, G, heads, kv_heads, head_dim, stream)
 
 
 def la_step_attention_batch_paged(seqs, k_pages, v_pages, W, N, G, heads, kv_heads, head_dim, stream=None):
     """Several steps over one paged cache in one launch.  `seqs`: dicts with q, block_table (int32
     tensor, >= ceil(P / page_size) entries, or None if P == 0), step_k, step_v, out, P; asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    n_pages, page_size = int(k_pages.shape[0]), int(k_pages.shape[2])
-    shape = (n_pages, kv_heads, page_size, head_dim)
-    descs = (StepDescPaged * len(seqs))()
-    for d, x in zip(descs, seqs):
-        P = int(x["P"])
-        need = (P + page_size - 1) // page_size
-        bt = x.get("block_table")
-        if need > 0 and (bt is None or bt.numel() < need):
-            raise ValueError("block_table must hold at least %d entries" % need)
-        d.q = _ptr(x["q"], bf, (T, heads, head_dim), "q")
-        d.block_table = None if bt is None else _ptr(bt, torch.int32, (bt.numel(),), "block_table", allow_empty_null=True)
-        d.step_k = _ptr(x["step_k"], bf, (T, kv_heads, head_dim), "step_k")
-        d.step_v = _ptr(x["step_v"], bf, (T, kv_heads, head_dim), "step_v")
-        d.out = _ptr(x["out"], bf, (T, heads, head_dim), "out")
-        d.P, d.reserved = P, 0
-    _check(load().la_step_attention_batch_paged(ctypes.cast(descs, ctypes.c_void_p), len(seqs),
-                                                _ptr(k_pages, bf, shape, "k_pages"), _ptr(v_pages, bf, shape, "v_pages"),
-                                                page_size, n_pages, W, N, G, heads, kv_heads, head_dim, _stream(stream)))
+    _native.step_attention_batch_paged(seqs, k_pages, v_pages, W, N, G, heads, kv_heads, head_dim, stream)
 
 
 def la_step_attention_rows(q, k_cache, v_cache, step_k, step_v, row_ids, P, W, N, G, heads, kv_heads, head_dim, out,
                            stream=None):
     """la_step_attention over the rows `row_ids` (int32 tensor) of the (W, N, G) layout: a device's
     share under lookahead parallelism; asynchronous."""
-    n = int(row_ids.numel())
-    bf = torch.bfloat16
-    rc = load().la_step_attention_rows(
-        _ptr(q, bf, (n, heads, head_dim), "q"),
-        _ptr(k_cache, bf, (kv_heads, P, head_dim), "k_cache", allow_empty_null=True),
-        _ptr(v_cache, bf, (kv_heads, P, head_dim), "v_cache", allow_empty_null=True),
-        _ptr(step_k, bf, (n, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (n, kv_heads, head_dim), "step_v"),
-        _ptr(row_ids, torch.int32, (n,), "row_ids"), n, P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (n, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_rows(q, k_cache, v_cache, step_k, step_v, row_ids, P, W, N, G, heads, kv_heads, head_dim, out,
+                                stream)
     return out
-
-
-def _pages(k_pages, v_pages, block_table, kv_heads, head_dim, rows):
-    n_pages, page_size = int(k_pages.shape[0]), int(k_pages.shape[2])
-    shape = (n_pages, kv_heads, page_size, head_dim)
-    need = (rows + page_size - 1) // page_size
-    if need > 0 and (block_table is None or block_table.numel() < need):
-        raise ValueError("block_table must hold at least %d entries" % need)
-    bt = None if block_table is None else _ptr(block_table, torch.int32, (block_table.numel(),), "block_table",
-                                               allow_empty_null=True)
-    return (_ptr(k_pages, torch.bfloat16, shape, "k_pages"), _ptr(v_pages, torch.bfloat16, shape, "v_pages"), bt,
-            page_size, n_pages)
 
 
 def la_step_attention_paged(q, k_pages, v_pages, block_table, step_k, step_v, P, W, N, G, heads, kv_heads,
                             head_dim, out, stream=None):
     """la_step_attention over pages [n_pages, kv_heads, page_size, head_dim] named by the int32
     block_table (>= ceil(P / page_size) entries); asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    kp, vp, bt, page_size, n_pages = _pages(k_pages, v_pages, block_table, kv_heads, head_dim, P)
-    rc = load().la_step_attention_paged(
-        _ptr(q, bf, (T, heads, head_dim), "q"), kp, vp, bt, page_size, n_pages,
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, heads, kv_heads, head_dim,
-        _ptr(out, bf, (T, heads, head_dim), "out"), _stream(stream))
-    _check(rc)
+    _native.step_attention_paged(q, k_pages, v_pages, block_table, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim,
+                                 out, stream)
     return out
 
 
 def la_kv_commit_paged(k_pages, v_pages, block_table, step_k, step_v, P, W, N, G, kv_heads, head_dim, best,
                        n_out, stream=None):
     """la_kv_commit into pages; block_table needs >= ceil((P + N) / page_size) entries; asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    kp, vp, bt, page_size, n_pages = _pages(k_pages, v_pages, block_table, kv_heads, head_dim, P + N)
-    rc = load().la_kv_commit_paged(
-        kp, vp, bt, page_size, n_pages,
-        _ptr(step_k, bf, (T, kv_heads, head_dim), "step_k"),
-        _ptr(step_v, bf, (T, kv_heads, head_dim), "step_v"),
-        P, W, N, G, kv_heads, head_dim,
-        _ptr(best, torch.int32, (1,), "best"), _ptr(n_out, torch.int32, (1,), "n_out"), _stream(stream))
-    _check(rc)
+    _native.kv_commit_paged(k_pages, v_pages, block_table, step_k, step_v, P, W, N, G, kv_heads, head_dim, best, n_out, stream)
 
 
 def la_kv_commit_batch(appends, W, N, G, kv_heads, head_dim, stream=None):
     """Several appends in one launch.  `appends`: dicts with k_cache, v_cache, step_k, step_v, best,
     n_out, P and, for a paged cache, block_table (then k_cache / v_cache are the page pools
     [n_pages, kv_heads, page_size, head_dim], the same geometry in all of them); asynchronous."""
-    T = 1 + (W + G) * (N - 1)
-    bf = torch.bfloat16
-    descs = (CommitDesc * len(appends))()
-    page_size = n_pages = 0
-    for d, x in zip(descs, appends):
-        P = int(x["P"])
-        bt = x.get("block_table")
-        if bt is not None:
-            kp, vp, btp, ps, npg = _pages(x["k_cache"], x["v_cache"], bt, kv_heads, head_dim, P + N)
-            if page_size and (ps, npg) != (page_size, n_pages):
-                raise ValueError("all page pools of a launch must have the same geometry")
-            page_size, n_pages = ps, npg
-            d.k_cache, d.v_cache, d.block_table, d.capacity = kp, vp, btp, 0
-        else:
-            cap = int(x["k_cache"].shape[1])
-            d.k_cache = _ptr(x["k_cache"], bf, (kv_heads, cap, head_dim), "k_cache")
-            d.v_cache = _ptr(x["v_cache"], bf, (kv_heads, cap, head_dim), "v_cache")
-            d.block_table, d.capacity = None, cap
-        d.step_k = _ptr(x["step_k"], bf, (T, kv_heads, head_dim), "step_k")
-        d.step_v = _ptr(x["step_v"], bf, (T, kv_heads, head_dim), "step_v")
-        d.best = _ptr(x["best"], torch.int32, (1,), "best")
-        d.n_out = _ptr(x["n_out"], torch.int32, (1,), "n_out")
-        d.P, d.reserved = P, 0
-    _check(load().la_kv_commit_batch(ctypes.cast(descs, ctypes.c_void_p), len(appends), page_size, n_pages, W, N, G,
-                                     kv_heads, head_dim, _stream(stream)))
+    _native.kv_commit_batch(appends, W, N, G, kv_heads, head_dim, stream)
 
 
 def la_verify(logits, cand_tokens, G, N, V, accept_len, accepted, stream=None):
     """accept_len[G], accepted[G, N-1] (int32) <- greedy verification; asynchronous."""
-    rc = load().la_verify(
-        _ptr(logits, torch.float32, (G, N - 1, V), "logits"),
-        _ptr(cand_tokens, torch.int32, (G, N - 1), "cand_tokens"), G, N, V,
-        _ptr(accept_len, torch.int32, (G,), "accept_len"),
-        _ptr(accepted, torch.int32, (G, N - 1), "accepted"), _stream(stream))
-    _check(rc)
+    _native.verify(logits, cand_tokens, G, N, V, accept_len, accepted, stream)
     return accept_len, accepted
 
 
@@ -462,16 +288,8 @@ def la_verify_step(logits_cur, logits_look, logits_cand, cand_tokens, W, N, G, V
     """out_tokens[N], n_out[1], best[1], new_window[W], accept_len[G] (int32) <- the end of a greedy
     step (accepted tokens of the best candidate plus correction or bonus token; new window tokens);
     asynchronous."""
-    rc = load().la_verify_step(
-        _ptr(logits_cur, torch.float32, (V,), "logits_cur"),
-        _ptr(logits_look, torch.float32, (W, V), "logits_look", allow_empty_null=True),
-        _ptr(logits_cand, torch.float32, (G, N - 1, V), "logits_cand", allow_empty_null=True),
-        _ptr(cand_tokens, torch.int32, (G, N - 1), "cand_tokens", allow_empty_null=True), W, N, G, V,
-        _ptr(out_tokens, torch.int32, (N,), "out_tokens"), _ptr(n_out, torch.int32, (1,), "n_out"),
-        _ptr(best, torch.int32, (1,), "best"),
-        _ptr(new_window, torch.int32, (W,), "new_window", allow_empty_null=True),
-        _ptr(accept_len, torch.int32, (G,), "accept_len", allow_empty_null=True), _stream(stream))
-    _check(rc)
+    _native.verify_step(logits_cur, logits_look, logits_cand, cand_tokens, W, N, G, V, out_tokens, n_out, best, new_window,
+                        accept_len, stream)
     return out_tokens, n_out, best, new_window, accept_len
 
 
@@ -479,33 +297,14 @@ def la_verify_step_batch(seqs, W, N, G, V, stream=None):
     """The ends of several sequences' steps in one launch.  `seqs`: dicts with logits_cur, logits_look,
     logits_cand, cand_tokens, out_tokens, n_out, best, new_window and optionally accept_len (tensors
     as for la_verify_step); asynchronous."""
-    descs = (VerifyDesc * len(seqs))()
-    f, i32 = torch.float32, torch.int32
-    for d, x in zip(descs, seqs):
-        d.logits_cur = _ptr(x["logits_cur"], f, (V,), "logits_cur")
-        d.logits_look = _ptr(x.get("logits_look"), f, (W, V), "logits_look", allow_empty_null=True)
-        d.logits_cand = _ptr(x.get("logits_cand"), f, (G, N - 1, V), "logits_cand", allow_empty_null=True)
-        d.cand_tokens = _ptr(x.get("cand_tokens"), i32, (G, N - 1), "cand_tokens", allow_empty_null=True)
-        d.out_tokens = _ptr(x["out_tokens"], i32, (N,), "out_tokens")
-        d.n_out = _ptr(x["n_out"], i32, (1,), "n_out")
-        d.best = _ptr(x["best"], i32, (1,), "best")
-        d.new_window = _ptr(x.get("new_window"), i32, (W,), "new_window", allow_empty_null=True)
-        d.accept_len = _ptr(x.get("accept_len"), i32, (G,), "accept_len", allow_empty_null=True)
-    _check(load().la_verify_step_batch(ctypes.cast(descs, ctypes.c_void_p), len(seqs), W, N, G, V, _stream(stream)))
+    _native.verify_step_batch(seqs, W, N, G, V, stream)
 
 
 def la_verify_sample(logits_cur, logits_cand, cand_tokens, u_test, u_final, temperature, N, G, V, out_tokens,
                      n_out, stream=None):
     """out_tokens[N], n_out[1] (int32) <- sampling verification (Algorithm 4); asynchronous."""
-    rc = load().la_verify_sample(
-        _ptr(logits_cur, torch.float32, (V,), "logits_cur"),
-        _ptr(logits_cand, torch.float32, (G, N - 1, V), "logits_cand", allow_empty_null=True),
-        _ptr(cand_tokens, torch.int32, (G, N - 1), "cand_tokens", allow_empty_null=True),
-        _ptr(u_test, torch.float32, (N - 1, G), "u_test", allow_empty_null=True),
-        _ptr(u_final, torch.float32, (1,), "u_final"), float(temperature), N, G, V,
-        _ptr(out_tokens, torch.int32, (N,), "out_tokens"), _ptr(n_out, torch.int32, (1,), "n_out"),
-        _stream(stream))
-    _check(rc)
+    _native.verify_sample(logits_cur, logits_cand, cand_tokens, u_test, u_final, temperature, N, G, V, out_tokens, n_out,
+                          stream)
     return out_tokens, n_out
 
 
@@ -513,18 +312,7 @@ def la_verify_sample_batch(seqs, N, G, V, stream=None):
     """Sampling verification of several sequences in one launch.  `seqs`: dicts with logits_cur,
     logits_cand, cand_tokens, u_test, u_final, temperature, out_tokens, n_out (tensors as for
     la_verify_sample); asynchronous."""
-    descs = (SampleDesc * len(seqs))()
-    f, i32 = torch.float32, torch.int32
-    for d, x in zip(descs, seqs):
-        d.logits_cur = _ptr(x["logits_cur"], f, (V,), "logits_cur")
-        d.logits_cand = _ptr(x.get("logits_cand"), f, (G, N - 1, V), "logits_cand", allow_empty_null=True)
-        d.cand_tokens = _ptr(x.get("cand_tokens"), i32, (G, N - 1), "cand_tokens", allow_empty_null=True)
-        d.u_test = _ptr(x.get("u_test"), f, (N - 1, G), "u_test", allow_empty_null=True)
-        d.u_final = _ptr(x["u_final"], f, (1,), "u_final")
-        d.out_tokens = _ptr(x["out_tokens"], i32, (N,), "out_tokens")
-        d.n_out = _ptr(x["n_out"], i32, (1,), "n_out")
-        d.temperature, d.reserved = float(x["temperature"]), 0
-    _check(load().la_verify_sample_batch(ctypes.cast(descs, ctypes.c_void_p), len(seqs), N, G, V, _stream(stream)))
+    _native.verify_sample_batch(seqs, N, G, V, stream)
 
 
 def la_step_attention_kernel(P, W, N, G, heads, kv_heads, head_dim):
