@@ -1563,6 +1563,74 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
 
 namespace {
 
+// How a batched launch is cut.  A workgroup has a compute unit to itself, the compute units of an
+// XCD (32) take its workgroups in slot order as they become free, and a workgroup costs its chunks
+// plus a part that does not depend on them (start, merge, writing the rows: 6 chunks' time in the
+// 128-row form, 8 in the 64-row one, and 1 or 3 more with partial results to exchange; from steps
+// of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends when the fullest compute
+// unit does, and that is evaluated: starting from uncut steps, the step with the longest ranges is cut
+// once more as long as the sum of all workgroups leaves room for a better end than the best one seen.
+// A rule on the number of workgroups alone (256 for steps of one length, 384 otherwise, which this
+// replaces) cuts steps whose workgroups then fill a second or third round with a few stragglers:
+// 32/8 heads, 16 prefixes of 466 to 1021 keys, 81 rows: 528 workgroups 49.6 us, 400 as chosen here
+// 42.3; 8 prefixes of 512 keys, 81 rows: 29.3 with every step cut in two, 18.5 uncut; 8 prefixes
+// of 1253 to 14559 keys, 121 rows: 178 with ranges of up to 69 chunks placed in the order of the
+// prefixes, 174 with fewer cuts placed longest range first.
+// cuts[i]: ranges of step i.  place[]: the steps in slot order, longest ranges first.
+constexpr int kXcdUnits = 32;           // compute units of an XCD
+constexpr int kPlanPlacements = 1536;   // bound on the host's work: placements evaluated per launch
+
+void plan_batch(const int* chunks, int n, int units, bool rows128, int* cuts, int* place)
+{
+    const int fixed = rows128 ? 6 : 8, exchange = rows128 ? 1 : 3;
+    int xs[kMaxBatch], budget = kPlanPlacements;
+    for (int i = 0; i < n; ++i) xs[i] = 1;
+    auto range = [&](int i) { return (chunks[i] + xs[i] - 1) / xs[i]; };
+    auto cost = [&](int i) { return range(i) + fixed + (xs[i] > 1 ? exchange : 0); };
+    auto on_xcd = [&](int i) { return (units * xs[i] + 7) / 8; };
+    long long best = -1;
+    for (;;) {
+        int ord[kMaxBatch], items = 0;
+        long long sum = 0;
+        for (int i = 0; i < n; ++i) {
+            int j = i;
+            for (; j > 0 && cost(ord[j - 1]) < cost(i); --j) ord[j] = ord[j - 1];
+            ord[j] = i;
+            items += on_xcd(i);
+            sum += (long long)on_xcd(i) * cost(i);
+        }
+        if (best >= 0 && (sum >= best * kXcdUnits || items > budget)) break;
+        budget -= items;
+        // the end of the fullest compute unit; loads[] is a heap with the emptiest on top
+        long long loads[kXcdUnits] = {0}, end = 0;
+        for (int k = 0; k < n && items <= kPlanPlacements; ++k) {
+            const int c = cost(ord[k]);
+            for (int m = on_xcd(ord[k]); m > 0; --m) {
+                const long long v = loads[0] + c;
+                int at = 0;
+                for (int ch = 1; ch < kXcdUnits; ch = 2 * at + 1) {
+                    if (ch + 1 < kXcdUnits && loads[ch + 1] < loads[ch]) ++ch;
+                    if (loads[ch] >= v) break;
+                    loads[at] = loads[ch];
+                    at = ch;
+                }
+                loads[at] = v;
+                if (v > end) end = v;
+            }
+        }
+        if (best < 0 || end < best) {
+            best = end;
+            for (int i = 0; i < n; ++i) { cuts[i] = xs[i]; place[i] = ord[i]; }
+        }
+        if (items > kPlanPlacements) break;  // dozens of rounds: the ends are even without cuts
+        int longest = -1;
+        for (int i = 0; i < n; ++i)
+            if (xs[i] < 64 && xs[i] + 1 <= chunks[i] / 2 && (longest < 0 || range(i) > range(longest))) longest = i;
+        if (longest < 0) break;
+        ++xs[longest];
+    }
+}
+
 template <int D, int RT, int KS, int NSTAGE, bool PAGED = false>
 la_status launch_batch_cfg(const BatchParams& bp, unsigned grid, hipStream_t stream)
 {
@@ -1609,12 +1677,10 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             if (st != LA_OK) return st;
             continue;
         }
-        // One decomposition (row tiles, key-split waves) for the whole launch; the key ranges are
-        // cut so that every workgroup gets about the same number of chunks, with enough
-        // workgroups for two rounds over the 256 compute units.
+        // One decomposition (row tiles, key-split waves) for the whole launch; how often each step's
+        // keys are cut, and the order of the steps, come from plan_batch.
         Plan pl[kMaxBatch];
         for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim);
-        long long work = 0;
         // 128-row workgroups (a chunk of K/V staged once for four row tiles: half the traffic into
         // LDS per flop) as soon as the batch fills three quarters of the GPU with them; otherwise
         // 64-row workgroups, twice as many.  (Measured: eight 7B-shaped steps 33 vs 40 us.)
@@ -1630,28 +1696,20 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         if (head_dim == 128 && ov.batch_rows == 2) { RT = 2; KS = 4; }
         const int rows_wg = RT * 32;
         const int n_row_blocks = (T * group + rows_wg - 1) / rows_wg;
-        for (int i = 0; i < n; ++i) work += (long long)kv_heads * n_row_blocks * pl[i].n_chunks;
-        // One round of workgroups when the steps are alike (a second round only waits for the
-        // first); half a round more when their lengths differ, to even out the ends (measured).
-        bool alike = true;
-        for (int i = 1; i < n; ++i) alike = alike && pl[i].n_chunks == pl[0].n_chunks;
-        const long long wgs = alike ? 256 : 384;
-        long long target = (work + wgs - 1) / wgs;   // chunks per workgroup
-        if (target < 4) target = 4;
+        int chunks[kMaxBatch], cuts[kMaxBatch], place[kMaxBatch];
+        for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
+        plan_batch(chunks, n, kv_heads * n_row_blocks, RT == 4, cuts, place);
         BatchParams bp;
         bp.slots.n = n;
         size_t partial_bytes = 0, ticket_count = 0;
         int slot = 0;
         for (int i = 0; i < n; ++i) {
-            const BatchSeq& d = seqs[order[first + i]];
-            Plan& q = pl[i];
+            const BatchSeq& d = seqs[order[first + place[i]]];
+            Plan& q = pl[place[i]];
             q.RT = RT; q.KS = KS; q.NS = 4; q.KC = 64; q.PRE = 0;
             q.n_row_blocks = n_row_blocks;
             q.partial_bytes_per_wg = partial_wg_bytes(head_dim, RT, KS);
-            int xs = (int)((q.n_chunks + target - 1) / target);
-            if (xs > q.n_chunks / 2) xs = q.n_chunks / 2;
-            if (xs > 64) xs = 64;
-            q.XS = xs < 1 ? 1 : xs;
+            q.XS = cuts[place[i]];
             const la_status st = build_params(bp.seq[i], ov, q, d.q, d.k_cache, d.v_cache, d.P,
                                               d.P > 0 ? d.block_table : nullptr, page_size, n_pages, nullptr, T,
                                               d.step_k, d.step_v, d.P, W, N, G, heads, kv_heads, head_dim, d.out);
@@ -1669,11 +1727,11 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             unsigned char* partials = (unsigned char*)scratch_workspace(partial_bytes, stream);
             if (!tickets || !partials) return last_failure();
             for (int i = 0; i < n; ++i) {
-                if (pl[i].XS <= 1) continue;
+                if (bp.seq[i].XS <= 1) continue;
                 bp.seq[i].tickets = tickets;
                 bp.seq[i].partials = partials;
                 tickets += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
-                partials += (size_t)bp.seq[i].total_wg * pl[i].partial_bytes_per_wg;
+                partials += (size_t)bp.seq[i].total_wg * partial_wg_bytes(head_dim, RT, KS);
             }
         }
         const unsigned grid = (unsigned)slot * 8u;
