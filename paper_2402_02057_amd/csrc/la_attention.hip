@@ -1565,9 +1565,9 @@ namespace {
 
 // How a batched launch is cut.  A workgroup has a compute unit to itself, the compute units of an
 // XCD (32) take its workgroups in slot order as they become free, and a workgroup costs its chunks
-// plus a part that does not depend on them (start, merge, writing the rows: 6 chunks' time in the
-// 128-row form, 8 in the 64-row one, and 1 or 3 more with partial results to exchange; from steps
-// of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends when the fullest compute
+// plus a part that does not depend on them (start, merge, writing the rows: 6 chunks' time of 1.22 us
+// in the 128-row form, 5 of 0.76 us in the 64-row one, and 1 or 2 more with partial results to
+// exchange; from steps of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends when the fullest compute
 // unit does, and that is evaluated: starting from uncut steps, the step with the longest ranges is cut
 // once more as long as the sum of all workgroups leaves room for a better end than the best one seen.
 // A rule on the number of workgroups alone (256 for steps of one length, 384 otherwise, which this
@@ -1576,13 +1576,22 @@ namespace {
 // 42.3; 8 prefixes of 512 keys, 81 rows: 29.3 with every step cut in two, 18.5 uncut; 8 prefixes
 // of 1253 to 14559 keys, 121 rows: 178 with ranges of up to 69 chunks placed in the order of the
 // prefixes, 174 with fewer cuts placed longest range first.
-// cuts[i]: ranges of step i.  place[]: the steps in slot order, longest ranges first.
+// The two forms are compared by the same measure, a chunk of the 128-row form counting 16 and one of
+// the 64-row form 11: it takes 0.76 us in one round but 0.84 in several, which pull twice the traffic
+// of the 128-row form through the L2s (the 16 prefixes above: 48.0 us with 64 rows, 42.3 with 128).
+// (A fixed line at 192 workgroups of 128 rows, which this replaces, took 64 rows
+// for 6 steps of 256 keys, 32/8 heads, 81 rows: 17.1 us against 13.3; 1024 keys 30.1 / 26.7;
+// 4 steps of 4096 keys: 53.9 / 47.7; and for 4 steps of 4096 keys, 32/32 heads, 121 rows: 74.9 /
+// 66.9.  Short steps that fill one round of 64-row workgroups stay there: 4 steps of 256 keys, 32/8
+// heads, 121 rows 10.0 us against 13.2.)
+// cuts[i]: ranges of step i.  place[]: the steps in slot order, longest ranges first.  Returns the
+// time at which the launch ends.
 constexpr int kXcdUnits = 32;           // compute units of an XCD
 constexpr int kPlanPlacements = 1536;   // bound on the host's work: placements evaluated per launch
 
-void plan_batch(const int* chunks, int n, int units, bool rows128, int* cuts, int* place)
+long long plan_batch(const int* chunks, int n, int units, bool rows128, int* cuts, int* place)
 {
-    const int fixed = rows128 ? 6 : 8, exchange = rows128 ? 1 : 3;
+    const int fixed = rows128 ? 6 : 5, exchange = rows128 ? 1 : 2;
     int xs[kMaxBatch], budget = kPlanPlacements;
     for (int i = 0; i < n; ++i) xs[i] = 1;
     auto range = [&](int i) { return (chunks[i] + xs[i] - 1) / xs[i]; };
@@ -1622,13 +1631,17 @@ void plan_batch(const int* chunks, int n, int units, bool rows128, int* cuts, in
             best = end;
             for (int i = 0; i < n; ++i) { cuts[i] = xs[i]; place[i] = ord[i]; }
         }
-        if (items > kPlanPlacements) break;  // dozens of rounds: the ends are even without cuts
+        if (items > kPlanPlacements) {  // dozens of rounds: the ends are even without cuts
+            best = (sum + kXcdUnits - 1) / kXcdUnits;
+            break;
+        }
         int longest = -1;
         for (int i = 0; i < n; ++i)
             if (xs[i] < 64 && xs[i] + 1 <= chunks[i] / 2 && (longest < 0 || range(i) > range(longest))) longest = i;
         if (longest < 0) break;
         ++xs[longest];
     }
+    return best * (rows128 ? 16 : 11);
 }
 
 template <int D, int RT, int KS, int NSTAGE, bool PAGED = false>
@@ -1681,24 +1694,24 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         // keys are cut, and the order of the steps, come from plan_batch.
         Plan pl[kMaxBatch];
         for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim);
-        // 128-row workgroups (a chunk of K/V staged once for four row tiles: half the traffic into
-        // LDS per flop) as soon as the batch fills three quarters of the GPU with them; otherwise
-        // 64-row workgroups, twice as many.  (Measured: eight 7B-shaped steps 33 vs 40 us.)
-        int RT = 2, KS = 4;
-        if (head_dim == 128) {
-            const int tiles = (T * group + 31) / 32;
-            const long long units128 = (long long)n * kv_heads * ((tiles + 3) / 4);
-            if (tiles >= 3 && units128 >= 192) { RT = 4; KS = 2; }
-        } else {
-            KS = 2;
-        }
-        if (head_dim == 128 && ov.batch_rows == 4) { RT = 4; KS = 2; }  // testing hook
-        if (head_dim == 128 && ov.batch_rows == 2) { RT = 2; KS = 4; }
-        const int rows_wg = RT * 32;
-        const int n_row_blocks = (T * group + rows_wg - 1) / rows_wg;
         int chunks[kMaxBatch], cuts[kMaxBatch], place[kMaxBatch];
         for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
-        plan_batch(chunks, n, kv_heads * n_row_blocks, RT == 4, cuts, place);
+        // 128-row workgroups stage a chunk of K/V once for four row tiles (half the traffic into LDS
+        // per flop), 64-row workgroups are twice as many: whichever ends first (plan_batch)
+        const int tiles = (T * group + 31) / 32;
+        int RT = 2, KS = head_dim == 128 ? 4 : 2;
+        const long long end64 = plan_batch(chunks, n, kv_heads * ((tiles + 1) / 2), false, cuts, place);
+        if (head_dim == 128 && ((tiles >= 3 && ov.batch_rows != 2) || ov.batch_rows == 4)) {
+            int cuts128[kMaxBatch], place128[kMaxBatch];
+            const long long end128 = plan_batch(chunks, n, kv_heads * ((tiles + 3) / 4), true, cuts128, place128);
+            if (end128 < end64 || ov.batch_rows == 4) {  // (the second: testing hook)
+                RT = 4;
+                KS = 2;
+                for (int i = 0; i < n; ++i) { cuts[i] = cuts128[i]; place[i] = place128[i]; }
+            }
+        }
+        const int rows_wg = RT * 32;
+        const int n_row_blocks = (T * group + rows_wg - 1) / rows_wg;
         BatchParams bp;
         bp.slots.n = n;
         size_t partial_bytes = 0, ticket_count = 0;
