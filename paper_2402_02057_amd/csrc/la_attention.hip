@@ -1567,9 +1567,10 @@ namespace {
 // XCD (32) take its workgroups in slot order as they become free, and a workgroup costs its chunks
 // plus a part that does not depend on them (start, merge, writing the rows: 6 chunks' time of 1.22 us
 // in the 128-row form, 5 of 0.76 us in the 64-row one, and 1 or 2 more with partial results to
-// exchange; from steps of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends when the fullest compute
-// unit does, and that is evaluated: starting from uncut steps, the step with the longest ranges is cut
-// once more as long as the sum of all workgroups leaves room for a better end than the best one seen.
+// exchange; from steps of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends
+// when the fullest compute unit does, and that is evaluated: starting from uncut steps, the step
+// with the longest ranges is cut once more as long as the sum of all workgroups leaves room for a
+// better end than the best one seen.
 // A rule on the number of workgroups alone (256 for steps of one length, 384 otherwise, which this
 // replaces) cuts steps whose workgroups then fill a second or third round with a few stragglers:
 // 32/8 heads, 16 prefixes of 466 to 1021 keys, 81 rows: 528 workgroups 49.6 us, 400 as chosen here
@@ -1581,7 +1582,7 @@ namespace {
 // of the 128-row form through the L2s (the 16 prefixes above: 48.0 us with 64 rows, 42.3 with 128).
 // (A fixed line at 192 workgroups of 128 rows, which this replaces, took 64 rows
 // for 6 steps of 256 keys, 32/8 heads, 81 rows: 17.1 us against 13.3; 1024 keys 30.1 / 26.7;
-// 4 steps of 4096 keys: 53.9 / 47.7; and for 4 steps of 4096 keys, 32/32 heads, 121 rows: 74.9 /
+// 4 steps of 4096 keys: 53.9 / 49.5; and for 4 steps of 4096 keys, 32/32 heads, 121 rows: 74.9 /
 // 66.9.  Short steps that fill one round of 64-row workgroups stay there: 4 steps of 256 keys, 32/8
 // heads, 121 rows 10.0 us against 13.2.)
 // cuts[i]: ranges of step i.  place[]: the steps in slot order, longest ranges first.  Returns the
