@@ -54,6 +54,7 @@
 
 #include "la_internal.h"
 #include "la_attention_common.h"
+#include "la_batch_plan.h"
 #include "la_rope_common.h"
 
 #ifdef LA_DEV_HOOKS
@@ -1099,7 +1100,6 @@ __global__ __launch_bounds__(RT* KS * 64) void step_attention_kernel(const AttnP
 // Several independent steps (sequences) in one launch: on every XCD, step i owns the slots
 // slot0[i] .. slot0[i+1]-1.  Workgroups are handed out in id order, so the steps start in the
 // order given (longest first) and the tail of one overlaps the head of the next.
-constexpr int kMaxBatch = 16;
 struct BatchSlots {
     int slot0[kMaxBatch + 1];
     int n;
@@ -1563,88 +1563,6 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
 
 namespace {
 
-// How a batched launch is cut.  A workgroup has a compute unit to itself, the compute units of an
-// XCD (32) take its workgroups in slot order as they become free, and a workgroup costs its chunks
-// plus a part that does not depend on them (start, merge, writing the rows: 6 chunks' time of 1.22 us
-// in the 128-row form, 5 of 0.76 us in the 64-row one, and 1 or 2 more with partial results to
-// exchange; from steps of 4 to 66 chunks, one and two rounds, cut and uncut).  So the launch ends
-// when the fullest compute unit does, and that is evaluated: starting from uncut steps, the step
-// with the longest ranges is cut once more as long as the sum of all workgroups leaves room for a
-// better end than the best one seen.
-// A rule on the number of workgroups alone (256 for steps of one length, 384 otherwise, which this
-// replaces) cuts steps whose workgroups then fill a second or third round with a few stragglers:
-// 32/8 heads, 16 prefixes of 466 to 1021 keys, 81 rows: 528 workgroups 49.6 us, 400 as chosen here
-// 42.3; 8 prefixes of 512 keys, 81 rows: 29.3 with every step cut in two, 18.5 uncut; 8 prefixes
-// of 1253 to 14559 keys, 121 rows: 178 with ranges of up to 69 chunks placed in the order of the
-// prefixes, 174 with fewer cuts placed longest range first.
-// The two forms are compared by the same measure, a chunk of the 128-row form counting 16 and one of
-// the 64-row form 11: it takes 0.76 us in one round but 0.84 in several, which pull twice the traffic
-// of the 128-row form through the L2s (the 16 prefixes above: 48.0 us with 64 rows, 42.3 with 128).
-// (A fixed line at 192 workgroups of 128 rows, which this replaces, took 64 rows
-// for 6 steps of 256 keys, 32/8 heads, 81 rows: 17.1 us against 13.3; 1024 keys 30.1 / 26.7;
-// 4 steps of 4096 keys: 53.9 / 49.5; and for 4 steps of 4096 keys, 32/32 heads, 121 rows: 74.9 /
-// 66.9.  Short steps that fill one round of 64-row workgroups stay there: 4 steps of 256 keys, 32/8
-// heads, 121 rows 10.0 us against 13.2.)
-// cuts[i]: ranges of step i.  place[]: the steps in slot order, longest ranges first.  Returns the
-// time at which the launch ends.
-constexpr int kXcdUnits = 32;           // compute units of an XCD
-constexpr int kPlanPlacements = 1536;   // bound on the host's work: placements evaluated per launch
-
-long long plan_batch(const int* chunks, int n, int units, bool rows128, int* cuts, int* place)
-{
-    const int fixed = rows128 ? 6 : 5, exchange = rows128 ? 1 : 2;
-    int xs[kMaxBatch], budget = kPlanPlacements;
-    for (int i = 0; i < n; ++i) xs[i] = 1;
-    auto range = [&](int i) { return (chunks[i] + xs[i] - 1) / xs[i]; };
-    auto cost = [&](int i) { return range(i) + fixed + (xs[i] > 1 ? exchange : 0); };
-    auto on_xcd = [&](int i) { return (units * xs[i] + 7) / 8; };
-    long long best = -1;
-    for (;;) {
-        int ord[kMaxBatch], items = 0;
-        long long sum = 0;
-        for (int i = 0; i < n; ++i) {
-            int j = i;
-            for (; j > 0 && cost(ord[j - 1]) < cost(i); --j) ord[j] = ord[j - 1];
-            ord[j] = i;
-            items += on_xcd(i);
-            sum += (long long)on_xcd(i) * cost(i);
-        }
-        if (best >= 0 && (sum >= best * kXcdUnits || items > budget)) break;
-        budget -= items;
-        // the end of the fullest compute unit; loads[] is a heap with the emptiest on top
-        long long loads[kXcdUnits] = {0}, end = 0;
-        for (int k = 0; k < n && items <= kPlanPlacements; ++k) {
-            const int c = cost(ord[k]);
-            for (int m = on_xcd(ord[k]); m > 0; --m) {
-                const long long v = loads[0] + c;
-                int at = 0;
-                for (int ch = 1; ch < kXcdUnits; ch = 2 * at + 1) {
-                    if (ch + 1 < kXcdUnits && loads[ch + 1] < loads[ch]) ++ch;
-                    if (loads[ch] >= v) break;
-                    loads[at] = loads[ch];
-                    at = ch;
-                }
-                loads[at] = v;
-                if (v > end) end = v;
-            }
-        }
-        if (best < 0 || end < best) {
-            best = end;
-            for (int i = 0; i < n; ++i) { cuts[i] = xs[i]; place[i] = ord[i]; }
-        }
-        if (items > kPlanPlacements) {  // dozens of rounds: the ends are even without cuts
-            best = (sum + kXcdUnits - 1) / kXcdUnits;
-            break;
-        }
-        int longest = -1;
-        for (int i = 0; i < n; ++i)
-            if (xs[i] < 64 && xs[i] + 1 <= chunks[i] / 2 && (longest < 0 || range(i) > range(longest))) longest = i;
-        if (longest < 0) break;
-        ++xs[longest];
-    }
-    return best * (rows128 ? 16 : 11);
-}
-
 template <int D, int RT, int KS, int NSTAGE, bool PAGED = false>
 la_status launch_batch_cfg(const BatchParams& bp, unsigned grid, hipStream_t stream)
 {
@@ -1695,22 +1613,10 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         // keys are cut, and the order of the steps, come from plan_batch.
         Plan pl[kMaxBatch];
         for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim);
-        int chunks[kMaxBatch], cuts[kMaxBatch], place[kMaxBatch];
+        int chunks[kMaxBatch];
         for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
-        // 128-row workgroups stage a chunk of K/V once for four row tiles (half the traffic into LDS
-        // per flop), 64-row workgroups are twice as many: whichever ends first (plan_batch)
-        const int tiles = (T * group + 31) / 32;
-        int RT = 2, KS = head_dim == 128 ? 4 : 2;
-        const long long end64 = plan_batch(chunks, n, kv_heads * ((tiles + 1) / 2), false, cuts, place);
-        if (head_dim == 128 && ((tiles >= 3 && ov.batch_rows != 2) || ov.batch_rows == 4)) {
-            int cuts128[kMaxBatch], place128[kMaxBatch];
-            const long long end128 = plan_batch(chunks, n, kv_heads * ((tiles + 3) / 4), true, cuts128, place128);
-            if (end128 < end64 || ov.batch_rows == 4) {  // (the second: testing hook)
-                RT = 4;
-                KS = 2;
-                for (int i = 0; i < n; ++i) { cuts[i] = cuts128[i]; place[i] = place128[i]; }
-            }
-        }
+        const BatchPlan plan = plan_batch(chunks, n, (T * group + 31) / 32, kv_heads, head_dim, ov.batch_rows * 32);
+        const int RT = plan.rows128 ? 4 : 2, KS = plan.rows128 || head_dim != 128 ? 2 : 4;
         const int rows_wg = RT * 32;
         const int n_row_blocks = (T * group + rows_wg - 1) / rows_wg;
         BatchParams bp;
@@ -1718,12 +1624,12 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         size_t partial_bytes = 0, ticket_count = 0;
         int slot = 0;
         for (int i = 0; i < n; ++i) {
-            const BatchSeq& d = seqs[order[first + place[i]]];
-            Plan& q = pl[place[i]];
+            const BatchSeq& d = seqs[order[first + plan.place[i]]];
+            Plan& q = pl[plan.place[i]];
             q.RT = RT; q.KS = KS; q.NS = 4; q.KC = 64; q.PRE = 0;
             q.n_row_blocks = n_row_blocks;
             q.partial_bytes_per_wg = partial_wg_bytes(head_dim, RT, KS);
-            q.XS = cuts[place[i]];
+            q.XS = plan.cuts[plan.place[i]];
             const la_status st = build_params(bp.seq[i], ov, q, d.q, d.k_cache, d.v_cache, d.P,
                                               d.P > 0 ? d.block_table : nullptr, page_size, n_pages, nullptr, T,
                                               d.step_k, d.step_v, d.P, W, N, G, heads, kv_heads, head_dim, d.out);

@@ -1,0 +1,170 @@
+// How a batched attention launch is cut: host code without HIP, so that it can be built and tested on its own.
+//
+// A workgroup has a compute unit to itself and owns (KV head, block of 64 or 128 query rows, one of
+// `cuts` ranges of a step's 64-key chunks).  The steps of a launch share the height of the row block.
+#pragma once
+
+namespace la {
+
+constexpr int kMaxBatch = 16;    // steps of a launch
+constexpr int kXcds = 8, kXcdUnits = 32;  // XCDs, and compute units of one
+
+struct BatchPlan {
+    bool rows128;            // 128-row workgroups (head_dim 128 only), else 64
+    int cuts[kMaxBatch];     // ranges of step i
+    int place[kMaxBatch];    // the steps in slot order
+};
+
+// Workgroups of a step on every XCD (they are numbered XCD by XCD).
+inline int batch_wgs_per_xcd(int units, int cuts) { return (int)(((long long)units * cuts + kXcds - 1) / kXcds); }
+
+namespace batch_plan {
+
+// Chunk and fixed times: a workgroup costs its chunks plus a part that does not depend on them
+// (start, merge, writing the rows): 6 chunks' time of 1.22 us in the 128-row form, 5 of 0.76 us in the
+// 64-row one, and 1 or 2 more with partial results to exchange; from steps of 4 to 66 chunks, one and
+// two rounds, cut and uncut.  The two forms are compared with a chunk of the 128-row form counting 16
+// and one of the 64-row form 11: it takes 0.76 us in one round but 0.84 in several, which pull twice
+// the traffic of the 128-row form through the L2s.
+struct Form {
+    int units;      // (KV head, row block) pairs of a step
+    int fixed, exchange, chunk;
+};
+inline Form form_of(bool rows128, int kv_heads, int tiles)
+{
+    return rows128 ? Form{kv_heads * ((tiles + 3) / 4), 6, 1, 16} : Form{kv_heads * ((tiles + 1) / 2), 5, 2, 11};
+}
+
+// Time, in chunks, at which the compute units of an XCD are done when they take the workgroups in
+// slot order as they become free; load[] is a heap with the emptiest on top.
+inline long long launch_end(const int* order, int n, const int* wgs, const long long* cost)
+{
+    long long load[kXcdUnits] = {0}, end = 0;
+    for (int k = 0; k < n; ++k) {
+        const long long c = cost[order[k]];
+        for (int m = wgs[order[k]]; m > 0; --m) {
+            const long long v = load[0] + c;
+            int at = 0;
+            for (int ch = 1; ch < kXcdUnits; ch = 2 * at + 1) {
+                if (ch + 1 < kXcdUnits && load[ch + 1] < load[ch]) ++ch;
+                if (load[ch] >= v) break;
+                load[at] = load[ch];
+                at = ch;
+            }
+            load[at] = v;
+            if (v > end) end = v;
+        }
+    }
+    return end;
+}
+
+// A set of cuts as workgroups: keys of each (in chunks), how many on every XCD, what each costs, longest first.
+struct Layout {
+    int cuts[kMaxBatch], range[kMaxBatch], wgs[kMaxBatch], order[kMaxBatch];
+    long long cost[kMaxBatch], sum;  // sum: of all workgroups of an XCD
+
+    void cut(int i, int x, int chunks, const Form& f)
+    {
+        cuts[i] = x;
+        wgs[i] = batch_wgs_per_xcd(f.units, x);
+        range[i] = (chunks + x - 1) / x;
+        cost[i] = range[i] + f.fixed + (x > 1 ? f.exchange : 0);
+    }
+    void sort(int n)
+    {
+        sum = 0;
+        for (int i = 0; i < n; ++i) {
+            int j = i;
+            for (; j > 0 && cost[order[j - 1]] < cost[i]; --j) order[j] = order[j - 1];
+            order[j] = i;
+            sum += wgs[i] * cost[i];
+        }
+    }
+};
+
+// Cuts and order for one form: all cuts allowed (limit[i]), or fewer where that ends earlier.  From
+// uncut steps on, the step with the longest ranges is cut once more as long as the sum of all
+// workgroups leaves room for a better end than the best one seen.  Returns the launch's end.
+inline long long search(const int* chunks, const int* limit, int n, const Form& f, int* cuts, int* place)
+{
+    Layout l;
+    long long best = -1;
+    auto consider = [&] {
+        l.sort(n);
+        const long long end = launch_end(l.order, n, l.wgs, l.cost);
+        if (best >= 0 && end >= best) return;
+        best = end;
+        for (int i = 0; i < n; ++i) { cuts[i] = l.cuts[i]; place[i] = l.order[i]; }
+    };
+    for (int i = 0; i < n; ++i) l.cut(i, limit[i], chunks[i], f);
+    consider();
+    for (int i = 0; i < n; ++i) l.cut(i, 1, chunks[i], f);
+    for (;;) {
+        consider();
+        if (l.sum >= best * kXcdUnits) break;
+        int longest = -1;
+        for (int i = 0; i < n; ++i)
+            if (l.cuts[i] < limit[i] && (longest < 0 || l.range[i] > l.range[longest])) longest = i;
+        if (longest < 0) break;
+        l.cut(longest, l.cuts[longest] + 1, chunks[longest], f);
+    }
+    return best * f.chunk;
+}
+
+}  // namespace batch_plan
+
+// chunks[i]: 64-key chunks of step i (longest steps first); tiles: 32-row tiles of a KV head's query rows;
+// rows: 128 or 64 to force the form (a testing hook), 0 to choose it.
+inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows = 0)
+{
+    using namespace batch_plan;
+    BatchPlan p;
+    // The plan that bounds the others.  128-row workgroups (a chunk of K/V staged once for four row
+    // tiles: half the traffic into LDS per flop) as soon as the batch fills three quarters of the GPU
+    // with them, otherwise 64-row workgroups; ranges of at least four chunks, one round of workgroups
+    // when the steps are alike, half a round more when their lengths differ.
+    // Nothing below takes a step to a plan of less accuracy.  A cut step's partial results are rounded to
+    // bf16 (against 64 bits, 12 steps of 4096 keys, 32/8 heads, 81 rows: 2.6e-3 uncut, 3.1e-3 cut), and so
+    // are the sums of three of a 64-row workgroup's four key-split waves, but of one in two of a 128-row
+    // one (10 steps of 14 to 184 keys, 32/8 heads, 121 rows: 2.44e-3 and 2.36e-3).  So only a step that is
+    // cut here may be cut, and the form may only change from 64 to 128 rows.
+    // (Cutting those 12 steps, too, would take 126 us instead of 158; partial results in fp32 cost every
+    // cut launch 1 to 4 us.)
+    p.rows128 = head_dim == 128 && (rows ? rows == 128 : tiles >= 3 && (long long)n * kv_heads * ((tiles + 3) / 4) >= 192);
+    const Form f = form_of(p.rows128, kv_heads, tiles);
+    long long work = 0;
+    bool alike = true, may_cut = false;
+    for (int i = 0; i < n; ++i) {
+        work += (long long)f.units * chunks[i];
+        alike = alike && chunks[i] == chunks[0];
+    }
+    const long long wgs = alike ? 256 : 384;
+    long long target = (work + wgs - 1) / wgs;   // chunks per workgroup
+    if (target < 4) target = 4;
+    int limit[kMaxBatch];
+    for (int i = 0; i < n; ++i) {
+        long long x = (chunks[i] + target - 1) / target;
+        if (x > chunks[i] / 2) x = chunks[i] / 2;
+        if (x > 64) x = 64;
+        if (x < 1) x = 1;
+        limit[i] = p.cuts[i] = (int)x;
+        p.place[i] = i;
+        may_cut = may_cut || x > 1;
+    }
+    // Fewer cuts, or 128 rows, where the launch ends earlier by the times above.  Measured at 32/8 heads, this rule alone
+    // and with what follows: 8 steps of 512 keys, 81 rows 29.9 and 19.4 us (uncut); 16 of 466 to 1021
+    // keys, 81 rows 52.3 and 48.1 (504 workgroups of 128 rows instead of 528); 8 of 1253 to 14559 keys, 121 rows
+    // 175 and 170; 6 of 1024 keys, 81 rows 33.9 and 28.0 (128 rows).  Where the ends are equal all cuts
+    // stay: 12 of 148 to 1278 keys, 32/32 heads, 25 rows 27.9 us, uncut 28.9.
+    const bool may_grow = !p.rows128 && !rows && head_dim == 128 && tiles >= 3;
+    if (!may_cut && !may_grow) return p;
+    const long long end = search(chunks, limit, n, f, p.cuts, p.place);
+    if (may_grow) {
+        BatchPlan g;
+        g.rows128 = true;
+        if (search(chunks, limit, n, form_of(true, kv_heads, tiles), g.cuts, g.place) < end) p = g;
+    }
+    return p;
+}
+
+}  // namespace la

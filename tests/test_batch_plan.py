@@ -1,0 +1,77 @@
+"""How a batched attention launch is cut (csrc/la_batch_plan.h, host code): built here on its own with
+the host compiler and compared with the rule that bounds it."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2402_02057_amd import buildlib
+
+SHIM = r"""
+#include "la_batch_plan.h"
+extern "C" int plan(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows, int* cuts, int* place)
+{
+    const la::BatchPlan p = la::plan_batch(chunks, n, tiles, kv_heads, head_dim, rows);
+    for (int i = 0; i < n; ++i) { cuts[i] = p.cuts[i]; place[i] = p.place[i]; }
+    return p.rows128 ? 128 : 64;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("batch_plan")
+    source, so = d / "shim.cpp", d / "shim.so"
+    source.write_text(SHIM)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", buildlib.CSRC,
+                    str(source), "-o", str(so)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+class Batch:
+    """Prefixes (longest first) and a step as the launcher hands them to the planner."""
+
+    def __init__(self, prefixes, T, heads, kv_heads, head_dim):
+        self.chunks = [-(-P // 64) + -(-T // 64) for P in sorted(prefixes, reverse=True)]
+        self.tiles, self.kv_heads, self.head_dim = -(-T * (heads // kv_heads) // 32), kv_heads, head_dim
+
+    def plan(self, lib, rows=0):
+        n = len(self.chunks)
+        arr = ctypes.c_int * n
+        cuts, place = arr(), arr()
+        form = lib.plan(arr(*self.chunks), n, self.tiles, self.kv_heads, self.head_dim, rows, cuts, place)
+        return form, list(cuts), list(place)
+
+    def units(self, form):
+        return self.kv_heads * -(-self.tiles // (form // 32))
+
+    def bound(self):
+        """Form and cuts that every plan is at least as accurate as."""
+        form = 128 if self.head_dim == 128 and self.tiles >= 3 and len(self.chunks) * self.units(128) >= 192 else 64
+        work = sum(self.chunks) * self.units(form)
+        target = max(4, -(-work // (256 if len(set(self.chunks)) == 1 else 384)))
+        return form, [max(1, min(-(-c // target), c // 2, 64)) for c in self.chunks]
+
+
+def batches(count, seed, head_dims=(64, 128)):
+    rng = random.Random(seed)
+    for _ in range(count):
+        top, n = round(64 * 256 ** rng.random()), rng.randint(2, 16)
+        N, W = rng.choice([3, 4, 5, 7]), rng.choice([1, 3, 5, 10, 15, 30])
+        heads, kv_heads = rng.choice([(32, 8), (32, 32), (64, 8), (8, 2), (16, 4), (10, 10), (4, 1)])
+        alike = rng.random() < 0.3
+        prefixes = [top if alike else rng.randint(0, top) for _ in range(n)]
+        yield Batch(prefixes, 1 + 2 * W * (N - 1), heads, kv_heads, rng.choice(head_dims))
+
+
+def test_no_step_is_less_accurate_than_under_the_bounding_rule(lib):
+    """A step that the rule leaves uncut stays uncut (its partial results would be rounded to bf16), and a
+    128-row launch stays one (a 64-row workgroup rounds more sums between its key-split waves)."""
+    for b in batches(3000, seed=1):
+        form, cuts, place = b.plan(lib)
+        bound_form, bound = b.bound()
+        assert form >= bound_form, (b.chunks, b.tiles, b.kv_heads)
+        assert all(1 <= x <= most for x, most in zip(cuts, bound)), (b.chunks, b.tiles, b.kv_heads, cuts, bound)
+        assert sorted(place) == list(range(len(cuts)))
