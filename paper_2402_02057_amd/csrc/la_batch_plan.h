@@ -157,7 +157,10 @@ inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, i
     // 175 and 170; 6 of 1024 keys, 81 rows 33.9 and 28.0 (128 rows).  Where the ends are equal all cuts
     // stay: 12 of 148 to 1278 keys, 32/32 heads, 25 rows 27.9 us, uncut 28.9.
     const bool may_grow = !p.rows128 && !rows && head_dim == 128 && tiles >= 3;
-    if (!may_cut && !may_grow) return p;
+    // The times hold for the two forms of head_dim 128.  The four-wave workgroups of head_dim 64 gain from
+    // every cut the rule allows (3 steps of 509 to 3864 keys, 32/8 heads, 121 rows: 19.5 us, with the times
+    // above 30.1; 9 of 688 to 7706 keys, 81 rows: 54.9 and 61.4): they stay with it.
+    if (head_dim != 128 || (!may_cut && !may_grow)) return p;
     const long long end = search(chunks, limit, n, f, p.cuts, p.place);
     if (may_grow) {
         BatchPlan g;

@@ -75,3 +75,11 @@ def test_no_step_is_less_accurate_than_under_the_bounding_rule(lib):
         assert form >= bound_form, (b.chunks, b.tiles, b.kv_heads)
         assert all(1 <= x <= most for x, most in zip(cuts, bound)), (b.chunks, b.tiles, b.kv_heads, cuts, bound)
         assert sorted(place) == list(range(len(cuts)))
+
+
+def test_head_dim_64_keeps_the_bounding_rule(lib):
+    """The times the search goes by are those of the head_dim 128 kernels."""
+    for b in batches(500, seed=2, head_dims=(64,)):
+        form, cuts, place = b.plan(lib)
+        assert (form, cuts) == b.bound(), (b.chunks, b.tiles, b.kv_heads)
+        assert place == list(range(len(cuts)))
