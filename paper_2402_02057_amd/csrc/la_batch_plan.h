@@ -18,6 +18,10 @@ struct BatchPlan {
 // Workgroups of a step on every XCD (they are numbered XCD by XCD).
 inline int batch_wgs_per_xcd(int units, int cuts) { return (int)(((long long)units * cuts + kXcds - 1) / kXcds); }
 
+// The workgroups that share a row block's keys exchange partial results through the L2 of their XCD;
+// the last one of a group that lies on two XCDs computes the rows again over all keys instead.
+inline bool batch_groups_whole(int units, int cuts) { return batch_wgs_per_xcd(units, cuts) % cuts == 0; }
+
 namespace batch_plan {
 
 // Chunk and fixed times: a workgroup costs its chunks plus a part that does not depend on them
@@ -96,17 +100,26 @@ inline long long search(const int* chunks, const int* limit, int n, const Form& 
         best = end;
         for (int i = 0; i < n; ++i) { cuts[i] = l.cuts[i]; place[i] = l.order[i]; }
     };
-    for (int i = 0; i < n; ++i) l.cut(i, limit[i], chunks[i], f);
+    for (int i = 0; i < n; ++i) {
+        int x = limit[i];
+        while (!batch_groups_whole(f.units, x)) --x;
+        l.cut(i, x, chunks[i], f);
+    }
     consider();
     for (int i = 0; i < n; ++i) l.cut(i, 1, chunks[i], f);
     for (;;) {
         consider();
         if (l.sum >= best * kXcdUnits) break;
-        int longest = -1;
-        for (int i = 0; i < n; ++i)
-            if (l.cuts[i] < limit[i] && (longest < 0 || l.range[i] > l.range[longest])) longest = i;
+        int longest = -1, more = 0;
+        for (int i = 0; i < n; ++i) {
+            int x = l.cuts[i] + 1;
+            while (x <= limit[i] && !batch_groups_whole(f.units, x)) ++x;
+            if (x > limit[i] || (longest >= 0 && l.range[i] <= l.range[longest])) continue;
+            longest = i;
+            more = x;
+        }
         if (longest < 0) break;
-        l.cut(longest, l.cuts[longest] + 1, chunks[longest], f);
+        l.cut(longest, more, chunks[longest], f);
     }
     return best * f.chunk;
 }
@@ -122,7 +135,9 @@ inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, i
     // The plan that bounds the others.  128-row workgroups (a chunk of K/V staged once for four row
     // tiles: half the traffic into LDS per flop) as soon as the batch fills three quarters of the GPU
     // with them, otherwise 64-row workgroups; ranges of at least four chunks, one round of workgroups
-    // when the steps are alike, half a round more when their lengths differ.
+    // when the steps are alike, half a round more when their lengths differ; no cuts that leave a group
+    // on two XCDs (3 steps of 4096 keys, 4/1 heads, 81 rows: 6 units cut into 14 ranges 57.6 us, uncut 45.1;
+    // 12 of 350 to 900 keys, 16/4 heads of 64, 43 rows: 22.4 and 17.1).
     // Nothing below takes a step to a plan of less accuracy.  A cut step's partial results are rounded to
     // bf16 (against 64 bits, 12 steps of 4096 keys, 32/8 heads, 81 rows: 2.6e-3 uncut, 3.1e-3 cut), and so
     // are the sums of three of a 64-row workgroup's four key-split waves, but of one in two of a 128-row
@@ -146,7 +161,7 @@ inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, i
         long long x = (chunks[i] + target - 1) / target;
         if (x > chunks[i] / 2) x = chunks[i] / 2;
         if (x > 64) x = 64;
-        if (x < 1) x = 1;
+        if (x < 1 || !batch_groups_whole(f.units, (int)x)) x = 1;
         limit[i] = p.cuts[i] = (int)x;
         p.place[i] = i;
         may_cut = may_cut || x > 1;

@@ -52,7 +52,15 @@ class Batch:
         form = 128 if self.head_dim == 128 and self.tiles >= 3 and len(self.chunks) * self.units(128) >= 192 else 64
         work = sum(self.chunks) * self.units(form)
         target = max(4, -(-work // (256 if len(set(self.chunks)) == 1 else 384)))
-        return form, [max(1, min(-(-c // target), c // 2, 64)) for c in self.chunks]
+        cuts = [max(1, min(-(-c // target), c // 2, 64)) for c in self.chunks]
+        return form, [x if self.groups_whole(form, x) else 1 for x in cuts]
+
+    def groups_whole(self, form, cuts):
+        """Workgroups are numbered XCD by XCD, the ranges of a row block one after the other: no XCD ends
+        inside a group."""
+        total = self.units(form) * cuts
+        per_xcd = -(-total // 8)
+        return all(first // per_xcd == (first + cuts - 1) // per_xcd for first in range(0, total, cuts))
 
 
 def batches(count, seed, head_dims=(64, 128)):
@@ -83,3 +91,13 @@ def test_head_dim_64_keeps_the_bounding_rule(lib):
         form, cuts, place = b.plan(lib)
         assert (form, cuts) == b.bound(), (b.chunks, b.tiles, b.kv_heads)
         assert place == list(range(len(cuts)))
+
+
+def test_no_group_lies_on_two_xcds(lib):
+    """It would exchange nothing: its last workgroup would compute the rows again over all keys."""
+    many = list(batches(2000, seed=3)) + [Batch([4096] * n, T, H, KV, 128) for n in (2, 3, 16) for T in (13, 41, 81)
+                                          for H, KV in [(4, 4), (8, 2), (4, 1), (10, 10), (7, 7), (40, 10)]]
+    for b in many:
+        for rows in (0, 64, 128):
+            form, cuts, _ = b.plan(lib, rows)
+            assert all(b.groups_whole(form, x) for x in set(cuts)), (b.chunks, b.tiles, b.kv_heads, form, cuts)
