@@ -1,6 +1,7 @@
 """How a batched attention launch is cut (csrc/la_batch_plan.h, host code): built here on its own with
 the host compiler and compared with the rule that bounds it."""
 import ctypes
+import heapq
 import os
 import random
 import subprocess
@@ -10,12 +11,29 @@ import pytest
 from paper_2402_02057_amd import buildlib
 
 SHIM = r"""
+#include <chrono>
 #include "la_batch_plan.h"
 extern "C" int plan(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows, int* cuts, int* place)
 {
     const la::BatchPlan p = la::plan_batch(chunks, n, tiles, kv_heads, head_dim, rows);
     for (int i = 0; i < n; ++i) { cuts[i] = p.cuts[i]; place[i] = p.place[i]; }
     return p.rows128 ? 128 : 64;
+}
+extern "C" long long launch_end(const int* order, int n, const int* wgs, const long long* cost)
+{
+    return la::batch_plan::launch_end(order, n, wgs, cost);
+}
+extern "C" double plan_us(const int* chunks, int n, int tiles, int kv_heads, int head_dim)
+{
+    double best = 1e9;
+    for (int r = 0; r < 20; ++r) {
+        const auto from = std::chrono::steady_clock::now();
+        volatile int sink = 0;
+        for (int k = 0; k < 5; ++k) sink += la::plan_batch(chunks, n, tiles, kv_heads, head_dim).cuts[0];
+        const double us = std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - from).count() / 5;
+        if (us < best) best = us;
+    }
+    return best;
 }
 """
 
@@ -27,7 +45,9 @@ def lib(tmp_path_factory):
     source.write_text(SHIM)
     subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", buildlib.CSRC,
                     str(source), "-o", str(so)], check=True)
-    return ctypes.CDLL(str(so))
+    lib = ctypes.CDLL(str(so))
+    lib.launch_end.restype, lib.plan_us.restype = ctypes.c_longlong, ctypes.c_double
+    return lib
 
 
 class Batch:
@@ -101,3 +121,30 @@ def test_no_group_lies_on_two_xcds(lib):
         for rows in (0, 64, 128):
             form, cuts, _ = b.plan(lib, rows)
             assert all(b.groups_whole(form, x) for x in set(cuts)), (b.chunks, b.tiles, b.kv_heads, form, cuts)
+
+
+def test_launch_end_is_that_of_placing_workgroups_one_by_one(lib):
+    rng = random.Random(4)
+    for _ in range(500):
+        n = rng.randint(1, 16)
+        wgs = [rng.choice([1, 2, 3, 5, 31, 32, 33, 64, rng.randint(1, 200)]) for _ in range(n)]
+        cost = [rng.choice([7, 8, 12, rng.randint(1, 300)]) for _ in range(n)]
+        order = sorted(range(n), key=lambda i: -cost[i])
+        loads = [0] * 32
+        for i in order:
+            for _ in range(wgs[i]):
+                heapq.heapreplace(loads, loads[0] + cost[i])
+        got = lib.launch_end((ctypes.c_int * n)(*order), n, (ctypes.c_int * n)(*wgs), (ctypes.c_longlong * n)(*cost))
+        assert got == max(loads), (order, wgs, cost)
+
+
+def test_planning_takes_less_than_a_launch(lib):
+    """It runs in every call, so once per layer.  The quickest of twenty runs, and a bound of three times
+    what an idle 2.7 GHz core takes for the slowest."""
+    def us(b):
+        n = len(b.chunks)
+        return lib.plan_us((ctypes.c_int * n)(*b.chunks), n, b.tiles, b.kv_heads, b.head_dim)
+    times = sorted(us(b) for b in batches(300, seed=5, head_dims=(128,)))
+    assert times[len(times) // 2] < 3, times[::30]
+    assert times[-1] < 30, times[::30]
+    assert us(Batch([4096] * 16, 41, 8, 2, 128)) < 12
