@@ -35,15 +35,19 @@
  * All pointers are DEVICE pointers unless said otherwise.  The caller owns
  * every buffer; nothing is retained after the call's work has run.  Calls are
  * asynchronous on `stream` (a hipStream_t passed as void*, NULL = the default
- * stream) and never synchronise the device.  The library keeps a small device
- * workspace per device (split partials, tickets), grown on demand with
- * hipMalloc - so the first call at a new size may allocate - and shared by
+ * stream) and never synchronise the device.  The library keeps a small
+ * workspace per device and set (split partials, tickets; 33 MB, what the
+ * attention calls need), allocated on demand with hipMalloc - so a first call, or
+ * the first at a size that needs more, may allocate - and shared by
  * all calls on that device: calls issued to one stream are ordered; calls on
  * different streams of the same device must not overlap in time unless they use
  * different workspace sets (la_select_workspace).  The calls may
- * be recorded into a HIP graph once a call of the same (or a larger) shape has
- * run outside the capture: that one sizes and clears the workspace, the kernels
- * leave it cleared.  A workspace block that a later, larger call replaces stays
+ * be recorded into a HIP graph once the same call has run outside the capture:
+ * that one sizes and clears the workspace, the kernels leave it cleared.  (A larger
+ * shape will not always do: its workgroups may fill the device without exchanging
+ * partials, and then it needs no workspace.  A batched attention call of two or
+ * more steps reserves what any attention call needs.)  A workspace block that a
+ * later, larger call replaces stays
  * allocated until la_shutdown, so graphs recorded before remain valid (do not
  * call la_shutdown while such a graph may still be launched).
  *

@@ -65,15 +65,24 @@ la_status select_workspace(int set)
 }
 
 namespace {
+// A block is at least this large: what any batched launch needs (768 workgroups of cut steps with 36 KB
+// of partial results each and 384 split groups with eight tickets, la_batch_plan.h), and more than any one step.
+constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(32) << 20;
+
 // Growing a block means hipMalloc (and a clear on the stream): neither may happen while the
 // stream is being captured into a graph - the allocation would invalidate the capture, the
 // clear would be recorded as a node of it.
-bool growth_allowed(hipStream_t stream)
+bool capturing(hipStream_t stream)
 {
     hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone) {
+    return hipStreamIsCapturing(stream, &status) == hipSuccess && status != hipStreamCaptureStatusNone;
+}
+
+bool growth_allowed(hipStream_t stream)
+{
+    if (capturing(stream)) {
         fail(LA_EUNSUPPORTED, "the device workspace must grow for this shape, which cannot happen while the stream is "
-                              "being captured: run a call of this (or a larger) shape outside the capture first");
+                              "being captured: run this call outside the capture first");
         return false;
     }
     return true;
@@ -89,7 +98,7 @@ void* zeroed_workspace(size_t bytes, hipStream_t stream)
     if (!growth_allowed(stream)) return nullptr;
     // Growing (only when a larger shape than any before is seen): a fresh block, cleared on
     // this stream ahead of the kernel that will use it; the old one is retired, not freed.
-    size_t want = bytes < (1u << 16) ? (1u << 16) : bytes;
+    size_t want = bytes < kLeastZeroed ? kLeastZeroed : bytes;
     void* fresh = nullptr;
     if (hipMalloc(&fresh, want) != hipSuccess) {
         fail(LA_ENOMEM, "hipMalloc of %zu bytes of ticket workspace failed", want);
@@ -113,7 +122,7 @@ void* scratch_workspace(size_t bytes, hipStream_t stream)
     if (!p) return nullptr;
     if (bytes <= p->scratch_bytes) return p->scratch;
     if (!growth_allowed(stream)) return nullptr;
-    size_t want = bytes < (size_t(8) << 20) ? (size_t(8) << 20) : bytes + bytes / 4;
+    size_t want = bytes < kLeastScratch ? kLeastScratch : bytes + bytes / 4;
     void* fresh = nullptr;
     if (hipMalloc(&fresh, want) != hipSuccess) {
         fail(LA_ENOMEM, "hipMalloc of %zu bytes of partial-result workspace failed", want);
@@ -123,6 +132,22 @@ void* scratch_workspace(size_t bytes, hipStream_t stream)
     p->scratch = fresh;
     p->scratch_bytes = want;
     return fresh;
+}
+
+void reserve_workspace(hipStream_t stream)
+{
+    {
+        std::lock_guard<std::mutex> lock(g_mutex);
+        const Pool* p = current_pool();
+        if (!p || (p->zeroed && p->scratch)) return;
+    }
+    if (capturing(stream)) return;
+    // (an allocation nobody needs yet must not disturb a capture that runs on another stream)
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
+    const bool ok = zeroed_workspace(1, stream) && scratch_workspace(1, stream);
+    (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!ok) (void)hipGetLastError();
 }
 
 void free_workspaces()

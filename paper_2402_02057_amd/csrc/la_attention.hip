@@ -1642,6 +1642,9 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             }
         }
         for (int i = n; i <= kMaxBatch; ++i) bp.slots.slot0[i] = slot;
+        // (whether a batch is cut depends on all its lengths: one that is not reserves for one that is, so
+        // that the latter can be captured after the former has run)
+        reserve_workspace(stream);
         if (partial_bytes) {
             unsigned* tickets = (unsigned*)zeroed_workspace(ticket_count * sizeof(unsigned), stream);
             unsigned char* partials = (unsigned char*)scratch_workspace(partial_bytes, stream);

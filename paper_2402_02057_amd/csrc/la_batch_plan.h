@@ -9,6 +9,10 @@ namespace la {
 constexpr int kMaxBatch = 16;    // steps of a launch
 constexpr int kXcds = 8, kXcdUnits = 32;  // XCDs, and compute units of one
 
+// What the steps of a launch that are cut amount to at most: ranges of at least a 384th of the
+// launch's chunks make twice as many workgroups at most when they are rounded up.
+constexpr int kMaxCutWorkgroups = 768, kMaxCutGroups = 384;
+
 struct BatchPlan {
     bool rows128;            // 128-row workgroups (head_dim 128 only), else 64
     int cuts[kMaxBatch];     // ranges of step i

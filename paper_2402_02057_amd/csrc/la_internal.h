@@ -21,6 +21,9 @@ la_status last_failure();
 // (and records the error) on failure.
 void* zeroed_workspace(size_t bytes, hipStream_t stream);
 void* scratch_workspace(size_t bytes, hipStream_t stream);
+// Both blocks at their least size, if they do not exist yet and `stream` is not being captured; a
+// failure is no error (the call that needs more than there is reports it).
+void reserve_workspace(hipStream_t stream);
 void free_workspaces();
 la_status select_workspace(int set);
 // Testing hooks of the attention launchers (la_debug_override).

@@ -123,6 +123,18 @@ def test_no_group_lies_on_two_xcds(lib):
             assert all(b.groups_whole(form, x) for x in set(cuts)), (b.chunks, b.tiles, b.kv_heads, form, cuts)
 
 
+def test_workspace_of_a_launch_is_bounded(lib):
+    """What the library reserves (la_api.hip: 32 MB of partial results, 512 KB of tickets) holds any batch."""
+    for b in batches(2000, seed=6):
+        for rows in (0, 64, 128):
+            form, cuts, _ = b.plan(lib, rows)
+            workgroups = sum(b.units(form) * x for x in cuts if x > 1)
+            groups = sum(b.units(form) for x in cuts if x > 1)
+            assert workgroups <= 768 and groups <= 384, (b.chunks, b.tiles, b.kv_heads, form, cuts)
+    waves, slices = 8, 2                                                        # of a 128-row workgroup, the largest
+    assert 768 * waves * (slices * 16 * 64 * 2 + 64 * 8) <= 32 << 20 and 384 * waves * 128 <= 512 << 10
+
+
 def test_launch_end_is_that_of_placing_workgroups_one_by_one(lib):
     rng = random.Random(4)
     for _ in range(500):

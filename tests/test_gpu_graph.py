@@ -230,3 +230,36 @@ def test_the_row_tile_kernel_in_a_graph_with_an_empty_workspace():
         binding.la_step_attention(q, kc, vc, sk, sv, P, W, N, G, H, KV, d, torch.empty_like(out))  # eager work between
         torch.cuda.synchronize()
     assert not torch.equal(eager, eager_r)
+
+
+def test_a_batch_that_is_cut_is_captured_after_one_that_is_not():
+    """Six steps of 512 keys fill the device uncut, four are cut in two: the first call reserves the
+    workspace that the second, smaller one needs inside the capture."""
+    W = G = N = 5
+    H, KV, d, P, T = 32, 8, 128, 512, 41
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(11)
+
+    def rb(*shape):
+        return torch.randn(shape, device="cuda", generator=gen).bfloat16()
+    seqs = [dict(q=rb(T, H, d), k_cache=rb(KV, P, d), v_cache=rb(KV, P, d), step_k=rb(T, KV, d), step_v=rb(T, KV, d), P=P,
+                 out=torch.empty((T, H, d), dtype=torch.bfloat16, device="cuda")) for _ in range(6)]
+    few = [dict(x, out=torch.empty_like(x["out"])) for x in seqs[:4]]
+    binding.la_select_workspace(14)                           # (a set that no other test uses)
+    try:
+        binding.la_step_attention_batch(seqs, W, N, G, H, KV, d)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            binding.la_step_attention_batch(few, W, N, G, H, KV, d)
+        eager = [dict(x, out=torch.empty_like(x["out"])) for x in few]
+        for _ in range(4):
+            for x in few:
+                x["q"].copy_(rb(T, H, d))
+            graph.replay()
+            torch.cuda.synchronize()
+            binding.la_step_attention_batch(eager, W, N, G, H, KV, d)
+            torch.cuda.synchronize()
+            assert all(torch.equal(a["out"], b["out"]) for a, b in zip(few, eager))
+    finally:
+        binding.la_select_workspace(0)
