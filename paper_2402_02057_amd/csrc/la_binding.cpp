@@ -180,34 +180,45 @@ struct Heads {
 // The key `s` as an interned Python string, made once.
 #define KEY(s) ([]() -> PyObject* { static PyObject* const k = PyUnicode_InternFromString(s); return k; }())
 
-PyObject* item(PyObject* x, PyObject* k, bool or_none = false)
-{
-    PyObject* v = nullptr;
-    if (PyDict_Check(x)) {
-        v = PyDict_GetItemWithError(x, k);  // borrowed from the dict, which outlives the call
-    } else {
-        v = PyObject_GetItem(x, k);
-        Py_XDECREF(v);                      // (held by the mapping)
-        if (!v && or_none && PyErr_ExceptionMatches(PyExc_KeyError)) PyErr_Clear();
-    }
-    if (!v && !PyErr_Occurred()) {
-        if (or_none) v = Py_None;
-        else PyErr_SetObject(PyExc_KeyError, k);
-    }
-    if (!v) throw Raised();
-    return v;
-}
-
-// The sequence of descriptor dicts, as borrowed references (a tuple or list is used as it is).
-struct Items {
-    PyObject* fast;
+// The sequence of descriptors (a tuple or list is used as it is).
+class Items {
+public:
     explicit Items(PyObject* o) : fast(PySequence_Fast(o, "a sequence of dicts is expected"))
     {
         if (!fast) throw Raised();
     }
-    ~Items() { Py_DECREF(fast); }
+    ~Items()
+    {
+        Py_DECREF(fast);
+        for (PyObject* v : held) Py_DECREF(v);
+    }
+    Items(const Items&) = delete;
     int size() const { return (int)PySequence_Fast_GET_SIZE(fast); }
-    PyObject* operator[](int i) const { return PySequence_Fast_GET_ITEM(fast, i); }
+
+    // The value of descriptor i under `k`, valid until this object goes: a dict holds its values, what
+    // another mapping hands out may exist nowhere else and is kept here until the call has returned.
+    PyObject* at(int i, PyObject* k, bool or_none = false)
+    {
+        PyObject* const x = PySequence_Fast_GET_ITEM(fast, i);
+        PyObject* v = nullptr;
+        if (PyDict_Check(x)) {
+            v = PyDict_GetItemWithError(x, k);
+        } else {
+            v = PyObject_GetItem(x, k);
+            if (v) held.push_back(v);
+            else if (or_none && PyErr_ExceptionMatches(PyExc_KeyError)) PyErr_Clear();
+        }
+        if (!v && !PyErr_Occurred()) {
+            if (or_none) v = Py_None;
+            else PyErr_SetObject(PyExc_KeyError, k);
+        }
+        if (!v) throw Raised();
+        return v;
+    }
+
+private:
+    PyObject* fast;
+    std::vector<PyObject*> held;
 };
 
 struct Pages {
@@ -375,18 +386,18 @@ LA_ENTRY(kv_commit_rope)
 
 LA_ENTRY(step_attention_batch)
 {
-    const Items x(a[0]);
+    Items x(a[0]);
     const Step s(a + 1);
     const Heads h(a + 4);
     std::vector<la_step_desc> d((size_t)x.size());
     for (int i = 0; i < x.size(); ++i) {
-        const int P = whole_number(item(x[i], KEY("P")));
-        d[i].q = ptr(item(x[i], KEY("q")), kBF16, {s.T, h.heads, h.d}, "q");
-        d[i].k_cache = ptr(item(x[i], KEY("k_cache")), kBF16, {h.kv, P, h.d}, "k_cache", true);
-        d[i].v_cache = ptr(item(x[i], KEY("v_cache")), kBF16, {h.kv, P, h.d}, "v_cache", true);
-        d[i].step_k = ptr(item(x[i], KEY("step_k")), kBF16, {s.T, h.kv, h.d}, "step_k");
-        d[i].step_v = ptr(item(x[i], KEY("step_v")), kBF16, {s.T, h.kv, h.d}, "step_v");
-        d[i].out = ptr(item(x[i], KEY("out")), kBF16, {s.T, h.heads, h.d}, "out");
+        const int P = whole_number(x.at(i, KEY("P")));
+        d[i].q = ptr(x.at(i, KEY("q")), kBF16, {s.T, h.heads, h.d}, "q");
+        d[i].k_cache = ptr(x.at(i, KEY("k_cache")), kBF16, {h.kv, P, h.d}, "k_cache", true);
+        d[i].v_cache = ptr(x.at(i, KEY("v_cache")), kBF16, {h.kv, P, h.d}, "v_cache", true);
+        d[i].step_k = ptr(x.at(i, KEY("step_k")), kBF16, {s.T, h.kv, h.d}, "step_k");
+        d[i].step_v = ptr(x.at(i, KEY("step_v")), kBF16, {s.T, h.kv, h.d}, "step_v");
+        d[i].out = ptr(x.at(i, KEY("out")), kBF16, {s.T, h.heads, h.d}, "out");
         d[i].P = P;
         d[i].reserved = 0;
     }
@@ -396,18 +407,18 @@ LA_ENTRY(step_attention_batch)
 
 LA_ENTRY(step_attention_batch_paged)
 {
-    const Items x(a[0]);
+    Items x(a[0]);
     const Step s(a + 3);
     const Heads h(a + 6);
     const Pages pg = pages_of(a[1], a[2], h.kv, h.d);
     std::vector<la_step_desc_paged> d((size_t)x.size());
     for (int i = 0; i < x.size(); ++i) {
-        const int P = whole_number(item(x[i], KEY("P")));
-        d[i].block_table = table_of(item(x[i], KEY("block_table"), true), P, pg.page_size);
-        d[i].q = ptr(item(x[i], KEY("q")), kBF16, {s.T, h.heads, h.d}, "q");
-        d[i].step_k = ptr(item(x[i], KEY("step_k")), kBF16, {s.T, h.kv, h.d}, "step_k");
-        d[i].step_v = ptr(item(x[i], KEY("step_v")), kBF16, {s.T, h.kv, h.d}, "step_v");
-        d[i].out = ptr(item(x[i], KEY("out")), kBF16, {s.T, h.heads, h.d}, "out");
+        const int P = whole_number(x.at(i, KEY("P")));
+        d[i].block_table = table_of(x.at(i, KEY("block_table"), true), P, pg.page_size);
+        d[i].q = ptr(x.at(i, KEY("q")), kBF16, {s.T, h.heads, h.d}, "q");
+        d[i].step_k = ptr(x.at(i, KEY("step_k")), kBF16, {s.T, h.kv, h.d}, "step_k");
+        d[i].step_v = ptr(x.at(i, KEY("step_v")), kBF16, {s.T, h.kv, h.d}, "step_v");
+        d[i].out = ptr(x.at(i, KEY("out")), kBF16, {s.T, h.heads, h.d}, "out");
         d[i].P = P;
         d[i].reserved = 0;
     }
@@ -474,15 +485,15 @@ LA_ENTRY(kv_commit_paged)
 
 LA_ENTRY(kv_commit_batch)
 {
-    const Items x(a[0]);
+    Items x(a[0]);
     const Step s(a + 1);
     const int kv = integer(a[4]), d = integer(a[5]);
     std::vector<la_commit_desc> c((size_t)x.size());
     int page_size = 0, n_pages = 0;
     for (int i = 0; i < x.size(); ++i) {
-        const int P = whole_number(item(x[i], KEY("P")));
-        PyObject* const table = item(x[i], KEY("block_table"), true);
-        PyObject *const kc = item(x[i], KEY("k_cache")), *const vc = item(x[i], KEY("v_cache"));
+        const int P = whole_number(x.at(i, KEY("P")));
+        PyObject* const table = x.at(i, KEY("block_table"), true);
+        PyObject *const kc = x.at(i, KEY("k_cache")), *const vc = x.at(i, KEY("v_cache"));
         if (table != Py_None) {
             c[i].block_table = table_of(table, (int64_t)P + s.N, (int)size_of(kc, 2, "k_pages"));
             const Pages pg = pages_of(kc, vc, kv, d);
@@ -502,10 +513,10 @@ LA_ENTRY(kv_commit_batch)
             c[i].block_table = nullptr;
             c[i].capacity = cap;
         }
-        c[i].step_k = ptr(item(x[i], KEY("step_k")), kBF16, {s.T, kv, d}, "step_k");
-        c[i].step_v = ptr(item(x[i], KEY("step_v")), kBF16, {s.T, kv, d}, "step_v");
-        c[i].best = ptr<int>(item(x[i], KEY("best")), kI32, {1}, "best");
-        c[i].n_out = ptr<int>(item(x[i], KEY("n_out")), kI32, {1}, "n_out");
+        c[i].step_k = ptr(x.at(i, KEY("step_k")), kBF16, {s.T, kv, d}, "step_k");
+        c[i].step_v = ptr(x.at(i, KEY("step_v")), kBF16, {s.T, kv, d}, "step_v");
+        c[i].best = ptr<int>(x.at(i, KEY("best")), kI32, {1}, "best");
+        c[i].n_out = ptr<int>(x.at(i, KEY("n_out")), kI32, {1}, "n_out");
         c[i].P = P;
         c[i].reserved = 0;
     }
@@ -553,14 +564,14 @@ LA_ENTRY(verify_step)
 
 LA_ENTRY(verify_step_batch)
 {
-    const Items x(a[0]);
+    Items x(a[0]);
     const Step s(a + 1);
     const int V = integer(a[4]);
     std::vector<la_verify_desc> d((size_t)x.size());
     for (int i = 0; i < x.size(); ++i)
-        fill(d[i], item(x[i], KEY("logits_cur")), item(x[i], KEY("logits_look"), true), item(x[i], KEY("logits_cand"), true),
-             item(x[i], KEY("cand_tokens"), true), item(x[i], KEY("out_tokens")), item(x[i], KEY("n_out")), item(x[i], KEY("best")),
-             item(x[i], KEY("new_window"), true), item(x[i], KEY("accept_len"), true), s, V);
+        fill(d[i], x.at(i, KEY("logits_cur")), x.at(i, KEY("logits_look"), true), x.at(i, KEY("logits_cand"), true),
+             x.at(i, KEY("cand_tokens"), true), x.at(i, KEY("out_tokens")), x.at(i, KEY("n_out")), x.at(i, KEY("best")),
+             x.at(i, KEY("new_window"), true), x.at(i, KEY("accept_len"), true), s, V);
     void* st = stream_of(a[5]);
     call([&] { return la_verify_step_batch(d.data(), x.size(), s.W, s.N, s.G, V, st); });
 }
@@ -593,13 +604,13 @@ LA_ENTRY(verify_sample)
 
 LA_ENTRY(verify_sample_batch)
 {
-    const Items x(a[0]);
+    Items x(a[0]);
     const int N = integer(a[1]), G = integer(a[2]), V = integer(a[3]);
     std::vector<la_sample_desc> d((size_t)x.size());
     for (int i = 0; i < x.size(); ++i)
-        fill(d[i], item(x[i], KEY("logits_cur")), item(x[i], KEY("logits_cand"), true), item(x[i], KEY("cand_tokens"), true),
-             item(x[i], KEY("u_test"), true), item(x[i], KEY("u_final")), item(x[i], KEY("temperature")), item(x[i], KEY("out_tokens")),
-             item(x[i], KEY("n_out")), N, G, V);
+        fill(d[i], x.at(i, KEY("logits_cur")), x.at(i, KEY("logits_cand"), true), x.at(i, KEY("cand_tokens"), true),
+             x.at(i, KEY("u_test"), true), x.at(i, KEY("u_final")), x.at(i, KEY("temperature")), x.at(i, KEY("out_tokens")),
+             x.at(i, KEY("n_out")), N, G, V);
     void* st = stream_of(a[4]);
     call([&] { return la_verify_sample_batch(d.data(), x.size(), N, G, V, st); });
 }

@@ -1,5 +1,9 @@
 """What the binding refuses before anything reaches the library: tensors of the wrong kind, place,
 type, shape or layout raise, and name the argument."""
+import os
+import subprocess
+import sys
+
 import pytest
 import torch
 
@@ -50,3 +54,56 @@ def test_refused_on_the_gpu(name):
         step(dict(good, **{name: torch.zeros(SHAPES[name] + (2,), dtype=torch.bfloat16, device="cuda")[..., 0]}))
     with pytest.raises(ValueError, match="%s must live on the GPU" % name):
         step(dict(good, **{name: good[name].cpu()}))
+
+
+class Made:
+    """A descriptor that makes its values when it is asked for them: nobody else holds them."""
+
+    def __init__(self, values):
+        self.values = values
+
+    def __getitem__(self, key):
+        v = self.values[key]
+        return v.view(v.shape) if isinstance(v, torch.Tensor) else int(str(v)) if isinstance(v, int) else v
+
+
+MADE_ON_ACCESS = """
+import torch
+from paper_2402_02057_amd import binding
+
+class Made:
+    def __getitem__(self, key):
+        return int("123456789") if key == "P" else torch.zeros(1, 2, 64, 64)
+
+for call in (lambda x: binding.la_step_attention_batch(x, 2, 3, 1, 4, 2, 64),
+             lambda x: binding.la_step_attention_batch_paged(x, torch.zeros(1, 2, 64, 64), torch.zeros(1, 2, 64, 64), 2, 3, 1, 4, 2, 64),
+             lambda x: binding.la_kv_commit_batch(x, 2, 3, 1, 2, 64),
+             lambda x: binding.la_verify_step_batch(x, 2, 3, 1, 50),
+             lambda x: binding.la_verify_sample_batch(x, 3, 1, 50)):
+    try:
+        call([Made()])
+        raise SystemExit("accepted")
+    except ValueError as e:
+        print(e)
+"""
+
+
+def test_values_made_on_access_are_held():
+    """Under Python's debugging allocator, which overwrites what is freed."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", MADE_ON_ACCESS], cwd=root, env=dict(os.environ, PYTHONMALLOC="debug"),
+                       stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True, timeout=300)
+    assert r.returncode == 0, (r.returncode, r.stderr[-500:])
+    assert r.stdout.count("GPU") >= 3 and "block_table must hold at least" in r.stdout, r.stdout
+
+
+@pytest.mark.gpu
+def test_descriptors_that_make_their_values_give_what_dicts_give():
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    seqs = [dict({k: torch.randn(s, device="cuda", generator=gen).bfloat16() for k, s in SHAPES.items()}, P=P) for _ in range(3)]
+    binding.la_step_attention_batch([Made(x) for x in seqs], W, N, G, H, KV, D)
+    made = [x["out"].clone() for x in seqs]
+    binding.la_step_attention_batch(seqs, W, N, G, H, KV, D)
+    torch.cuda.synchronize()
+    assert all(torch.equal(x["out"], m) for x, m in zip(seqs, made))
