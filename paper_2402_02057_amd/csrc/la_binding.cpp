@@ -180,7 +180,8 @@ struct Heads {
 // The key `s` as an interned Python string, made once.
 #define KEY(s) ([]() -> PyObject* { static PyObject* const k = PyUnicode_InternFromString(s); return k; }())
 
-// The sequence of descriptors (a tuple or list is used as it is).
+// The sequence of descriptors (a tuple or list is used as it is).  A value is what x[key] gives, an
+// optional one what x.get(key) gives.
 class Items {
 public:
     explicit Items(PyObject* o) : fast(PySequence_Fast(o, "a sequence of dicts is expected"))
@@ -201,12 +202,19 @@ public:
     {
         PyObject* const x = PySequence_Fast_GET_ITEM(fast, i);
         PyObject* v = nullptr;
-        if (PyDict_Check(x)) {
+        if (PyDict_CheckExact(x)) {
             v = PyDict_GetItemWithError(x, k);
-        } else {
-            v = PyObject_GetItem(x, k);
+        } else {                               // (a subclass of dict may answer for itself, too)
+            PyObject* const get = or_none ? PyObject_GetAttrString(x, "get") : nullptr;
+            if (or_none && !get) {
+                if (!PyErr_ExceptionMatches(PyExc_AttributeError)) throw Raised();
+                PyErr_Clear();
+            }
+            v = get ? PyObject_CallFunctionObjArgs(get, k, nullptr) : PyObject_GetItem(x, k);
+            Py_XDECREF(get);
             if (v) held.push_back(v);
-            else if (or_none && PyErr_ExceptionMatches(PyExc_KeyError)) PyErr_Clear();
+            else if (!or_none || get || !PyErr_ExceptionMatches(PyExc_KeyError)) throw Raised();
+            else PyErr_Clear();
         }
         if (!v && !PyErr_Occurred()) {
             if (or_none) v = Py_None;

@@ -97,6 +97,26 @@ def test_values_made_on_access_are_held():
     assert r.stdout.count("GPU") >= 3 and "block_table must hold at least" in r.stdout, r.stdout
 
 
+class Answering(dict):
+    """A dict that answers for itself: missing keys, and another value than the one it stores."""
+
+    def __missing__(self, key):
+        raise RuntimeError("asked for " + key)
+
+    def __getitem__(self, key):
+        return None if key == "q" else super().__getitem__(key)
+
+
+def test_dict_subclasses_answer_for_themselves():
+    with pytest.raises(RuntimeError, match="asked for P"):
+        binding.la_step_attention_batch([Answering()], W, N, G, H, KV, D)
+    with pytest.raises(ValueError, match="q is None"):
+        binding.la_step_attention_batch([Answering(tensors("cpu"), P=P)], W, N, G, H, KV, D)
+    # an optional key is asked for with get(), which does not run __missing__
+    with pytest.raises(ValueError, match="k_cache must live on the GPU"):
+        binding.la_kv_commit_batch([Answering(tensors("cpu"), P=P)], W, N, G, KV, D)
+
+
 @pytest.mark.gpu
 def test_descriptors_that_make_their_values_give_what_dicts_give():
     gen = torch.Generator(device="cuda")
