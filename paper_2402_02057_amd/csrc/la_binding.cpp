@@ -180,27 +180,28 @@ struct Heads {
 // The key `s` as an interned Python string, made once.
 #define KEY(s) ([]() -> PyObject* { static PyObject* const k = PyUnicode_InternFromString(s); return k; }())
 
-// The sequence of descriptors (a tuple or list is used as it is).  A value is what x[key] gives, an
+// The sequence of descriptors, as a tuple of our own: a list may grow or shrink while a descriptor is
+// asked for its values, or, from another thread, while the call runs without the lock.  A value is what x[key] gives, an
 // optional one what x.get(key) gives.
 class Items {
 public:
-    explicit Items(PyObject* o) : fast(PySequence_Fast(o, "a sequence of dicts is expected"))
+    explicit Items(PyObject* o) : items(PySequence_Tuple(o))
     {
-        if (!fast) throw Raised();
+        if (!items) throw Raised();
     }
     ~Items()
     {
-        Py_DECREF(fast);
+        Py_DECREF(items);
         for (PyObject* v : held) Py_DECREF(v);
     }
     Items(const Items&) = delete;
-    int size() const { return (int)PySequence_Fast_GET_SIZE(fast); }
+    int size() const { return (int)PyTuple_GET_SIZE(items); }
 
     // The value of descriptor i under `k`, valid until this object goes: a dict holds its values, what
     // another mapping hands out may exist nowhere else and is kept here until the call has returned.
     PyObject* at(int i, PyObject* k, bool or_none = false)
     {
-        PyObject* const x = PySequence_Fast_GET_ITEM(fast, i);
+        PyObject* const x = PyTuple_GET_ITEM(items, i);
         PyObject* v = nullptr;
         if (PyDict_CheckExact(x)) {
             v = PyDict_GetItemWithError(x, k);
@@ -225,7 +226,7 @@ public:
     }
 
 private:
-    PyObject* fast;
+    PyObject* items;
     std::vector<PyObject*> held;
 };
 

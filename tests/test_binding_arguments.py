@@ -127,3 +127,18 @@ def test_descriptors_that_make_their_values_give_what_dicts_give():
     binding.la_step_attention_batch(seqs, W, N, G, H, KV, D)
     torch.cuda.synchronize()
     assert all(torch.equal(x["out"], m) for x, m in zip(seqs, made))
+
+
+@pytest.mark.gpu
+def test_a_list_that_grows_during_the_call_is_taken_as_it_was():
+    class Growing(Made):
+        def __getitem__(self, key):
+            seqs.extend([self] * 64)
+            return super().__getitem__(key)
+
+    x = dict(tensors("cuda"), P=P)
+    seqs = [Growing(x), Growing(dict(x, out=torch.full_like(x["out"], float("nan"))))]
+    last = seqs[-1]
+    binding.la_step_attention_batch(seqs, W, N, G, H, KV, D)
+    torch.cuda.synchronize()
+    assert len(seqs) > 64 and bool(torch.isfinite(last.values["out"]).all())
