@@ -23,6 +23,13 @@ namespace {
 
 struct Raised {};  // a Python exception is set
 
+struct Owned {     // a reference that goes with its scope
+    PyObject* const o;
+    explicit Owned(PyObject* p) : o(p) {}
+    ~Owned() { Py_XDECREF(o); }
+    Owned(const Owned&) = delete;
+};
+
 PyObject* g_la_error = nullptr;  // binding.LaError
 
 constexpr at::ScalarType kBF16 = at::kBFloat16, kF32 = at::kFloat, kI32 = at::kInt, kU8 = at::kByte;
@@ -98,23 +105,36 @@ int64_t size_of(PyObject* o, int dim, const char* name)
     return t.size(dim);
 }
 
+// A size that the C functions take as an int: what does not fit one is refused, before anything is
+// compared with the rest of it.
 int integer(PyObject* o)
 {
-    const long v = PyLong_AsLong(o);
-    if (v == -1 && PyErr_Occurred()) throw Raised();
+    int overflow = 0;
+    const long v = PyLong_AsLongAndOverflow(o, &overflow);
+    if (v == -1 && !overflow && PyErr_Occurred()) throw Raised();
+    if (overflow || v != (int)v) {
+        PyErr_Format(PyExc_ValueError, "%S does not fit 32 bits", o);
+        throw Raised();
+    }
     return (int)v;
+}
+
+int integer(int64_t n, const char* name)
+{
+    if (n != (int)n) {
+        PyErr_Format(PyExc_ValueError, "%s: a size of %lld does not fit 32 bits", name, (long long)n);
+        throw Raised();
+    }
+    return (int)n;
 }
 
 // (a descriptor's prefix length may be anything int() takes)
 int whole_number(PyObject* o)
 {
     if (PyLong_Check(o)) return integer(o);
-    PyObject* n = PyNumber_Long(o);
-    if (!n) throw Raised();
-    const long v = PyLong_AsLong(n);
-    Py_DECREF(n);
-    if (v == -1 && PyErr_Occurred()) throw Raised();
-    return (int)v;
+    const Owned n(PyNumber_Long(o));
+    if (!n.o) throw Raised();
+    return integer(n.o);
 }
 
 int truth(PyObject* o)
@@ -167,7 +187,7 @@ void call(F&& f)
 struct Step {
     int W, N, G;
     int64_t T;
-    explicit Step(PyObject* const* a) : W(integer(a[0])), N(integer(a[1])), G(integer(a[2])), T(1 + (int64_t)(W + G) * (N - 1)) {}
+    explicit Step(PyObject* const* a) : W(integer(a[0])), N(integer(a[1])), G(integer(a[2])), T(1 + ((int64_t)W + G) * ((int64_t)N - 1)) {}
 };
 
 struct Heads {
@@ -238,8 +258,8 @@ struct Pages {
 Pages pages_of(PyObject* k_pages, PyObject* v_pages, int kv_heads, int d)
 {
     Pages p;
-    p.n_pages = (int)size_of(k_pages, 0, "k_pages");
-    p.page_size = (int)size_of(k_pages, 2, "k_pages");
+    p.n_pages = integer(size_of(k_pages, 0, "k_pages"), "k_pages");
+    p.page_size = integer(size_of(k_pages, 2, "k_pages"), "k_pages");
     p.k = ptr(k_pages, kBF16, {p.n_pages, kv_heads, p.page_size, d}, "k_pages");
     p.v = ptr(v_pages, kBF16, {p.n_pages, kv_heads, p.page_size, d}, "v_pages");
     return p;
@@ -324,14 +344,14 @@ LA_ENTRY(step_rope)
     const int P = integer(a[4]);
     const Step s(a + 5);
     const Heads h(a + 8);
-    const int64_t n_pos = size_of(a[2], 0, "cos");
+    const int n_pos = integer(size_of(a[2], 0, "cos"), "cos");
     void* q = ptr(a[0], kBF16, {s.T, h.heads, h.d}, "q", true);   // None: the keys alone
     void* sk = ptr(a[1], kBF16, {s.T, h.kv, h.d}, "step_k");
     const float* c = ptr<float>(a[2], kF32, {n_pos, h.d / 2}, "cos");
     const float* n = ptr<float>(a[3], kF32, {n_pos, h.d / 2}, "sin");
     const int inter = truth(a[11]);
     void* st = stream_of(a[12]);
-    call([&] { return la_step_rope(q, sk, c, n, (int)n_pos, P, s.W, s.N, s.G, h.heads, h.kv, h.d, inter, st); });
+    call([&] { return la_step_rope(q, sk, c, n, n_pos, P, s.W, s.N, s.G, h.heads, h.kv, h.d, inter, st); });
 }
 
 LA_ENTRY(step_attention_rope)
@@ -339,7 +359,7 @@ LA_ENTRY(step_attention_rope)
     const int P = integer(a[7]);
     const Step s(a + 8);
     const Heads h(a + 11);
-    const int64_t n_pos = size_of(a[5], 0, "cos");
+    const int n_pos = integer(size_of(a[5], 0, "cos"), "cos");
     const void* q = ptr(a[0], kBF16, {s.T, h.heads, h.d}, "q");
     const void* kc = ptr(a[1], kBF16, {h.kv, P, h.d}, "k_cache", true);
     const void* vc = ptr(a[2], kBF16, {h.kv, P, h.d}, "v_cache", true);
@@ -351,7 +371,7 @@ LA_ENTRY(step_attention_rope)
     const int inter = truth(a[15]), rotate = truth(a[16]);
     void* st = stream_of(a[17]);
     call([&] {
-        return la_step_attention_rope(q, kc, vc, sk, sv, c, n, (int)n_pos, inter, rotate, P, s.W, s.N, s.G, h.heads, h.kv, h.d,
+        return la_step_attention_rope(q, kc, vc, sk, sv, c, n, n_pos, inter, rotate, P, s.W, s.N, s.G, h.heads, h.kv, h.d,
                                       out, st);
     });
 }
@@ -377,7 +397,8 @@ LA_ENTRY(kv_commit_rope)
     const int P = integer(a[6]);
     const Step s(a + 7);
     const int kv = integer(a[10]), d = integer(a[11]);
-    const int64_t cap = size_of(a[0], 1, "k_cache"), n_pos = size_of(a[4], 0, "cos");
+    const int64_t cap = size_of(a[0], 1, "k_cache");
+    const int n_pos = integer(size_of(a[4], 0, "cos"), "cos");
     void* kc = ptr(a[0], kBF16, {kv, cap, d}, "k_cache");
     void* vc = ptr(a[1], kBF16, {kv, cap, d}, "v_cache");
     const void* sk = ptr(a[2], kBF16, {s.T, kv, d}, "step_k");
@@ -389,7 +410,7 @@ LA_ENTRY(kv_commit_rope)
     const int inter = truth(a[14]);
     void* st = stream_of(a[15]);
     call([&] {
-        return la_kv_commit_rope(kc, vc, cap, sk, sv, c, n, (int)n_pos, inter, P, s.W, s.N, s.G, kv, d, best, n_out, st);
+        return la_kv_commit_rope(kc, vc, cap, sk, sv, c, n, n_pos, inter, P, s.W, s.N, s.G, kv, d, best, n_out, st);
     });
 }
 
@@ -443,7 +464,7 @@ LA_ENTRY(step_attention_rows)
     const int P = integer(a[6]);
     const Step s(a + 7);
     const Heads h(a + 10);
-    const int64_t n = tensor(a[5], "row_ids").numel();
+    const int n = integer(tensor(a[5], "row_ids").numel(), "row_ids");
     const void* q = ptr(a[0], kBF16, {n, h.heads, h.d}, "q");
     const void* kc = ptr(a[1], kBF16, {h.kv, P, h.d}, "k_cache", true);
     const void* vc = ptr(a[2], kBF16, {h.kv, P, h.d}, "v_cache", true);
@@ -453,7 +474,7 @@ LA_ENTRY(step_attention_rows)
     void* out = ptr(a[13], kBF16, {n, h.heads, h.d}, "out");
     void* st = stream_of(a[14]);
     call([&] {
-        return la_step_attention_rows(q, kc, vc, sk, sv, ids, (int)n, P, s.W, s.N, s.G, h.heads, h.kv, h.d, out, st);
+        return la_step_attention_rows(q, kc, vc, sk, sv, ids, n, P, s.W, s.N, s.G, h.heads, h.kv, h.d, out, st);
     });
 }
 
@@ -462,7 +483,7 @@ LA_ENTRY(step_attention_paged)
     const int P = integer(a[6]);
     const Step s(a + 7);
     const Heads h(a + 10);
-    const int* table = table_of(a[3], P, (int)size_of(a[1], 2, "k_pages"));
+    const int* table = table_of(a[3], P, integer(size_of(a[1], 2, "k_pages"), "k_pages"));
     const Pages pg = pages_of(a[1], a[2], h.kv, h.d);
     const void* q = ptr(a[0], kBF16, {s.T, h.heads, h.d}, "q");
     const void* sk = ptr(a[4], kBF16, {s.T, h.kv, h.d}, "step_k");
@@ -480,7 +501,7 @@ LA_ENTRY(kv_commit_paged)
     const int P = integer(a[5]);
     const Step s(a + 6);
     const int kv = integer(a[9]), d = integer(a[10]);
-    const int* table = table_of(a[2], (int64_t)P + s.N, (int)size_of(a[0], 2, "k_pages"));
+    const int* table = table_of(a[2], (int64_t)P + s.N, integer(size_of(a[0], 2, "k_pages"), "k_pages"));
     const Pages pg = pages_of(a[0], a[1], kv, d);
     const void* sk = ptr(a[3], kBF16, {s.T, kv, d}, "step_k");
     const void* sv = ptr(a[4], kBF16, {s.T, kv, d}, "step_v");
@@ -504,7 +525,7 @@ LA_ENTRY(kv_commit_batch)
         PyObject* const table = x.at(i, KEY("block_table"), true);
         PyObject *const kc = x.at(i, KEY("k_cache")), *const vc = x.at(i, KEY("v_cache"));
         if (table != Py_None) {
-            c[i].block_table = table_of(table, (int64_t)P + s.N, (int)size_of(kc, 2, "k_pages"));
+            c[i].block_table = table_of(table, (int64_t)P + s.N, integer(size_of(kc, 2, "k_pages"), "k_pages"));
             const Pages pg = pages_of(kc, vc, kv, d);
             if (page_size && (pg.page_size != page_size || pg.n_pages != n_pages)) {
                 PyErr_SetString(PyExc_ValueError, "all page pools of a launch must have the same geometry");

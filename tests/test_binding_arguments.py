@@ -41,6 +41,20 @@ def test_refused_without_a_gpu(name, value, error, text):
         step(tensors("cpu"), W="2")
 
 
+@pytest.mark.parametrize("name", ["P", "W", "N", "G", "heads", "kv_heads", "head_dim"])
+@pytest.mark.parametrize("by", [1 << 32, -(1 << 32), 1 << 31, 1 << 64, -(1 << 80)])
+def test_sizes_that_do_not_fit_are_refused(name, by):
+    """Before the tensors are looked at, which live on the host here: the rest of 2^32 fits them."""
+    right = dict(P=P, W=W, N=N, G=G, heads=H, kv_heads=KV, head_dim=D)
+    with pytest.raises(ValueError, match="%d does not fit 32 bits" % (right[name] + by)):
+        step(tensors("cpu"), **{name: right[name] + by})
+    if name == "P":
+        with pytest.raises(ValueError, match="does not fit 32 bits"):
+            binding.la_step_attention_batch([dict(tensors("cpu"), P=P + by)], W, N, G, H, KV, D)
+        with pytest.raises(ValueError, match="does not fit 32 bits"):
+            binding.la_step_attention_batch([dict(tensors("cpu"), P=str(P + by))], W, N, G, H, KV, D)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", sorted(SHAPES))
 def test_refused_on_the_gpu(name):
