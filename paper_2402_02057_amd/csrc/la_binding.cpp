@@ -144,11 +144,12 @@ int truth(PyObject* o)
     return v;
 }
 
+// (anything float() takes)
 float real(PyObject* o)
 {
-    const double v = PyFloat_AsDouble(o);
-    if (v == -1.0 && PyErr_Occurred()) throw Raised();
-    return (float)v;
+    const Owned f(PyNumber_Float(o));
+    if (!f.o) throw Raised();
+    return (float)PyFloat_AS_DOUBLE(f.o);
 }
 
 // None: the current stream of the current device; a torch stream; or a stream handle as a number.

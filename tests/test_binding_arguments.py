@@ -132,6 +132,25 @@ def test_dict_subclasses_answer_for_themselves():
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("temperature", ["0.5", 0.5, torch.tensor(0.5), b"0.5"])
+def test_temperature_is_anything_float_takes(temperature):
+    V = 50
+    logits = torch.linspace(0.0, 3.0, V, device="cuda")
+    u = torch.full((1,), 0.25, device="cuda")
+    outs = []
+    for t in (temperature, 0.5):
+        out, n_out = (torch.zeros(n, dtype=torch.int32, device="cuda") for n in (N, 1))
+        binding.la_verify_sample(logits, None, None, None, u, t, N, 0, V, out, n_out)
+        batched, n_batched = torch.zeros_like(out), torch.zeros_like(n_out)
+        binding.la_verify_sample_batch([dict(logits_cur=logits, u_final=u, temperature=t, out_tokens=batched, n_out=n_batched)], N, 0, V)
+        outs += [out, batched]
+        assert int(n_out) == int(n_batched) == 1
+    assert all(torch.equal(o, outs[0]) for o in outs)
+    with pytest.raises(ValueError, match="could not convert"):
+        binding.la_verify_sample(logits, None, None, None, u, "warm", N, 0, V, out, n_out)
+
+
+@pytest.mark.gpu
 def test_descriptors_that_make_their_values_give_what_dicts_give():
     gen = torch.Generator(device="cuda")
     gen.manual_seed(3)
@@ -141,6 +160,38 @@ def test_descriptors_that_make_their_values_give_what_dicts_give():
     binding.la_step_attention_batch(seqs, W, N, G, H, KV, D)
     torch.cuda.synchronize()
     assert all(torch.equal(x["out"], m) for x, m in zip(seqs, made))
+
+
+@pytest.mark.gpu
+def test_streams_are_none_a_stream_or_a_handle():
+    x = tensors("cuda")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+
+    class Handle:
+        def __int__(self):
+            return side.cuda_stream
+
+    outs = []
+    for stream in (None, side, side.cuda_stream, Handle(), 0, torch.cuda.ExternalStream(side.cuda_stream)):
+        out = torch.full_like(x["out"], float("nan"))
+        side.wait_stream(torch.cuda.current_stream())
+        binding.la_step_attention(*(x[k] for k in ("q", "k_cache", "v_cache", "step_k", "step_v")), P, W, N, G, H, KV, D, out, stream)
+        torch.cuda.synchronize()
+        outs.append(out)
+    assert all(torch.equal(o, outs[0]) and bool(torch.isfinite(o).all()) for o in outs)
+    with pytest.raises(TypeError):
+        binding.la_step_attention(*(x[k] for k in ("q", "k_cache", "v_cache", "step_k", "step_v")), P, W, N, G, H, KV, D, out, object())
+
+
+@pytest.mark.gpu
+def test_tuples_do_as_well_as_lists():
+    x = dict(tensors("cuda"), P=P)
+    for seqs in ([x, x], (x, x)):
+        x["out"].fill_(float("nan"))
+        binding.la_step_attention_batch(seqs, W, N, G, H, KV, D)
+        torch.cuda.synchronize()
+        assert bool(torch.isfinite(x["out"]).all())
 
 
 @pytest.mark.gpu
