@@ -123,6 +123,33 @@ def test_no_group_lies_on_two_xcds(lib):
             assert all(b.groups_whole(form, x) for x in set(cuts)), (b.chunks, b.tiles, b.kv_heads, form, cuts)
 
 
+@pytest.mark.parametrize("prefixes, W, heads, kv_heads, form, cuts, place", [
+    ([256] * 6, 10, 32, 8, 128, [1] * 6, [0, 1, 2, 3, 4, 5]),
+    ([256] * 4, 15, 32, 8, 64, [1] * 4, [0, 1, 2, 3]),
+    ([2000, 1300, 700, 90, 40], 10, 32, 8, 128, [4, 3, 2, 1, 1], [0, 1, 2, 3, 4]),
+    ([1101, 1100, 1099, 130, 64, 0], 5, 8, 2, 64, [1] * 6, [0, 1, 2, 3, 4, 5]),
+    ([100] * 16, 5, 64, 64, 64, [1] * 16, list(range(16))),
+    ([3000, 900, 800, 700], 5, 32, 8, 64, [5, 2, 2, 1], [0, 3, 1, 2]),
+    ([1021 - 37 * i for i in range(16)], 10, 32, 8, 128, [2] * 5 + [1] * 11, [5, 6, 7, 8, 9, 10, 11, 12, 13, 0, 1, 2, 3, 14, 15, 4]),
+    ([14559, 13246, 13048, 7849, 2492, 2413, 2180, 1253], 15, 32, 8, 128, [2, 2, 2, 1, 1, 1, 1, 1], [3, 0, 1, 2, 4, 5, 6, 7]),
+], ids=["rows128", "rows64", "mixed", "few-heads", "rounds", "reordered", "serving", "ragged"])
+def test_form_cuts_and_order(lib, prefixes, W, heads, kv_heads, form, cuts, place):
+    assert Batch(prefixes, 1 + 8 * W, heads, kv_heads, 128).plan(lib) == (form, cuts, place)
+
+
+def test_longest_ranges_start_first(lib):
+    """Cost of a workgroup in chunks: its range, 6 more in the 128-row form and 5 in the 64-row one, and 1
+    or 2 for the exchange of a cut step."""
+    reordered = 0
+    for b in batches(1000, seed=7, head_dims=(128,)):
+        form, cuts, place = b.plan(lib)
+        cost = [-(-c // x) + (0 if x == 1 else 1 if form == 128 else 2) for c, x in zip(b.chunks, cuts)]
+        if place != sorted(place):
+            assert all(cost[i] >= cost[j] for i, j in zip(place, place[1:])), (b.chunks, cuts, place)
+            reordered += 1
+    assert reordered > 50
+
+
 def test_workspace_of_a_launch_is_bounded(lib):
     """What the library reserves (la_api.hip: 32 MB of partial results, 512 KB of tickets) holds any batch."""
     for b in batches(2000, seed=6):

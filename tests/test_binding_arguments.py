@@ -24,6 +24,75 @@ def step(x, **sizes):
     return binding.la_step_attention(x["q"], x["k_cache"], x["v_cache"], x["step_k"], x["step_v"], out=x["out"], **s)
 
 
+BF, F, I, U = torch.bfloat16, torch.float32, torch.int32, torch.uint8
+V, CAP, PAGE, POS = 50, 16, 64, 32
+STEP = {"P": P, "W": W, "N": N, "G": G, "heads": H, "kv_heads": KV, "head_dim": D}
+CACHE = {"k_cache": ((KV, P, D), BF), "v_cache": ((KV, P, D), BF)}
+PAGES = {"k_pages": ((2, KV, PAGE, D), BF), "v_pages": ((2, KV, PAGE, D), BF)}
+ROOM = {"k_cache": ((KV, CAP, D), BF), "v_cache": ((KV, CAP, D), BF)}
+ROWS = {"q": ((T, H, D), BF), "step_k": ((T, KV, D), BF), "step_v": ((T, KV, D), BF), "out": ((T, H, D), BF)}
+KEYS = {"step_k": ((T, KV, D), BF), "step_v": ((T, KV, D), BF)}
+TABLES = {"cos": ((POS, D // 2), F), "sin": ((POS, D // 2), F)}
+ENDED = {"best": ((1,), I), "n_out": ((1,), I)}
+GREEDY = {"logits_cur": ((V,), F), "logits_look": ((W, V), F), "logits_cand": ((G, N - 1, V), F), "cand_tokens": ((G, N - 1), I),
+          "out_tokens": ((N,), I), "n_out": ((1,), I), "best": ((1,), I), "new_window": ((W,), I), "accept_len": ((G,), I)}
+SAMPLED = {"logits_cur": ((V,), F), "logits_cand": ((G, N - 1, V), F), "cand_tokens": ((G, N - 1), I), "u_test": ((N - 1, G), F),
+           "u_final": ((1,), F), "out_tokens": ((N,), I), "n_out": ((1,), I)}
+# every entry point: its tensors (of a descriptor, in a batch), the sizes it takes, and a batch's own tensors
+ENTRIES = {
+    "la_step_attention": (dict(ROWS, **CACHE), STEP),
+    "la_step_attention_noalloc": (dict(ROWS, **CACHE), STEP),
+    "la_step_attention_fp8kv": (dict(ROWS, **{k: (v[0], U) for k, v in dict(CACHE, **KEYS).items()}, k_scale=((KV,), F), v_scale=((KV,), F)), STEP),
+    "la_step_attention_cap": (dict(ROWS, **ROOM), STEP),
+    "la_step_rope": (dict({k: ROWS[k] for k in ("q", "step_k")}, **TABLES), STEP),
+    "la_step_attention_rope": (dict(ROWS, **CACHE, **TABLES), STEP),
+    "la_step_attention_rows": (dict(ROWS, **CACHE, row_ids=((T,), I)), STEP),
+    "la_step_attention_paged": (dict(ROWS, **PAGES, block_table=((1,), I)), STEP),
+    "la_kv_commit": (dict(KEYS, **ROOM, **ENDED), {k: v for k, v in STEP.items() if k != "heads"}),
+    "la_kv_commit_rope": (dict(KEYS, **ROOM, **TABLES, **ENDED), {k: v for k, v in STEP.items() if k != "heads"}),
+    "la_kv_commit_paged": (dict(KEYS, **PAGES, block_table=((1,), I), **ENDED), {k: v for k, v in STEP.items() if k != "heads"}),
+    "la_verify": ({"logits": ((G, N - 1, V), F), "cand_tokens": ((G, N - 1), I), "accept_len": ((G,), I), "accepted": ((G, N - 1), I)},
+                  dict(G=G, N=N, V=V)),
+    "la_verify_step": (GREEDY, dict(W=W, N=N, G=G, V=V)),
+    "la_verify_sample": (SAMPLED, dict(temperature=0.8, N=N, G=G, V=V)),
+    "la_step_attention_batch": (dict(ROWS, **CACHE), {k: v for k, v in STEP.items() if k != "P"}, {}),
+    "la_step_attention_batch_paged": (dict(ROWS, block_table=((1,), I)), {k: v for k, v in STEP.items() if k != "P"}, PAGES),
+    "la_kv_commit_batch": (dict(KEYS, **ROOM, **ENDED), dict(W=W, N=N, G=G, kv_heads=KV, head_dim=D), {}),
+    "la_verify_step_batch": (GREEDY, dict(W=W, N=N, G=G, V=V), {}),
+    "la_verify_sample_batch": (SAMPLED, dict(N=N, G=G, V=V), {}),
+}
+
+
+def call(entry, change=None, device="cuda"):
+    """The entry point with all its tensors as they should be, but for the one named `change`."""
+    made, sizes, *batch = ENTRIES[entry]
+
+    def make(tensors):
+        x = {k: torch.zeros(shape, dtype=dtype, device=device) for k, (shape, dtype) in tensors.items()}
+        return {k: v.to({BF: F, F: torch.float64, I: torch.int64, U: torch.int8}[v.dtype]) if k == change else v for k, v in x.items()}
+    f = getattr(binding, entry)
+    if not batch:
+        return f(**make(made), **sizes)
+    descs = [dict(make(made), P=P, temperature=0.8) for _ in range(2)]
+    return f(descs, **make(batch[0]), **sizes)
+
+
+@pytest.mark.parametrize("entry", sorted(ENTRIES))
+def test_every_entry_point_refuses_host_tensors(entry):
+    with pytest.raises(ValueError, match="must live on the GPU"):
+        call(entry, device="cpu")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("entry", sorted(ENTRIES))
+def test_every_entry_point_checks_every_tensor(entry):
+    call(entry)
+    torch.cuda.synchronize()
+    for name in list(ENTRIES[entry][0]) + list(ENTRIES[entry][2] if len(ENTRIES[entry]) > 2 else []):
+        with pytest.raises(ValueError, match="^%s must be torch" % name):
+            call(entry, change=name)
+
+
 @pytest.mark.parametrize("name, value, error, text", [
     ("q", None, ValueError, "q is None"),
     ("q", [1.0], TypeError, "q must be a torch.Tensor"),

@@ -62,13 +62,15 @@ def test_batch_matches_the_oracle_and_the_single_calls(prefixes, W, N, G, H, KV,
     run_batch(list(prefixes), W, N, G, H, KV, d, seed=len(prefixes) + W, check_oracle={int(order[0]), int(order[-1])})
 
 
+# (what the planner makes of these is asserted in test_batch_plan.py)
 @pytest.mark.parametrize("prefixes,W,H,KV", [
     ([256] * 6, 10, 32, 8),                       # 128 rows uncut, where 64 rows would need a second round
     ([256] * 4, 15, 32, 8),                       # one round of 64-row workgroups, uncut
-    ([700, 40, 1300, 90, 2000], 10, 32, 8),       # cut once, twice and not at all; not in the order given
-    ([130, 0, 1100, 1099, 1101, 64], 5, 8, 2),    # fewer KV heads than XCDs, many cuts, nearly equal ranges
+    ([700, 40, 1300, 90, 2000], 10, 32, 8),       # 128 rows, cut into four, three and two ranges and not at all
+    ([130, 0, 1100, 1099, 1101, 64], 5, 8, 2),    # six row blocks: uncut, as a group would lie on two XCDs
     ([100] * 16 + [37], 5, 64, 64),               # several rounds, and one step left over for a second launch
-], ids=["rows128", "rows64", "mixed", "few-heads", "rounds"])
+    ([3000, 800, 900, 700], 5, 32, 8),            # the uncut step's workgroups before those of longer, cut ones
+], ids=["rows128", "rows64", "mixed", "few-heads", "rounds", "reordered"])
 def test_cuts_and_order_of_the_steps(prefixes, W, H, KV):
     print("case", dict(prefixes=prefixes, W=W, H=H, KV=KV), flush=True)
     order = np.argsort(prefixes, kind="stable")
