@@ -8,7 +8,7 @@ import subprocess
 
 import pytest
 
-from paper_2402_02057_amd import buildlib
+from paper_2402_02057_amd import buildlib, workloads as wl
 
 SHIM = r"""
 #include <chrono>
@@ -135,6 +135,22 @@ def test_no_group_lies_on_two_xcds(lib):
 ], ids=["rows128", "rows64", "mixed", "few-heads", "rounds", "reordered", "serving", "ragged"])
 def test_form_cuts_and_order(lib, prefixes, W, heads, kv_heads, form, cuts, place):
     assert Batch(prefixes, 1 + 8 * W, heads, kv_heads, 128).plan(lib) == (form, cuts, place)
+
+
+def ends(lib, b, form, cuts, place):
+    fixed, exchange = (6, 1) if form == 128 else (5, 2)
+    n, arr = len(cuts), ctypes.c_int * len(cuts)
+    wgs = [-(-b.units(form) * x // 8) for x in cuts]
+    cost = [-(-c // x) + fixed + (exchange if x > 1 else 0) for c, x in zip(b.chunks, cuts)]
+    return lib.launch_end(arr(*place), n, arr(*wgs), (ctypes.c_longlong * n)(*cost)) * (16 if form == 128 else 11)
+
+
+def test_no_launch_ends_later_than_under_the_bounding_rule(lib):
+    """By the planner's own times, with the steps in the order they come, longest prefix first."""
+    many = list(batches(2000, seed=8, head_dims=(128,))) + [Batch(wl.ragged_prefix_lengths(), 1 + 8 * W, 32, 8, 128) for W in wl.RAGGED_W]
+    for b in many:
+        form, cuts = b.bound()
+        assert ends(lib, b, *b.plan(lib)) <= ends(lib, b, form, cuts, range(len(cuts))), (b.chunks, b.tiles, b.kv_heads)
 
 
 def test_longest_ranges_start_first(lib):
