@@ -7,6 +7,7 @@
 #include <mutex>
 #include <vector>
 
+#include "la_batch_plan.h"
 #include "la_internal.h"
 
 namespace la {
@@ -65,9 +66,12 @@ la_status select_workspace(int set)
 }
 
 namespace {
-// A block is at least this large: what any batched launch needs (768 workgroups of cut steps with 36 KB
-// of partial results each and 384 split groups with eight tickets, la_batch_plan.h), and more than any one step.
+// A block is at least this large: what any batched launch needs (of 128-row workgroups, the largest:
+// 36 KB of partial results each, and for a group of them eight tickets 128 bytes apart), and more than
+// any one step.
 constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(32) << 20;
+static_assert(kMaxCutWorkgroups * (size_t(36) << 10) <= kLeastScratch && kMaxCutGroups * size_t(8 * 128) <= kLeastZeroed,
+              "a batched launch fits the least blocks");
 
 // Growing a block means hipMalloc (and a clear on the stream): neither may happen while the
 // stream is being captured into a graph - the allocation would invalidate the capture, the

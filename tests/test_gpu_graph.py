@@ -263,3 +263,37 @@ def test_a_batch_that_is_cut_is_captured_after_one_that_is_not():
             assert all(torch.equal(a["out"], b["out"]) for a, b in zip(few, eager))
     finally:
         binding.la_select_workspace(0)
+
+
+def test_a_batch_on_another_stream_leaves_a_running_capture_alone():
+    """An uncut batch needs no workspace; that it reserves one must not end the capture."""
+    W = G = N = 5
+    H, KV, d, P, T = 32, 8, 128, 512, 41
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(12)
+
+    def rb(*shape):
+        return torch.randn(shape, device="cuda", generator=gen).bfloat16()
+    seqs = [dict(q=rb(T, H, d), k_cache=rb(KV, P, d), v_cache=rb(KV, P, d), step_k=rb(T, KV, d), step_v=rb(T, KV, d), P=P,
+                 out=torch.empty((T, H, d), dtype=torch.bfloat16, device="cuda")) for _ in range(6)]
+    binding.la_step_attention_batch(seqs, W, N, G, H, KV, d)
+    torch.cuda.synchronize()
+    want = [x["out"].clone() for x in seqs]
+    x, side = torch.zeros(64, device="cuda"), torch.cuda.Stream()
+    for s in seqs:
+        s["out"].zero_()
+    torch.cuda.synchronize()
+    binding.la_select_workspace(13)                           # (a set that no other test uses)
+    try:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            x.add_(1.0)
+            binding.la_step_attention_batch(seqs, W, N, G, H, KV, d, stream=side)
+        torch.cuda.synchronize()
+        assert all(torch.equal(s["out"], w) for s, w in zip(seqs, want))
+        for _ in range(3):
+            graph.replay()
+        torch.cuda.synchronize()
+        assert x.tolist() == [3.0] * 64
+    finally:
+        binding.la_select_workspace(0)
