@@ -627,6 +627,8 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     // o[0 .. SPW-1] are the tile's 32-column slices db0 .. db0+SPW-1 summed over all key splits
     f32x16 o[C::DB];
     float m_run, l_run;
+    f32x4 lsum;                                   // row sums while the loop runs
+    const bf16x8 pick = row_sum_operand(lane);
     const int db0 = KS > 1 ? ks * C::SPW : 0;
     // Which of an iteration's chunks this wave takes.  Waves w and w + NW/2 (equal key index,
     // different tiles when RT = 2) share a SIMD: odd tiles take the chunks in rotated order, so
@@ -688,7 +690,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 
     for (int pass = 0;; ++pass) {
         m_run = kNegInf;
-        l_run = 0.0f;
+        lsum = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -879,7 +881,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 const float neg_mc = -m_use * sl2;
                 if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                     const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                    l_run *= alpha;
+                    scale_row_sums(lsum, alpha, lane);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -887,27 +889,15 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 }
                 m_run = m_new;
                 // P in bf16, as the PV product uses it; the row sum adds up those same rounded
-                // values (two per instruction), so that numerator and denominator agree
+                // values (on the matrix cores), so that numerator and denominator agree
                 bf16x8 pf[2];
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
                     pf[i >> 3][i & 7] = (__bf16)fast_exp2(__builtin_fmaf(s[i], sl2, neg_mc));
-                {
-                    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-                    float psum0 = 0.0f, psum1 = 0.0f;
-#pragma unroll
-                    for (int kk = 0; kk < 2; ++kk) {
-                        psum0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][0], pf[kk][1]}, ones, psum0, false);
-                        psum1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][2], pf[kk][3]}, ones, psum1, false);
-                        psum0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][4], pf[kk][5]}, ones, psum0, false);
-                        psum1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][6], pf[kk][7]}, ones, psum1, false);
-                    }
-                    l_run += psum0 + psum1;
-                }
-
                 // ---- O^T += V^T P^T
 #pragma unroll
-                for (int kk = 0; kk < 2; ++kk)
+                for (int kk = 0; kk < 2; ++kk) {
+                    lsum = add_row_sums(pick, pf[kk], lsum);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db) {
                         bf16x8 a;
@@ -915,6 +905,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                         else a = fp8x8_to_bf16((unsigned)vraw[kk][db][0], (unsigned)vraw[kk][db][1]);
                         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, pf[kk], o[db], 0, 0, 0);
                     }
+                }
             }
             }
 #pragma unroll
@@ -928,8 +919,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
         }
 
         LA_STAMP(3);
-        // the two half-waves of a row hold the sums over their own keys
-        l_run += __shfl_xor(l_run, 32, 64);
+        l_run = row_sum(lsum, lane);
 
         // ---- where the merge leaves its data: ring stages that nobody reads any more.  The
         //      waves are at most one iteration apart, so once a wave is past the loop the others

@@ -107,6 +107,37 @@ __device__ __forceinline__ float max_across_halves(float x)
     return max2(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
+// Row sums of the softmax weights on the matrix cores.  v_dot2c_f32_bf16 over pairs of weights is one
+// instruction a pair, but holds the matrix cores up for 16 cycles (measured: 49 instead of 33 cycles for a
+// 32x32x16 product and one of them); one 16x16x32 product adds up 16 keys of 32 rows in 16 cycles.  The
+// weights stay as the PV product takes them (lane l: row l % 32, eight keys of half l / 32); read as an
+// operand of 16 columns, lane l holds column l % 16, keys 8 * (l / 16) .. +7: row 0 of `row_sum_operand`
+// has ones at the keys that are rows 0 .. 15, row 1 at those of rows 16 .. 31.  The sums of row r and
+// r + 16 end up in elements 0 and 1 of lane r, both half-waves' keys included.
+__device__ __forceinline__ bf16x8 row_sum_operand(int lane)
+{
+    bf16x8 v;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
+    return v;
+}
+__device__ __forceinline__ f32x4 add_row_sums(const bf16x8& pick, const bf16x8& weights, const f32x4& sums)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick, weights, sums, 0, 0, 0);
+}
+// alpha: factor of row lane % 32
+__device__ __forceinline__ void scale_row_sums(f32x4& sums, float alpha, int lane)
+{
+    sums[0] *= alpha;                                        // (lanes 0 .. 15 count)
+    sums[1] *= __shfl(alpha, (lane & 15) + 16, 64);
+}
+// the sum of row lane % 32, in every lane
+__device__ __forceinline__ float row_sum(const f32x4& sums, int lane)
+{
+    const float a = __shfl(sums[0], lane & 15, 64), b = __shfl(sums[1], lane & 15, 64);
+    return (lane & 16) ? b : a;
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
 template <int N>

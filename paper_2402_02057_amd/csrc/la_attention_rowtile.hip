@@ -133,7 +133,9 @@ void step_attention_rowtile_kernel(const RowTileParams)
     const int n_iter = (n_chunks + CPI - 1) / CPI;
 
     f32x16 o[2];
-    float m_run = kNegInf, l_run = 0.0f;
+    float m_run = kNegInf, l_run;
+    f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};  // row sums while the loop runs
+    const bf16x8 pick = row_sum_operand(lane);
     const float sl2 = p.scale_log2;
 
     // ---- rotating variant: what every thread of the workgroup does behind an iteration's barrier.
@@ -393,7 +395,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
                     const float neg_mc = -m_use * sl2;
                     if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                         const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                        l_run *= alpha;
+                        scale_row_sums(lsum, alpha, lane);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -404,31 +406,21 @@ void step_attention_rowtile_kernel(const RowTileParams)
                     bf16x8 pf[2];
 #pragma unroll
                     for (int i = 0; i < 16; ++i) pf[i >> 3][i & 7] = (__bf16)fast_exp2(__builtin_fmaf(s[i], sl2, neg_mc));
-                    {
-                        const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-                        float psum0 = 0.0f, psum1 = 0.0f;
-#pragma unroll
-                        for (int kk = 0; kk < 2; ++kk) {
-                            psum0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][0], pf[kk][1]}, ones, psum0, false);
-                            psum1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][2], pf[kk][3]}, ones, psum1, false);
-                            psum0 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][4], pf[kk][5]}, ones, psum0, false);
-                            psum1 = __builtin_amdgcn_fdot2_f32_bf16(bf16x2{pf[kk][6], pf[kk][7]}, ones, psum1, false);
-                        }
-                        l_run += psum0 + psum1;
-                    }
                     // ---- O^T += V^T P^T (this workgroup's half of the columns)
 #pragma unroll
-                    for (int kk = 0; kk < 2; ++kk)
+                    for (int kk = 0; kk < 2; ++kk) {
+                        lsum = add_row_sums(pick, pf[kk], lsum);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
                             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk][db], pf[kk], o[db], 0, 0, 0);
+                    }
                 }
             }
         }
         if (it < 4) LA_STAMP(9 + 2 * it);
     }
     LA_STAMP(3);
-    l_run += __shfl_xor(l_run, 32, 64);  // the two half-waves of a row hold the sums over their own keys
+    l_run = row_sum(lsum, lane);
 
     // ---- merge the four waves: every wave leaves its two slices and (m, l); after the barrier wave w
     //      sums registers (w/2)*8 .. +7 of slice w%2 over the four states, in key order, and writes
