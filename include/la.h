@@ -467,7 +467,8 @@ la_status la_step_attention_noalloc(const void* q, const void* k_cache, const vo
  *                                            (a forced decomposition is one of the staged kernel)
  *   "attn_rowtile"     (no variable)         "1" / "0": the row-tile kernel forced on (where it
  *                                            applies) / off; NULL = the library's choice
- *   "batch_plan"       (LA_BATCH_PLAN)       "2" or "4": 32-row tiles per workgroup of a batched launch
+ *   "batch_plan"       (LA_BATCH_PLAN)       32-row tiles per workgroup of a batched launch: "2" or "4"
+ *                                            (staged kernel), "8" (pipelined kernel, where it applies)
  *   "force_recompute"  (LA_FORCE_RECOMPUTE)  "1": treat every split group as spread over several
  *                                            XCDs, so that the recompute path runs
  * Returns LA_EINVAL for an unknown key or a malformed plan.

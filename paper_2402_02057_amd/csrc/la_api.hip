@@ -66,11 +66,12 @@ la_status select_workspace(int set)
 }
 
 namespace {
-// A block is at least this large: what any batched launch needs (of 128-row workgroups, the largest:
-// 36 KB of partial results each, and for a group of them eight tickets 128 bytes apart), and more than
-// any one step.
-constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(32) << 20;
-static_assert(kMaxCutWorkgroups * (size_t(36) << 10) <= kLeastScratch && kMaxCutGroups * size_t(8 * 128) <= kLeastZeroed,
+// A block is at least this large: what any batched launch needs (partial results: 36 KB a workgroup of the
+// staged kernel, 132 KB of the pipelined one; tickets, of the staged kernel alone: eight a group, 128
+// bytes apart), and more than any one step.
+constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(64) << 20;
+static_assert(kMaxCutWorkgroups * (size_t(36) << 10) <= kLeastScratch && kMaxCutGroups * size_t(8 * 128) <= kLeastZeroed &&
+                  kMaxWideCutWorkgroups * (size_t(132) << 10) <= kLeastScratch,
               "a batched launch fits the least blocks");
 
 // Growing a block means hipMalloc (and a clear on the stream): neither may happen while the

@@ -50,6 +50,7 @@
 #include <stdlib.h>
 
 #include <mutex>
+#include <type_traits>
 #include <string>
 
 #include "la_internal.h"
@@ -95,7 +96,10 @@ struct AttnParams {
         const float* v_scale;
         const float* rope_sin;
     };
-    int rope_rows;         // positions P .. P + rope_rows - 1 are staged in LDS
+    union {
+        int rope_rows;     // positions P .. P + rope_rows - 1 are staged in LDS
+        int block_rows;    // pipelined kernel: rows of a row block (a multiple of 32)
+    };
     int rope_block;        // LDS bytes reserved per table (rope_rows * head_dim * 2 rounded up to 1 KB)
     int rope_flags;  // bit 0: pairing of the rotation, 0 (x[i], x[i + d/2]), 1 (x[2i], x[2i + 1]);
                      // bit 1: the step keys are rotated in the kernel as well
@@ -244,10 +248,10 @@ struct Cfg {
 // the workgroup, columns db*32 + i4*8 + hi*4 .. +3 in vals[i4*4 .. +3].  The two half-waves of a
 // row fill 16 contiguous bytes per i4, 64 per slice.
 template <class C, int D = C::HEAD_DIM>
-__device__ __forceinline__ void store_slice(const AttnParams& p, int rb, int kvh, int tile, int db, int l32,
+__device__ __forceinline__ void store_slice(const AttnParams& p, int row_base, int kvh, int db, int l32,
                                             int hi, const f32x16& vals, float inv)
 {
-    const int rr = rb * C::ROWS + tile * 32 + l32;
+    const int rr = row_base + l32;
     if (rr >= p.R) return;
     const int t = div_small(rr, p.inv_group), hh = rr - t * p.group;
     __bf16* row = p.out + ((size_t)t * p.heads + (size_t)kvh * p.group + hh) * D + db * 32 + hi * 4;
@@ -1053,7 +1057,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                     f32x16 vals;
 #pragma unroll
                     for (int i = 0; i < 16; ++i) vals[i] = acc[u][i];
-                    store_slice<C>(p, rb, kvh, rt, db0 + u, l32, hi, vals, inv);
+                    store_slice<C>(p, row_base, kvh, db0 + u, l32, hi, vals, inv);
                 }
                 LA_STAMP(7);
             }
@@ -1076,7 +1080,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     if (wave_active && ((store_mask >> wave) & 1u)) {
         const float inv = out_scale / l_run;
 #pragma unroll
-        for (int u = 0; u < C::SPW; ++u) store_slice<C>(p, rb, kvh, rt, db0 + u, l32, hi, o[u], inv);
+        for (int u = 0; u < C::SPW; ++u) store_slice<C>(p, row_base, kvh, db0 + u, l32, hi, o[u], inv);
     }
 }
 
@@ -1086,6 +1090,8 @@ __global__ __launch_bounds__(RT* KS * 64) void step_attention_kernel(const AttnP
     const AttnParams& p = warmed_arguments<AttnParams>();
     step_attention_body<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE>(p, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3));
 }
+
+#include "la_attention_wide.h"
 
 // Several independent steps (sequences) in one launch: on every XCD, step i owns the slots
 // slot0[i] .. slot0[i+1]-1.  Workgroups are handed out in id order, so the steps start in the
@@ -1113,6 +1119,35 @@ __global__ __launch_bounds__(RT* KS * 64) void step_attention_batch_kernel(const
     step_attention_body<D, RT, KS, KC, NSTAGE, PAGED>(p, (int)(blockIdx.x & 7), slot - sl.slot0[i]);
 }
 
+// (two waves per SIMD are all there will be: the compiler need not save registers for more)
+template <bool PAGED>
+__global__ __launch_bounds__(WideCfg::NT) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void wide_attention_batch_kernel(const BatchParams)
+{
+    const BatchSlots& sl = warmed_arguments<BatchSlots>((unsigned)offsetof(BatchParams, slots));
+    const int slot = (int)(blockIdx.x >> 3);
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < kMaxBatch; ++k)
+        if (k < sl.n && slot >= sl.slot0[k]) i = k;
+    const AttnParams& p = warmed_arguments<AttnParams>((unsigned)i * (unsigned)sizeof(AttnParams));
+    wide_attention_body<PAGED>(p, (int)(blockIdx.x & 7), slot - sl.slot0[i]);
+}
+
+// slots: slot0[i] = first unit of step i among the units of the launch's cut steps
+__global__ __launch_bounds__(256) void wide_combine_kernel(const BatchParams)
+{
+    constexpr int JOBS = WideCfg::COMBINE_WGS;
+    const BatchSlots& sl = warmed_arguments<BatchSlots>((unsigned)offsetof(BatchParams, slots));
+    const int at = (int)blockIdx.x / JOBS;
+    int i = 0;
+#pragma unroll
+    for (int k = 1; k < kMaxBatch; ++k)
+        if (k < sl.n && at >= sl.slot0[k]) i = k;
+    const AttnParams& p = warmed_arguments<AttnParams>((unsigned)i * (unsigned)sizeof(AttnParams));
+    wide_combine_body(p, at - sl.slot0[i], ((int)blockIdx.x % JOBS) * 4 + (int)(threadIdx.x >> 6));
+}
+
 // Scratch memory of the entry point that allocates nothing (la_step_attention_noalloc): the
 // tickets and the split partials of one step, in the library's own image.  Every device the
 // library runs on holds one copy until the process ends.  In host code the name below is only a
@@ -1136,7 +1171,7 @@ __global__ void clear_words_kernel(unsigned* words, int n)
 struct Overrides {
     bool has_plan = false;
     int plan[6] = {0, 0, 0, 0, 0, 0};  // RT, KS, XS, NS, KC, PRE (XS = 0, PRE = 0: heuristic)
-    int batch_rows = 0;                // 2 or 4: 32-row tiles per workgroup of a batched launch
+    int batch_rows = 0;                // form of a batched launch (LaunchPlan::rows; 0: heuristic)
     int rowtile = -1;                  // 1 / 0: the kernel without partials forced on / off (-1: heuristic)
     bool force_recompute = false;
 };
@@ -1152,13 +1187,19 @@ bool parse_plan(const char* text, Overrides& o)
     return o.has_plan;
 }
 
+// "2", "4": 64- or 128-row workgroups of the staged kernel; "8": 256-row ones of the pipelined kernel
+int parse_batch_form(const char* text)
+{
+    return text && (text[0] == '2' || text[0] == '4' || text[0] == '8') ? (text[0] - '0') * 32 : 0;
+}
+
 void overrides_from_env_locked()
 {
     if (g_overrides_from_env) return;
     g_overrides_from_env = true;
     parse_plan(getenv("LA_ATTN_PLAN"), g_overrides);
     const char* b = getenv("LA_BATCH_PLAN");
-    g_overrides.batch_rows = (b && (b[0] == '2' || b[0] == '4')) ? b[0] - '0' : 0;
+    g_overrides.batch_rows = parse_batch_form(b);
     const char* f = getenv("LA_FORCE_RECOMPUTE");
     g_overrides.force_recompute = f && f[0] == '1';
 }
@@ -1567,6 +1608,27 @@ la_status launch_batch_cfg(const BatchParams& bp, unsigned grid, hipStream_t str
     return LA_OK;
 }
 
+template <bool PAGED>
+la_status launch_wide_batch(BatchParams& bp, unsigned grid, hipStream_t stream)
+{
+    using C = WideCfg;
+    auto kern = wide_attention_batch_kernel<PAGED>;
+    static bool attr_set[16] = {false};
+    const la_status st = set_lds_attribute_once(reinterpret_cast<const void*>(kern), C::LDS_BYTES, attr_set);
+    if (st != LA_OK) return st;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(C::NT), C::LDS_BYTES, stream, bp);
+    int units = 0;  // of the steps that are cut
+    for (int i = 0; i < bp.slots.n; ++i) {
+        bp.slots.slot0[i] = units;
+        if (bp.seq[i].XS > 1) units += bp.seq[i].kv_heads * bp.seq[i].n_row_blocks;
+    }
+    for (int i = bp.slots.n; i <= kMaxBatch; ++i) bp.slots.slot0[i] = units;
+    if (units) hipLaunchKernelGGL(wide_combine_kernel, dim3(units * C::COMBINE_WGS), dim3(256), 0, stream, bp);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(LA_EHIP, "la_step_attention_batch launch: %s", hipGetErrorString(e));
+    return LA_OK;
+}
+
 }  // namespace
 
 static_assert(sizeof(BatchParams) <= 4000, "the batch travels as a kernel argument");
@@ -1599,16 +1661,19 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             if (st != LA_OK) return st;
             continue;
         }
-        // One decomposition (row tiles, key-split waves) for the whole launch; how often each step's
-        // keys are cut, and the order of the steps, come from plan_batch.
+        // One kernel and decomposition (row tiles, key-split waves) for the whole launch; those, how often each
+        // step's keys are cut, and the order of the steps come from plan_launch.
         Plan pl[kMaxBatch];
         for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim);
         int chunks[kMaxBatch];
         for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
-        const BatchPlan plan = plan_batch(chunks, n, (T * group + 31) / 32, kv_heads, head_dim, ov.batch_rows * 32);
-        const int RT = plan.rows128 ? 4 : 2, KS = plan.rows128 || head_dim != 128 ? 2 : 4;
-        const int rows_wg = RT * 32;
-        const int n_row_blocks = (T * group + rows_wg - 1) / rows_wg;
+        const int tiles = (T * group + 31) / 32;
+        const LaunchPlan plan = plan_launch(chunks, n, tiles, kv_heads, head_dim, ov.batch_rows);
+        const bool wide = plan.rows == kPipelinedRows;
+        const int RT = plan.rows / 32, KS = wide ? 1 : plan.rows == 128 || head_dim != 128 ? 2 : 4;
+        const int n_row_blocks = (tiles + RT - 1) / RT;
+        // (a pipelined launch shares a KV head's tiles evenly among its row blocks)
+        const int block_rows = 32 * (wide ? (tiles + n_row_blocks - 1) / n_row_blocks : RT);
         BatchParams bp;
         bp.slots.n = n;
         size_t partial_bytes = 0, ticket_count = 0;
@@ -1618,17 +1683,18 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             Plan& q = pl[plan.place[i]];
             q.RT = RT; q.KS = KS; q.NS = 4; q.KC = 64; q.PRE = 0;
             q.n_row_blocks = n_row_blocks;
-            q.partial_bytes_per_wg = partial_wg_bytes(head_dim, RT, KS);
+            q.partial_bytes_per_wg = wide ? WideCfg::PART_WG_BYTES : partial_wg_bytes(head_dim, RT, KS);
             q.XS = plan.cuts[plan.place[i]];
             const la_status st = build_params(bp.seq[i], ov, q, d.q, d.k_cache, d.v_cache, d.P,
                                               d.P > 0 ? d.block_table : nullptr, page_size, n_pages, nullptr, T,
                                               d.step_k, d.step_v, d.P, W, N, G, heads, kv_heads, head_dim, d.out);
             if (st != LA_OK) return st;
+            bp.seq[i].block_rows = block_rows;
             bp.slots.slot0[i] = slot;
             slot += bp.seq[i].wg_per_xcd;
             if (q.XS > 1) {
                 partial_bytes += (size_t)bp.seq[i].total_wg * q.partial_bytes_per_wg;
-                ticket_count += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
+                if (!wide) ticket_count += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
             }
         }
         for (int i = n; i <= kMaxBatch; ++i) bp.slots.slot0[i] = slot;
@@ -1644,12 +1710,14 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
                 bp.seq[i].tickets = tickets;
                 bp.seq[i].partials = partials;
                 tickets += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
-                partials += (size_t)bp.seq[i].total_wg * partial_wg_bytes(head_dim, RT, KS);
+                partials += (size_t)bp.seq[i].total_wg * pl[plan.place[i]].partial_bytes_per_wg;
             }
         }
         const unsigned grid = (unsigned)slot * 8u;
         la_status st;
-        if (paged) {
+        if (wide) {
+            st = paged ? launch_wide_batch<true>(bp, grid, stream) : launch_wide_batch<false>(bp, grid, stream);
+        } else if (paged) {
             if (head_dim == 128 && RT == 4) st = launch_batch_cfg<128, 4, 2, 4, true>(bp, grid, stream);
             else if (head_dim == 128) st = launch_batch_cfg<128, 2, 4, 4, true>(bp, grid, stream);
             else st = launch_batch_cfg<64, 2, 2, 4, true>(bp, grid, stream);
@@ -1673,7 +1741,7 @@ la_status set_override(const char* key, const char* value)
         if (!parse_plan(value, g_overrides) && value && value[0])
             return fail(LA_EINVAL, "la_debug_override: attn_plan wants \"RT,KS,XS,NS,KC[,PRE]\", got \"%s\"", value);
     } else if (k == "batch_plan") {
-        g_overrides.batch_rows = (value && (value[0] == '2' || value[0] == '4')) ? value[0] - '0' : 0;
+        g_overrides.batch_rows = parse_batch_form(value);
     } else if (k == "attn_rowtile") {
         g_overrides.rowtile = (value && (value[0] == '0' || value[0] == '1')) ? value[0] - '0' : -1;
     } else if (k == "force_recompute") {

@@ -222,4 +222,95 @@ inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, i
     return p;
 }
 
+// ---- staged or pipelined kernel (la_attention_wide.h: workgroups of up to 256 rows, head_dim 128)
+
+// What the cut steps of a pipelined launch amount to at most.  Their partial results are in fp32 and a
+// second kernel adds them up, so a step may be cut whatever the rule above says, and its ranges may lie
+// on any XCD.
+constexpr int kMaxWideCutWorkgroups = 448;
+constexpr int kPipelinedRows = 256;
+
+struct LaunchPlan {
+    int rows;                // rows of a workgroup: 64 or 128 (staged kernel), or kPipelinedRows
+    int cuts[kMaxBatch], place[kMaxBatch];  // as in BatchPlan
+};
+
+namespace batch_plan {
+
+struct WideForm {
+    int units, chunk, fixed;   // times in 10 ns
+};
+
+// As `search`, for the pipelined kernel, whose steps may all be cut: from uncut steps on, the step with the
+// longest ranges is cut once more, as long as the sum of all workgroups leaves room for a better end.
+inline long long search_wide(const int* chunks, int n, const WideForm& f, LaunchPlan& p)
+{
+    Layout l;
+    long long best = -1;
+    for (int i = 0; i < n; ++i) l.cuts[i] = 1;
+    for (;;) {
+        int cut_wgs = 0, longest = 0;
+        for (int i = 0; i < n; ++i) {
+            const int x = l.cuts[i];
+            l.wgs[i] = batch_wgs_per_xcd(f.units, x);
+            l.range[i] = (chunks[i] + x - 1) / x;
+            l.cost[i] = (long long)l.range[i] * f.chunk + f.fixed;
+            if (x > 1) cut_wgs += f.units * x;
+            if (l.range[i] > l.range[longest]) longest = i;
+        }
+        if (cut_wgs > kMaxWideCutWorkgroups) break;
+        l.arrange(n, true);
+        // (the second kernel, and what storing and reading fp32 partial results takes)
+        const long long extra = cut_wgs ? 350 + cut_wgs : 0;
+        if (best >= 0 && l.sum / kXcdUnits + extra >= best) break;
+        if (best < 0 || l.cost[l.order[0]] + extra < best) {
+            const long long end = launch_end(l.order, n, l.wgs, l.cost) + extra;
+            if (best < 0 || end < best) {
+                best = end;
+                p.rows = kPipelinedRows;
+                for (int i = 0; i < n; ++i) { p.cuts[i] = l.cuts[i]; p.place[i] = l.order[i]; }
+            }
+        }
+        if (l.range[longest] < 8) break;
+        ++l.cuts[longest];
+    }
+    return best;
+}
+
+}  // namespace batch_plan
+
+// As plan_batch; rows: kPipelinedRows to force that form, too.
+inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows = 0)
+{
+    using namespace batch_plan;
+    LaunchPlan p;
+    long long end = -1;
+    const bool can = head_dim == 128 && tiles >= 4;   // (fewer tiles fit one staged workgroup)
+    if (rows != kPipelinedRows || !can) {
+        const BatchPlan b = plan_batch(chunks, n, tiles, kv_heads, head_dim, rows == kPipelinedRows ? 0 : rows);
+        p.rows = b.rows128 ? 128 : 64;
+        for (int i = 0; i < n; ++i) { p.cuts[i] = b.cuts[i]; p.place[i] = b.place[i]; }
+        if (rows || !can) return p;
+        const Form f = form_of(b.rows128, kv_heads, tiles);
+        int wgs[kMaxBatch];
+        long long cost[kMaxBatch];
+        for (int i = 0; i < n; ++i) {
+            const int range = (chunks[i] + b.cuts[i] - 1) / b.cuts[i];
+            wgs[i] = batch_wgs_per_xcd(f.units, b.cuts[i]);
+            cost[i] = (long long)(range + f.fixed + (b.cuts[i] > 1 ? f.exchange : 0)) * (b.rows128 ? 122 : 80);
+        }
+        end = launch_end(b.place, n, wgs, cost);
+    }
+    // Times of the pipelined form, us: a chunk 1.81 with eight tiles (8 prefixes of 1024 and 3072 keys, 64/8 heads, 121
+    // rows: 50.2 and 108.0 a launch) and 0.4 of that however few, start and end 7 and 0.65 a tile.  Taken
+    // where the launch then ends 7 % sooner: of 90 drawn batches measured in every form it is taken for 24, at
+    // 0.62 to 0.97 of the staged forms' time (0.80 in the geometric mean); where the times say 0.93 to 1.0 it measures
+    // 0.81 to 1.17.
+    const int blocks = (tiles + 7) / 8, per_block = (tiles + blocks - 1) / blocks;
+    const WideForm f = {kv_heads * blocks, 72 + 109 * per_block / 8, 700 + 65 * per_block};
+    LaunchPlan q;
+    const long long e = search_wide(chunks, n, f, q);
+    return end < 0 || e * 100 < end * 93 ? q : p;
+}
+
 }  // namespace la

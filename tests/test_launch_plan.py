@@ -1,0 +1,82 @@
+"""Which kernel a batched attention launch takes and how it is cut (csrc/la_batch_plan.h, plan_launch: host
+code, built here on its own with the host compiler)."""
+import ctypes
+import os
+import random
+import subprocess
+
+import pytest
+
+from paper_2402_02057_amd import buildlib, workloads as wl
+
+SHIM = r"""
+#include "la_batch_plan.h"
+extern "C" int launch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows, int* cuts, int* place)
+{
+    const la::LaunchPlan p = la::plan_launch(chunks, n, tiles, kv_heads, head_dim, rows);
+    for (int i = 0; i < n; ++i) { cuts[i] = p.cuts[i]; place[i] = p.place[i]; }
+    return p.rows;
+}
+extern "C" int batch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows, int* cuts, int* place)
+{
+    const la::BatchPlan p = la::plan_batch(chunks, n, tiles, kv_heads, head_dim, rows);
+    for (int i = 0; i < n; ++i) { cuts[i] = p.cuts[i]; place[i] = p.place[i]; }
+    return p.rows128 ? 128 : 64;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launch_plan")
+    source, so = d / "shim.cpp", d / "shim.so"
+    source.write_text(SHIM)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", buildlib.CSRC,
+                    str(source), "-o", str(so)], check=True)
+    return ctypes.CDLL(str(so))
+
+
+def ask(entry, chunks, tiles, kv_heads, head_dim=128, rows=0):
+    arr = ctypes.c_int * len(chunks)
+    cuts, place = arr(), arr()
+    form = entry(arr(*chunks), len(chunks), tiles, kv_heads, head_dim, rows, cuts, place)
+    return form, list(cuts), list(place)
+
+
+def chunks_of(prefixes, T):
+    return [-(-P // 64) + -(-T // 64) for P in sorted(prefixes, reverse=True)]
+
+
+def test_every_plan_can_be_launched(lib):
+    """Each step once, no range empty, and partial results of a pipelined launch within what the library
+    reserves (la_api.hip: 64 MB; eight waves of 16 KB and 512 bytes each)."""
+    rng = random.Random(1)
+    taken = 0
+    for _ in range(3000):
+        T, group, kv_heads = 1 + rng.randint(1, 60) * rng.randint(2, 6), rng.choice([1, 4, 8]), rng.choice([1, 2, 8, 32])
+        top = round(64 * 256 ** rng.random())
+        chunks = chunks_of([rng.randint(0, top) for _ in range(rng.randint(2, 16))], T)
+        tiles, head_dim, rows = -(-T * group // 32), rng.choice([64, 128, 128]), rng.choice([0, 0, 64, 128, 256])
+        form, cuts, place = ask(lib.launch, chunks, tiles, kv_heads, head_dim, rows)
+        assert sorted(place) == list(range(len(chunks))) and all(1 <= x <= c for x, c in zip(cuts, chunks))
+        if form != 256:
+            assert (form, cuts, place) == ask(lib.batch, chunks, tiles, kv_heads, head_dim, rows if rows != 256 else 0)
+            assert rows != 256 or head_dim == 64 or tiles < 4
+            continue
+        assert head_dim == 128 and tiles >= 4 and rows in (0, 256)
+        taken += rows == 0
+        workgroups = sum(kv_heads * -(-tiles // 8) * x for x in cuts if x > 1)
+        assert workgroups * 8 * (16384 + 512) <= 64 << 20
+    assert taken > 100
+
+
+@pytest.mark.parametrize("prefixes, T, heads, kv_heads, form, cuts", [
+    (wl.ragged_prefix_lengths(), 121, 32, 8, 256, [4, 4, 3, 2, 1, 1, 1, 1]),   # long and ragged: ranges of about equal length
+    ([1021 - 37 * i for i in range(16)], 81, 32, 8, 256, [1] * 16),           # a serving batch, uncut
+    ([1024] * 8, 121, 32, 32, 128, [1] * 8),                                   # four tiles: nothing to share a chunk with
+    ([256] * 4, 121, 32, 8, 64, [1] * 4),
+    ([616, 300, 88], 361, 32, 8, 128, [2, 2, 1]),                              # the times too close to call
+], ids=["ragged", "serving", "7b", "small", "wide-windows"])
+def test_kernel_and_cuts(lib, prefixes, T, heads, kv_heads, form, cuts):
+    got = ask(lib.launch, chunks_of(prefixes, T), -(-T * (heads // kv_heads) // 32), kv_heads)
+    assert got[:2] == (form, cuts)
