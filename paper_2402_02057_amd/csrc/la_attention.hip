@@ -244,9 +244,8 @@ struct Cfg {
 };
 
 
-// Write one finished (tile, 32-column) slice: lane (l32, hi) holds, for query row tile*32 + l32 of
-// the workgroup, columns db*32 + i4*8 + hi*4 .. +3 in vals[i4*4 .. +3].  The two half-waves of a
-// row fill 16 contiguous bytes per i4, 64 per slice.
+// Write one finished (tile, 32-column) slice: lane (l32, hi) holds, for query row row_base + l32, columns
+// db*32 + i4*8 + hi*4 .. +3 in vals[i4*4 .. +3].
 template <class C, int D = C::HEAD_DIM>
 __device__ __forceinline__ void store_slice(const AttnParams& p, int row_base, int kvh, int db, int l32,
                                             int hi, const f32x16& vals, float inv)
@@ -254,14 +253,9 @@ __device__ __forceinline__ void store_slice(const AttnParams& p, int row_base, i
     const int rr = row_base + l32;
     if (rr >= p.R) return;
     const int t = div_small(rr, p.inv_group), hh = rr - t * p.group;
-    __bf16* row = p.out + ((size_t)t * p.heads + (size_t)kvh * p.group + hh) * D + db * 32 + hi * 4;
+    __bf16* row = p.out + ((size_t)t * p.heads + (size_t)kvh * p.group + hh) * D + db * 32 + hi * 8;
 #pragma unroll
-    for (int i4 = 0; i4 < 4; ++i4) {
-        bf16x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = (__bf16)(vals[i4 * 4 + e] * inv);
-        *reinterpret_cast<bf16x4*>(row + i4 * 8) = v;
-    }
+    for (int i8 = 0; i8 < 2; ++i8) *reinterpret_cast<bf16x8*>(row + i8 * 16) = sixteen_bytes(vals, i8 * 8, inv);
 }
 
 // Merge the KS key-split waves of a row tile, for the wave whose key index is MYKS.  Every

@@ -239,6 +239,28 @@ __device__ __forceinline__ bf16x8 fp8x8_to_bf16(unsigned lo, unsigned hi)
     return bf16x8{a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
 }
 
+// Eight values of a transposed result (lane (l32, hi): row l32, columns hi*4 .. +3 in the first four, 8 + hi*4 .. +3
+// in the others), scaled, as bf16, such that a lane has eight columns in a row, hi*8 .. +7: the half-waves
+// exchange what the other one stores, and a store is 16 bytes a lane instead of two of 8.
+template <class V>
+__device__ __forceinline__ bf16x8 sixteen_bytes(const V& vals, int first, float factor)
+{
+    union { bf16x4 h; unsigned u[2]; } a, b;
+    union { unsigned u[4]; bf16x8 v; } r;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        a.h[e] = (__bf16)(vals[first + e] * factor);
+        b.h[e] = (__bf16)(vals[first + 4 + e] * factor);
+    }
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+        const auto x = __builtin_amdgcn_permlane32_swap(a.u[w], b.u[w], false, false);
+        r.u[w] = x[0];
+        r.u[2 + w] = x[1];
+    }
+    return r.v;
+}
+
 // Id of the XCD (accelerator die, with its own L2) this wave runs on.
 __device__ __forceinline__ unsigned xcc_id()
 {

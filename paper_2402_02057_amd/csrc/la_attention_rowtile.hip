@@ -466,19 +466,16 @@ void step_attention_rowtile_kernel(const RowTileParams)
     if (rr < p.R) {
         const float inv = 1.0f / l;  // (>= 1 visible key per row, so l > 0)
         const int t = div_small(rr, p.inv_group), hh = rr - t * p.group;
-        __bf16* row = p.out + ((size_t)t * p.heads + (size_t)kvh * p.group + hh) * D + vpart * (D / 2) + my_db * 32 + hi * 4;
+        __bf16* row = p.out + ((size_t)t * p.heads + (size_t)kvh * p.group + hh) * D + vpart * (D / 2) + my_db * 32 + hi * 8;
+        static_assert(QW == 2, "a wave's two groups of four registers are one store");
+        float sum[QW * 4];
 #pragma unroll
-        for (int h = 0; h < QW; ++h) {
-            bf16x4 w;
+        for (int i = 0; i < QW * 4; ++i) {
+            sum[i] = v[0][i >> 2][i & 3] * a[0];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float acc = v[0][h][e] * a[0];
-#pragma unroll
-                for (int k = 1; k < NWC; ++k) acc = __builtin_fmaf(v[k][h][e], a[k], acc);
-                w[e] = (__bf16)(acc * inv);
-            }
-            *reinterpret_cast<bf16x4*>(row + (my_part * QW + h) * 8) = w;
+            for (int k = 1; k < NWC; ++k) sum[i] = __builtin_fmaf(v[k][i >> 2][i & 3], a[k], sum[i]);
         }
+        *reinterpret_cast<bf16x8*>(row + my_part * QW * 8) = sixteen_bytes(sum, 0, inv);
     }
     LA_STAMP(7);
 }
