@@ -130,36 +130,38 @@ struct AttnParams {
     int force_recompute;  // testing: treat every group as spread over several XCDs
 };
 
-// Row-subset variant: a row of the full layout as (branch, coordinates), and the pairwise rule
-// of Sec. 3.3 written out (the closed-form words above assume consecutive step keys).
-struct RowPos {
-    int cls;  // 0 current token, 1 lookahead (a = level, b = column), 2 candidate (a = candidate, b = token)
-    int a, b;
+// Row-subset variant: the pairwise rule of Sec. 3.3 (the closed-form words above assume consecutive step
+// keys).  Every row belongs to a line of rows that see their forerunners - a lookahead column with its
+// levels, a candidate with its tokens - and a lookahead row sees the oldest level up to its own column and
+// the current token as well.  With lines numbered from 1 (columns, then candidates):
+//   key    first   its column's line if it is of the oldest level, 0 the current token, else beyond any
+//          place   line * N + level, line * N + token
+//   row    upto    visible if first <= upto: its line for a lookahead row, 0 otherwise
+//          base    line * N: visible if 0 <= place - base <= back (its level or token)
+struct RowKey {
+    int first, place;
 };
+struct RowSees {
+    int upto, base;
+    unsigned back;
+};
+constexpr int kNoLine = 1 << 30;
 
-__device__ __forceinline__ RowPos row_position(int t, int W, int N, float inv_W, float inv_n1)
+__device__ __forceinline__ void row_place(int t, int W, int N, float inv_W, float inv_n1, RowKey& k, RowSees& q)
 {
-    RowPos r;
     const int n_look = W * (N - 1);
     if (t == 0) {
-        r.cls = 0; r.a = 0; r.b = 0;
+        k = RowKey{0, kNoLine};
+        q = RowSees{0, kNoLine / 2, 0u};
     } else if (t <= n_look) {
-        const int x = t - 1;
-        r.cls = 1; r.a = div_small(x, inv_W); r.b = x - r.a * W;
+        const int level = div_small(t - 1, inv_W), line = t - level * W;
+        k = RowKey{level == 0 ? line : kNoLine, line * N + level};
+        q = RowSees{line, line * N, (unsigned)level};
     } else {
-        const int x = t - 1 - n_look;
-        r.cls = 2; r.a = div_small(x, inv_n1); r.b = x - r.a * (N - 1);
+        const int x = t - 1 - n_look, g = div_small(x, inv_n1), token = x - g * (N - 1);
+        k = RowKey{kNoLine, (W + 1 + g) * N + token};
+        q = RowSees{0, (W + 1 + g) * N, (unsigned)token};
     }
-    return r;
-}
-
-__device__ __forceinline__ bool visible_pair(const RowPos& q, int tk, int W, int N, float inv_W, float inv_n1)
-{
-    if (tk == 0) return true;  // everyone sees the current token
-    const RowPos k = row_position(tk, W, N, inv_W, inv_n1);
-    if (q.cls != k.cls) return false;
-    if (q.cls == 1) return (k.a == 0 && k.b <= q.b) || (k.b == q.b && k.a <= q.a);
-    return q.cls == 2 && k.a == q.a && k.b <= q.b;
 }
 
 // KVB: bytes per key / value element (2: bf16; 1: 8-bit float, quantised cache).  Q rows are bf16 always.
@@ -236,10 +238,11 @@ struct Cfg {
     static constexpr int ROPE_POS_BYTES = D * 2;           // one position of one table (D/2 fp32)
     static constexpr int ROPE_MAX_BYTES = (160 * 1024 - LDS_BYTES) / 2048 * 2048 < 64 * 1024
                                               ? (160 * 1024 - LDS_BYTES) / 2048 * 2048 : 64 * 1024;  // both tables
-    // row-subset variant: the ids of up to ROWSET_MAX rows, staged behind everything else
+    // row-subset variant: the ids of up to ROWSET_MAX rows, staged behind everything else, and their places as keys
     static constexpr int ROWSET_MAX = 1024;
     static constexpr int ROWIDS_OFFSET = LDS_BYTES;
-    static constexpr int ROWIDS_BYTES = ROWSET_MAX * 4;
+    static constexpr int ROWKEYS_OFFSET = ROWIDS_OFFSET + ROWSET_MAX * 4;
+    static constexpr int ROWSET_BYTES = ROWSET_MAX * (4 + 8);
     static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
 
@@ -618,7 +621,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     // which step keys this lane's row may see
     const int t_lane = div_small(min(row_base + l32, p.R - 1), p.inv_group);  // step row of this lane's query row
     const RowVis vis = row_visibility(t_lane, p.W, p.N, p.inv_W, p.inv_n1);
-    RowPos qpos = {0, 0, 0};  // row-subset variant: filled once the ids have landed
+    RowSees sees = {0, kNoLine / 2, 0u};  // row-subset variant: filled once the ids have landed
     bf16x8 qreg[D / 16];  // B operand of S^T = K Q^T: row l32, d = k16*16 + hi*8 .. +8
 
     // o[db]: O^T accumulators of this wave's tile in the main loop; after the key-split merge,
@@ -743,10 +746,22 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                     const int piece = KVB == 2 ? k16 * 2 + hi : (k16 >> 1) * 4 + hi * 2 + (k16 & 1);
                     qreg[k16] = *reinterpret_cast<const bf16x8*>(qr + ((piece ^ qsw) << 4));
                 }
-                if constexpr (ROWSET) {
+            }
+            if constexpr (ROWSET) {
+                // The step's rows as keys, worked out once per workgroup (not by every lane for every key it
+                // meets, 260 vector instructions a block: 18.8 -> 14.8 us for 166 of 481 rows on 1024 keys)
+                if (it == 0 && (pass > 0 || c_end > n_prefix_chunks)) {
                     const int t_full = 1 + (p.W + p.G) * (p.N - 1);
-                    const int tq = *reinterpret_cast<const int*>(lds + C::ROWIDS_OFFSET + t_lane * 4);
-                    qpos = row_position(min(max(tq, 0), t_full - 1), p.W, p.N, p.inv_W, p.inv_n1);
+                    auto id = [&](int i) { return min(max(*reinterpret_cast<const int*>(lds + C::ROWIDS_OFFSET + i * 4), 0), t_full - 1); };
+                    RowKey k;
+                    RowSees unused;
+                    row_place(id(t_lane), p.W, p.N, p.inv_W, p.inv_n1, k, sees);
+                    for (int i = tid; i < (n_T + 31) / 32 * 32; i += C::NT) {
+                        row_place(id(i), p.W, p.N, p.inv_W, p.inv_n1, k, unused);
+                        if (i >= n_T) k = RowKey{kNoLine, kNoLine};
+                        *reinterpret_cast<RowKey*>(lds + C::ROWKEYS_OFFSET + i * (int)sizeof(RowKey)) = k;
+                    }
+                    __syncthreads();
                 }
             }
             // Up to CPI chunks are requested per iteration, into stages the last iteration freed:
@@ -785,18 +800,20 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 unsigned word = 0xFFFFFFFFu;
                 if (!full) {
                     if (is_step && ROWSET) {
-                        // pair by pair over this lane's 16 keys of the block (ids from LDS, four at a time)
+                        // pair by pair over this lane's 16 keys of the block
                         word = 0;
 #pragma unroll
                         for (int grp = 0; grp < 4; ++grp) {
-                            const int c0 = key0 + grp * 8 + hi * 4;
-                            const i32x4 g4 = *reinterpret_cast<const i32x4*>(lds + C::ROWIDS_OFFSET + c0 * 4);
+                            const unsigned char* at = lds + C::ROWKEYS_OFFSET + (key0 + grp * 8 + hi * 4) * (int)sizeof(RowKey);
+                            const i32x4 two[2] = {*reinterpret_cast<const i32x4*>(at), *reinterpret_cast<const i32x4*>(at + 16)};
 #pragma unroll
                             for (int e = 0; e < 4; ++e) {
-                                const bool ok = c0 + e < n_T && visible_pair(qpos, g4[e], p.W, p.N, p.inv_W, p.inv_n1);
-                                word |= (ok ? 1u : 0u) << (grp * 8 + hi * 4 + e);
+                                const int first = two[e >> 1][(e & 1) * 2], place = two[e >> 1][(e & 1) * 2 + 1];
+                                const bool ok = first <= sees.upto || (unsigned)(place - sees.base) <= sees.back;
+                                word |= (ok ? 1u : 0u) << (grp * 8 + e);
                             }
                         }
+                        word <<= hi * 4;
                     } else if (is_step) {
                         word = step_block_word(vis, key0);
                     } else {
@@ -1320,7 +1337,7 @@ template <int D, int RT, int KS, int NSTAGE, int KC = 64, bool PAGED = false, bo
 la_status launch_cfg(const AttnParams& prm, hipStream_t stream)
 {
     using C = Cfg<D, RT, KS, KC, NSTAGE, KVB>;
-    constexpr int kLds = C::LDS_BYTES + (ROWSET ? C::ROWIDS_BYTES : 0) + (ROPE ? C::ROPE_MAX_BYTES : 0);
+    constexpr int kLds = C::LDS_BYTES + (ROWSET ? C::ROWSET_BYTES : 0) + (ROPE ? C::ROPE_MAX_BYTES : 0);
     static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
     if (ROPE && 2 * prm.rope_block > C::ROPE_MAX_BYTES)
         return fail(LA_EUNSUPPORTED, "la_step_attention_rope: %d positions of cosines and sines do not fit beside this "
