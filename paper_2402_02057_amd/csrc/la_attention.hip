@@ -874,13 +874,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 read_v(1);  // in flight during the softmax arithmetic
 
                 // ---- mask, running max, exponentials
-                if (!full) {
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int bit = (i >> 2) * 8 + (i & 3);  // hi*4 already shifted out
-                        if (!((word >> bit) & 1u)) s[i] = kNegInf;
-                    }
-                }
+                if (!full) mask_scores(s, word);  // (hi*4 already shifted out)
                 if (full) settle_mfma_result(s);  // (the mask above is compiler-visible arithmetic on s)
                 float mx = max3(s[0], s[1], s[2]);
 #pragma unroll

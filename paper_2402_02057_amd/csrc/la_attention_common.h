@@ -69,6 +69,18 @@ __device__ __forceinline__ unsigned step_block_word(const RowVis& v, int key0)
     return w;
 }
 
+// Scores of keys that a row does not see become -inf.  Bit (i/4)*8 + i%4 of `word` stands for register i: one
+// bit spread over a mask and one select of bits, two instructions a score.
+template <class V>
+__device__ __forceinline__ void mask_scores(V& s, unsigned word)
+{
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const unsigned hidden = (unsigned)__builtin_amdgcn_sbfe((int)~word, (i >> 2) * 8 + (i & 3), 1);
+        s[i] = __uint_as_float((hidden & 0xFF800000u) | (~hidden & __float_as_uint(s[i])));
+    }
+}
+
 // Three-way maximum in one instruction; unlike fmaxf the compiler adds no NaN-quieting moves
 // around it (scores are MFMA results or -inf, never signalling NaNs).
 __device__ __forceinline__ float max3(float a, float b, float c)

@@ -318,6 +318,11 @@ void step_attention_rowtile_kernel(const RowTileParams)
     }
 
     const int n_P = p.P, n_T = p.T;
+    // what this wave's first two step blocks show of themselves, worked out while the first chunks are on their way
+    const int word_c = n_prefix_chunks + ((my_chunk - n_prefix_chunks) & (CPI - 1)), word_key0 = (word_c - n_prefix_chunks) * KC + kb * 32;
+    unsigned word0 = 0, word1 = 0;
+    if (word_c < n_chunks) word0 = step_block_word(vis, word_key0);
+    if (word_c + CPI < n_chunks) word1 = step_block_word(vis, word_key0 + CPI * KC);
     bf16x8 qreg[D / 16];
     for (int it = 0, done = 0; it < n_iter; ++it, done += CPI) {
         __syncthreads();  // this iteration's chunks have landed; everyone is done with the last ones
@@ -342,7 +347,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
                 unsigned word = 0xFFFFFFFFu;
                 bool skip = false;
                 if (!full) {
-                    if (is_step) word = step_block_word(vis, key0);
+                    if (is_step) word = c == word_c ? word0 : c == word_c + CPI ? word1 : step_block_word(vis, key0);
                     else word = (1u << (limit - key0)) - 1u;  // 1..31 keys left
                     word = (word >> (hi * 4)) & 0x0F0F0F0Fu;
                     skip = is_step && __builtin_amdgcn_ballot_w64(word != 0u) == 0ull;
@@ -377,13 +382,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
                         s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[k16], qreg[k16], s, 0, 0, 0);
                     read_v(1);  // in flight during the softmax arithmetic
                     // ---- mask, running maximum, exponentials (as in the staged kernel)
-                    if (!full) {
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) {
-                            const int bit = (i >> 2) * 8 + (i & 3);  // hi*4 already shifted out
-                            if (!((word >> bit) & 1u)) s[i] = kNegInf;
-                        }
-                    }
+                    if (!full) mask_scores(s, word);  // (hi*4 already shifted out)
                     if (full) settle_mfma_result(s);  // (the mask above is compiler-visible arithmetic on s)
                     float mx = max3(s[0], s[1], s[2]);
 #pragma unroll

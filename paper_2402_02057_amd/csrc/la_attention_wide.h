@@ -388,9 +388,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
                 for (int i = 0; i < 8; ++i) read_k(opA[i], k_base + at, 0, i);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) { qk(opA[i], 0, i); read_v(opB[i], v_base + at, 0, i >> 2, i & 3); }
-#pragma unroll
-                for (int i = 0; i < 16; ++i)
-                    if (!((word >> ((i >> 2) * 8 + (i & 3))) & 1u)) s[0][i] = kNegInf;
+                mask_scores(s[0], word);
                 softmax(one);
 #pragma unroll
                 for (int i = 0; i < 8; ++i) pv(opB[i], 0, i >> 2, i & 3);
