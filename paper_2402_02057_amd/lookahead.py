@@ -112,11 +112,9 @@ class LookaheadDecoder:
         self.model, self.W, self.N, self.G, self.seed = model, W, N, G, seed
         self.temperature, self.uniform = temperature, uniform
         model.append([int(t) for t in prompt[:-1]])
-        dev = "cuda"
-        self._out = torch.empty((N,), dtype=torch.int32, device=dev)
-        self._n_out = torch.empty((1,), dtype=torch.int32, device=dev)
-        self._best = torch.empty((1,), dtype=torch.int32, device=dev)
-        self._new = torch.empty((W,), dtype=torch.int32, device=dev)
+        # the step's results side by side, so that the host reads them in one go
+        self._result = torch.zeros((N + 2 + W,), dtype=torch.int32, device="cuda")
+        self._out, self._n_out, self._best, self._new = self._result.split((N, 1, 1, W))
 
     window = property(lambda self: self._seq.window)
     pool = property(lambda self: self._seq.pool)
@@ -139,8 +137,9 @@ class LookaheadDecoder:
             binding.la_verify_step(logits[0], look, cand_logits, cand, W, N, g, V, self._out, self._n_out,
                                    self._best, self._new if W else None, None)
             self.model.commit(self._best, self._n_out)                    # queued behind the verification
-            n = int(self._n_out.item())                                   # (synchronises)
-            accepted = self._out[:n].tolist()
+            result = self._result.tolist()                                # (synchronises)
+            n, best = result[N], result[N + 1]
+            accepted = result[:n]
         else:
             # the window's new level: greedy tokens of the lookahead rows (no candidates in this call)
             binding.la_verify_step(logits[0], look, None, None, W, N, 0, V, self._out, self._n_out, self._best,
@@ -151,17 +150,18 @@ class LookaheadDecoder:
             u_final = torch.tensor([float(self.uniform(self.seed, step, 1 << 20))], dtype=torch.float32).to(logits.device)
             binding.la_verify_sample(logits[0], cand_logits, cand, u_test, u_final, self.temperature, N, g, V,
                                      self._out, self._n_out)
-            n = int(self._n_out.item())
-            accepted = self._out[:n].tolist()
+            result = self._result.tolist()
+            n = result[N]
+            accepted = result[:n]
             # any candidate that starts with the accepted tokens has their keys and values
             k = n - 1
             best = next((i for i, tail in enumerate(tails) if list(tail[:k]) == accepted[:k]), -1) if k else -1
             self._best.fill_(best)
             self.model.commit(self._best, self._n_out)
-        new = self._new.tolist() if W else []
+        new = result[N + 2:]
         self._seq.absorb(accepted, new)
         self.model.advance(n)       # the cache now holds cur and accepted[:-1]
-        return accepted, tokens, int(self._best.item()), new
+        return accepted, tokens, best, new
 
     def generate(self, n_tokens):
         out = []
@@ -190,11 +190,9 @@ class BatchedLookaheadDecoder:
         self.seqs = [_Sequence(p, W, N, G, sd, random_token, prompt_as_reference) for p, sd in zip(prompts, seeds)]
         for i, p in enumerate(prompts):
             model.append(i, [int(t) for t in p[:-1]])
-        dev, i32 = "cuda", torch.int32
-        self._out = torch.empty((n, N), dtype=i32, device=dev)
-        self._n_out = torch.empty((n, 1), dtype=i32, device=dev)
-        self._best = torch.empty((n, 1), dtype=i32, device=dev)
-        self._new = torch.empty((n, W), dtype=i32, device=dev)
+        # a row of results per sequence, so that the host reads them in one go
+        self._result = torch.zeros((n, N + 2 + W), dtype=torch.int32, device="cuda")
+        self._out, self._n_out, self._best, self._new = self._result.split((N, 1, 1, W), dim=1)
 
     def step(self):
         """One step of every sequence; returns per sequence (accepted tokens, step tokens without the
@@ -206,27 +204,27 @@ class BatchedLookaheadDecoder:
         padded = [t + [t[0] if t else placeholder] * (g_step - len(t)) for t in tails]
         tokens = [s.step_tokens(p) for s, p in zip(self.seqs, padded)]
         logits = self.model.forward_step(tokens, W, N, g_step)
+        cand = torch.tensor(padded, dtype=torch.int32, device=logits[0].device).view(-1, g_step, n1) if g_step else None
         descs = []
         for i, lg in enumerate(logits):
             descs.append(dict(
                 logits_cur=lg[0], logits_look=lg[1 + (n1 - 1) * W:1 + n1 * W] if W else None,
                 logits_cand=lg[1 + W * n1:].view(g_step, n1, V) if g_step else None,
-                cand_tokens=torch.tensor(padded[i], dtype=torch.int32, device=lg.device).view(g_step, n1) if g_step else None,
+                cand_tokens=cand[i] if g_step else None,
                 out_tokens=self._out[i], n_out=self._n_out[i], best=self._best[i],
                 new_window=self._new[i] if W else None))
         binding.la_verify_step_batch(descs, W, N, g_step, V)
         self.model.commit([self._best[i] for i in range(len(self.seqs))],
                           [self._n_out[i] for i in range(len(self.seqs))])   # queued behind the verification
-        out, n_out = self._out.tolist(), self._n_out.view(-1).tolist()           # (synchronises)
-        best, new = self._best.view(-1).tolist(), self._new.tolist()
+        result = self._result.tolist()                                             # (synchronises)
         results = []
         for i, s in enumerate(self.seqs):
             real = len(tails[i])
-            n = n_out[i] if real else 1          # a placeholder's acceptance does not count
-            accepted = out[i][:n]
-            s.absorb(accepted, new[i] if W else [])
+            n = result[i][N] if real else 1      # a placeholder's acceptance does not count
+            accepted, new = result[i][:n], result[i][N + 2:]
+            s.absorb(accepted, new)
             self.model.advance(i, n)            # (rows the device appended beyond that are never read)
-            results.append((accepted, tokens[i][:1 + (W + real) * n1], best[i] if real else -1, new[i] if W else []))
+            results.append((accepted, tokens[i][:1 + (W + real) * n1], result[i][N + 1] if real else -1, new))
         return results
 
     def generate(self, n_tokens):
@@ -252,7 +250,8 @@ class ToyAttentionLM:
 
         def table(x):
             return torch.from_numpy(x).to(device).to(torch.bfloat16).view(self.vocab, 1, d)
-        self._q, self._k, self._v = table(t["q"]), table(t["k"]), table(t["v"])
+        self._qkv = torch.stack([table(t["q"]), table(t["k"]), table(t["v"])])   # (one gather for all three)
+        _, self._k, self._v = self._qkv
         self._logits = torch.from_numpy(t["logits"]).to(device)
         self.page_size = page_size
         if page_size:
@@ -293,15 +292,13 @@ class ToyAttentionLM:
         if P + N > self.capacity:
             raise ValueError("KV cache full")
         out = torch.empty((T, 1, d), dtype=torch.bfloat16, device=self.device)
-        self._step = (self._k[idx].contiguous(), self._v[idx].contiguous(), W, N, G)
+        q, k, v = self._qkv[:, idx]
+        self._step = (k, v, W, N, G)
         if self.page_size:
-            binding.la_step_attention_paged(self._q[idx].contiguous(), self._k_cache, self._v_cache,
-                                            self.block_table, self._step[0], self._step[1], P, W, N, G, 1, 1, d, out)
+            binding.la_step_attention_paged(q, self._k_cache, self._v_cache, self.block_table, k, v, P, W, N, G, 1, 1, d, out)
         else:
-            binding.la_step_attention_cap(self._q[idx].contiguous(), self._k_cache, self._v_cache, self._step[0],
-                                          self._step[1], P, W, N, G, 1, 1, d, out)
-        found = (out[:, 0, 0].float() > 0.5).long()
-        return self._logits[idx * 2 + found].contiguous()
+            binding.la_step_attention_cap(q, self._k_cache, self._v_cache, k, v, P, W, N, G, 1, 1, d, out)
+        return self._logits[torch.add(out[:, 0, 0] > 0.5, idx, alpha=2)]
 
     def commit(self, best, n_out):
         step_k, step_v, W, N, G = self._step
@@ -328,7 +325,8 @@ class ToyBatchLM:
 
         def table(x):
             return torch.from_numpy(x).to(device).to(torch.bfloat16).view(self.vocab, 1, d)
-        self._q, self._k, self._v = table(t["q"]), table(t["k"]), table(t["v"])
+        self._qkv = torch.stack([table(t["q"]), table(t["k"]), table(t["v"])])   # (one gather for all three)
+        _, self._k, self._v = self._qkv
         self._logits = torch.from_numpy(t["logits"]).to(device)
         self.page_size, self.device = page_size, device
         per_seq = (max_len + page_size - 1) // page_size
@@ -356,20 +354,18 @@ class ToyBatchLM:
     def forward_step(self, tokens, W, N, G):
         d = wl.TOY_HEAD_DIM
         T = 1 + (W + G) * (N - 1)
-        seqs, idxs = [], []
         for i, toks in enumerate(tokens):
             assert len(toks) == T
             if self.lengths[i] + N > self.capacity:
                 raise ValueError("KV cache full")
-            idx = torch.tensor(toks, dtype=torch.long, device=self.device)
-            idxs.append(idx)
-            seqs.append(dict(q=self._q[idx].contiguous(), block_table=self.block_tables[i],
-                             step_k=self._k[idx].contiguous(), step_v=self._v[idx].contiguous(),
-                             out=torch.empty((T, 1, d), dtype=torch.bfloat16, device=self.device), P=self.lengths[i]))
+        idx = torch.tensor(tokens, dtype=torch.long, device=self.device)
+        q, k, v = self._qkv[:, idx]
+        out = torch.empty((len(tokens), T, 1, d), dtype=torch.bfloat16, device=self.device)
+        seqs = [dict(q=q[i], block_table=self.block_tables[i], step_k=k[i], step_v=v[i], out=out[i], P=self.lengths[i])
+                for i in range(len(tokens))]
         binding.la_step_attention_batch_paged(seqs, self._k_pages, self._v_pages, W, N, G, 1, 1, d)
         self._step = (seqs, W, N, G)
-        return [self._logits[idx * 2 + (x["out"][:, 0, 0].float() > 0.5).long()].contiguous()
-                for idx, x in zip(idxs, seqs)]
+        return list(self._logits[torch.add(out[:, :, 0, 0] > 0.5, idx, alpha=2)])
 
     def commit(self, bests, n_outs):
         seqs, W, N, G = self._step
