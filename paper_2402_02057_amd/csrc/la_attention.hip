@@ -629,7 +629,6 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     f32x16 o[C::DB];
     float m_run, l_run;
     f32x4 lsum;                                   // row sums while the loop runs
-    const bf16x8 pick = row_sum_operand(lane);
     const int db0 = KS > 1 ? ks * C::SPW : 0;
     // Which of an iteration's chunks this wave takes.  Waves w and w + NW/2 (equal key index,
     // different tiles when RT = 2) share a SIMD: odd tiles take the chunks in rotated order, so
@@ -890,7 +889,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 const float neg_mc = -m_use * sl2;
                 if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                     const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                    scale_row_sums(lsum, alpha, lane);
+                    scale_row_sums(lsum, alpha);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -906,7 +905,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 // ---- O^T += V^T P^T
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
-                    lsum = add_row_sums(pick, pf[kk], lsum);
+                    lsum = add_row_sums(pf[kk], lsum);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db) {
                         bf16x8 a;
@@ -928,7 +927,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
         }
 
         LA_STAMP(3);
-        l_run = row_sum(lsum, lane);
+        l_run = row_sum(lsum);
 
         // ---- where the merge leaves its data: ring stages that nobody reads any more.  The
         //      waves are at most one iteration apart, so once a wave is past the loop the others

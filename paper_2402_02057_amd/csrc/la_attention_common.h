@@ -121,34 +121,31 @@ __device__ __forceinline__ float max_across_halves(float x)
 
 // Row sums of the softmax weights on the matrix cores.  v_dot2c_f32_bf16 over pairs of weights is one
 // instruction a pair, but holds the matrix cores up for 16 cycles (measured: 49 instead of 33 cycles for a
-// 32x32x16 product and one of them); one 16x16x32 product adds up 16 keys of 32 rows in 16 cycles.  The
-// weights stay as the PV product takes them (lane l: row l % 32, eight keys of half l / 32); read as an
-// operand of 16 columns, lane l holds column l % 16, keys 8 * (l / 16) .. +7: row 0 of `row_sum_operand`
-// has ones at the keys that are rows 0 .. 15, row 1 at those of rows 16 .. 31.  The sums of row r and
-// r + 16 end up in elements 0 and 1 of lane r, both half-waves' keys included.
-__device__ __forceinline__ bf16x8 row_sum_operand(int lane)
+// 32x32x16 product and one of them).  A 4x4x4 product of 16 blocks with ones on the left adds up four keys
+// per lane: column l % 4 of block l / 4 is lane l's, so the weights stay as the PV product takes them, a lane
+// gets the sum over its own half-wave's keys, and no row meets another one's weights.  (One 16x16x32 product that
+// picks rows r and r + 16 apart with ones and zeros did the same work, but 0 * NaN is NaN: a row whose
+// scores are not finite spoilt the row 16 from it.)
+__device__ __forceinline__ f32x4 add_row_sums4(const bf16x8& weights, int half, const f32x4& sums)
 {
-    bf16x8 v;
+    typedef __attribute__((ext_vector_type(4))) short short4;
+    union { bf16x8 v; short4 h[2]; } u;
+    u.v = weights;
+    constexpr short one = 0x3F80;   // 1.0 in bf16
+    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(short4{one, one, one, one}, u.h[half], sums, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4 add_row_sums(const bf16x8& weights, const f32x4& sums)
+{
+    return add_row_sums4(weights, 1, add_row_sums4(weights, 0, sums));
+}
+// alpha: factor of the lane's row (the four elements are the same sum)
+__device__ __forceinline__ void scale_row_sums(f32x4& sums, float alpha)
+{
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
-    return v;
+    for (int i = 0; i < 4; ++i) sums[i] *= alpha;
 }
-__device__ __forceinline__ f32x4 add_row_sums(const bf16x8& pick, const bf16x8& weights, const f32x4& sums)
-{
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick, weights, sums, 0, 0, 0);
-}
-// alpha: factor of row lane % 32
-__device__ __forceinline__ void scale_row_sums(f32x4& sums, float alpha, int lane)
-{
-    sums[0] *= alpha;                                        // (lanes 0 .. 15 count)
-    sums[1] *= __shfl(alpha, (lane & 15) + 16, 64);
-}
-// the sum of row lane % 32, in every lane
-__device__ __forceinline__ float row_sum(const f32x4& sums, int lane)
-{
-    const float a = __shfl(sums[0], lane & 15, 64), b = __shfl(sums[1], lane & 15, 64);
-    return (lane & 16) ? b : a;
-}
+// the sum of the lane's row over both half-waves' keys
+__device__ __forceinline__ float row_sum(const f32x4& sums) { return sums[0] + __shfl_xor(sums[0], 32, 64); }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 

@@ -135,7 +135,6 @@ void step_attention_rowtile_kernel(const RowTileParams)
     f32x16 o[2];
     float m_run = kNegInf, l_run;
     f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};  // row sums while the loop runs
-    const bf16x8 pick = row_sum_operand(lane);
     const float sl2 = p.scale_log2;
 
     // ---- rotating variant: what every thread of the workgroup does behind an iteration's barrier.
@@ -394,7 +393,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
                     const float neg_mc = -m_use * sl2;
                     if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
                         const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                        scale_row_sums(lsum, alpha, lane);
+                        scale_row_sums(lsum, alpha);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -408,7 +407,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
                     // ---- O^T += V^T P^T (this workgroup's half of the columns)
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk) {
-                        lsum = add_row_sums(pick, pf[kk], lsum);
+                        lsum = add_row_sums(pf[kk], lsum);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
                             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk][db], pf[kk], o[db], 0, 0, 0);
@@ -419,7 +418,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
         if (it < 4) LA_STAMP(9 + 2 * it);
     }
     LA_STAMP(3);
-    l_run = row_sum(lsum, lane);
+    l_run = row_sum(lsum);
 
     // ---- merge the four waves: every wave leaves its two slices and (m, l); after the barrier wave w
     //      sums registers (w/2)*8 .. +7 of slice w%2 over the four states, in key order, and writes

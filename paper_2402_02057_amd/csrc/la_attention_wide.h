@@ -9,7 +9,7 @@
 //
 // A wave owns one 32-row tile and walks all keys of its workgroup's range: eight tiles share a chunk.  Waves
 // 4 .. 7 (w and w + 4 share a SIMD) run half a period behind: between two barriers the early wave does
-// its matrix phase (PV of the last chunk, scores of this one: 36 products whose operands are read a batch
+// its matrix phase (PV of the last chunk, scores of this one: 32 products, and the row sums; operands are read a batch
 // ahead) and then its softmax, the late one its softmax and then its matrix phase, on the same data.
 // K of a chunk is read in its own period, V in the next, so a stage is free two barriers after its
 // chunk arrived; five stages of 32 KB leave three chunks in flight.  The query rows pass through the two
@@ -220,7 +220,6 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
     f32x16 o[C::DB];
     float m_run, l_run;
     f32x4 lsum;
-    const bf16x8 pick = row_sum_operand(lane);
 
     // LDS addresses of the reads in stage 0.  Piece and column of a read are XORed in as it is made (address
     // bits 5 to 7, which the swizzle leaves as a plain XOR): fifteen registers less than an address each.
@@ -278,7 +277,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
         dst = u.v;
     };
     auto pv = [&](const bf16x8& v, int b, int kk, int db) {
-        if (db == 0) lsum = add_row_sums(pick, pf[b][kk], lsum);
+        if (db % 2 == 0) lsum = add_row_sums4(pf[b][kk], db / 2, lsum);
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[b][kk], o[db], 0, 0, 0);
     };
     auto qk = [&](const bf16x8& k, int b, int k16) {
@@ -306,7 +305,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
         const float neg_mc = -m_use * sl2;
         if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
             const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-            scale_row_sums(lsum, alpha, lane);
+            scale_row_sums(lsum, alpha);
 #pragma unroll
             for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -397,7 +396,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
         }
     }
 
-    l_run = row_sum(lsum, lane);
+    l_run = row_sum(lsum);
     __syncthreads();  // everyone is through with the ring
     if (!wave_active) return;
     if (p.XS == 1) {
