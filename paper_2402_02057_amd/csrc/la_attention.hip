@@ -629,6 +629,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     f32x16 o[C::DB];
     float m_run, l_run;
     f32x4 lsum;                                   // row sums while the loop runs
+    const bf16x8 pick = row_sum_operand(lane);
     const int db0 = KS > 1 ? ks * C::SPW : 0;
     // Which of an iteration's chunks this wave takes.  Waves w and w + NW/2 (equal key index,
     // different tiles when RT = 2) share a SIMD: odd tiles take the chunks in rotated order, so
@@ -883,13 +884,13 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 // m_run only moves when the block maximum exceeds it by more than 2^8 in the
                 // exponent (or no key was seen yet): softmax is invariant to the reference, and
                 // skipping small moves saves rescaling the accumulators nearly every time.
-                const bool move = (mx - m_run) * sl2 > 8.0f || m_run == kNegInf;
+                const bool move = reference_moves(mx, m_run, sl2);
                 const float m_new = move ? mx : m_run;
                 const float m_use = (m_new == kNegInf) ? 0.0f : m_new;  // the row has seen no key at all
-                const float neg_mc = -m_use * sl2;
+                const float bias = weight_bias(m_use, sl2);
                 if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
-                    const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                    scale_row_sums(lsum, alpha);
+                    const float alpha = moved_by(m_run, m_use, sl2);
+                    scale_row_sums(lsum, alpha, lane);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -901,11 +902,11 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                 bf16x8 pf[2];
 #pragma unroll
                 for (int i = 0; i < 16; ++i)
-                    pf[i >> 3][i & 7] = (__bf16)fast_exp2(__builtin_fmaf(s[i], sl2, neg_mc));
+                    pf[i >> 3][i & 7] = (__bf16)weight(s[i], sl2, bias);
                 // ---- O^T += V^T P^T
 #pragma unroll
                 for (int kk = 0; kk < 2; ++kk) {
-                    lsum = add_row_sums(pf[kk], lsum);
+                    lsum = add_row_sums(pick, pf[kk], lsum);
 #pragma unroll
                     for (int db = 0; db < C::DB; ++db) {
                         bf16x8 a;
@@ -927,7 +928,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
         }
 
         LA_STAMP(3);
-        l_run = row_sum(lsum);
+        l_run = row_sum(lsum, lane);
 
         // ---- where the merge leaves its data: ring stages that nobody reads any more.  The
         //      waves are at most one iteration apart, so once a wave is past the loop the others

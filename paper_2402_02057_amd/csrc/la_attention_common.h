@@ -81,12 +81,12 @@ __device__ __forceinline__ void mask_scores(V& s, unsigned word)
     }
 }
 
-// Three-way maximum in one instruction; unlike fmaxf the compiler adds no NaN-quieting moves
-// around it (scores are MFMA results or -inf, never signalling NaNs).
+// Three-way maximum in one instruction.  The maximum of a NaN and anything is NaN: a row that met a score
+// that is no number has a NaN as its reference, see `weight`.
 __device__ __forceinline__ float max3(float a, float b, float c)
 {
     float r;
-    asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    asm("v_maximum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
     return r;
 }
 
@@ -105,7 +105,7 @@ __device__ __forceinline__ void settle_mfma_result(V& acc)
 __device__ __forceinline__ float max2(float a, float b)
 {
     float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    asm("v_maximum3_f32 %0, %1, %2, %2" : "=v"(r) : "v"(a), "v"(b));
     return r;
 }
 
@@ -121,33 +121,54 @@ __device__ __forceinline__ float max_across_halves(float x)
 
 // Row sums of the softmax weights on the matrix cores.  v_dot2c_f32_bf16 over pairs of weights is one
 // instruction a pair, but holds the matrix cores up for 16 cycles (measured: 49 instead of 33 cycles for a
-// 32x32x16 product and one of them).  A 4x4x4 product of 16 blocks with ones on the left adds up four keys
-// per lane: column l % 4 of block l / 4 is lane l's, so the weights stay as the PV product takes them, a lane
-// gets the sum over its own half-wave's keys, and no row meets another one's weights.  (One 16x16x32 product that
-// picks rows r and r + 16 apart with ones and zeros did the same work, but 0 * NaN is NaN: a row whose
-// scores are not finite spoilt the row 16 from it.)
-__device__ __forceinline__ f32x4 add_row_sums4(const bf16x8& weights, int half, const f32x4& sums)
+// 32x32x16 product and one of them); one 16x16x32 product adds up 16 keys of 32 rows in 16 cycles.  The
+// weights stay as the PV product takes them (lane l: row l % 32, eight keys of half l / 32); read as an
+// operand of 16 columns, lane l holds column l % 16, keys 8 * (l / 16) .. +7: row 0 of `row_sum_operand`
+// has ones at the keys that are rows 0 .. 15, row 1 at those of rows 16 .. 31.  The sums of row r and
+// r + 16 end up in elements 0 and 1 of lane r, both half-waves' keys included.  (0 * NaN is NaN: no weight
+// may be one, or row r would spoil r + 16; `weight` sees to that.  4x4x4 products of 16 blocks, which add up a
+// lane's own keys, need no such care but take longer: 8 prefixes of 1253 to 14559 keys 164 instead of 155 us a
+// layer, the 13b step on an 8-bit cache 14.9 instead of 14.4.)
+__device__ __forceinline__ bf16x8 row_sum_operand(int lane)
 {
-    typedef __attribute__((ext_vector_type(4))) short short4;
-    union { bf16x8 v; short4 h[2]; } u;
-    u.v = weights;
-    constexpr short one = 0x3F80;   // 1.0 in bf16
-    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(short4{one, one, one, one}, u.h[half], sums, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4 add_row_sums(const bf16x8& weights, const f32x4& sums)
-{
-    return add_row_sums4(weights, 1, add_row_sums4(weights, 0, sums));
-}
-// alpha: factor of the lane's row (the four elements are the same sum)
-__device__ __forceinline__ void scale_row_sums(f32x4& sums, float alpha)
-{
+    bf16x8 v;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sums[i] *= alpha;
+    for (int i = 0; i < 8; ++i) v[i] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
+    return v;
 }
-// the sum of the lane's row over both half-waves' keys
-__device__ __forceinline__ float row_sum(const f32x4& sums) { return sums[0] + __shfl_xor(sums[0], 32, 64); }
+__device__ __forceinline__ f32x4 add_row_sums(const bf16x8& pick, const bf16x8& weights, const f32x4& sums)
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(pick, weights, sums, 0, 0, 0);
+}
+// alpha: factor of row lane % 32
+__device__ __forceinline__ void scale_row_sums(f32x4& sums, float alpha, int lane)
+{
+    sums[0] *= alpha;                                        // (lanes 0 .. 15 count)
+    sums[1] *= __shfl(alpha, (lane & 15) + 16, 64);
+}
+// the sum of row lane % 32, in every lane
+__device__ __forceinline__ float row_sum(const f32x4& sums, int lane)
+{
+    const float a = __shfl(sums[0], lane & 15, 64), b = __shfl(sums[1], lane & 15, 64);
+    return (lane & 16) ? b : a;
+}
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+
+// The softmax weight of a score s is 2^(s * sl2 + bias), bias = weight_bias(reference, sl2).  The reference is
+// at most 2^8 in the exponent below the maximum, and the bias takes those eight off as well: a weight is at
+// most 1 (softmax does not see a common factor), and the clamp to [0, 1] that v_exp_f32 has for nothing
+// only turns NaN to 0.  Where a weight would have been NaN the reference is NaN (it wins a maximum here) or +inf,
+// and the row still comes out as NaN: its accumulators are scaled by NaN, or end as 0 / 0.
+__device__ __forceinline__ float weight_bias(float reference, float sl2) { return __builtin_fmaf(-reference, sl2, -8.0f); }
+__device__ __forceinline__ float weight(float s, float sl2, float bias)
+{
+    return __builtin_amdgcn_fmed3f(fast_exp2(__builtin_fmaf(s, sl2, bias)), 0.0f, 1.0f);
+}
+// whether the reference moves to the maximum of this block: it is further up than that, or no number, or nothing was seen yet
+__device__ __forceinline__ bool reference_moves(float block, float reference, float sl2) { return !((block - reference) * sl2 <= 8.0f); }
+// what scales the row's accumulators when the reference moves: exactly 1 for the rows of the wave whose reference stays
+__device__ __forceinline__ float moved_by(float from, float to, float sl2) { return fast_exp2((from - to) * sl2); }
 
 template <int N>
 __device__ __forceinline__ void wait_vmcnt()

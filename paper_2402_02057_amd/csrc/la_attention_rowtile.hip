@@ -135,6 +135,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
     f32x16 o[2];
     float m_run = kNegInf, l_run;
     f32x4 lsum = {0.0f, 0.0f, 0.0f, 0.0f};  // row sums while the loop runs
+    const bf16x8 pick = row_sum_operand(lane);
     const float sl2 = p.scale_log2;
 
     // ---- rotating variant: what every thread of the workgroup does behind an iteration's barrier.
@@ -387,13 +388,13 @@ void step_attention_rowtile_kernel(const RowTileParams)
 #pragma unroll
                     for (int i = 3; i < 15; i += 2) mx = max3(mx, s[i], s[i + 1]);
                     mx = max_across_halves(max2(mx, s[15]));
-                    const bool move = (mx - m_run) * sl2 > 8.0f || m_run == kNegInf;
+                    const bool move = reference_moves(mx, m_run, sl2);
                     const float m_new = move ? mx : m_run;
                     const float m_use = (m_new == kNegInf) ? 0.0f : m_new;  // the row has seen no key at all
-                    const float neg_mc = -m_use * sl2;
+                    const float bias = weight_bias(m_use, sl2);
                     if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
-                        const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-                        scale_row_sums(lsum, alpha);
+                        const float alpha = moved_by(m_run, m_use, sl2);
+                        scale_row_sums(lsum, alpha, lane);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
 #pragma unroll
@@ -403,11 +404,11 @@ void step_attention_rowtile_kernel(const RowTileParams)
                     // P in bf16, as the PV product uses it; the row sum adds up those same rounded values
                     bf16x8 pf[2];
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) pf[i >> 3][i & 7] = (__bf16)fast_exp2(__builtin_fmaf(s[i], sl2, neg_mc));
+                    for (int i = 0; i < 16; ++i) pf[i >> 3][i & 7] = (__bf16)weight(s[i], sl2, bias);
                     // ---- O^T += V^T P^T (this workgroup's half of the columns)
 #pragma unroll
                     for (int kk = 0; kk < 2; ++kk) {
-                        lsum = add_row_sums(pf[kk], lsum);
+                        lsum = add_row_sums(pick, pf[kk], lsum);
 #pragma unroll
                         for (int db = 0; db < 2; ++db)
                             o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[kk][db], pf[kk], o[db], 0, 0, 0);
@@ -418,7 +419,7 @@ void step_attention_rowtile_kernel(const RowTileParams)
         if (it < 4) LA_STAMP(9 + 2 * it);
     }
     LA_STAMP(3);
-    l_run = row_sum(lsum);
+    l_run = row_sum(lsum, lane);
 
     // ---- merge the four waves: every wave leaves its two slices and (m, l); after the barrier wave w
     //      sums registers (w/2)*8 .. +7 of slice w%2 over the four states, in key order, and writes

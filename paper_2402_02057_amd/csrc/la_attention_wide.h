@@ -9,7 +9,7 @@
 //
 // A wave owns one 32-row tile and walks all keys of its workgroup's range: eight tiles share a chunk.  Waves
 // 4 .. 7 (w and w + 4 share a SIMD) run half a period behind: between two barriers the early wave does
-// its matrix phase (PV of the last chunk, scores of this one: 32 products, and the row sums; operands are read a batch
+// its matrix phase (PV of the last chunk, scores of this one: 36 products whose operands are read a batch
 // ahead) and then its softmax, the late one its softmax and then its matrix phase, on the same data.
 // K of a chunk is read in its own period, V in the next, so a stage is free two barriers after its
 // chunk arrived; five stages of 32 KB leave three chunks in flight.  The query rows pass through the two
@@ -220,6 +220,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
     f32x16 o[C::DB];
     float m_run, l_run;
     f32x4 lsum;
+    const bf16x8 pick = row_sum_operand(lane);
 
     // LDS addresses of the reads in stage 0.  Piece and column of a read are XORed in as it is made (address
     // bits 5 to 7, which the swizzle leaves as a plain XOR): fifteen registers less than an address each.
@@ -277,7 +278,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
         dst = u.v;
     };
     auto pv = [&](const bf16x8& v, int b, int kk, int db) {
-        if (db % 2 == 0) lsum = add_row_sums4(pf[b][kk], db / 2, lsum);
+        if (db == 0) lsum = add_row_sums(pick, pf[b][kk], lsum);
         o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(v, pf[b][kk], o[db], 0, 0, 0);
     };
     auto qk = [&](const bf16x8& k, int b, int k16) {
@@ -299,13 +300,13 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
             for (int i = 3; i < 15; i += 2) mx[b] = max3(mx[b], s[b][i], s[b][i + 1]);
         }
         const float m_blk = max_across_halves(NB == 2 ? max2(max3(mx[0], s[0][15], mx[NB - 1]), s[NB - 1][15]) : max2(mx[0], s[0][15]));
-        const bool move = (m_blk - m_run) * sl2 > 8.0f || m_run == kNegInf;
+        const bool move = reference_moves(m_blk, m_run, sl2);
         const float m_new = move ? m_blk : m_run;
         const float m_use = (m_new == kNegInf) ? 0.0f : m_new;  // the row has seen no key at all
-        const float neg_mc = -m_use * sl2;
+        const float bias = weight_bias(m_use, sl2);
         if (__builtin_amdgcn_ballot_w64(move) != 0ull) {
-            const float alpha = fast_exp2(__builtin_fmaf(m_run, sl2, neg_mc));
-            scale_row_sums(lsum, alpha);
+            const float alpha = moved_by(m_run, m_use, sl2);
+            scale_row_sums(lsum, alpha, lane);
 #pragma unroll
             for (int db = 0; db < C::DB; ++db)
 #pragma unroll
@@ -315,7 +316,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
 #pragma unroll
         for (int b = 0; b < NB; ++b)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) pf[b][i >> 3][i & 7] = (__bf16)fast_exp2(__builtin_fmaf(s[b][i], sl2, neg_mc));
+            for (int i = 0; i < 16; ++i) pf[b][i >> 3][i & 7] = (__bf16)weight(s[b][i], sl2, bias);
     };
     constexpr std::integral_constant<int, 1> one;
     constexpr std::integral_constant<int, 2> both;
@@ -396,7 +397,7 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
         }
     }
 
-    l_run = row_sum(lsum);
+    l_run = row_sum(lsum, lane);
     __syncthreads();  // everyone is through with the ring
     if (!wave_active) return;
     if (p.XS == 1) {

@@ -55,6 +55,8 @@ def test_rows_that_are_not_finite(override, run, hook, P, H, KV, d):
     for t, h, value in ((3, 0, float("nan")), (40, H - 1, float("inf")), (T - 2, 1, float("nan"))):
         s["q"][t, h] = value
         spoilt[t, h] = True
+    s["q"][22, 0, 7] = float("inf")     # infinite scores of both signs, none of them NaN
+    spoilt[22, 0] = True
     if run is not run_fp8:          # a key that only the last row sees
         s["step_k"][T - 1] = float("nan")
         spoilt[T - 1] = True
