@@ -117,9 +117,10 @@ struct Layout {
 // steps on, the step with the longest ranges is cut once more as long as the sum of all
 // workgroups leaves room for a better end than the best one seen; cuts whose longest workgroup alone
 // takes that long are passed over unplaced.  Returns the launch's end.
-// (Host time of a plan, which every call and so every layer pays for: over 300 batches of 2 to 16 steps
-// of all sizes in use median 0.5 us, one in ten above 2.5, at most 7.7.  Placing every set of cuts, one
-// workgroup at a time, with no bound on the cuts: 5.3, 25.5 and 68.)
+// (Host time, which every call and so every layer pays for: of this plan, over 3000 batches of 2 to 16 steps
+// of all sizes in use, median 0.4 us, one in ten above 2.0, at most 11; with the pipelined kernel's, `search_wide`,
+// 0.7, 2.8 and 16.  Placing every set of cuts, one workgroup at a time, with no bound on the cuts: 5.3, 25.5
+// and 68 for this one.)
 inline long long search(const int* chunks, const int* limit, int n, const Form& f, int* cuts, int* place)
 {
     Layout l;
@@ -241,40 +242,124 @@ struct WideForm {
     int units, chunk, fixed;   // times in 10 ns
 };
 
-// As `search`, for the pipelined kernel, whose steps may all be cut: from uncut steps on, the step with the
-// longest ranges is cut once more, as long as the sum of all workgroups leaves room for a better end.
-inline long long search_wide(const int* chunks, int n, const WideForm& f, LaunchPlan& p)
-{
-    Layout l;
-    long long best = -1;
-    for (int i = 0; i < n; ++i) l.cuts[i] = 1;
-    for (;;) {
-        int cut_wgs = 0, longest = 0;
+// A set of cuts of a pipelined launch as workgroups, longest first (equal ones in the steps' order).
+struct WideLayout {
+    const int* chunks;
+    WideForm f;
+    int n, cuts[kMaxBatch], range[kMaxBatch], wgs[kMaxBatch], order[kMaxBatch];
+    long long cost[kMaxBatch];
+    long long sum = 0;                        // of all workgroups of an XCD
+    long long workgroups = 0, cut_workgroups = 0, work = 0;   // of the launch; work: its chunks' time
+
+    WideLayout(const int* chunks_, int n_, const WideForm& f_) : chunks(chunks_), f(f_), n(n_)
+    {
         for (int i = 0; i < n; ++i) {
-            const int x = l.cuts[i];
-            l.wgs[i] = batch_wgs_per_xcd(f.units, x);
-            l.range[i] = (chunks[i] + x - 1) / x;
-            l.cost[i] = (long long)l.range[i] * f.chunk + f.fixed;
-            if (x > 1) cut_wgs += f.units * x;
-            if (l.range[i] > l.range[longest]) longest = i;
+            work += (long long)f.units * chunks[i] * f.chunk;
+            set(i, 1);
+            order[i] = i;
+            settle(i);
         }
-        if (cut_wgs > kMaxWideCutWorkgroups) break;
-        l.arrange(n, true);
-        // (the second kernel, and what storing and reading fp32 partial results takes)
-        const long long extra = cut_wgs ? 350 + cut_wgs : 0;
-        if (best >= 0 && l.sum / kXcdUnits + extra >= best) break;
-        if (best < 0 || l.cost[l.order[0]] + extra < best) {
-            const long long end = launch_end(l.order, n, l.wgs, l.cost) + extra;
-            if (best < 0 || end < best) {
-                best = end;
-                p.rows = kPipelinedRows;
-                for (int i = 0; i < n; ++i) { p.cuts[i] = l.cuts[i]; p.place[i] = l.order[i]; }
-            }
-        }
-        if (l.range[longest] < 8) break;
-        ++l.cuts[longest];
     }
-    return best;
+    void set(int i, int x)
+    {
+        cuts[i] = x;
+        range[i] = (chunks[i] + x - 1) / x;
+        wgs[i] = batch_wgs_per_xcd(f.units, x);
+        cost[i] = (long long)range[i] * f.chunk + f.fixed;
+        sum += wgs[i] * cost[i];
+        workgroups += (long long)f.units * x;
+        if (x > 1) cut_workgroups += (long long)f.units * x;
+    }
+    void cut(int i, int x)
+    {
+        sum -= wgs[i] * cost[i];
+        workgroups -= (long long)f.units * cuts[i];
+        if (cuts[i] > 1) cut_workgroups -= (long long)f.units * cuts[i];
+        set(i, x);
+    }
+    void settle(int at)  // order[at] among the steps before it
+    {
+        const int i = order[at];
+        for (; at > 0 && (cost[order[at - 1]] < cost[i] || (cost[order[at - 1]] == cost[i] && order[at - 1] > i)); --at) order[at] = order[at - 1];
+        order[at] = i;
+    }
+    int longest() const { return range[order[0]]; }
+    // No range of more than `most` chunks; false: that takes more workgroups than a launch may have.
+    bool cut_to(int most)
+    {
+        for (int i = 0; i < n; ++i)
+            if (range[i] > most) {
+                cut(i, (int)(((long long)chunks[i] + most - 1) / most));
+                if (!allowed()) return false;
+            }
+        for (int i = 1; i < n; ++i) settle(i);
+        return true;
+    }
+    void cut_longest()
+    {
+        const int i = order[0];
+        cut(i, cuts[i] + 1);
+        int at = 0;
+        for (; at + 1 < n && (cost[order[at + 1]] > cost[i] || (cost[order[at + 1]] == cost[i] && order[at + 1] < i)); ++at) order[at] = order[at + 1];
+        order[at] = i;
+    }
+    bool allowed() const { return cut_workgroups <= kMaxWideCutWorkgroups; }
+    // the second kernel, and what storing and reading fp32 partial results takes
+    long long extra() const { return cut_workgroups ? 350 + cut_workgroups : 0; }
+    // what no launch of these cuts or of more ends before
+    long long floor() const { return (work + workgroups * f.fixed) / (kXcds * kXcdUnits) + extra(); }
+    // when the launch ends, or `late` if that is no earlier
+    long long end(long long late) const
+    {
+        const long long before = late - extra();
+        if (cost[order[0]] >= before || sum / kXcdUnits >= before) return late;
+        for (int k = 0, rounds = 1, at = 0; k < n; ++k)   // of 32 * r + 1 workgroups r + 1 share a unit
+            for (at += wgs[order[k]]; at > rounds * kXcdUnits;)
+                if (++rounds * cost[order[k]] >= before) return late;
+        const long long e = launch_end(order, n, wgs, cost);
+        return e < before ? e + extra() : late;
+    }
+};
+
+// As `search`, for the pipelined kernel, whose steps may all be cut: from uncut steps on, the step with the
+// longest ranges is cut once more, down to ranges of four to seven chunks, and the plan is that of the
+// earliest end, if one ends before `late`.  This runs in every call, so only what can still win is placed:
+// the cuts at which a workgroup's own time meets the average unit's are placed first, which bounds the
+// longest range of a better plan from above (the walk starts there) and the number of its workgroups (it
+// ends there).  (Of 20000 drawn batches nine have another plan than if every set of cuts is placed until the
+// sum of its workgroups exceeds the best end, all of an earlier end.  Host time of a launch's plan, placed and as
+// here: 16 steps of 16k keys, 8 tiles, one KV head 23 and 2.6 us; 16 of 4096 keys, 41 rows, 8/2 heads 12.6
+// and 3.3; eight of 1253 to 14559 keys, 121 rows, 32/8 heads 3.9 and 1.7; one in a hundred of 3000 above 14 and 6.5.)
+inline bool search_wide(const int* chunks, int n, const WideForm& f, long long late, LaunchPlan& p)
+{
+    constexpr int kShort = 7;    // no longer ranges are cut
+    const WideLayout uncut(chunks, n, f);
+    if (uncut.floor() >= late) return false;
+    long long even = uncut.longest();
+    for (int k = 0; k < 4; ++k) {
+        const long long workgroups = uncut.work / (even * f.chunk) + (long long)f.units * n / 2;
+        const long long r = ((uncut.work + workgroups * f.fixed) / (kXcds * kXcdUnits) - f.fixed) / f.chunk + 1;
+        even = r < kShort ? kShort : r < uncut.longest() ? r : uncut.longest();
+    }
+    WideLayout l = uncut;
+    if (l.cut_to((int)even)) {
+        const long long e = l.end(late);
+        if (e < late) late = e + 1;    // (found again below, if nothing is better)
+    }
+    l = uncut;
+    const long long fits = (late - 1 - f.fixed) / f.chunk;
+    if (fits < l.longest() && !l.cut_to(fits > kShort ? (int)fits : kShort)) return false;
+    for (bool found = false;; l.cut_longest()) {
+        if (!l.allowed() || l.floor() >= late) return found;
+        const long long e = l.end(late);
+        if (e < late) {
+            late = e;
+            found = true;
+            p.rows = kPipelinedRows;
+            for (int i = 0; i < n; ++i) { p.cuts[i] = l.cuts[i]; p.place[i] = l.order[i]; }
+        }
+        if (l.longest() <= kShort) return found;
+    }
 }
 
 }  // namespace batch_plan
@@ -309,8 +394,7 @@ inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads,
     const int blocks = (tiles + 7) / 8, per_block = (tiles + blocks - 1) / blocks;
     const WideForm f = {kv_heads * blocks, 72 + 109 * per_block / 8, 700 + 65 * per_block};
     LaunchPlan q;
-    const long long e = search_wide(chunks, n, f, q);
-    return end < 0 || e * 100 < end * 93 ? q : p;
+    return search_wide(chunks, n, f, end < 0 ? 1ll << 60 : (end * 93 + 99) / 100, q) ? q : p;
 }
 
 }  // namespace la
