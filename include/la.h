@@ -37,7 +37,9 @@
  * asynchronous on `stream` (a hipStream_t passed as void*, NULL = the default
  * stream) and never synchronise the device.  The library keeps a small
  * workspace per device and set (split partials, tickets; 33 MB, what the
- * attention calls need), allocated on demand with hipMalloc - so a first call, or
+ * attention calls need, and 58 MB in a second block once a batch has run that may take
+ * the kernel of 256-row workgroups: head_dim 128, four or more 32-row tiles per KV head),
+ * allocated on demand with hipMalloc - so a first call, or
  * the first at a size that needs more, may allocate - and shared by
  * all calls on that device: calls issued to one stream are ordered; calls on
  * different streams of the same device must not overlap in time unless they use
@@ -46,7 +48,8 @@
  * that one sizes and clears the workspace, the kernels leave it cleared.  (A larger
  * shape will not always do: its workgroups may fill the device without exchanging
  * partials, and then it needs no workspace.  A batched attention call of two or
- * more steps reserves what any attention call needs.)  A workspace block that a
+ * more steps reserves what any attention call needs, and takes a kernel that
+ * needs less where that much is neither there nor to be had.)  A workspace block that a
  * later, larger call replaces stays
  * allocated until la_shutdown, so graphs recorded before remain valid (do not
  * call la_shutdown while such a graph may still be launched).

@@ -37,6 +37,7 @@ struct Pool {
     // Blocks that a growth replaced.  They are kept until la_shutdown: work already issued, and
     // HIP graphs recorded earlier, still name them (and no call has to wait for the device).
     std::vector<void*> retired;
+    unsigned pause = 0;   // so many calls do not try again to reserve what could not be allocated
 };
 // Per device, a few independent sets of blocks.  A thread's calls use the set it selected
 // (la_select_workspace, set 0 unless told otherwise): calls that may overlap in time - on different
@@ -66,13 +67,12 @@ la_status select_workspace(int set)
 }
 
 namespace {
-// A block is at least this large: what any batched launch needs (partial results: 36 KB a workgroup of the
-// staged kernel, 132 KB of the pipelined one; tickets, of the staged kernel alone: eight a group, 128
-// bytes apart), and more than any one step.
-constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(64) << 20;
-static_assert(kMaxCutWorkgroups * (size_t(36) << 10) <= kLeastScratch && kMaxCutGroups * size_t(8 * 128) <= kLeastZeroed &&
-                  kMaxWideCutWorkgroups * (size_t(132) << 10) <= kLeastScratch,
-              "a batched launch fits the least blocks");
+// A block is at least this large: what any batched launch of the staged kernel needs (36 KB of partial
+// results a workgroup; eight tickets a group, 128 bytes apart), and more than any one step.
+constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(32) << 20;
+static_assert(kMaxCutWorkgroups * kStagedPartialBytes <= kLeastScratch && kMaxCutGroups * kStagedTicketBytes <= kLeastZeroed,
+              "a staged batch fits the least blocks");
+constexpr unsigned kReservePause = 256;
 
 // Growing a block means hipMalloc (and a clear on the stream): neither may happen while the
 // stream is being captured into a graph - the allocation would invalidate the capture, the
@@ -94,6 +94,40 @@ bool growth_allowed(hipStream_t stream)
 }
 }  // namespace
 
+// A fresh block of the pool (g_mutex is held): the old one is retired, not freed.  False where there is no
+// memory for it, which nobody else hears of.
+static bool grow_scratch(Pool& p, size_t want)
+{
+    void* fresh = nullptr;
+    if (hipMalloc(&fresh, want) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (p.scratch) p.retired.push_back(p.scratch);
+    p.scratch = fresh;
+    p.scratch_bytes = want;
+    return true;
+}
+// (cleared on this stream, ahead of the kernel that will use it)
+static bool grow_zeroed(Pool& p, size_t want, hipStream_t stream)
+{
+    void* fresh = nullptr;
+    if (hipMalloc(&fresh, want) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (hipMemsetAsync(fresh, 0, want, stream) != hipSuccess) {
+        (void)hipGetLastError();
+        (void)hipFree(fresh);
+        return false;
+    }
+    if (p.zeroed) p.retired.push_back(p.zeroed);
+    p.zeroed = fresh;
+    p.zeroed_bytes = want;
+    return true;
+}
+
+// Growing happens only when a larger shape than any before is seen.
 void* zeroed_workspace(size_t bytes, hipStream_t stream)
 {
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -101,23 +135,12 @@ void* zeroed_workspace(size_t bytes, hipStream_t stream)
     if (!p) return nullptr;
     if (bytes <= p->zeroed_bytes) return p->zeroed;
     if (!growth_allowed(stream)) return nullptr;
-    // Growing (only when a larger shape than any before is seen): a fresh block, cleared on
-    // this stream ahead of the kernel that will use it; the old one is retired, not freed.
-    size_t want = bytes < kLeastZeroed ? kLeastZeroed : bytes;
-    void* fresh = nullptr;
-    if (hipMalloc(&fresh, want) != hipSuccess) {
-        fail(LA_ENOMEM, "hipMalloc of %zu bytes of ticket workspace failed", want);
+    const size_t want = bytes < kLeastZeroed ? kLeastZeroed : bytes;
+    if (!grow_zeroed(*p, want, stream)) {
+        fail(LA_ENOMEM, "%zu bytes of ticket workspace could not be allocated and cleared", want);
         return nullptr;
     }
-    if (hipMemsetAsync(fresh, 0, want, stream) != hipSuccess) {
-        (void)hipFree(fresh);
-        fail(LA_EHIP, "hipMemsetAsync on the ticket workspace failed");
-        return nullptr;
-    }
-    if (p->zeroed) p->retired.push_back(p->zeroed);
-    p->zeroed = fresh;
-    p->zeroed_bytes = want;
-    return fresh;
+    return p->zeroed;
 }
 
 void* scratch_workspace(size_t bytes, hipStream_t stream)
@@ -127,32 +150,33 @@ void* scratch_workspace(size_t bytes, hipStream_t stream)
     if (!p) return nullptr;
     if (bytes <= p->scratch_bytes) return p->scratch;
     if (!growth_allowed(stream)) return nullptr;
-    size_t want = bytes < kLeastScratch ? kLeastScratch : bytes + bytes / 4;
-    void* fresh = nullptr;
-    if (hipMalloc(&fresh, want) != hipSuccess) {
+    const size_t want = bytes < kLeastScratch ? kLeastScratch : bytes + bytes / 4;
+    if (!grow_scratch(*p, want)) {
         fail(LA_ENOMEM, "hipMalloc of %zu bytes of partial-result workspace failed", want);
         return nullptr;
     }
-    if (p->scratch) p->retired.push_back(p->scratch);
-    p->scratch = fresh;
-    p->scratch_bytes = want;
-    return fresh;
+    return p->scratch;
 }
 
-void reserve_workspace(hipStream_t stream)
+size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream)
 {
-    {
-        std::lock_guard<std::mutex> lock(g_mutex);
-        const Pool* p = current_pool();
-        if (!p || (p->zeroed && p->scratch)) return;
+    const size_t want = scratch_bytes < kLeastScratch ? kLeastScratch : scratch_bytes;
+    std::lock_guard<std::mutex> lock(g_mutex);
+    Pool* p = current_pool();
+    if (!p) return 0;
+    if (p->zeroed && p->scratch_bytes >= want) return p->scratch_bytes;
+    if (p->pause) {
+        --p->pause;
+        return p->scratch_bytes;
     }
-    if (capturing(stream)) return;
-    // (an allocation nobody needs yet must not disturb a capture that runs on another stream)
+    // (an allocation that can be done without must not disturb a capture that runs on another stream)
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return;
-    const bool ok = zeroed_workspace(1, stream) && scratch_workspace(1, stream);
+    if (capturing(stream) || hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return p->scratch_bytes;
+    const bool ok = (p->zeroed || grow_zeroed(*p, kLeastZeroed, stream)) &&
+                    (p->scratch_bytes >= want || grow_scratch(*p, want) || (!p->scratch && grow_scratch(*p, kLeastScratch)));
     (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!ok) (void)hipGetLastError();
+    if (!ok || p->scratch_bytes < want) p->pause = kReservePause;
+    return p->scratch_bytes;
 }
 
 void free_workspaces()

@@ -1637,6 +1637,9 @@ la_status launch_wide_batch(BatchParams& bp, unsigned grid, hipStream_t stream)
 }  // namespace
 
 static_assert(sizeof(BatchParams) <= 4000, "the batch travels as a kernel argument");
+static_assert(Cfg<128, 4, 2, 64, 4>::PART_WG_BYTES <= kStagedPartialBytes && Cfg<128, 2, 4, 64, 4>::PART_WG_BYTES <= kStagedPartialBytes &&
+                  Cfg<64, 2, 2, 64, 4>::PART_WG_BYTES <= kStagedPartialBytes && 8 * kTicketStride * sizeof(unsigned) <= kStagedTicketBytes,
+              "what a workgroup of a batched launch and its tickets take");
 
 la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page_size, int n_pages, int W, int N,
                                       int G, int heads, int kv_heads, int head_dim, hipStream_t stream)
@@ -1673,7 +1676,18 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         int chunks[kMaxBatch];
         for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
         const int tiles = (T * group + 31) / 32;
-        const LaunchPlan plan = plan_launch(chunks, n, tiles, kv_heads, head_dim, ov.batch_rows);
+        LaunchPlan plan = plan_launch(chunks, n, tiles, kv_heads, head_dim, ov.batch_rows);
+        // Whether a batch is cut, and by which kernel, depends on all its lengths: one reserves for another that
+        // may follow, so that the latter can be captured after the former has run.  Where the partial results
+        // of the pipelined kernel have no room (nothing reserved ahead of a capture, or no memory left) the staged one,
+        // whose take half as much, does the work.
+        const size_t scratch = reserve_workspace(pipelined_applies(tiles, head_dim) ? kMaxWideCutWorkgroups * (size_t)WideCfg::PART_WG_BYTES : 0, stream);
+        if (plan.rows == kPipelinedRows && !ov.batch_rows) {
+            size_t ranges = 0;  // of cut steps
+            for (int i = 0; i < n; ++i) ranges += plan.cuts[i] > 1 ? plan.cuts[i] : 0;
+            if (ranges * (size_t)kv_heads * ((tiles + 7) / 8) * WideCfg::PART_WG_BYTES > scratch)
+                plan = plan_launch(chunks, n, tiles, kv_heads, head_dim, 0, false);
+        }
         const bool wide = plan.rows == kPipelinedRows;
         const int RT = plan.rows / 32, KS = wide ? 1 : plan.rows == 128 || head_dim != 128 ? 2 : 4;
         const int n_row_blocks = (tiles + RT - 1) / RT;
@@ -1703,18 +1717,16 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
             }
         }
         for (int i = n; i <= kMaxBatch; ++i) bp.slots.slot0[i] = slot;
-        // (whether a batch is cut depends on all its lengths: one that is not reserves for one that is, so
-        // that the latter can be captured after the former has run)
-        reserve_workspace(stream);
         if (partial_bytes) {
-            unsigned* tickets = (unsigned*)zeroed_workspace(ticket_count * sizeof(unsigned), stream);
+            unsigned* tickets = wide ? nullptr : (unsigned*)zeroed_workspace(ticket_count * sizeof(unsigned), stream);
+            if (!tickets && !wide) return last_failure();
             unsigned char* partials = (unsigned char*)scratch_workspace(partial_bytes, stream);
-            if (!tickets || !partials) return last_failure();
+            if (!partials) return last_failure();
             for (int i = 0; i < n; ++i) {
                 if (bp.seq[i].XS <= 1) continue;
                 bp.seq[i].tickets = tickets;
                 bp.seq[i].partials = partials;
-                tickets += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
+                if (!wide) tickets += (size_t)kv_heads * n_row_blocks * RT * KS * kTicketStride;
                 partials += (size_t)bp.seq[i].total_wg * pl[plan.place[i]].partial_bytes_per_wg;
             }
         }

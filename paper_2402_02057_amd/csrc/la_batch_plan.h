@@ -230,6 +230,7 @@ inline BatchPlan plan_batch(const int* chunks, int n, int tiles, int kv_heads, i
 // on any XCD.
 constexpr int kMaxWideCutWorkgroups = 448;
 constexpr int kPipelinedRows = 256;
+inline bool pipelined_applies(int tiles, int head_dim) { return head_dim == 128 && tiles >= 4; }  // (fewer tiles fit one staged workgroup)
 
 struct LaunchPlan {
     int rows;                // rows of a workgroup: 64 or 128 (staged kernel), or kPipelinedRows
@@ -364,13 +365,13 @@ inline bool search_wide(const int* chunks, int n, const WideForm& f, long long l
 
 }  // namespace batch_plan
 
-// As plan_batch; rows: kPipelinedRows to force that form, too.
-inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows = 0)
+// As plan_batch; rows: kPipelinedRows to force that form, too; pipelined: false to leave that form out.
+inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows = 0, bool pipelined = true)
 {
     using namespace batch_plan;
     LaunchPlan p;
     long long end = -1;
-    const bool can = head_dim == 128 && tiles >= 4;   // (fewer tiles fit one staged workgroup)
+    const bool can = pipelined && pipelined_applies(tiles, head_dim);
     if (rows != kPipelinedRows || !can) {
         const BatchPlan b = plan_batch(chunks, n, tiles, kv_heads, head_dim, rows == kPipelinedRows ? 0 : rows);
         p.rows = b.rows128 ? 128 : 64;

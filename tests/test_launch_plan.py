@@ -30,7 +30,7 @@ extern "C" double plan_us(const int* chunks, int n, int tiles, int kv_heads)
 }
 extern "C" int launch(const int* chunks, int n, int tiles, int kv_heads, int head_dim, int rows, int* cuts, int* place)
 {
-    const la::LaunchPlan p = la::plan_launch(chunks, n, tiles, kv_heads, head_dim, rows);
+    const la::LaunchPlan p = la::plan_launch(chunks, n, tiles, kv_heads, head_dim, rows < 0 ? 0 : rows, rows >= 0);
     for (int i = 0; i < n; ++i) { cuts[i] = p.cuts[i]; place[i] = p.place[i]; }
     return p.rows;
 }
@@ -68,7 +68,7 @@ def chunks_of(prefixes, T):
 
 def test_every_plan_can_be_launched(lib):
     """Each step once, no range empty, and partial results of a pipelined launch within what the library
-    reserves (la_api.hip: 64 MB; eight waves of 16 KB and 512 bytes each)."""
+    reserves for one (58 MB; eight waves of 16 KB and 512 bytes each)."""
     rng = random.Random(1)
     taken = 0
     for _ in range(3000):
@@ -85,7 +85,7 @@ def test_every_plan_can_be_launched(lib):
         assert head_dim == 128 and tiles >= 4 and rows in (0, 256)
         taken += rows == 0
         workgroups = sum(kv_heads * -(-tiles // 8) * x for x in cuts if x > 1)
-        assert workgroups * 8 * (16384 + 512) <= 64 << 20
+        assert workgroups * 8 * (16384 + 512) <= 58 << 20
     assert taken > 100
 
 
@@ -95,10 +95,22 @@ def test_every_plan_can_be_launched(lib):
     ([1024] * 8, 121, 32, 32, 128, [1] * 8),                                   # four tiles: nothing to share a chunk with
     ([256] * 4, 121, 32, 8, 64, [1] * 4),
     ([616, 300, 88], 361, 32, 8, 128, [2, 2, 1]),                              # the times too close to call
-], ids=["ragged", "serving", "7b", "small", "wide-windows"])
+    ([512] * 6, 41, 32, 8, 64, [1] * 6),                                       # test_gpu_graph.py: an uncut batch, and
+    ([512] * 4, 41, 32, 8, 64, [2] * 4),                                       # a smaller one that is cut
+    ([8000, 8000], 121, 32, 8, 256, [8, 8]),                                   # test_gpu_workspace.py
+], ids=["ragged", "serving", "7b", "small", "wide-windows", "six", "four", "two"])
 def test_kernel_and_cuts(lib, prefixes, T, heads, kv_heads, form, cuts):
     got = ask(lib.launch, chunks_of(prefixes, T), -(-T * (heads // kv_heads) // 32), kv_heads)
     assert got[:2] == (form, cuts)
+
+
+def test_without_the_pipelined_kernel_a_launch_is_the_staged_one(lib):
+    """Where its partial results have no room (test_gpu_workspace.py)."""
+    for chunks, tiles, kv_heads in drawn(300, seed=13):
+        assert ask(lib.launch, chunks, tiles, kv_heads, rows=-1) == ask(lib.batch, chunks, tiles, kv_heads)
+    two = chunks_of([8000, 8000], 121)
+    assert ask(lib.batch, two, 16, 8)[:2] == (64, [2, 2]) == ask(lib.batch, two, 16, 8, rows=64)[:2]
+    assert 16 * 16 * 8 * (16384 + 512) > 32 << 20
 
 
 def drawn(count, seed):
