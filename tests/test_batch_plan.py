@@ -167,7 +167,7 @@ def test_longest_ranges_start_first(lib):
 
 
 def test_workspace_of_a_launch_is_bounded(lib):
-    """What the library reserves (la_api.hip: 32 MB of partial results, 512 KB of tickets) holds any batch."""
+    """What the library reserves (la_api.hip: 32 MB of partial results, 512 KB of tickets) holds any batch of the staged kernel."""
     for b in batches(2000, seed=6):
         for rows in (0, 64, 128):
             form, cuts, _ = b.plan(lib, rows)

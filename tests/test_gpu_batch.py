@@ -53,7 +53,7 @@ def run_batch(prefixes, W, N, G, H, KV, d, seed, check_oracle):
     ([0, 64, 1, 65, 700], 4, 3, 2, 4, 2, 64),                    # empty and tiny prefixes, head_dim 64
     ([100 * i + 7 for i in range(11)], 7, 5, 7, 8, 2, 128),      # more than one launch (eight at a time)
     ([5000, 13], 10, 5, 10, 16, 16, 128),
-    ([16000, 16000, 9000], 30, 5, 30, 32, 8, 128),               # the 128-row plan for all
+    ([16000, 16000, 9000], 30, 5, 30, 32, 8, 128),               # long and wide
 ])
 def test_batch_matches_the_oracle_and_the_single_calls(prefixes, W, N, G, H, KV, d):
     print("case", dict(prefixes=list(prefixes), W=W, N=N, G=G, H=H, KV=KV, d=d), flush=True)
@@ -87,6 +87,13 @@ def test_ragged_sweep_every_sequence_against_the_oracle(W):
     run_batch(prefixes, W, 5, W, 32, 8, 128, seed=40 + W, check_oracle=set(range(len(prefixes))))
 
 
+@pytest.mark.parametrize("W", [5, 15])
+def test_ragged_sweep_on_the_staged_kernel(override, W):
+    """128-row workgroups, cut and not, which the pipelined kernel leaves to other batches."""
+    override("batch_plan", "4")
+    run_batch(list(wl.ragged_prefix_lengths()), W, 5, W, 32, 8, 128, seed=60 + W, check_oracle={0, 7})
+
+
 def test_batch_recompute_path(override):
     override("force_recompute", "1")
     run_batch([2492, 13246, 1253], 5, 5, 5, 32, 8, 128, seed=1, check_oracle={2})
@@ -110,15 +117,19 @@ def test_both_batch_decompositions(override, plan):
     run_batch([500, 2000], 4, 5, 4, 32, 8, 128, seed=4, check_oracle={0})
 
 
-@pytest.mark.parametrize("prefixes,page_size,W,N,G,H,KV,d", [
-    ([1024] * 8, 64, 15, 5, 15, 32, 32, 128),
-    ([2492, 13246, 1253, 7849], 256, 5, 5, 5, 32, 8, 128),
-    ([0, 64, 1, 65, 700], 64, 4, 3, 2, 4, 2, 64),
-    ([900, 10], 128, 10, 5, 10, 16, 16, 128),
+@pytest.mark.parametrize("prefixes,page_size,W,N,G,H,KV,d,plan", [
+    ([1024] * 8, 64, 15, 5, 15, 32, 32, 128, None),
+    ([2492, 13246, 1253, 7849], 256, 5, 5, 5, 32, 8, 128, None),   # pipelined, all cut
+    ([2492, 13246, 1253, 7849], 256, 5, 5, 5, 32, 8, 128, "4"),    # 128 rows, cut into eight, five and two ranges and not at all
+    ([2492, 13246, 1253, 7849], 256, 5, 5, 5, 32, 8, 128, "2"),    # 64 rows, two of four cut
+    ([0, 64, 1, 65, 700], 64, 4, 3, 2, 4, 2, 64, None),
+    ([900, 10], 128, 10, 5, 10, 16, 16, 128, None),
 ])
-def test_paged_batch(prefixes, page_size, W, N, G, H, KV, d):
+def test_paged_batch(override, prefixes, page_size, W, N, G, H, KV, d, plan):
     """All sequences in one pool of pages, each with its own block table: per sequence the oracle's
     step over the packed cache its table stands for, and the bits of the packed batch."""
+    if plan:
+        override("batch_plan", plan)
     print("case", dict(prefixes=prefixes, page=page_size, W=W, N=N, G=G, H=H, KV=KV, d=d), flush=True)
     rng = np.random.default_rng(sum(prefixes) + page_size)
     T = 1 + (W + G) * (N - 1)

@@ -104,6 +104,15 @@ def test_kernel_and_cuts(lib, prefixes, T, heads, kv_heads, form, cuts):
     assert got[:2] == (form, cuts)
 
 
+@pytest.mark.parametrize("prefixes, heads, kv_heads, rows, cuts", [
+    ([300, 200], 8, 2, 64, [1, 1]), ([4000, 300], 32, 8, 64, [4, 1]), ([300, 200], 4, 1, 128, [1, 1]),
+    ([4000, 300], 32, 8, 128, [9, 1]), ([300, 200], 4, 1, 256, [1, 1]), ([4000, 300], 4, 1, 256, [10, 1]),
+])
+def test_cuts_of_a_forced_form(lib, prefixes, heads, kv_heads, rows, cuts):
+    """What test_gpu_row_isolation.py goes by: 81 rows."""
+    assert ask(lib.launch, chunks_of(prefixes, 81), -(-81 * (heads // kv_heads) // 32), kv_heads, rows=rows)[:2] == (rows, cuts)
+
+
 def test_without_the_pipelined_kernel_a_launch_is_the_staged_one(lib):
     """Where its partial results have no room (test_gpu_workspace.py)."""
     for chunks, tiles, kv_heads in drawn(300, seed=13):
