@@ -178,7 +178,7 @@ def run_ragged(args):
         abytes = sum(algorithmic_bytes(s) for s in shapes)
         aflops = sum(algorithmic_flops(s) for s in shapes)
         traffic, source = profile_traffic("ragged") if W == 15 else (None, None)
-        roof, t_roof = roofline_object(abytes, aflops, launch_us, peaks, "step_attention_batch_kernel", traffic, source)
+        roof, t_roof = roofline_object(abytes, aflops, launch_us, peaks, "wide_attention_batch_kernel + wide_combine_kernel", traffic, source)
         sweep.append({"W": W, "rows": s0.T, "one_launch_us": launch_us, "eight_calls_us": calls_us,
                       "algorithmic_bytes": abytes, "algorithmic_flops": aflops, "bound": roof["bound"],
                       "roofline_us": t_roof * 1e6, "frac": roof["frac"], "frac_of_achievable": roof["frac_of_achievable"],
