@@ -1661,7 +1661,11 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         }
     for (int first = 0; first < n_seqs; first += kMaxBatch) {
         const int n = n_seqs - first < kMaxBatch ? n_seqs - first : kMaxBatch;
-        if (n == 1) {  // nothing to share a launch with: the one-step path and its own decomposition
+        // Nothing to share a launch with: the one-step path and its own decomposition, at every length.  (The pipelined
+        // kernel beside it, us: 64/8 heads, 57 rows 14.2 and 27.2 on 2048 keys, 31.2 and 33.7 on 8192, 53.0 and 47.8 on
+        // 16384; 32/8 heads, 121 rows 14.0 and 27.3, 33.5 and 34.8, 54.4 and 49.0.  One-step calls do not reserve
+        // its partial results.)
+        if (n == 1) {
             const BatchSeq& d = seqs[order[first]];
             const la_status st = launch_step_attention(d.q, d.k_cache, d.v_cache, d.P, d.P > 0 ? d.block_table : nullptr,
                                                        page_size, n_pages, nullptr, 0, d.step_k, d.step_v, d.P, W, N, G,

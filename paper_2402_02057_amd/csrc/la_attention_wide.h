@@ -23,6 +23,8 @@
 // Measured (us a launch in a graph, staged and here): 8 x 1024 keys, 64/8 heads, 121 rows 61 and 50; 8 x 3072 keys
 // 139 and 108 (1.81 us a chunk of 256 rows, 2.3 staged); 8 x 1024 keys, 128/32 heads, 61 rows 63 and 47; 8
 // prefixes of 1253 to 14559 keys, 32/8 heads, 121 rows 158 and 134; 16 of 466 to 1021 keys, 81 rows 44 and 38.
+// The ragged eight on pages of 64 keys take 147 where packed ones take 133, on pages of 256 140; a table in the order
+// of the pool takes as long as a shuffled one, so it is not the scattered reads.
 // Relative error against 64 bits, staged and here: 2.66e-3 and 2.33e-3 for the ragged eight, 2.71e-3 and 2.31e-3 for the sixteen.
 // What bounds it now is power: with random operands 32x32x16 products alone run at 2.0 GHz, with a
 // block's softmax and operand reads beside them at 1.8 (3160 cycles a chunk, 2100 of them products).

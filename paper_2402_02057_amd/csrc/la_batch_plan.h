@@ -1,7 +1,9 @@
 // How a batched attention launch is cut: host code without HIP, so that it can be built and tested on its own.
 //
-// A workgroup has a compute unit to itself and owns (KV head, block of 64 or 128 query rows, one of
-// `cuts` ranges of a step's 64-key chunks).  The steps of a launch share the height of the row block.
+// A workgroup has a compute unit to itself and owns (KV head, block of query rows - 64 or 128 in the staged
+// kernel, up to 256 in the pipelined one - and one of `cuts` ranges of a step's 64-key chunks).  The steps of
+// a launch share the kernel and the height of the row block.  plan_batch plans the staged kernel, plan_launch
+// (which the launcher calls) chooses between that and the pipelined one.
 #pragma once
 
 namespace la {
