@@ -391,9 +391,11 @@ inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads,
     }
     // Times of the pipelined form, us: a chunk 1.81 with eight tiles (8 prefixes of 1024 and 3072 keys, 64/8 heads, 121
     // rows: 50.2 and 108.0 a launch) and 0.4 of that however few, start and end 7 and 0.65 a tile.  Taken
-    // where the launch then ends 7 % sooner: of 90 drawn batches measured in every form it is taken for 24, at
-    // 0.62 to 0.97 of the staged forms' time (0.80 in the geometric mean); where the times say 0.93 to 1.0 it measures
-    // 0.81 to 1.17.
+    // where the launch then ends 7 % sooner: of 240 drawn batches (2 to 16 steps of 1 to 8000 keys, 25 to 361 rows)
+    // measured in every form it is taken for 61, at 0.56 to 1.03 of the staged form's time, 0.81 in the geometric
+    // mean; two are slower, by 2 and 3 % (of 70 others one, by 5 %: five steps of 30 to 341 keys, 201 rows, 32/8
+    // heads).  At 14 % none would be, for an eighth of the gain; where the times say 0.93 to 1.0 it measures 0.78
+    // to 1.05, where they say 1.0 to 1.1 0.86 to 1.16.
     const int blocks = (tiles + 7) / 8, per_block = (tiles + blocks - 1) / blocks;
     const WideForm f = {kv_heads * blocks, 72 + 109 * per_block / 8, 700 + 65 * per_block};
     LaunchPlan q;
