@@ -23,8 +23,7 @@
 // Measured (us a launch in a graph, staged and here): 8 x 1024 keys, 64/8 heads, 121 rows 61 and 50; 8 x 3072 keys
 // 139 and 108 (1.81 us a chunk of 256 rows, 2.3 staged); 8 x 1024 keys, 128/32 heads, 61 rows 63 and 47; 8
 // prefixes of 1253 to 14559 keys, 32/8 heads, 121 rows 158 and 134; 16 of 466 to 1021 keys, 81 rows 44 and 38.
-// The ragged eight on pages of 64 keys take 147 where packed ones take 133, on pages of 256 140; a table in the order
-// of the pool takes as long as a shuffled one, so it is not the scattered reads.
+// Pages cost nothing here: the ragged eight take 132 to 135 packed, on pages of 64 or 256 keys, shuffled or in order.
 // Relative error against 64 bits, staged and here: 2.66e-3 and 2.33e-3 for the ragged eight, 2.71e-3 and 2.31e-3 for the sixteen.
 // What bounds it now is power: with random operands 32x32x16 products alone run at 2.0 GHz, with a
 // block's softmax and operand reads beside them at 1.8 (3160 cycles a chunk, 2100 of them products).
@@ -128,16 +127,23 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
     const unsigned char* iss_v;
     int iss_c;                    // next chunk to request
     unsigned iss_stage;
-    // paged cache: lane i holds the table entry of page pg_base + i
+    // Paged cache: lane i holds the table entry of page pg_base + i.  Entries are loaded 64 at a time, with
+    // their wait in the same statement: the compiler's own wait stood in front of every use, once a page, and a wait
+    // for a vector load is one for all chunks in flight (the ragged eight, pages of 64 keys 149 -> 134 us a layer, of 256 141 -> 135).
     int pg_base = 0, pg_ents = 0, iss_page = 0, iss_page_left = 0;
+    const int page_last = PAGED ? p.n_pages - 1 : 0;
+    const size_t page_bytes = PAGED ? (size_t)p.page_bytes : 0;
     auto load_entries = [&](int first) {
         pg_base = first;
-        pg_ents = p.block_table[min(first + lane, p.table_last)];
+        asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)"
+                     : "=&v"(pg_ents)
+                     : "v"((unsigned)min(first + lane, p.table_last) * 4u), "s"(p.block_table)
+                     : "memory");
     };
     auto page_base = [&]() {
         if (iss_page - pg_base >= 64) load_entries(iss_page);
         const int raw = __builtin_amdgcn_readlane(pg_ents, iss_page - pg_base);
-        return (size_t)min(max(raw, 0), p.n_pages - 1) * (size_t)p.page_bytes;
+        return (size_t)min(max(raw, 0), page_last) * page_bytes;
     };
     auto seek = [&](int c) {
         iss_c = c;
