@@ -47,18 +47,34 @@ class NgramPool:
     """n-grams collected from the Jacobi trajectory, by first token; most recent last."""
 
     def __init__(self):
-        self._tails = {}
+        self._tails = {}    # first token -> its tails as the keys of a dict, which keeps their order
 
     def add(self, gram):
-        bucket = self._tails.setdefault(gram[0], [])
-        tail = tuple(gram[1:])
-        if tail in bucket:
-            bucket.remove(tail)
-        bucket.append(tail)
+        bucket, tail = self._tails.setdefault(gram[0], {}), tuple(gram[1:])
+        bucket.pop(tail, None)
+        bucket[tail] = None
 
     def lookup(self, first_token, limit):
         """At most `limit` tails of n-grams starting with first_token, the most recent ones."""
-        return self._tails.get(first_token, [])[-limit:] if limit > 0 else []
+        return list(self._tails.get(first_token, ()))[-limit:] if limit > 0 else []
+
+
+class _StepTokens(list):
+    """A step's tokens for a model's forward pass (a list of them per sequence side by side), with the same tokens
+    on the GPU: `on_gpu`, int32 [T] or [sequences, T]."""
+
+    def __init__(self, tokens, on_gpu):
+        super().__init__(tokens)
+        self.on_gpu = on_gpu
+
+
+def _on_gpu(tokens):
+    """Tokens, or a list of them per sequence, as an int32 tensor of the current GPU."""
+    if isinstance(tokens, _StepTokens):
+        return tokens.on_gpu
+    if tokens and not isinstance(tokens[0], int):
+        return binding._native.upload([list(t) for t in tokens], False).view(len(tokens), -1)
+    return binding._native.upload([list(tokens)], False)
 
 
 class _Sequence:
@@ -70,7 +86,7 @@ class _Sequence:
             raise ValueError("need N >= 2, W >= 0, G >= 0 and a non-empty prompt")
         self.W, self.N, self.G, self.seed, self.random_token = W, N, G, seed, random_token
         n1 = N - 1
-        self.window = [[random_token(seed, l - n1, j) for j in range(W)] for l in range(n1)]
+        self.window = [self._random_level(l - n1) for l in range(n1)]
         self.pool = NgramPool()
         if prompt_as_reference:     # the prompt's own n-grams as first candidates (ablation study, Sec. 5.4)
             for i in range(len(prompt) - N + 1):
@@ -78,6 +94,11 @@ class _Sequence:
         self.current = int(prompt[-1])
         self.index = 0          # Algorithm 2's loop index: tokens decided so far
         self.steps = 0
+
+    def _random_level(self, index):
+        if self.random_token is wl.window_random_token and type(self.seed) is int:
+            return binding._native.window_random_tokens(self.seed, index, wl.TOY_VOCAB, self.W)   # (a level in one call)
+        return [self.random_token(self.seed, index, j) for j in range(self.W)]
 
     def candidates(self):
         return self.pool.lookup(self.current, self.G)
@@ -87,13 +108,12 @@ class _Sequence:
 
     def absorb(self, accepted, new):
         """The step's outcome: the window's columns become n-grams of the pool, the window moves on."""
-        W, n1, n = self.W, self.N - 1, len(accepted)
-        for j in range(W):
-            self.pool.add(tuple(self.window[l][j] for l in range(n1)) + (new[j],))
-        self.window = self.window[1:] + [new]
-        for extra in range(1, n):   # skipped loop indices: a "random" level each (Algorithm 2)
-            self.window = self.window[1:] + [[self.random_token(self.seed, self.index + extra, j)
-                                              for j in range(W)]]
+        n = len(accepted)
+        for gram in zip(*self.window, new):
+            self.pool.add(gram)
+        # skipped loop indices: a "random" level each (Algorithm 2)
+        levels = self.window + [new] + [self._random_level(self.index + extra) for extra in range(1, n)]
+        self.window = levels[n:]
         self.index += n
         self.current = accepted[-1]
         self.steps += 1
@@ -128,11 +148,12 @@ class LookaheadDecoder:
         tails = self._seq.candidates()
         g = len(tails)
         tokens = self._seq.step_tokens(tails)
-        logits = self.model.forward_step(tokens, W, N, g)
+        on_gpu = binding._native.upload([tokens], False)      # one upload for the model and the verification
+        logits = self.model.forward_step(_StepTokens(tokens, on_gpu), W, N, g)
         V = self.model.vocab
         look = logits[1 + (n1 - 1) * W:1 + n1 * W] if W else None        # newest level of the window
         cand_logits = logits[1 + W * n1:].view(g, n1, V) if g else None
-        cand = torch.tensor(tails, dtype=torch.int32, device=logits.device).view(g, n1) if g else None
+        cand = on_gpu[1 + W * n1:].view(g, n1) if g else None
         if self.temperature is None:
             binding.la_verify_step(logits[0], look, cand_logits, cand, W, N, g, V, self._out, self._n_out,
                                    self._best, self._new if W else None, None)
@@ -145,9 +166,12 @@ class LookaheadDecoder:
             binding.la_verify_step(logits[0], look, None, None, W, N, 0, V, self._out, self._n_out, self._best,
                                    self._new if W else None, None)
             step = self.steps + 1
-            u_test = torch.tensor([float(self.uniform(self.seed, step, i * g + j)) for i in range(n1) for j in range(g)],
-                                  dtype=torch.float32).view(n1, g).to(logits.device) if g else None
-            u_final = torch.tensor([float(self.uniform(self.seed, step, 1 << 20))], dtype=torch.float32).to(logits.device)
+            if self.uniform is wl.uniform_draw and type(self.seed) is int:
+                u = binding._native.uniform_draws(self.seed, step, 0, n1 * g)
+            else:
+                u = [float(self.uniform(self.seed, step, i)) for i in range(n1 * g)]
+            u = binding._native.upload([u, [float(self.uniform(self.seed, step, 1 << 20))]], True)
+            u_test, u_final = u[:n1 * g].view(n1, g) if g else None, u[n1 * g:]
             binding.la_verify_sample(logits[0], cand_logits, cand, u_test, u_final, self.temperature, N, g, V,
                                      self._out, self._n_out)
             result = self._result.tolist()
@@ -203,8 +227,9 @@ class BatchedLookaheadDecoder:
         placeholder = (0,) * n1
         padded = [t + [t[0] if t else placeholder] * (g_step - len(t)) for t in tails]
         tokens = [s.step_tokens(p) for s, p in zip(self.seqs, padded)]
-        logits = self.model.forward_step(tokens, W, N, g_step)
-        cand = torch.tensor(padded, dtype=torch.int32, device=logits[0].device).view(-1, g_step, n1) if g_step else None
+        on_gpu = binding._native.upload(tokens, False).view(len(tokens), -1)   # one upload for the model and the verification
+        logits = self.model.forward_step(_StepTokens(tokens, on_gpu), W, N, g_step)
+        cand = on_gpu[:, 1 + W * n1:].contiguous().view(-1, g_step, n1) if g_step else None
         descs = []
         for i, lg in enumerate(logits):
             descs.append(dict(
@@ -286,19 +311,19 @@ class ToyAttentionLM:
         self.length += n
 
     def forward_step(self, tokens, W, N, G):
-        idx = torch.tensor(tokens, dtype=torch.long, device=self.device)
+        idx = _on_gpu(tokens)
         T, P, d = len(tokens), self.length, wl.TOY_HEAD_DIM
         assert T == 1 + (W + G) * (N - 1)
         if P + N > self.capacity:
             raise ValueError("KV cache full")
         out = torch.empty((T, 1, d), dtype=torch.bfloat16, device=self.device)
-        q, k, v = self._qkv[:, idx]
+        q, k, v = self._qkv.index_select(1, idx)
         self._step = (k, v, W, N, G)
         if self.page_size:
             binding.la_step_attention_paged(q, self._k_cache, self._v_cache, self.block_table, k, v, P, W, N, G, 1, 1, d, out)
         else:
             binding.la_step_attention_cap(q, self._k_cache, self._v_cache, k, v, P, W, N, G, 1, 1, d, out)
-        return self._logits[torch.add(out[:, 0, 0] > 0.5, idx, alpha=2)]
+        return self._logits.index_select(0, torch.add(out[:, 0, 0] > 0.5, idx, alpha=2))
 
     def commit(self, best, n_out):
         step_k, step_v, W, N, G = self._step
@@ -358,14 +383,15 @@ class ToyBatchLM:
             assert len(toks) == T
             if self.lengths[i] + N > self.capacity:
                 raise ValueError("KV cache full")
-        idx = torch.tensor(tokens, dtype=torch.long, device=self.device)
-        q, k, v = self._qkv[:, idx]
+        idx = _on_gpu(tokens)
+        q, k, v = self._qkv.index_select(1, idx.view(-1)).view(3, len(tokens), T, 1, d)
         out = torch.empty((len(tokens), T, 1, d), dtype=torch.bfloat16, device=self.device)
         seqs = [dict(q=q[i], block_table=self.block_tables[i], step_k=k[i], step_v=v[i], out=out[i], P=self.lengths[i])
                 for i in range(len(tokens))]
         binding.la_step_attention_batch_paged(seqs, self._k_pages, self._v_pages, W, N, G, 1, 1, d)
         self._step = (seqs, W, N, G)
-        return list(self._logits[torch.add(out[:, :, 0, 0] > 0.5, idx, alpha=2)])
+        rows = torch.add(out[:, :, 0, 0] > 0.5, idx, alpha=2)
+        return list(self._logits.index_select(0, rows.view(-1)).view(len(tokens), T, self.vocab))
 
     def commit(self, bests, n_outs):
         seqs, W, N, G = self._step

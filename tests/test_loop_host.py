@@ -1,0 +1,47 @@
+"""The decoding loop's host work in the extension module against its definitions in Python: the random
+window levels, the draws of sampling, the pool's order, uploads."""
+import random
+
+import pytest
+import torch
+
+from paper_2402_02057_amd import binding, lookahead, workloads as wl
+
+
+@pytest.mark.parametrize("seed", [0, 3, -7, 2**40 + 1, 2**70])
+@pytest.mark.parametrize("count", [0, 1, 15, 61])
+def test_generators_equal_their_definitions(seed, count):
+    for step in (-4, -1, 0, 1, 1000):
+        assert binding._native.window_random_tokens(seed, step, wl.TOY_VOCAB, count) == \
+            [wl.window_random_token(seed, step, j) for j in range(count)]
+        assert binding._native.uniform_draws(seed, step, 5, count) == \
+            [float(wl.uniform_draw(seed, step, 5 + j)) for j in range(count)]
+
+
+def test_pool_keeps_the_most_recent_last():
+    rng, pool, want = random.Random(1), lookahead.NgramPool(), {}
+    for _ in range(2000):
+        gram = tuple(rng.randrange(4) for _ in range(4))
+        pool.add(gram)
+        bucket = want.setdefault(gram[0], [])
+        if gram[1:] in bucket:
+            bucket.remove(gram[1:])
+        bucket.append(gram[1:])
+    for first in range(5):
+        for limit in (0, 1, 7, 1000):
+            assert pool.lookup(first, limit) == (want.get(first, [])[-limit:] if limit else [])
+
+
+@pytest.mark.gpu
+def test_uploads():
+    sent = []
+    for i in range(200):                       # none is waited for: each keeps its numbers until it has run
+        lists = [[i * 1000 + j for j in range(i % 7)], [], [-1, 2**31 - 1, -2**31]]
+        sent.append((sum(lists, []), binding._native.upload(lists, False)))
+    for want, got in sent:
+        assert got.dtype == torch.int32 and got.is_cuda and got.tolist() == want
+    assert binding._native.upload([[0.5, 1], [2.0**-24]], True).tolist() == [0.5, 1.0, 2.0**-24]
+    assert binding._native.upload([], False).numel() == 0
+    for bad, error in ((((1,),), TypeError), ([(1,)], TypeError), ([["a"]], TypeError), ([[2**31]], ValueError)):
+        with pytest.raises(error):
+            binding._native.upload(bad, False)
