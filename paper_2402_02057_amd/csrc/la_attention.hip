@@ -165,7 +165,8 @@ __device__ __forceinline__ void row_place(int t, int W, int N, float inv_W, floa
 }
 
 // KVB: bytes per key / value element (2: bf16; 1: 8-bit float, quantised cache).  Q rows are bf16 always.
-template <int D, int RT, int KS, int KC, int NSTAGE, int KVB = 2>
+// PB: bytes per element of a range's partial result (2: bf16, 4: fp32).
+template <int D, int RT, int KS, int KC, int NSTAGE, int KVB = 2, int PB = 2>
 struct Cfg {
     static constexpr int HEAD_DIM = D;
     static constexpr int NW = RT * KS;
@@ -217,9 +218,9 @@ struct Cfg {
     static constexpr bool MERGE_EARLY = KS > 1 && MERGE_BYTES + 16 <= FREE_STAGES * STAGE_BYTES;
     static_assert(!(D == 128 && RT == 2 && KS == 4 && NSTAGE == 4 && KVB == 2) || MERGE_EARLY,
                   "the plan of the benchmark shapes merges without a barrier after the loop");
-    // a split's partial in global memory, per wave: its SPW slices as bf16 in fragment order
-    // ([8 values][lane], 16 bytes per lane and access) followed by (m, l) of its rows per lane in fp32
-    static constexpr int PART_ACC_BYTES = SPW * 16 * 64 * 2;
+    // a split's partial in global memory, per wave: its SPW slices in fragment order (PB bytes a value, 16 bytes
+    // per lane and access) followed by (m, l) of its rows per lane in fp32
+    static constexpr int PART_ACC_BYTES = SPW * 16 * 64 * PB;
     static constexpr int PART_WAVE_BYTES = PART_ACC_BYTES + 64 * 8;
     static constexpr int PART_WG_BYTES = NW * PART_WAVE_BYTES;
     static constexpr int Q_BYTES = ROWS * QRBYTES;        // the workgroup's query rows
@@ -346,12 +347,17 @@ __device__ __forceinline__ void merge_key_splits(unsigned char* area, int rt, in
 // lookahead parallelism, Sec. 3.4); row ids come from p.row_ids and the mask is evaluated pair by pair.
 // The body is shared by the one-step kernel and the batched one: `xcd` is the XCD this workgroup
 // runs on (its id modulo 8) and `slot` its index among the step's workgroups on that XCD.
-template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false>
+// PB: see Cfg.
+template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false, int PB = 2>
 __device__ __forceinline__ void step_attention_body(const AttnParams& p, const int xcd, const int slot)
 {
-    using C = Cfg<D, RT, KS, KC, NSTAGE, KVB>;
+    using C = Cfg<D, RT, KS, KC, NSTAGE, KVB, PB>;
     static_assert(KVB == 2 || (KVB == 1 && !PAGED && !ROWSET), "the quantised cache is packed and takes whole steps");
     static_assert(!ROPE || (!PAGED && !ROWSET && KVB == 2), "the rotating variant takes packed bf16 caches and whole steps");
+    static_assert(PB == 2 || PB == 4, "partial results in bf16 or fp32");
+    typedef std::conditional_t<PB == 4, float, __bf16> PartElement;
+    typedef std::conditional_t<PB == 4, f32x4, bf16x8> Part;   // a lane's 16 bytes of a partial result
+    constexpr int PE = 16 / PB;                                // values in them
     extern __shared__ __attribute__((aligned(1024))) unsigned char lds[];
 
     // Consecutive workgroup ids go round-robin over the 8 XCDs (each with its own L2); put
@@ -973,16 +979,16 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                                               (size_t)unit * p.XS * C::PART_WG_BYTES + (size_t)wave * C::PART_WAVE_BYTES;
             {
                 unsigned char* dst = group_base + (size_t)xs * C::PART_WG_BYTES;
+                // (streaming stores: the partials are read once, by one other wave, and measured
+                // faster this way than with the default cache policy)
 #pragma unroll
                 for (int u = 0; u < C::SPW; ++u)
 #pragma unroll
-                    for (int i8 = 0; i8 < 2; ++i8) {
-                        bf16x8 v;
+                    for (int i = 0; i < PB; ++i) {
+                        Part v;
 #pragma unroll
-                        for (int e = 0; e < 8; ++e) v[e] = (__bf16)o[u][i8 * 8 + e];
-                        // (streaming stores: the partials are read once, by one other wave, and measured
-                        // faster this way than with the default cache policy)
-                        __builtin_nontemporal_store(v, reinterpret_cast<bf16x8*>(dst + ((u * 2 + i8) * 64 + lane) * 16));
+                        for (int e = 0; e < PE; ++e) v[e] = (PartElement)o[u][i * PE + e];
+                        __builtin_nontemporal_store(v, reinterpret_cast<Part*>(dst + ((u * PB + i) * 64 + lane) * 16));
                     }
                 *reinterpret_cast<f32x2*>(dst + C::PART_ACC_BYTES + lane * 8) = f32x2{m_run, l_run};
             }
@@ -1005,8 +1011,8 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
             role = __builtin_amdgcn_readfirstlane(role);
             LA_STAMP(6);
             if (role == 1) {
-                // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2
-                constexpr int MB = 4;
+                // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2 (fp32: two)
+                constexpr int MB = 8 / PB;
                 float m_acc = kNegInf, l_acc = 0.0f;
                 float acc[C::SPW][16];
 #pragma unroll
@@ -1015,7 +1021,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                     for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
                 for (int s0 = 0; s0 < p.XS; s0 += MB) {
                     f32x2 ml[MB];
-                    bf16x8 v[MB][C::SPW][2];
+                    Part v[MB][C::SPW][PB];
 #pragma unroll
                     for (int w = 0; w < MB; ++w) {
                         const int s2 = min(s0 + w, p.XS - 1);
@@ -1024,8 +1030,8 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 #pragma unroll
                         for (int u = 0; u < C::SPW; ++u)
 #pragma unroll
-                            for (int i8 = 0; i8 < 2; ++i8)
-                                v[w][u][i8] = *reinterpret_cast<const bf16x8*>(src + ((u * 2 + i8) * 64 + lane) * 16);
+                            for (int i = 0; i < PB; ++i)
+                                v[w][u][i] = *reinterpret_cast<const Part*>(src + ((u * PB + i) * 64 + lane) * 16);
                     }
                     LA_STAMP(18);
                     // batch maximum, then one weight per split: acc = acc * a0 + sum_w v_w * a_w
@@ -1050,10 +1056,10 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 #pragma unroll
                         for (int u = 0; u < C::SPW; ++u)
 #pragma unroll
-                            for (int i8 = 0; i8 < 2; ++i8)
+                            for (int i = 0; i < PB; ++i)
 #pragma unroll
-                                for (int e = 0; e < 8; ++e)
-                                    acc[u][i8 * 8 + e] = __builtin_fmaf((float)v[w][u][i8][e], aw, acc[u][i8 * 8 + e]);
+                                for (int e = 0; e < PE; ++e)
+                                    acc[u][i * PE + e] = __builtin_fmaf((float)v[w][u][i][e], aw, acc[u][i * PE + e]);
                     }
                 }
                 const float inv = out_scale / l_acc;
@@ -1089,11 +1095,11 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     }
 }
 
-template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false>
+template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false, int PB = 2>
 __global__ __launch_bounds__(RT* KS * 64) void step_attention_kernel(const AttnParams)
 {
     const AttnParams& p = warmed_arguments<AttnParams>();
-    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE>(p, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3));
+    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE, PB>(p, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3));
 }
 
 #include "la_attention_wide.h"
@@ -1159,7 +1165,7 @@ __global__ __launch_bounds__(256) void wide_combine_kernel(const BatchParams)
 // handle: its device address is looked up once per device (fixed_workspace) and only that
 // pointer is handed to kernels.
 constexpr size_t kFixedTicketBytes = (size_t)128 << 10;          // 128 split groups x 8 waves, 128 bytes apart
-constexpr size_t kFixedPartialBytes = (size_t)12 << 20;         // 12 MiB of partials
+constexpr size_t kFixedPartialBytes = (size_t)17 << 20;         // 256 workgroups of 128 rows with fp32 partials
 static __device__ __align__(256) unsigned char scratch[kFixedTicketBytes + kFixedPartialBytes];
 
 __global__ void clear_words_kernel(unsigned* words, int n)
@@ -1236,14 +1242,15 @@ struct Plan {
     int KC;                   // keys per chunk
     int n_row_blocks;
     int n_prefix_chunks, n_chunks;
+    bool fp32_partials;       // of the ranges (else bf16)
     size_t partial_bytes_per_wg;
 };
 
 // Bytes of one workgroup's partial (Cfg::PART_WG_BYTES): per wave its slices as bf16 and (m, l).
-size_t partial_wg_bytes(int D, int RT, int KS)
+size_t partial_wg_bytes(int D, int RT, int KS, int bytes = 2)
 {
     const int DB = D / 32, SPW = KS > 1 ? DB / KS : DB;
-    return (size_t)RT * KS * ((size_t)SPW * 16 * 64 * 2 + 64 * 8);
+    return (size_t)RT * KS * ((size_t)SPW * 16 * 64 * bytes + 64 * 8);
 }
 
 // Most LDS stages that fit beside the workgroup's Q rows.
@@ -1280,8 +1287,17 @@ bool rowset_plan_supported(int D, int RT, int KS, int NS, int KC)
     return paged_plan_supported(D, RT, KS, NS, KC) && RT != 4;
 }
 
-Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D, bool paged = false, bool rowset = false,
-               bool rope = false)
+// Whether a step takes 128-row workgroups (the kernels for a row subset and for the rotary embedding have none: no LDS
+// is left for ids or tables).
+bool always_rows128(int P, int T, int group) { return T * group > 15 * 32 && (P + T) / 64 >= 64; }
+bool picks_rows128(int P, int T, int group, int kv_heads, int D, bool codes)
+{
+    const int tiles = (T * group + 31) / 32;
+    return D == 128 && tiles > 1 && step_rows128((P + 63) / 64 + (T + 63) / 64, tiles, kv_heads, always_rows128(P, T, group), codes);
+}
+
+Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D, bool rows128, bool paged = false,
+               bool rowset = false)
 {
     Plan pl;
     const int R = T * group;
@@ -1290,11 +1306,10 @@ Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D
     // Workgroups of eight waves, two per SIMD, so that one wave's MFMAs overlap the other's
     // softmax arithmetic: 64 rows whose four waves per tile split the keys (measured best from the
     // 7B shape up to grouped-query shapes with a few hundred rows per KV head), or 128 rows with two
-    // key-split waves per tile when there are many rows and a long prefix (more reuse of each
-    // chunk in LDS).  Head dimension 64 and single-tile problems keep four-wave workgroups.
+    // key-split waves per tile.  Head dimension 64 and single-tile problems keep four-wave workgroups.
     if (tiles <= 1) { pl.RT = 1; pl.KS = 2; }
     else if (D != 128) { pl.RT = 2; pl.KS = 2; }
-    else if (tiles >= 16 && (P + T) / pl.KC >= 64 && !rowset && !rope) { pl.RT = 4; pl.KS = 2; }  // (no LDS left for tables)
+    else if (rows128) { pl.RT = 4; pl.KS = 2; }
     else { pl.RT = 2; pl.KS = 4; }
     pl.XS = 0;
     pl.NS = 0;
@@ -1316,28 +1331,30 @@ Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D
     if (pl.XS <= 0) {
         // One workgroup per compute unit and never more than 256 in all: a workgroup owns most
         // of a compute unit's LDS, so a second round would only start when the first has ended.
-        const int units = kv_heads * pl.n_row_blocks;
-        int xs = 256 / units;
-        if (xs > pl.n_chunks / 2) xs = pl.n_chunks / 2;
-        pl.XS = xs < 1 ? 1 : xs;
+        pl.XS = step_cuts(kv_heads * pl.n_row_blocks, pl.n_chunks);
     }
     if (pl.XS > pl.n_chunks) pl.XS = pl.n_chunks;
     if (pl.XS > 64) pl.XS = 64;
-    pl.partial_bytes_per_wg = partial_wg_bytes(D, pl.RT, pl.KS);
+    // A step that is cut only because its row blocks became larger was not rounded to bf16 on the way before, and is
+    // not now (40/40 heads, 241 rows on 804 keys, relative error against 64 bits: 2.73e-3 with 64 rows and one range,
+    // 3.10e-3 with 128, three ranges and bf16, 2.61e-3 with fp32; which costs 1 to 4 us: 24 -> 27 of 34 with 64 rows).
+    pl.fp32_partials = !ov.has_plan && pl.RT == 4 && pl.XS > 1 && step_cuts(kv_heads * ((tiles + 1) / 2), pl.n_chunks) == 1 &&
+                       !always_rows128(P, T, group);
+    pl.partial_bytes_per_wg = partial_wg_bytes(D, pl.RT, pl.KS, pl.fp32_partials ? 4 : 2);
     return pl;
 }
 
-template <int D, int RT, int KS, int NSTAGE, int KC = 64, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false>
+template <int D, int RT, int KS, int NSTAGE, int KC = 64, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false, int PB = 2>
 la_status launch_cfg(const AttnParams& prm, hipStream_t stream)
 {
-    using C = Cfg<D, RT, KS, KC, NSTAGE, KVB>;
+    using C = Cfg<D, RT, KS, KC, NSTAGE, KVB, PB>;
     constexpr int kLds = C::LDS_BYTES + (ROWSET ? C::ROWSET_BYTES : 0) + (ROPE ? C::ROPE_MAX_BYTES : 0);
     static_assert(kLds <= 160 * 1024, "LDS of a compute unit");
     if (ROPE && 2 * prm.rope_block > C::ROPE_MAX_BYTES)
         return fail(LA_EUNSUPPORTED, "la_step_attention_rope: %d positions of cosines and sines do not fit beside this "
                                      "decomposition (%d bytes of LDS left): rotate q with la_step_rope instead",
                     prm.rope_rows, C::ROPE_MAX_BYTES);
-    auto kern = step_attention_kernel<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE>;
+    auto kern = step_attention_kernel<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE, PB>;
     static bool attr_set[16] = {false};
     const la_status st = set_lds_attribute_once(reinterpret_cast<const void*>(kern), kLds, attr_set);
     if (st != LA_OK) return st;
@@ -1353,7 +1370,9 @@ la_status launch_cfg(const AttnParams& prm, hipStream_t stream)
 size_t step_attention_workspace_bytes(int P, int W, int N, int G, int heads, int kv_heads, int head_dim)
 {
     const int T = 1 + (W + G) * (N - 1);
-    const Plan pl = make_plan(current_overrides(), P, T, heads / kv_heads, kv_heads, head_dim);
+    const int group = heads / kv_heads;
+    const Plan pl = make_plan(current_overrides(), P, T, group, kv_heads, head_dim,
+                              picks_rows128(P, T, group, kv_heads, head_dim, false));
     if (pl.XS <= 1) return 0;
     return (size_t)kv_heads * pl.n_row_blocks * pl.XS * pl.partial_bytes_per_wg;
 }
@@ -1470,8 +1489,13 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
             return launch_step_attention_rowtile(q, k_cache, v_cache, capacity, step_k, step_v, P, W, N, G, heads,
                                                  kv_heads, out, stream, rope);
     }
-    const Plan pl = make_plan(ov, P, T, group, kv_heads, head_dim, block_table != nullptr, row_ids != nullptr,
-                              rope != nullptr);
+    const bool rows128 = !row_ids && !rope && picks_rows128(P, T, group, kv_heads, head_dim, k_scale != nullptr);
+    Plan pl = make_plan(ov, P, T, group, kv_heads, head_dim, rows128, block_table != nullptr, row_ids != nullptr);
+    if (rows128 && pl.XS > 1 && !fixed && !always_rows128(P, T, group)) {
+        // 64 rows need no workspace where all keys are one range: they do it where none is to be had (a capture)
+        const Plan whole = make_plan(ov, P, T, group, kv_heads, head_dim, false, block_table != nullptr, false);
+        if (whole.XS == 1 && (size_t)kv_heads * pl.n_row_blocks * pl.XS * pl.partial_bytes_per_wg > reserve_workspace(0, stream)) pl = whole;
+    }
     AttnParams prm;
     const la_status st = build_params(prm, ov, pl, q, k_cache, v_cache, capacity, block_table, page_size, n_pages, row_ids,
                                       T, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out);
@@ -1535,7 +1559,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
                         head_dim, pl.RT, pl.KS, pl.NS);
         if (head_dim == 128) {
             if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, true>(prm, stream);
-            if (pl.RT == 4) return launch_cfg<128, 4, 2, 4, 64, true>(prm, stream);
+            if (pl.RT == 4) return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, true, false, 2, false, 4>(prm, stream)
+                                                    : launch_cfg<128, 4, 2, 4, 64, true>(prm, stream);
             if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, true>(prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, true>(prm, stream);
         }
@@ -1568,7 +1593,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
     if (quantised) {
         if (head_dim == 128) {
             if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, false, false, 1>(prm, stream);
-            if (pl.RT == 4) return launch_cfg<128, 4, 2, 4, 64, false, false, 1>(prm, stream);
+            if (pl.RT == 4) return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, false, false, 1, false, 4>(prm, stream)
+                                                    : launch_cfg<128, 4, 2, 4, 64, false, false, 1>(prm, stream);
             if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, false, false, 1>(prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, false, false, 1>(prm, stream);
         }
@@ -1577,7 +1603,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
     }
     if (pl.KC == 32) return launch_cfg<128, 2, 2, 9, 32>(prm, stream);
     if (pl.KS == 4) return launch_cfg<128, 2, 4, 4>(prm, stream);
-    if (pl.RT == 4 && pl.KS == 2) return launch_cfg<128, 4, 2, 4>(prm, stream);
+    if (pl.RT == 4 && pl.KS == 2)
+        return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, false, false, 2, false, 4>(prm, stream) : launch_cfg<128, 4, 2, 4>(prm, stream);
 #define LA_DISPATCH(D_, RT_, KS_, NSMAX_)                                        \
     if (head_dim == D_ && pl.RT == RT_ && pl.KS == KS_) {                       \
         if (pl.NS == 2) return launch_cfg<D_, RT_, KS_, 2>(prm, stream);        \
@@ -1676,7 +1703,7 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
         // One kernel and decomposition (row tiles, key-split waves) for the whole launch; those, how often each
         // step's keys are cut, and the order of the steps come from plan_launch.
         Plan pl[kMaxBatch];
-        for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim);
+        for (int i = 0; i < n; ++i) pl[i] = make_plan(Overrides(), seqs[order[first + i]].P, T, group, kv_heads, head_dim, false);
         int chunks[kMaxBatch];
         for (int i = 0; i < n; ++i) chunks[i] = pl[i].n_chunks;
         const int tiles = (T * group + 31) / 32;

@@ -402,4 +402,46 @@ inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads,
     return search_wide(chunks, n, f, end < 0 ? 1ll << 60 : (end * 93 + 99) / 100, q) ? q : p;
 }
 
+// ---- one step alone
+
+// Ranges of its keys: one round of workgroups, two chunks each at least.
+inline int step_cuts(int units, int chunks)
+{
+    int x = 256 / units;
+    if (x > chunks / 2) x = chunks / 2;
+    if (x > 64) x = 64;
+    return x < 1 ? 1 : x;
+}
+
+namespace batch_plan {
+
+// When the staged kernel ends a step, in 10 ns, from 150 drawn steps of 400 to 16384 keys, 9 to 361 rows, 32/32, 40/40,
+// 64/8 and 32/8 heads: a round of workgroups takes 4.4 us and 0.70 a chunk with 64 rows, 5.3 and 1.15 with 128 (8-bit
+// cache: 0.62 and 1.18), a range to exchange 0.7, and 1.1 where few KV heads make the stream from HBM short.
+inline long long staged_step_end(bool rows128, int chunks, int tiles, int kv_heads, bool codes)
+{
+    const int units = kv_heads * (rows128 ? (tiles + 3) / 4 : (tiles + 1) / 2), x = step_cuts(units, chunks);
+    const long long rounds = ((long long)units * x + 255) / 256, range = (chunks + x - 1) / x;
+    return 150 + rounds * (rows128 ? 530 + (codes ? 118 : 115) * range : 440 + (codes ? 62 : 70) * range) + (kv_heads < 32 ? 110 : 70) * x;
+}
+
+}  // namespace batch_plan
+
+// Whether a step alone takes 128-row workgroups of the staged kernel (head_dim 128) instead of 64-row ones: where its times
+// end it half a microsecond sooner.  80 drawn steps (bf16 packed and paged, 8-bit) on that side of the line take 0.63 to
+// 1.02 of the time they take with 64 rows, 0.86 in the geometric mean: 32/32 heads, 161 rows on 6117 keys 47.9 -> 40.2 us,
+// 40/40, 241 rows on 13347 keys 163 -> 103, 64/8, 133 rows on 3449 keys 43.3 -> 31.9.  Errors against 64 bits are 3 to 10 %
+// smaller.
+// A step with one range has no partial results: 128 rows then have to be 2 us ahead, which is what
+// the noalloc entry point takes to clear its tickets.  many_rows: a step that has always had 128 rows, which round fewer
+// sums between key-split waves, never goes back to 64.  codes: the 8-bit cache.
+inline bool step_rows128(int chunks, int tiles, int kv_heads, bool many_rows, bool codes)
+{
+    using namespace batch_plan;
+    if (many_rows) return true;
+    const bool cut64 = step_cuts(kv_heads * ((tiles + 1) / 2), chunks) > 1, cut128 = step_cuts(kv_heads * ((tiles + 3) / 4), chunks) > 1;
+    return staged_step_end(true, chunks, tiles, kv_heads, codes) + (cut128 && !cut64 ? 250 : 50) <
+           staged_step_end(false, chunks, tiles, kv_heads, codes);
+}
+
 }  // namespace la
