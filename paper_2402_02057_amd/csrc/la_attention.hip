@@ -119,7 +119,7 @@ struct AttnParams {
     int n_row_blocks;
     int XS;
     int total_wg;         // kv_heads * n_row_blocks * XS
-    int wg_per_xcd;       // ceil(total_wg / 8)
+    int wg_per_xcd;       // ceil(total_wg / 8), or more where that keeps the ranges of a row block on one XCD
     float scale_log2;     // log2(e) / sqrt(head_dim)
     // Integer division costs dozens of instructions, and a wave issues about one instruction
     // every four cycles: quotients by these small divisors are taken with a float reciprocal
@@ -1335,11 +1335,13 @@ Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D
     }
     if (pl.XS > pl.n_chunks) pl.XS = pl.n_chunks;
     if (pl.XS > 64) pl.XS = 64;
-    // A step that is cut only because its row blocks became larger was not rounded to bf16 on the way before, and is
-    // not now (40/40 heads, 241 rows on 804 keys, relative error against 64 bits: 2.73e-3 with 64 rows and one range,
-    // 3.10e-3 with 128, three ranges and bf16, 2.61e-3 with fp32; which costs 1 to 4 us: 24 -> 27 of 34 with 64 rows).
-    pl.fp32_partials = !ov.has_plan && pl.RT == 4 && pl.XS > 1 && step_cuts(kv_heads * ((tiles + 1) / 2), pl.n_chunks) == 1 &&
-                       !always_rows128(P, T, group);
+    // Results of ranges are exchanged in bf16 where row blocks of 64 rows (128: `always_rows128`) and an even deal always
+    // did so, and in fp32 where those computed a row in one go: in one range (40/40 heads, 241 rows on 804 keys, relative
+    // error against 64 bits: 2.73e-3 with 64 rows and one range, 3.10e-3 with 128, three ranges and bf16, 2.61e-3 with
+    // fp32; which costs 1 to 4 us: 24 -> 27 of 34 with 64 rows), or again over all keys, the ranges being on two XCDs
+    // (20/20 heads, 57 rows on 4096 keys: 2.73e-3 that way, 3.11e-3 with bf16, 2.65e-3 with fp32).
+    const int even_blocks = pl.RT == 4 && !always_rows128(P, T, group) ? (tiles + 1) / 2 : pl.n_row_blocks;
+    pl.fp32_partials = !ov.has_plan && pl.XS > 1 && !step_cuts_even(kv_heads * even_blocks, pl.n_chunks);
     pl.partial_bytes_per_wg = partial_wg_bytes(D, pl.RT, pl.KS, pl.fp32_partials ? 4 : 2);
     return pl;
 }
@@ -1363,6 +1365,14 @@ la_status launch_cfg(const AttnParams& prm, hipStream_t stream)
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(LA_EHIP, "la_step_attention launch: %s", hipGetErrorString(e));
     return LA_OK;
+}
+
+// The same with partial results in bf16 or in fp32.
+template <int D, int RT, int KS, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false>
+la_status launch_plan_cfg(const Plan& pl, const AttnParams& prm, hipStream_t stream)
+{
+    return pl.fp32_partials ? launch_cfg<D, RT, KS, 4, 64, PAGED, ROWSET, KVB, ROPE, 4>(prm, stream)
+                            : launch_cfg<D, RT, KS, 4, 64, PAGED, ROWSET, KVB, ROPE, 2>(prm, stream);
 }
 
 }  // namespace
@@ -1501,6 +1511,7 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
                                       T, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out);
     if (st != LA_OK) return st;
     const long long total = prm.total_wg;
+    if (pl.XS > 1) prm.wg_per_xcd = step_units_per_xcd(kv_heads * pl.n_row_blocks) * pl.XS;
     const bool quantised = k_scale != nullptr;
     if (quantised) {
         // 8-bit keys and values: rows of head_dim bytes (cache_rows counts rows, so it stands)
@@ -1546,26 +1557,25 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
             return fail(LA_EUNSUPPORTED, "la_step_attention_rows: no kernel for head_dim=%d plan (%d,%d,%d), %d rows",
                         head_dim, pl.RT, pl.KS, pl.NS, n_rows);
         if (head_dim == 128) {
-            if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, false, true>(prm, stream);
-            if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, false, true>(prm, stream);
+            if (pl.KS == 4) return launch_plan_cfg<128, 2, 4, false, true>(pl, prm, stream);
+            if (pl.RT == 1) return launch_plan_cfg<128, 1, 2, false, true>(pl, prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, false, true>(prm, stream);
         }
-        if (pl.RT == 1) return launch_cfg<64, 1, 2, 4, 64, false, true>(prm, stream);
-        return launch_cfg<64, 2, 2, 4, 64, false, true>(prm, stream);
+        if (pl.RT == 1) return launch_plan_cfg<64, 1, 2, false, true>(pl, prm, stream);
+        return launch_plan_cfg<64, 2, 2, false, true>(pl, prm, stream);
     }
     if (block_table) {
         if (!paged_plan_supported(head_dim, pl.RT, pl.KS, pl.NS, pl.KC))
             return fail(LA_EUNSUPPORTED, "la_step_attention_paged: no kernel for head_dim=%d plan (%d,%d,%d)",
                         head_dim, pl.RT, pl.KS, pl.NS);
         if (head_dim == 128) {
-            if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, true>(prm, stream);
-            if (pl.RT == 4) return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, true, false, 2, false, 4>(prm, stream)
-                                                    : launch_cfg<128, 4, 2, 4, 64, true>(prm, stream);
-            if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, true>(prm, stream);
+            if (pl.KS == 4) return launch_plan_cfg<128, 2, 4, true>(pl, prm, stream);
+            if (pl.RT == 4) return launch_plan_cfg<128, 4, 2, true>(pl, prm, stream);
+            if (pl.RT == 1) return launch_plan_cfg<128, 1, 2, true>(pl, prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, true>(prm, stream);
         }
-        if (pl.RT == 1) return launch_cfg<64, 1, 2, 4, 64, true>(prm, stream);
-        return launch_cfg<64, 2, 2, 4, 64, true>(prm, stream);
+        if (pl.RT == 1) return launch_plan_cfg<64, 1, 2, true>(pl, prm, stream);
+        return launch_plan_cfg<64, 2, 2, true>(pl, prm, stream);
     }
     if (rope) {
         // the furthest position of the step: the newest window level's last column, or a candidate's last token
@@ -1583,28 +1593,31 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
         prm.rope_cos = rope->cos + (size_t)P * (head_dim / 2);
         prm.rope_sin = rope->sin + (size_t)P * (head_dim / 2);
         if (head_dim == 128) {
-            if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, false, false, 2, true>(prm, stream);
-            if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, false, false, 2, true>(prm, stream);
+            if (pl.KS == 4) return launch_plan_cfg<128, 2, 4, false, false, 2, true>(pl, prm, stream);
+            if (pl.RT == 1) return launch_plan_cfg<128, 1, 2, false, false, 2, true>(pl, prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, false, false, 2, true>(prm, stream);
         }
-        if (pl.RT == 1) return launch_cfg<64, 1, 2, 4, 64, false, false, 2, true>(prm, stream);
-        return launch_cfg<64, 2, 2, 4, 64, false, false, 2, true>(prm, stream);
+        if (pl.RT == 1) return launch_plan_cfg<64, 1, 2, false, false, 2, true>(pl, prm, stream);
+        return launch_plan_cfg<64, 2, 2, false, false, 2, true>(pl, prm, stream);
     }
     if (quantised) {
         if (head_dim == 128) {
-            if (pl.KS == 4) return launch_cfg<128, 2, 4, 4, 64, false, false, 1>(prm, stream);
-            if (pl.RT == 4) return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, false, false, 1, false, 4>(prm, stream)
-                                                    : launch_cfg<128, 4, 2, 4, 64, false, false, 1>(prm, stream);
-            if (pl.RT == 1) return launch_cfg<128, 1, 2, 4, 64, false, false, 1>(prm, stream);
+            if (pl.KS == 4) return launch_plan_cfg<128, 2, 4, false, false, 1>(pl, prm, stream);
+            if (pl.RT == 4) return launch_plan_cfg<128, 4, 2, false, false, 1>(pl, prm, stream);
+            if (pl.RT == 1) return launch_plan_cfg<128, 1, 2, false, false, 1>(pl, prm, stream);
             return launch_cfg<128, 2, 2, 4, 64, false, false, 1>(prm, stream);
         }
-        if (pl.RT == 1) return launch_cfg<64, 1, 2, 4, 64, false, false, 1>(prm, stream);
-        return launch_cfg<64, 2, 2, 4, 64, false, false, 1>(prm, stream);
+        if (pl.RT == 1) return launch_plan_cfg<64, 1, 2, false, false, 1>(pl, prm, stream);
+        return launch_plan_cfg<64, 2, 2, false, false, 1>(pl, prm, stream);
     }
     if (pl.KC == 32) return launch_cfg<128, 2, 2, 9, 32>(prm, stream);
-    if (pl.KS == 4) return launch_cfg<128, 2, 4, 4>(prm, stream);
-    if (pl.RT == 4 && pl.KS == 2)
-        return pl.fp32_partials ? launch_cfg<128, 4, 2, 4, 64, false, false, 2, false, 4>(prm, stream) : launch_cfg<128, 4, 2, 4>(prm, stream);
+    if (pl.KS == 4) return launch_plan_cfg<128, 2, 4>(pl, prm, stream);
+    if (pl.RT == 4 && pl.KS == 2) return launch_plan_cfg<128, 4, 2>(pl, prm, stream);
+    if (pl.fp32_partials) {   // (the plans that are never forced)
+        if (head_dim == 128) return launch_plan_cfg<128, 1, 2>(pl, prm, stream);
+        if (pl.RT == 1) return launch_plan_cfg<64, 1, 2>(pl, prm, stream);
+        return launch_plan_cfg<64, 2, 2>(pl, prm, stream);
+    }
 #define LA_DISPATCH(D_, RT_, KS_, NSMAX_)                                        \
     if (head_dim == D_ && pl.RT == RT_ && pl.KS == KS_) {                       \
         if (pl.NS == 2) return launch_cfg<D_, RT_, KS_, 2>(prm, stream);        \
