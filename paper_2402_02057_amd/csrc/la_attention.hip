@@ -1296,8 +1296,9 @@ bool picks_rows128(int P, int T, int group, int kv_heads, int D, bool codes)
     return D == 128 && tiles > 1 && step_rows128((P + 63) / 64 + (T + 63) / 64, tiles, kv_heads, always_rows128(P, T, group), codes);
 }
 
+// back_from_128: 64 rows although such a step always had 128, see `step_rows128`.
 Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D, bool rows128, bool paged = false,
-               bool rowset = false)
+               bool rowset = false, bool back_from_128 = false)
 {
     Plan pl;
     const int R = T * group;
@@ -1328,20 +1329,24 @@ Plan make_plan(const Overrides& ov, int P, int T, int group, int kv_heads, int D
     pl.n_chunks = pl.n_prefix_chunks + (T + pl.KC - 1) / pl.KC;
     const int rows_wg = pl.RT * 32;
     pl.n_row_blocks = (R + rows_wg - 1) / rows_wg;
-    if (pl.XS <= 0) {
-        // One workgroup per compute unit and never more than 256 in all: a workgroup owns most
-        // of a compute unit's LDS, so a second round would only start when the first has ended.
-        pl.XS = step_cuts(kv_heads * pl.n_row_blocks, pl.n_chunks);
-    }
-    if (pl.XS > pl.n_chunks) pl.XS = pl.n_chunks;
-    if (pl.XS > 64) pl.XS = 64;
     // Results of ranges are exchanged in bf16 where row blocks of 64 rows (128: `always_rows128`) and an even deal always
     // did so, and in fp32 where those computed a row in one go: in one range (40/40 heads, 241 rows on 804 keys, relative
     // error against 64 bits: 2.73e-3 with 64 rows and one range, 3.10e-3 with 128, three ranges and bf16, 2.61e-3 with
     // fp32; which costs 1 to 4 us: 24 -> 27 of 34 with 64 rows), or again over all keys, the ranges being on two XCDs
     // (20/20 heads, 57 rows on 4096 keys: 2.73e-3 that way, 3.11e-3 with bf16, 2.65e-3 with fp32).
-    const int even_blocks = pl.RT == 4 && !always_rows128(P, T, group) ? (tiles + 1) / 2 : pl.n_row_blocks;
-    pl.fp32_partials = !ov.has_plan && pl.XS > 1 && !step_cuts_even(kv_heads * even_blocks, pl.n_chunks);
+    const bool always = always_rows128(P, T, group);
+    const int even_blocks = pl.RT == 4 && !always ? (tiles + 1) / 2 : pl.n_row_blocks;
+    const bool whole = !step_cuts_even(kv_heads * even_blocks, pl.n_chunks);
+    pl.fp32_partials = false;
+    if (ov.has_plan) {
+        if (pl.XS <= 0) pl.XS = step_cuts(kv_heads * pl.n_row_blocks, pl.n_chunks);
+    } else {
+        const StepRanges ranges = step_ranges(kv_heads * pl.n_row_blocks, pl.n_chunks, rows_wg, D, whole || back_from_128);
+        pl.XS = ranges.x;
+        pl.fp32_partials = ranges.fp32;
+    }
+    if (pl.XS > pl.n_chunks) pl.XS = pl.n_chunks;
+    if (pl.XS > 64) pl.XS = 64;
     pl.partial_bytes_per_wg = partial_wg_bytes(D, pl.RT, pl.KS, pl.fp32_partials ? 4 : 2);
     return pl;
 }
@@ -1381,8 +1386,9 @@ size_t step_attention_workspace_bytes(int P, int W, int N, int G, int heads, int
 {
     const int T = 1 + (W + G) * (N - 1);
     const int group = heads / kv_heads;
-    const Plan pl = make_plan(current_overrides(), P, T, group, kv_heads, head_dim,
-                              picks_rows128(P, T, group, kv_heads, head_dim, false));
+    const bool rows128 = picks_rows128(P, T, group, kv_heads, head_dim, false);
+    const Plan pl = make_plan(current_overrides(), P, T, group, kv_heads, head_dim, rows128, false, false,
+                              head_dim == 128 && !rows128 && always_rows128(P, T, group));
     if (pl.XS <= 1) return 0;
     return (size_t)kv_heads * pl.n_row_blocks * pl.XS * pl.partial_bytes_per_wg;
 }
@@ -1500,7 +1506,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
                                                  kv_heads, out, stream, rope);
     }
     const bool rows128 = !row_ids && !rope && picks_rows128(P, T, group, kv_heads, head_dim, k_scale != nullptr);
-    Plan pl = make_plan(ov, P, T, group, kv_heads, head_dim, rows128, block_table != nullptr, row_ids != nullptr);
+    Plan pl = make_plan(ov, P, T, group, kv_heads, head_dim, rows128, block_table != nullptr, row_ids != nullptr,
+                        !row_ids && !rope && head_dim == 128 && !rows128 && always_rows128(P, T, group));
     if (rows128 && pl.XS > 1 && !fixed && !always_rows128(P, T, group)) {
         // 64 rows need no workspace where all keys are one range: they do it where none is to be had (a capture)
         const Plan whole = make_plan(ov, P, T, group, kv_heads, head_dim, false, block_table != nullptr, false);

@@ -425,6 +425,33 @@ inline bool step_cuts_even(int units, int chunks)
     return x > 1 && (units * x + kXcds - 1) / kXcds % x == 0;
 }
 
+// In how many ranges, and whether they exchange fp32.  One workgroup per compute unit is not always best: the last one of a
+// group reads all its ranges' results, 0.16 to 0.20 us a range in bf16 and 0.18 to 0.31 in fp32, where a chunk of a range
+// takes 0.55 to 0.80 (64 rows of 128 dimensions in pairs of chunks, one tile, 64 dimensions; 13 to 361 rows on 1024 to
+// 16384 keys).  Fewer ranges in bf16 would be further from 64 bits (4/4 heads, 121 rows on 4096 keys: 2.98e-3 with 32 ranges,
+// 3.11e-3 with 12), in fp32 they are nearer (2.64e-3): so fewer are taken where the results are fp32 anyway or that is half a
+// microsecond ahead in fp32 too, which is from 45 to 80 chunks where 32 ranges fit.  4/4 heads 14.8 -> 13.6 us, 8/1, 57 rows
+// 15.3 -> 12.0, 32/8, 13 rows 15.1 -> 13.8, 4/4 with 64 dimensions 11.0 -> 10.1, 4/4, 31 rows (fp32 before) 16.7 -> 13.2.
+struct StepRanges {
+    int x;
+    bool fp32;
+};
+inline StepRanges step_ranges(int units, int chunks, int rows, int head_dim, bool fp32)
+{
+    const int most = step_cuts(units, chunks);
+    if (most == 1 || rows > 64) return StepRanges{most, fp32 && most > 1};
+    const bool pairs = head_dim == 128 && rows == 64;
+    const int chunk = head_dim == 64 ? 64 : pairs ? 55 : 80, r32 = head_dim == 64 ? 18 : 30, r16 = head_dim == 64 ? 16 : pairs ? 17 : 20;
+    auto walk = [&](int x) {
+        const int n = (chunks + x - 1) / x;
+        return (pairs ? (n + 1) / 2 * 2 : n) * chunk;
+    };
+    int best = 2;
+    for (int x = 3; x <= most; ++x)
+        if (walk(x) + x * r32 < walk(best) + best * r32) best = x;
+    return fp32 || walk(best) + best * r32 + 50 < walk(most) + most * r16 ? StepRanges{best, true} : StepRanges{most, false};
+}
+
 namespace batch_plan {
 
 // When the staged kernel ends a step, in 10 ns, from 150 drawn steps of 400 to 16384 keys, 9 to 361 rows, 32/32, 40/40,
@@ -446,11 +473,16 @@ inline long long staged_step_end(bool rows128, int chunks, int tiles, int kv_hea
 // smaller.
 // A step with one range has no partial results: 128 rows then have to be 2 us ahead, which is what
 // the noalloc entry point takes to clear its tickets.  many_rows: a step that has always had 128 rows, which round fewer
-// sums between key-split waves, never goes back to 64.  codes: the 8-bit cache.
+// sums between key-split waves, goes back to 64 only with fp32 results and where 128 rows would be cut 16 times or more, to 20
+// chunks at most (8/1 heads, 121 rows on 4096 keys 21.2 -> 13.2 us, on 32768 48.3 -> 40.4; 16/2 on 8192 28.0 -> 23.1, on 16384
+// 37.2 -> 33.9; 3.05e-3 -> 2.70e-3.  Beyond: 16/2 on 32768, 33 chunks: 55.2 -> 55.6; cut 8 times, 32/4: 19.8 -> 18.9, 50.9 -> 53.7).  codes: the 8-bit cache.
 inline bool step_rows128(int chunks, int tiles, int kv_heads, bool many_rows, bool codes)
 {
     using namespace batch_plan;
-    if (many_rows) return true;
+    if (many_rows) {
+        const int x = step_cuts(kv_heads * ((tiles + 3) / 4), chunks);
+        return x < 16 || chunks > 20 * x;
+    }
     const bool cut64 = step_cuts(kv_heads * ((tiles + 1) / 2), chunks) > 1, cut128 = step_cuts(kv_heads * ((tiles + 3) / 4), chunks) > 1;
     return staged_step_end(true, chunks, tiles, kv_heads, codes) + (cut128 && !cut64 ? 250 : 50) <
            staged_step_end(false, chunks, tiles, kv_heads, codes);

@@ -17,6 +17,12 @@ SHIM = """
 extern "C" int per_xcd(int units) { return la::step_units_per_xcd(units); }
 extern "C" int cuts(int units, int chunks) { return la::step_cuts(units, chunks); }
 extern "C" int even(int units, int chunks) { return la::step_cuts_even(units, chunks); }
+extern "C" int rows128(int chunks, int tiles, int kv_heads) { return la::step_rows128(chunks, tiles, kv_heads, true, false); }
+extern "C" int ranges(int units, int chunks, int rows, int head_dim, int fp32)
+{
+    const la::StepRanges r = la::step_ranges(units, chunks, rows, head_dim, fp32);
+    return r.fp32 ? -r.x : r.x;
+}
 """
 
 
@@ -31,6 +37,11 @@ def test_the_ranges_of_a_row_block_are_on_one_xcd(tmp_path):
             if lib.even(units, chunks):
                 assert x == 256 // units or x == chunks // 2 or x == 64      # as many ranges as fill the compute units
             assert 1 <= x <= max(1, chunks // 2) and x <= 64 and most * 8 >= units
+            for rows, d in ((32, 128), (64, 128), (128, 128), (32, 64), (64, 64)):
+                for fp32 in (0, 1):                     # fewer only in fp32, which stays so
+                    n = lib.ranges(units, chunks, rows, d, fp32)
+                    assert n == x if n > 0 else 2 <= -n <= x and (fp32 or -n < x)
+                    assert n < 0 or not fp32 or x == 1
             if x == 1:
                 continue
             assert most * x <= 32                       # one round: the compute units of an XCD
@@ -42,6 +53,9 @@ def test_the_ranges_of_a_row_block_are_on_one_xcd(tmp_path):
             assert sorted(sum(seen, [])) == list(range(units * x))
             for of_xcd in seen:
                 assert len(of_xcd) % x == 0 and all(l // x == of_xcd[i - i % x] // x for i, l in enumerate(of_xcd))
+    assert not lib.rows128(66, 31, 1) and not lib.rows128(258, 31, 2)       # few KV heads: 64 rows again
+    assert lib.rows128(66, 31, 4) and lib.rows128(514, 31, 2)              # cut 8 times; to 33 chunks
+    assert lib.ranges(8, 66, 64, 128, 0) == -11 and lib.ranges(8, 18, 64, 128, 0) == 9 and lib.ranges(8, 258, 64, 128, 0) == 32
 
 
 SHAPES = [(700, 5, 4, 5, 4, 4, 128),       # 4 row blocks of 32 rows, 5 ranges each
@@ -50,6 +64,11 @@ SHAPES = [(700, 5, 4, 5, 4, 4, 128),       # 4 row blocks of 32 rows, 5 ranges e
           (900, 5, 4, 5, 4, 4, 64),
           (2500, 20, 5, 20, 4, 4, 64),
           (300, 15, 5, 15, 50, 50, 128)]   # 100, 2
+FEWER = [(4096, 15, 5, 15, 4, 4, 128),     # 8 row blocks: 11 ranges in fp32, 32 in bf16 before
+         (3900, 3, 4, 1, 32, 8, 128),
+         (4096, 15, 5, 15, 4, 4, 64),
+         (4096, 15, 5, 15, 8, 1, 128),     # 16 of 64 rows, 8 of 128 before
+         (4096, 16, 5, 15, 16, 2, 128)]
 
 
 def new_like(q):
@@ -97,6 +116,21 @@ def test_every_entry_point_agrees_and_none_is_further_off(shape, override):
     # groups spread over XCDs are computed again, over all keys and without partial results: that is no nearer
     override("force_recompute", "1")
     assert err <= error(binding.la_step_attention(q, *cache, *args, new_like(q)), want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", FEWER, ids=lambda s: "P%d-W%d-%d/%d-d%d" % (s[0], s[1], s[4], s[5], s[6]))
+def test_fewer_ranges_are_no_further_off_than_all(shape, override):
+    print("case", shape, flush=True)
+    P, W, N, G, H, KV, d = shape
+    T, rng = 1 + (W + G) * (N - 1), np.random.default_rng(P)
+    x = [wl.f32_to_bf16_bits(rng.standard_normal(size=s, dtype=np.float32)) for s in ((T, H, d), (KV, P, d), (KV, P, d), (T, KV, d), (T, KV, d))]
+    dev = [binding.bf16_tensor(v) for v in x]
+    want = orc.step_attention(*x, P, W, N, G, H, KV, d)
+    out = binding.la_step_attention(*dev, P, W, N, G, H, KV, d, new_like(dev[0]))
+    assert torch.equal(out, binding.la_step_attention_noalloc(*dev, P, W, N, G, H, KV, d, new_like(dev[0])))
+    override("attn_plan", "4,2,0,4,64" if T * H // KV > 480 else "2,4,0,4,64" if d == 128 else "2,2,0,4,64")
+    assert error(out, want) <= error(binding.la_step_attention(*dev, P, W, N, G, H, KV, d, new_like(dev[0])), want)
 
 
 @pytest.mark.gpu
