@@ -47,7 +47,9 @@
  * be recorded into a HIP graph once the same call has run outside the capture:
  * that one sizes and clears the workspace, the kernels leave it cleared.  (A larger
  * shape will not always do: its workgroups may fill the device without exchanging
- * partials, and then it needs no workspace.  A batched attention call of two or
+ * partials, and then it needs no workspace.  A step that can be computed without any
+ * but is faster with it allocates it inside a capture too, and is computed
+ * without, in another order of rounding, where no memory is left.  A batched attention call of two or
  * more steps reserves what any attention call needs, and takes a kernel that
  * needs less where that much is neither there nor to be had.)  A workspace block that a
  * later, larger call replaces stays
@@ -444,7 +446,8 @@ la_status la_verify_sample_batch(const la_sample_desc* descs, int n_descs, int N
 /*
  * la_step_attention for callers that cannot allocate device memory: code under HIP graph
  * capture with no warm-up call, tight serving loops, harnesses that forbid hipMalloc.  Same
- * arguments, same kernels, same result as la_step_attention; the difference is where the
+ * arguments, same kernels, same result as la_step_attention (where that finds memory for its
+ * workspace); the difference is where the
  * scratch memory (tickets and split partials) comes from: a fixed block of 128 KiB + 17 MiB
  * inside the library's own image, present once on every device the library runs on until the
  * process ends.  The call never calls hipMalloc, hipFree or any allocating routine.

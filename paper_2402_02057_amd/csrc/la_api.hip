@@ -108,15 +108,24 @@ static bool grow_scratch(Pool& p, size_t want)
     p.scratch_bytes = want;
     return true;
 }
-// (cleared on this stream, ahead of the kernel that will use it)
-static bool grow_zeroed(Pool& p, size_t want, hipStream_t stream)
+// Cleared before the call returns, on a stream of its own: of a stream that is being captured it would be a node.
+static bool clear_now(void* block, size_t bytes)
+{
+    hipStream_t own;
+    if (hipStreamCreateWithFlags(&own, hipStreamNonBlocking) != hipSuccess) return false;
+    const bool ok = hipMemsetAsync(block, 0, bytes, own) == hipSuccess && hipStreamSynchronize(own) == hipSuccess;
+    (void)hipStreamDestroy(own);
+    return ok;
+}
+// (cleared on this stream, ahead of the kernel that will use it, or at once)
+static bool grow_zeroed(Pool& p, size_t want, hipStream_t stream, bool at_once = false)
 {
     void* fresh = nullptr;
     if (hipMalloc(&fresh, want) != hipSuccess) {
         (void)hipGetLastError();
         return false;
     }
-    if (hipMemsetAsync(fresh, 0, want, stream) != hipSuccess) {
+    if (at_once ? !clear_now(fresh, want) : hipMemsetAsync(fresh, 0, want, stream) != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(fresh);
         return false;
@@ -158,7 +167,7 @@ void* scratch_workspace(size_t bytes, hipStream_t stream)
     return p->scratch;
 }
 
-size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream)
+size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream, bool in_capture)
 {
     const size_t want = scratch_bytes < kLeastScratch ? kLeastScratch : scratch_bytes;
     std::lock_guard<std::mutex> lock(g_mutex);
@@ -169,10 +178,11 @@ size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream)
         --p->pause;
         return p->scratch_bytes;
     }
-    // (an allocation that can be done without must not disturb a capture that runs on another stream)
+    // (an allocation that can be done without must not disturb a capture, on another stream or with in_capture on this)
+    const bool captured = capturing(stream);
     hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (capturing(stream) || hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return p->scratch_bytes;
-    const bool ok = (p->zeroed || grow_zeroed(*p, kLeastZeroed, stream)) &&
+    if ((captured && !in_capture) || hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) return p->scratch_bytes;
+    const bool ok = (p->zeroed || grow_zeroed(*p, kLeastZeroed, stream, captured)) &&
                     (p->scratch_bytes >= want || grow_scratch(*p, want) || (!p->scratch && grow_scratch(*p, kLeastScratch)));
     (void)hipThreadExchangeStreamCaptureMode(&mode);
     if (!ok || p->scratch_bytes < want) p->pause = kReservePause;

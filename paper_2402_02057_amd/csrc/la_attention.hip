@@ -1509,9 +1509,10 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
     Plan pl = make_plan(ov, P, T, group, kv_heads, head_dim, rows128, block_table != nullptr, row_ids != nullptr,
                         !row_ids && !rope && head_dim == 128 && !rows128 && always_rows128(P, T, group));
     if (rows128 && pl.XS > 1 && !fixed && !always_rows128(P, T, group)) {
-        // 64 rows need no workspace where all keys are one range: they do it where none is to be had (a capture)
+        // 64 rows need no workspace where all keys are one range: such a step can be captured with nothing reserved, so
+        // it reserves inside the capture too and has the eager call's bits; they do it where no memory is left.
         const Plan whole = make_plan(ov, P, T, group, kv_heads, head_dim, false, block_table != nullptr, false);
-        if (whole.XS == 1 && (size_t)kv_heads * pl.n_row_blocks * pl.XS * pl.partial_bytes_per_wg > reserve_workspace(0, stream)) pl = whole;
+        if (whole.XS == 1 && (size_t)kv_heads * pl.n_row_blocks * pl.XS * pl.partial_bytes_per_wg > reserve_workspace(0, stream, true)) pl = whole;
     }
     AttnParams prm;
     const la_status st = build_params(prm, ov, pl, q, k_cache, v_cache, capacity, block_table, page_size, n_pages, row_ids,

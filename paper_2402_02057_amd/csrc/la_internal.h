@@ -22,9 +22,9 @@ la_status last_failure();
 void* zeroed_workspace(size_t bytes, hipStream_t stream);
 void* scratch_workspace(size_t bytes, hipStream_t stream);
 // Both blocks at their least size, and the scratch block at `scratch_bytes` if that is more, unless `stream` is
-// being captured; returns the size of the scratch block then.  A failure is no error (the call that needs more
-// than there is reports it, or does with less), and not tried again at once.
-size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream);
+// being captured (in_capture: then too); returns the size of the scratch block then.  A failure is no error (the call that
+// needs more than there is reports it, or does with less), and not tried again at once.
+size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream, bool in_capture = false);
 // What the staged attention kernels take of them at most: of partial results per workgroup, of tickets per group.
 constexpr size_t kStagedPartialBytes = size_t(36) << 10, kStagedTicketBytes = 8 * 128;
 void free_workspaces();

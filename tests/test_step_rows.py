@@ -128,21 +128,30 @@ def test_quantised_cache(lib, override):
 
 
 @pytest.mark.gpu
-def test_captured_with_nothing_reserved(override):
-    """64-row workgroups need no workspace for a step whose keys are one range: recorded as ever, with their bits."""
-    P, W, N, G, H, KV = SHAPES[0]
-    dev = {k: binding.bf16_tensor(v) for k, v in inputs(*SHAPES[0], seed=3).items()}
+@pytest.mark.parametrize("shape", SHAPES[:2], ids=lambda s: "P%d-W%d-%d/%d" % (s[0], s[1], s[4], s[5]))
+def test_captured_with_nothing_reserved(shape, override):
+    """64-row workgroups need no workspace for a step whose keys are one range, so it can be captured with nothing reserved;
+    a graph of it has the eager call's bits all the same."""
+    print("case", shape, flush=True)
+    P, W, N, G, H, KV = shape
+    dev = {k: binding.bf16_tensor(v) for k, v in inputs(*shape, seed=3).items()}
     out = torch.full(dev["q"].shape, float("nan"), dtype=torch.bfloat16, device="cuda")
 
-    def call():
-        binding.la_step_attention(dev["q"], dev["k_cache"], dev["v_cache"], dev["step_k"], dev["step_v"], P, W, N, G, H, KV, 128, out)
+    def call(entry=binding.la_step_attention):
+        entry(dev["q"], dev["k_cache"], dev["v_cache"], dev["step_k"], dev["step_v"], P, W, N, G, H, KV, 128, out)
+
+    def result(*entry):
+        out.fill_(float("nan"))
+        call(*entry)
+        torch.cuda.synchronize()
+        return out.clone()
     binding.la_select_workspace(11)
-    call()                                   # (kernels loaded ahead of the capture)
+    want = result()                          # (kernels loaded ahead of the capture)
+    assert torch.equal(want, result(binding.la_step_attention_noalloc))
     override("attn_plan", "2,4,0,4,64")
-    call()
-    torch.cuda.synchronize()
-    want = out.clone()
+    assert not torch.equal(want, result())
     override("attn_plan", None)
+    torch.cuda.synchronize()
     binding.la_shutdown()
     binding.la_select_workspace(12)
     try:
@@ -154,5 +163,6 @@ def test_captured_with_nothing_reserved(override):
             graph.replay()
             torch.cuda.synchronize()
             assert torch.equal(out, want)
+            assert torch.equal(result(), want)      # (the workspace reserved in the capture, used outside it)
     finally:
         binding.la_select_workspace(0)
