@@ -706,6 +706,30 @@ PyObject* upload(PyObject*, PyObject* const* args, Py_ssize_t n_args)
     }
 }
 
+// in_range(lists, limit): whether this is a list of lists of ints (no subclass of either) of 0 .. limit-1
+PyObject* in_range(PyObject*, PyObject* const* args, Py_ssize_t n_args)
+{
+    if (n_args != 2) {
+        PyErr_SetString(PyExc_TypeError, "two arguments are expected");
+        return nullptr;
+    }
+    const long long limit = PyLong_AsLongLong(args[1]);
+    if (limit == -1 && PyErr_Occurred()) return nullptr;
+    if (!PyList_CheckExact(args[0])) Py_RETURN_FALSE;
+    for (Py_ssize_t i = 0; i < PyList_GET_SIZE(args[0]); ++i) {       // (none of this runs code that could change a list)
+        PyObject* const l = PyList_GET_ITEM(args[0], i);
+        if (!PyList_CheckExact(l)) Py_RETURN_FALSE;
+        for (Py_ssize_t j = 0; j < PyList_GET_SIZE(l); ++j) {
+            PyObject* const item = PyList_GET_ITEM(l, j);
+            if (!PyLong_CheckExact(item)) Py_RETURN_FALSE;
+            int overflow = 0;
+            const long long v = PyLong_AsLongLongAndOverflow(item, &overflow);
+            if (overflow || v < 0 || v >= limit) Py_RETURN_FALSE;
+        }
+    }
+    Py_RETURN_TRUE;
+}
+
 // Three arguments taken modulo 2^64, as the generators below are defined, and a count.
 bool words(PyObject* const* args, Py_ssize_t n_args, Py_ssize_t want, uint64_t* w, Py_ssize_t* count)
 {
@@ -818,6 +842,7 @@ PyMethodDef methods[] = {
     LA_METHOD(verify_sample, 12),
     LA_METHOD(verify_sample_batch, 5),
     {"upload", (PyCFunction)(void (*)(void))upload, METH_FASTCALL, nullptr},
+    {"in_range", (PyCFunction)(void (*)(void))in_range, METH_FASTCALL, nullptr},
     {"window_random_tokens", (PyCFunction)(void (*)(void))window_random_tokens, METH_FASTCALL, nullptr},
     {"uniform_draws", (PyCFunction)(void (*)(void))uniform_draws, METH_FASTCALL, nullptr},
     {"set_error_class", set_error_class, METH_O, nullptr},

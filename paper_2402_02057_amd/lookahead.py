@@ -68,13 +68,15 @@ class _StepTokens(list):
         self.on_gpu = on_gpu
 
 
-def _on_gpu(tokens):
-    """Tokens, or a list of them per sequence, as an int32 tensor of the current GPU."""
+def _indices(tokens, lists, table):
+    """Tokens of a step, or a list of them per sequence, as indices beside `table`: in any form that torch.tensor
+    takes, but lists of numbers of the vocabulary, all in `lists`, are uploaded without a wait."""
     if isinstance(tokens, _StepTokens):
         return tokens.on_gpu
-    if tokens and not isinstance(tokens[0], int):
-        return binding._native.upload([list(t) for t in tokens], False).view(len(tokens), -1)
-    return binding._native.upload([list(tokens)], False)
+    if binding._native.in_range(lists, wl.TOY_VOCAB):
+        idx = binding._native.upload(lists, False)
+        return idx if idx.device == table.device else idx.to(table.device)
+    return torch.tensor(tokens, dtype=torch.long, device=table.device)
 
 
 class _Sequence:
@@ -311,7 +313,7 @@ class ToyAttentionLM:
         self.length += n
 
     def forward_step(self, tokens, W, N, G):
-        idx = _on_gpu(tokens)
+        idx = _indices(tokens, [tokens], self._qkv)
         T, P, d = len(tokens), self.length, wl.TOY_HEAD_DIM
         assert T == 1 + (W + G) * (N - 1)
         if P + N > self.capacity:
@@ -383,7 +385,7 @@ class ToyBatchLM:
             assert len(toks) == T
             if self.lengths[i] + N > self.capacity:
                 raise ValueError("KV cache full")
-        idx = _on_gpu(tokens)
+        idx = _indices(tokens, tokens, self._qkv).view(len(tokens), T)
         q, k, v = self._qkv.index_select(1, idx.view(-1)).view(3, len(tokens), T, 1, d)
         out = torch.empty((len(tokens), T, 1, d), dtype=torch.bfloat16, device=self.device)
         seqs = [dict(q=q[i], block_table=self.block_tables[i], step_k=k[i], step_v=v[i], out=out[i], P=self.lengths[i])

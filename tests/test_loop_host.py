@@ -32,6 +32,13 @@ def test_pool_keeps_the_most_recent_last():
             assert pool.lookup(first, limit) == (want.get(first, [])[-limit:] if limit else [])
 
 
+def test_in_range():
+    ok = binding._native.in_range
+    assert ok([[0, 5], [], [9]], 10) and ok([], 10)
+    for lists in ([[0, 10]], [[-1]], [[2**70]], [[True]], [[1.0]], [(1,)], ([1],), [1], None, [[1], None]):
+        assert not ok(lists, 10)
+
+
 @pytest.mark.gpu
 def test_uploads():
     sent = []
