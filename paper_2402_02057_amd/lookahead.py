@@ -59,24 +59,33 @@ class NgramPool:
         return list(self._tails.get(first_token, ()))[-limit:] if limit > 0 else []
 
 
-class _StepTokens(list):
-    """A step's tokens for a model's forward pass (a list of them per sequence side by side), with the same tokens
-    on the GPU: `on_gpu`, int32 [T] or [sequences, T]."""
-
-    def __init__(self, tokens, on_gpu):
-        super().__init__(tokens)
-        self.on_gpu = on_gpu
-
-
 def _indices(tokens, lists, table):
     """Tokens of a step, or a list of them per sequence, as indices beside `table`: in any form that torch.tensor
     takes, but lists of numbers of the vocabulary, all in `lists`, are uploaded without a wait."""
-    if isinstance(tokens, _StepTokens):
-        return tokens.on_gpu
     if binding._native.in_range(lists, wl.TOY_VOCAB):
         idx = binding._native.upload(lists, False)
         return idx if idx.device == table.device else idx.to(table.device)
     return torch.tensor(tokens, dtype=torch.long, device=table.device)
+
+
+def _upload_step(lists, vocab):
+    """A step's tokens on the GPU, for the model and the verification alike; None unless all are of the vocabulary."""
+    return binding._native.upload(lists, False) if binding._native.in_range(lists, vocab) else None
+
+
+def _forward(model, tokens, on_gpu, W, N, G):
+    """The model's output for a step.  The toy models' own forward pass takes the tokens that are on the GPU already;
+    any other (it may change them, or run on a stream of its own) gets its lists and nothing else."""
+    if on_gpu is not None and getattr(model.forward_step, "__func__", None) in _OWN_STEPS and on_gpu.device == model._qkv.device:
+        return model._forward(on_gpu, W, N, G)
+    return model.forward_step(tokens, W, N, G)
+
+
+def _candidates(on_gpu, first, tails, device):
+    """The candidates' tokens beside the logits: the step's from column `first` on, or their tails."""
+    if on_gpu is not None and on_gpu.device == device:
+        return on_gpu[..., first:].contiguous()
+    return torch.tensor(tails, dtype=torch.int32, device=device)
 
 
 class _Sequence:
@@ -150,12 +159,12 @@ class LookaheadDecoder:
         tails = self._seq.candidates()
         g = len(tails)
         tokens = self._seq.step_tokens(tails)
-        on_gpu = binding._native.upload([tokens], False)      # one upload for the model and the verification
-        logits = self.model.forward_step(_StepTokens(tokens, on_gpu), W, N, g)
         V = self.model.vocab
+        on_gpu = _upload_step([tokens], V)
+        logits = _forward(self.model, tokens, on_gpu, W, N, g)
         look = logits[1 + (n1 - 1) * W:1 + n1 * W] if W else None        # newest level of the window
         cand_logits = logits[1 + W * n1:].view(g, n1, V) if g else None
-        cand = on_gpu[1 + W * n1:].view(g, n1) if g else None
+        cand = _candidates(on_gpu, 1 + W * n1, tails, logits.device).view(g, n1) if g else None
         if self.temperature is None:
             binding.la_verify_step(logits[0], look, cand_logits, cand, W, N, g, V, self._out, self._n_out,
                                    self._best, self._new if W else None, None)
@@ -172,7 +181,7 @@ class LookaheadDecoder:
                 u = binding._native.uniform_draws(self.seed, step, 0, n1 * g)
             else:
                 u = [float(self.uniform(self.seed, step, i)) for i in range(n1 * g)]
-            u = binding._native.upload([u, [float(self.uniform(self.seed, step, 1 << 20))]], True)
+            u = binding._native.upload([u, [float(self.uniform(self.seed, step, 1 << 20))]], True).to(logits.device)
             u_test, u_final = u[:n1 * g].view(n1, g) if g else None, u[n1 * g:]
             binding.la_verify_sample(logits[0], cand_logits, cand, u_test, u_final, self.temperature, N, g, V,
                                      self._out, self._n_out)
@@ -229,9 +238,11 @@ class BatchedLookaheadDecoder:
         placeholder = (0,) * n1
         padded = [t + [t[0] if t else placeholder] * (g_step - len(t)) for t in tails]
         tokens = [s.step_tokens(p) for s, p in zip(self.seqs, padded)]
-        on_gpu = binding._native.upload(tokens, False).view(len(tokens), -1)   # one upload for the model and the verification
-        logits = self.model.forward_step(_StepTokens(tokens, on_gpu), W, N, g_step)
-        cand = on_gpu[:, 1 + W * n1:].contiguous().view(-1, g_step, n1) if g_step else None
+        on_gpu = _upload_step(tokens, V)
+        if on_gpu is not None:
+            on_gpu = on_gpu.view(len(tokens), -1)
+        logits = _forward(self.model, tokens, on_gpu, W, N, g_step)
+        cand = _candidates(on_gpu, 1 + W * n1, padded, logits[0].device).view(-1, g_step, n1) if g_step else None
         descs = []
         for i, lg in enumerate(logits):
             descs.append(dict(
@@ -313,8 +324,10 @@ class ToyAttentionLM:
         self.length += n
 
     def forward_step(self, tokens, W, N, G):
-        idx = _indices(tokens, [tokens], self._qkv)
-        T, P, d = len(tokens), self.length, wl.TOY_HEAD_DIM
+        return self._forward(_indices(tokens, [tokens], self._qkv), W, N, G)
+
+    def _forward(self, idx, W, N, G):
+        T, P, d = len(idx), self.length, wl.TOY_HEAD_DIM
         assert T == 1 + (W + G) * (N - 1)
         if P + N > self.capacity:
             raise ValueError("KV cache full")
@@ -379,21 +392,24 @@ class ToyBatchLM:
         self.lengths[i] += n
 
     def forward_step(self, tokens, W, N, G):
+        for toks in tokens:
+            assert len(toks) == 1 + (W + G) * (N - 1)
+        return self._forward(_indices(tokens, tokens, self._qkv).view(len(tokens), -1), W, N, G)
+
+    def _forward(self, idx, W, N, G):
         d = wl.TOY_HEAD_DIM
-        T = 1 + (W + G) * (N - 1)
-        for i, toks in enumerate(tokens):
-            assert len(toks) == T
-            if self.lengths[i] + N > self.capacity:
-                raise ValueError("KV cache full")
-        idx = _indices(tokens, tokens, self._qkv).view(len(tokens), T)
-        q, k, v = self._qkv.index_select(1, idx.view(-1)).view(3, len(tokens), T, 1, d)
-        out = torch.empty((len(tokens), T, 1, d), dtype=torch.bfloat16, device=self.device)
+        n, T = idx.shape
+        assert T == 1 + (W + G) * (N - 1)
+        if any(length + N > self.capacity for length in self.lengths[:n]):
+            raise ValueError("KV cache full")
+        q, k, v = self._qkv.index_select(1, idx.view(-1)).view(3, n, T, 1, d)
+        out = torch.empty((n, T, 1, d), dtype=torch.bfloat16, device=self.device)
         seqs = [dict(q=q[i], block_table=self.block_tables[i], step_k=k[i], step_v=v[i], out=out[i], P=self.lengths[i])
-                for i in range(len(tokens))]
+                for i in range(n)]
         binding.la_step_attention_batch_paged(seqs, self._k_pages, self._v_pages, W, N, G, 1, 1, d)
         self._step = (seqs, W, N, G)
         rows = torch.add(out[:, :, 0, 0] > 0.5, idx, alpha=2)
-        return list(self._logits.index_select(0, rows.view(-1)).view(len(tokens), T, self.vocab))
+        return list(self._logits.index_select(0, rows.view(-1)).view(n, T, self.vocab))
 
     def commit(self, bests, n_outs):
         seqs, W, N, G = self._step
@@ -404,6 +420,9 @@ class ToyBatchLM:
 
     def advance(self, i, n):
         self.lengths[i] += n
+
+
+_OWN_STEPS = (ToyAttentionLM.forward_step, ToyBatchLM.forward_step)
 
 
 def _demo():

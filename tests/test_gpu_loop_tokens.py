@@ -1,4 +1,5 @@
-"""GPU: the tokens that the toy models' forward pass and the decoding loop take: every form that torch.tensor takes."""
+"""GPU: the tokens that the toy models' forward pass and the decoding loop take: every form that torch.tensor takes,
+and a model of the caller's own that changes them, or runs on a stream of its own."""
 import warnings
 
 import numpy as np
@@ -55,3 +56,62 @@ def test_batched_forward_step_takes_any_form_of_tokens(form):
             forms.append(FORMS[form](tokens))
         for f in forms:
             assert all(torch.equal(a, b) for a, b in zip(model.forward_step(f, W, N, G), want))
+
+
+def loop(model, n_tokens=60, **more):
+    """The tokens of a run; every step of the current stream starts behind some work."""
+    dec, out = lookahead.LookaheadDecoder(model, [0, 5, 9, 5], W, N, G, **more), []
+    torch.cuda.synchronize()
+    while len(out) < n_tokens:
+        torch.cuda._sleep(500000)
+        out += dec.step()[0]
+    return out[:n_tokens]
+
+
+class Changes(lookahead.ToyAttentionLM):
+    """Replaces a token of the window before the model runs."""
+
+    def forward_step(self, tokens, W, N, G):
+        tokens[1] = 1 + tokens[1] % (wl.TOY_VOCAB - 1)
+        got = super().forward_step(tokens, W, N, G)
+        assert torch.equal(got, super().forward_step([int(t) for t in tokens], W, N, G))
+        return got
+
+
+class ChangesBatch(lookahead.ToyBatchLM):
+    def forward_step(self, tokens, W, N, G):
+        tokens[1][1] = 1 + tokens[1][1] % (wl.TOY_VOCAB - 1)
+        got = super().forward_step(tokens, W, N, G)
+        assert all(torch.equal(a, b) for a, b in zip(got, super().forward_step([list(t) for t in tokens], W, N, G)))
+        return got
+
+
+def test_a_model_may_change_its_tokens():
+    dec = lookahead.LookaheadDecoder(Changes(0), [0, 5, 9, 5], W, N, G)
+    dec.generate(30)
+    prompts = [[0, 5, 9], [0, 6, 9]]
+    lookahead.BatchedLookaheadDecoder(ChangesBatch(0, 2, max_len=1024), prompts, W, N, G).generate(30)
+
+
+@pytest.mark.parametrize("kind", [float, np.int64, np.float64])
+def test_random_tokens_of_any_kind(kind):
+    want = loop(lookahead.ToyAttentionLM(0))
+    assert loop(lookahead.ToyAttentionLM(0), random_token=lambda *a: kind(wl.window_random_token(*a))) == want
+
+
+class OnAStreamOfItsOwn(lookahead.ToyAttentionLM):
+    """Its work waits for nothing of the caller's stream: the caller has read the last step's result."""
+
+    def __init__(self, seed):
+        super().__init__(seed)
+        self.stream = torch.cuda.Stream()
+
+    def forward_step(self, tokens, W, N, G):
+        with torch.cuda.stream(self.stream):
+            logits = super().forward_step(tokens, W, N, G)
+        torch.cuda.current_stream().wait_stream(self.stream)
+        return logits
+
+
+def test_a_model_on_a_stream_of_its_own():
+    assert loop(OnAStreamOfItsOwn(0)) == loop(lookahead.ToyAttentionLM(0))
