@@ -61,11 +61,15 @@ class NgramPool:
 
 def _indices(tokens, lists, table):
     """Tokens of a step, or a list of them per sequence, as indices beside `table`: in any form that torch.tensor
-    takes, but lists of numbers of the vocabulary, all in `lists`, are uploaded without a wait."""
+    takes and with negative ones that count from the vocabulary's end, but lists of numbers of the vocabulary, all
+    in `lists`, are uploaded without a wait."""
     if binding._native.in_range(lists, wl.TOY_VOCAB):
         idx = binding._native.upload(lists, False)
         return idx if idx.device == table.device else idx.to(table.device)
-    return torch.tensor(tokens, dtype=torch.long, device=table.device)
+    idx = torch.tensor(tokens, dtype=torch.long)
+    if idx.numel() and not -wl.TOY_VOCAB <= int(idx.min()) <= int(idx.max()) < wl.TOY_VOCAB:
+        raise IndexError("a token is not in the vocabulary of %d" % wl.TOY_VOCAB)
+    return torch.where(idx < 0, idx + wl.TOY_VOCAB, idx).to(table.device)
 
 
 def _upload_step(lists, vocab):

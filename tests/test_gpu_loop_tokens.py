@@ -58,6 +58,34 @@ def test_batched_forward_step_takes_any_form_of_tokens(form):
             assert all(torch.equal(a, b) for a, b in zip(model.forward_step(f, W, N, G), want))
 
 
+def test_negative_tokens_count_from_the_end():
+    tokens = tokens_of(3)
+    tokens[2] = wl.TOY_VOCAB - 1
+    turned = [t - wl.TOY_VOCAB if i % 3 == 2 else t for i, t in enumerate(tokens)]
+    model = single()
+    want = model.forward_step(tokens, W, N, G)
+    for form in (turned, tuple(turned), np.array(turned), torch.tensor(turned, device="cuda")):
+        with warnings.catch_warnings():
+            warnings.simplefilter("ignore")
+            assert torch.equal(model.forward_step(form, W, N, G), want)
+    model, two = batched(), [tokens, tokens_of(4)]
+    for a, b in zip(model.forward_step([turned, two[1]], W, N, G), model.forward_step(two, W, N, G)):
+        assert torch.equal(a, b)
+    for wrong in (wl.TOY_VOCAB, -wl.TOY_VOCAB - 1, 2**40):
+        with pytest.raises(IndexError):
+            single().forward_step(tokens[:-1] + [wrong], W, N, G)
+        with pytest.raises(IndexError):
+            model.forward_step([tokens, tokens[:-1] + [wrong]], W, N, G)
+
+
+def test_a_loop_with_negative_random_tokens():
+    """(they stand for others of the vocabulary to the model, and are no candidates' tokens to the verification)"""
+    runs = []
+    for turn in (0, wl.TOY_VOCAB):
+        runs.append(loop(lookahead.ToyAttentionLM(0), random_token=lambda *a: wl.window_random_token(*a) - turn))
+    assert runs[0] == runs[1]
+
+
 def loop(model, n_tokens=60, **more):
     """The tokens of a run; every step of the current stream starts behind some work."""
     dec, out = lookahead.LookaheadDecoder(model, [0, 5, 9, 5], W, N, G, **more), []
