@@ -751,13 +751,20 @@ PyObject* window_random_tokens(PyObject*, PyObject* const* args, Py_ssize_t n_ar
     uint64_t w[3];
     Py_ssize_t count;
     if (!words(args, n_args, 4, w, &count)) return nullptr;
+    int overflow = 0;
+    const long long vocab = PyLong_AsLongLongAndOverflow(args[2], &overflow);
+    if (vocab == -1 && !overflow && PyErr_Occurred()) return nullptr;
+    if (overflow || vocab < 2) {                    // (tokens of 1 .. vocab-1)
+        PyErr_Format(PyExc_ValueError, "no random token of a vocabulary of %S", args[2]);
+        return nullptr;
+    }
     PyObject* const list = PyList_New(count > 0 ? count : 0);
     for (Py_ssize_t j = 0; list && j < count; ++j) {
         uint64_t h = w[0] * 0x9E3779B97F4A7C15ull + w[1] * 0xBF58476D1CE4E5B9ull + (uint64_t)j * 0x94D049BB133111EBull;
         h ^= h >> 31;
         h *= 0xD6E8FEB86659FD93ull;
         h ^= h >> 29;
-        PyObject* const v = PyLong_FromUnsignedLongLong(1 + h % (w[2] - 1));
+        PyObject* const v = PyLong_FromUnsignedLongLong(1 + h % ((uint64_t)vocab - 1));
         if (!v) {
             Py_DECREF(list);
             return nullptr;

@@ -18,6 +18,13 @@ def test_generators_equal_their_definitions(seed, count):
             [float(wl.uniform_draw(seed, step, 5 + j)) for j in range(count)]
 
 
+@pytest.mark.parametrize("vocab", [1, 0, -5, -2**63, 2**64 + 1, 2**70])
+def test_random_tokens_of_no_vocabulary(vocab):
+    with pytest.raises(ValueError):
+        binding._native.window_random_tokens(1, 2, vocab, 3)
+    assert binding._native.window_random_tokens(1, 2, 2, 3) == [1, 1, 1]
+
+
 def test_pool_keeps_the_most_recent_last():
     rng, pool, want = random.Random(1), lookahead.NgramPool(), {}
     for _ in range(2000):
