@@ -33,6 +33,13 @@ struct Owned {     // a reference that goes with its scope
     Owned(const Owned&) = delete;
 };
 
+struct Unlocked {  // no interpreter lock within its scope
+    PyThreadState* const state = PyEval_SaveThread();
+    Unlocked() {}
+    ~Unlocked() { PyEval_RestoreThread(state); }
+    Unlocked(const Unlocked&) = delete;
+};
+
 PyObject* g_la_error = nullptr;  // binding.LaError
 
 constexpr at::ScalarType kBF16 = at::kBFloat16, kF32 = at::kFloat, kI32 = at::kInt, kU8 = at::kByte;
@@ -661,43 +668,42 @@ PyObject* upload(PyObject*, PyObject* const* args, Py_ssize_t n_args)
         PyErr_SetString(PyExc_TypeError, "a list of lists and a truth value are expected");
         return nullptr;
     }
-    const int floats = PyObject_IsTrue(args[1]);
-    if (floats < 0) return nullptr;
     try {
-        const Py_ssize_t n_lists = PyList_GET_SIZE(args[0]);
-        int64_t count = 0;
-        for (Py_ssize_t i = 0; i < n_lists; ++i) {
-            PyObject* const l = PyList_GET_ITEM(args[0], i);
-            if (!PyList_Check(l)) {
+        const bool floats = truth(args[1]);
+        // Converting an item may run code that changes any of the lists: their sizes are read anew each time, and what is
+        // in use is held.
+        std::vector<uint32_t> words;
+        for (Py_ssize_t i = 0; i < PyList_GET_SIZE(args[0]); ++i) {
+            const Owned l(PyList_GET_ITEM(args[0], i));
+            Py_INCREF(l.o);
+            if (!PyList_Check(l.o)) {
                 PyErr_SetString(PyExc_TypeError, "a list of lists is expected");
                 return nullptr;
             }
-            count += PyList_GET_SIZE(l);
-        }
-        const auto type = floats ? kF32 : kI32;
-        const at::Tensor host = at::empty({count}, at::TensorOptions().dtype(type).pinned_memory(true));
-        char* to = static_cast<char*>(host.data_ptr());
-        for (Py_ssize_t i = 0; i < n_lists; ++i) {
-            PyObject* const l = PyList_GET_ITEM(args[0], i);
-            for (Py_ssize_t j = 0; j < PyList_GET_SIZE(l) && count > 0; ++j, --count, to += 4) {
-                Owned item(PyList_GET_ITEM(l, j));   // (converting it may run code that changes the list)
+            words.reserve(words.size() + (size_t)PyList_GET_SIZE(l.o));
+            for (Py_ssize_t j = 0; j < PyList_GET_SIZE(l.o); ++j) {
+                const Owned item(PyList_GET_ITEM(l.o, j));
                 Py_INCREF(item.o);
+                uint32_t w;
                 if (floats) {
                     const double v = PyFloat_AsDouble(item.o);
                     if (v == -1.0 && PyErr_Occurred()) return nullptr;
                     const float f = (float)v;
-                    memcpy(to, &f, 4);
+                    memcpy(&w, &f, 4);
                 } else {
-                    const int v = integer(item.o);
-                    memcpy(to, &v, 4);
+                    w = (uint32_t)integer(item.o);
                 }
+                words.push_back(w);
             }
         }
-        if (count != 0) {
-            PyErr_SetString(PyExc_RuntimeError, "a list changed its size");
-            return nullptr;
+        at::Tensor on_gpu;
+        {
+            const Unlocked unlocked;   // (the first pinned block is an allocation of milliseconds)
+            const at::Tensor host = at::empty({(int64_t)words.size()}, at::TensorOptions().dtype(floats ? kF32 : kI32).pinned_memory(true));
+            if (!words.empty()) memcpy(host.data_ptr(), words.data(), words.size() * 4);
+            on_gpu = host.to(at::TensorOptions().device(at::kCUDA), /*non_blocking=*/true);
         }
-        return THPVariable_Wrap(host.to(at::TensorOptions().device(at::kCUDA).dtype(type), /*non_blocking=*/true));
+        return THPVariable_Wrap(on_gpu);
     } catch (const Raised&) {
         return nullptr;
     } catch (const std::exception& e) {

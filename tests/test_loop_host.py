@@ -59,3 +59,26 @@ def test_uploads():
     for bad, error in ((((1,),), TypeError), ([(1,)], TypeError), ([["a"]], TypeError), ([[2**31]], ValueError)):
         with pytest.raises(error):
             binding._native.upload(bad, False)
+
+
+class Clears:
+    """An int whose conversion changes the lists that it is in."""
+
+    def __init__(self, lists, do):
+        self.lists, self.do = lists, do
+
+    def __index__(self):
+        self.do(self.lists)
+        return 7
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("do,want", [(lambda l: l.clear(), [1, 7, 2, 3]), (lambda l: l[0].clear(), [1, 7, 4, 5]),
+                                     (lambda l: l.__setitem__(1, [9]), [1, 7, 2, 3, 9]), (lambda l: l.pop(), [1, 7, 2, 3])])
+def test_uploads_of_lists_that_change(do, want):
+    lists = []
+    lists += [[1, Clears(lists, do), 2, 3], [4, 5]]
+    assert binding._native.upload(lists, False).tolist() == want
+    lists[:] = [[1, Clears(lists, lambda l: l.__setitem__(1, None)), 2, 3], [4, 5]]
+    with pytest.raises(TypeError):
+        binding._native.upload(lists, False)
