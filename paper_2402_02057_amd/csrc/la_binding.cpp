@@ -658,10 +658,22 @@ LA_ENTRY(verify_sample_batch)
 
 // ---- the decoding loop's host work (lookahead.py)
 
-// upload(lists, floats): the numbers of the lists one after the other as a new int32 (or fp32) tensor of the
-// current GPU.  The copy is queued on the current stream and not waited for: it leaves from pinned memory
-// that torch's allocator holds back until the copy has run.  (torch.tensor(list, device="cuda") copies from
-// pageable memory and waits: 19 us for 121 tokens, here 7.)
+// Numbers as a new tensor of the current GPU.  The copy is queued on the current stream and not waited for: it leaves
+// from pinned memory that torch's allocator holds back until the copy has run.  (torch.tensor(list, device="cuda") copies
+// from pageable memory and waits: 19 us for 121 tokens, here 7.)
+PyObject* sent(const std::vector<uint32_t>& words, at::ScalarType type)
+{
+    at::Tensor on_gpu;
+    {
+        const Unlocked unlocked;   // (the first pinned block is an allocation of milliseconds)
+        const at::Tensor host = at::empty({(int64_t)words.size()}, at::TensorOptions().dtype(type).pinned_memory(true));
+        if (!words.empty()) memcpy(host.data_ptr(), words.data(), words.size() * 4);
+        on_gpu = host.to(at::TensorOptions().device(at::kCUDA), /*non_blocking=*/true);
+    }
+    return THPVariable_Wrap(on_gpu);
+}
+
+// upload(lists, floats): the numbers of the lists one after the other, in int32 (or fp32)
 PyObject* upload(PyObject*, PyObject* const* args, Py_ssize_t n_args)
 {
     if (n_args != 2 || !PyList_Check(args[0])) {
@@ -696,14 +708,7 @@ PyObject* upload(PyObject*, PyObject* const* args, Py_ssize_t n_args)
                 words.push_back(w);
             }
         }
-        at::Tensor on_gpu;
-        {
-            const Unlocked unlocked;   // (the first pinned block is an allocation of milliseconds)
-            const at::Tensor host = at::empty({(int64_t)words.size()}, at::TensorOptions().dtype(floats ? kF32 : kI32).pinned_memory(true));
-            if (!words.empty()) memcpy(host.data_ptr(), words.data(), words.size() * 4);
-            on_gpu = host.to(at::TensorOptions().device(at::kCUDA), /*non_blocking=*/true);
-        }
-        return THPVariable_Wrap(on_gpu);
+        return sent(words, floats ? kF32 : kI32);
     } catch (const Raised&) {
         return nullptr;
     } catch (const std::exception& e) {
@@ -712,28 +717,39 @@ PyObject* upload(PyObject*, PyObject* const* args, Py_ssize_t n_args)
     }
 }
 
-// in_range(lists, limit): whether this is a list of lists of ints (no subclass of either) of 0 .. limit-1
-PyObject* in_range(PyObject*, PyObject* const* args, Py_ssize_t n_args)
+// upload_in_range(lists, limit): the same in int32, or None unless this is a list of lists of ints (no subclass of either)
+// of 0 .. limit-1
+PyObject* upload_in_range(PyObject*, PyObject* const* args, Py_ssize_t n_args)
 {
     if (n_args != 2) {
         PyErr_SetString(PyExc_TypeError, "two arguments are expected");
         return nullptr;
     }
-    const long long limit = PyLong_AsLongLong(args[1]);
-    if (limit == -1 && PyErr_Occurred()) return nullptr;
-    if (!PyList_CheckExact(args[0])) Py_RETURN_FALSE;
-    for (Py_ssize_t i = 0; i < PyList_GET_SIZE(args[0]); ++i) {       // (none of this runs code that could change a list)
-        PyObject* const l = PyList_GET_ITEM(args[0], i);
-        if (!PyList_CheckExact(l)) Py_RETURN_FALSE;
-        for (Py_ssize_t j = 0; j < PyList_GET_SIZE(l); ++j) {
-            PyObject* const item = PyList_GET_ITEM(l, j);
-            if (!PyLong_CheckExact(item)) Py_RETURN_FALSE;
-            int overflow = 0;
-            const long long v = PyLong_AsLongLongAndOverflow(item, &overflow);
-            if (overflow || v < 0 || v >= limit) Py_RETURN_FALSE;
+    const long long most = PyLong_AsLongLong(args[1]);
+    if (most == -1 && PyErr_Occurred()) return nullptr;
+    const long long limit = most < (1ll << 31) ? most : 1ll << 31;
+    if (!PyList_CheckExact(args[0])) Py_RETURN_NONE;
+    try {
+        std::vector<uint32_t> words;
+        for (Py_ssize_t i = 0; i < PyList_GET_SIZE(args[0]); ++i) {       // (none of this runs code that could change a list)
+            PyObject* const l = PyList_GET_ITEM(args[0], i);
+            if (!PyList_CheckExact(l)) Py_RETURN_NONE;
+            const Py_ssize_t n = PyList_GET_SIZE(l);
+            words.reserve(words.size() + (size_t)n);
+            for (Py_ssize_t j = 0; j < n; ++j) {
+                PyObject* const item = PyList_GET_ITEM(l, j);
+                if (!PyLong_CheckExact(item)) Py_RETURN_NONE;
+                int overflow = 0;
+                const long long v = PyLong_AsLongLongAndOverflow(item, &overflow);
+                if (overflow || v < 0 || v >= limit) Py_RETURN_NONE;
+                words.push_back((uint32_t)v);
+            }
         }
+        return sent(words, kI32);
+    } catch (const std::exception& e) {
+        PyErr_SetString(PyExc_RuntimeError, e.what());
+        return nullptr;
     }
-    Py_RETURN_TRUE;
 }
 
 // Three arguments taken modulo 2^64, as the generators below are defined, and a count.
@@ -855,7 +871,7 @@ PyMethodDef methods[] = {
     LA_METHOD(verify_sample, 12),
     LA_METHOD(verify_sample_batch, 5),
     {"upload", (PyCFunction)(void (*)(void))upload, METH_FASTCALL, nullptr},
-    {"in_range", (PyCFunction)(void (*)(void))in_range, METH_FASTCALL, nullptr},
+    {"upload_in_range", (PyCFunction)(void (*)(void))upload_in_range, METH_FASTCALL, nullptr},
     {"window_random_tokens", (PyCFunction)(void (*)(void))window_random_tokens, METH_FASTCALL, nullptr},
     {"uniform_draws", (PyCFunction)(void (*)(void))uniform_draws, METH_FASTCALL, nullptr},
     {"set_error_class", set_error_class, METH_O, nullptr},

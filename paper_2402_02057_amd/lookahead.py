@@ -63,8 +63,8 @@ def _indices(tokens, lists, table):
     """Tokens of a step, or a list of them per sequence, as indices beside `table`: in any form that torch.tensor
     takes and with negative ones that count from the vocabulary's end, but lists of numbers of the vocabulary, all
     in `lists`, are uploaded without a wait."""
-    if binding._native.in_range(lists, wl.TOY_VOCAB):
-        idx = binding._native.upload(lists, False)
+    idx = binding._native.upload_in_range(lists, wl.TOY_VOCAB)
+    if idx is not None:
         return idx if idx.device == table.device else idx.to(table.device)
     idx = torch.tensor(tokens, dtype=torch.long)
     if idx.numel() and not -wl.TOY_VOCAB <= int(idx.min()) <= int(idx.max()) < wl.TOY_VOCAB:
@@ -72,24 +72,12 @@ def _indices(tokens, lists, table):
     return torch.where(idx < 0, idx + wl.TOY_VOCAB, idx).to(table.device)
 
 
-def _upload_step(lists, vocab):
-    """A step's tokens on the GPU, for the model and the verification alike; None unless all are of the vocabulary."""
-    return binding._native.upload(lists, False) if binding._native.in_range(lists, vocab) else None
-
-
 def _forward(model, tokens, on_gpu, W, N, G):
     """The model's output for a step.  The toy models' own forward pass takes the tokens that are on the GPU already;
     any other (it may change them, or run on a stream of its own) gets its lists and nothing else."""
-    if on_gpu is not None and getattr(model.forward_step, "__func__", None) in _OWN_STEPS and on_gpu.device == model._qkv.device:
+    if on_gpu is not None and getattr(model.forward_step, "__func__", None) in _OWN_STEPS and on_gpu.get_device() == model._qkv.get_device():
         return model._forward(on_gpu, W, N, G)
     return model.forward_step(tokens, W, N, G)
-
-
-def _candidates(on_gpu, first, tails, device):
-    """The candidates' tokens beside the logits: the step's from column `first` on, or their tails."""
-    if on_gpu is not None and on_gpu.device == device:
-        return on_gpu[..., first:].contiguous()
-    return torch.tensor(tails, dtype=torch.int32, device=device)
 
 
 class _Sequence:
@@ -164,11 +152,15 @@ class LookaheadDecoder:
         g = len(tails)
         tokens = self._seq.step_tokens(tails)
         V = self.model.vocab
-        on_gpu = _upload_step([tokens], V)
+        on_gpu = binding._native.upload_in_range([tokens], V)    # for the model and the verification alike
         logits = _forward(self.model, tokens, on_gpu, W, N, g)
         look = logits[1 + (n1 - 1) * W:1 + n1 * W] if W else None        # newest level of the window
         cand_logits = logits[1 + W * n1:].view(g, n1, V) if g else None
-        cand = _candidates(on_gpu, 1 + W * n1, tails, logits.device).view(g, n1) if g else None
+        cand = None
+        if g:       # (side by side with the logits)
+            beside = on_gpu is not None and on_gpu.get_device() == logits.get_device()
+            cand = on_gpu[1 + W * n1:] if beside else torch.tensor(tails, dtype=torch.int32, device=logits.device)
+            cand = cand.view(g, n1)
         if self.temperature is None:
             binding.la_verify_step(logits[0], look, cand_logits, cand, W, N, g, V, self._out, self._n_out,
                                    self._best, self._new if W else None, None)
@@ -185,7 +177,8 @@ class LookaheadDecoder:
                 u = binding._native.uniform_draws(self.seed, step, 0, n1 * g)
             else:
                 u = [float(self.uniform(self.seed, step, i)) for i in range(n1 * g)]
-            u = binding._native.upload([u, [float(self.uniform(self.seed, step, 1 << 20))]], True).to(logits.device)
+            u = binding._native.upload([u, [float(self.uniform(self.seed, step, 1 << 20))]], True)
+            u = u if u.get_device() == logits.get_device() else u.to(logits.device)
             u_test, u_final = u[:n1 * g].view(n1, g) if g else None, u[n1 * g:]
             binding.la_verify_sample(logits[0], cand_logits, cand, u_test, u_final, self.temperature, N, g, V,
                                      self._out, self._n_out)
@@ -242,11 +235,15 @@ class BatchedLookaheadDecoder:
         placeholder = (0,) * n1
         padded = [t + [t[0] if t else placeholder] * (g_step - len(t)) for t in tails]
         tokens = [s.step_tokens(p) for s, p in zip(self.seqs, padded)]
-        on_gpu = _upload_step(tokens, V)
+        on_gpu = binding._native.upload_in_range(tokens, V)      # for the model and the verification alike
         if on_gpu is not None:
             on_gpu = on_gpu.view(len(tokens), -1)
         logits = _forward(self.model, tokens, on_gpu, W, N, g_step)
-        cand = _candidates(on_gpu, 1 + W * n1, padded, logits[0].device).view(-1, g_step, n1) if g_step else None
+        cand = None
+        if g_step:  # (side by side with the logits)
+            beside = on_gpu is not None and on_gpu.get_device() == logits[0].get_device()
+            cand = on_gpu[:, 1 + W * n1:].contiguous() if beside else torch.tensor(padded, dtype=torch.int32, device=logits[0].device)
+            cand = cand.view(-1, g_step, n1)
         descs = []
         for i, lg in enumerate(logits):
             descs.append(dict(
@@ -331,7 +328,7 @@ class ToyAttentionLM:
         return self._forward(_indices(tokens, [tokens], self._qkv), W, N, G)
 
     def _forward(self, idx, W, N, G):
-        T, P, d = len(idx), self.length, wl.TOY_HEAD_DIM
+        T, P, d = idx.numel(), self.length, wl.TOY_HEAD_DIM
         assert T == 1 + (W + G) * (N - 1)
         if P + N > self.capacity:
             raise ValueError("KV cache full")

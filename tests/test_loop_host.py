@@ -39,11 +39,16 @@ def test_pool_keeps_the_most_recent_last():
             assert pool.lookup(first, limit) == (want.get(first, [])[-limit:] if limit else [])
 
 
-def test_in_range():
-    ok = binding._native.in_range
-    assert ok([[0, 5], [], [9]], 10) and ok([], 10)
+def test_what_is_not_in_range_is_not_uploaded():
     for lists in ([[0, 10]], [[-1]], [[2**70]], [[True]], [[1.0]], [(1,)], ([1],), [1], None, [[1], None]):
-        assert not ok(lists, 10)
+        assert binding._native.upload_in_range(lists, 10) is None
+    assert binding._native.upload_in_range([[2**31]], 2**40) is None
+
+
+@pytest.mark.gpu
+def test_uploads_in_range():
+    assert binding._native.upload_in_range([[0, 5], [], [9]], 10).tolist() == [0, 5, 9]
+    assert binding._native.upload_in_range([], 10).numel() == 0 and binding._native.upload_in_range([[1]], 2).dtype == torch.int32
 
 
 @pytest.mark.gpu
