@@ -23,6 +23,7 @@ loop end to end on the GPU and check it against plain greedy decoding.
     python -m paper_2402_02057_amd.lookahead      # demo: tokens per step and time per step
 """
 import time
+from itertools import islice
 
 import torch
 
@@ -56,7 +57,7 @@ class NgramPool:
 
     def lookup(self, first_token, limit):
         """At most `limit` tails of n-grams starting with first_token, the most recent ones."""
-        return list(self._tails.get(first_token, ()))[-limit:] if limit > 0 else []
+        return list(islice(reversed(self._tails.get(first_token, {})), limit))[::-1] if limit > 0 else []
 
 
 def _indices(tokens, lists, table):

@@ -45,6 +45,24 @@ def test_what_is_not_in_range_is_not_uploaded():
     assert binding._native.upload_in_range([[2**31]], 2**40) is None
 
 
+def test_lookup_reads_no_more_than_it_returns():
+    class Bucket(dict):
+        read = 0
+
+        def __iter__(self):
+            raise AssertionError("the whole bucket is read")
+
+        def __reversed__(self):
+            for key in dict.__reversed__(self):
+                self.read += 1
+                yield key
+    pool = lookahead.NgramPool()
+    pool._tails[3] = bucket = Bucket()
+    for i in range(1000):
+        pool.add((3, i, i + 1))
+    assert pool.lookup(3, 4) == [(i, i + 1) for i in range(996, 1000)] and bucket.read == 4
+
+
 @pytest.mark.gpu
 def test_uploads_in_range():
     assert binding._native.upload_in_range([[0, 5], [], [9]], 10).tolist() == [0, 5, 9]
