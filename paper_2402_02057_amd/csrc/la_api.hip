@@ -68,10 +68,12 @@ la_status select_workspace(int set)
 
 namespace {
 // A block is at least this large: what any batched launch of the staged kernel needs (36 KB of partial
-// results a workgroup; eight tickets a group, 128 bytes apart), and more than any one step.
+// results a workgroup; eight tickets a group, 128 bytes apart), and more than any one step (256 workgroups of 68 KB).
 constexpr size_t kLeastZeroed = size_t(512) << 10, kLeastScratch = size_t(32) << 20;
 static_assert(kMaxCutWorkgroups * kStagedPartialBytes <= kLeastScratch && kMaxCutGroups * kStagedTicketBytes <= kLeastZeroed,
               "a staged batch fits the least blocks");
+static_assert(kMaxStepWorkgroups * kStepPartialBytes <= kLeastScratch && kMaxStepGroups * kStagedTicketBytes <= kLeastZeroed,
+              "a step fits the least blocks");
 constexpr unsigned kReservePause = 256;
 
 // Growing a block means hipMalloc (and a clear on the stream): neither may happen while the

@@ -1166,6 +1166,12 @@ __global__ __launch_bounds__(256) void wide_combine_kernel(const BatchParams)
 // pointer is handed to kernels.
 constexpr size_t kFixedTicketBytes = (size_t)128 << 10;          // 128 split groups x 8 waves, 128 bytes apart
 constexpr size_t kFixedPartialBytes = (size_t)17 << 20;         // 256 workgroups of 128 rows with fp32 partials
+static_assert(kMaxStepGroups * kStagedTicketBytes <= kFixedTicketBytes && kMaxStepWorkgroups * kStepPartialBytes <= kFixedPartialBytes,
+              "every step that is not forced otherwise fits");
+template <int D, int RT, int KS>
+constexpr bool step_fits() { return Cfg<D, RT, KS, 64, 4, 2, 4>::PART_WG_BYTES <= kStepPartialBytes && RT * KS * kTicketStride * sizeof(unsigned) <= kStagedTicketBytes; }
+static_assert(step_fits<128, 4, 2>() && step_fits<128, 2, 4>() && step_fits<128, 1, 2>() && step_fits<64, 2, 2>() && step_fits<64, 1, 2>(),
+              "what a workgroup of a step alone and its tickets take");
 static __device__ __align__(256) unsigned char scratch[kFixedTicketBytes + kFixedPartialBytes];
 
 __global__ void clear_words_kernel(unsigned* words, int n)

@@ -410,6 +410,7 @@ inline LaunchPlan plan_launch(const int* chunks, int n, int tiles, int kv_heads,
 // computed again over all keys: 20/20 heads, 57 rows on 4096 keys 52.5 -> 21.2 us, 42/42 on 1000 21.7 -> 13.7 (8-bit cache
 // 20.8 -> 10.7, pages 24.1 -> 14.2), 4/4, head_dim 64, 31 rows on 4096 keys 53.6 -> 11.3, on 512 13.2 -> 6.3.  (Compute units
 // that this leaves idle do not matter: spreading the row blocks evenly over the XCDs measured the same.)
+constexpr int kMaxStepWorkgroups = kXcds * kXcdUnits, kMaxStepGroups = kMaxStepWorkgroups / 2;   // of a step that is cut
 inline int step_units_per_xcd(int units) { return (units + kXcds - 1) / kXcds; }
 inline int step_cuts_clipped(int x, int chunks)
 {

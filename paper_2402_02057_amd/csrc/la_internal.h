@@ -25,8 +25,9 @@ void* scratch_workspace(size_t bytes, hipStream_t stream);
 // being captured (in_capture: then too); returns the size of the scratch block then.  A failure is no error (the call that
 // needs more than there is reports it, or does with less), and not tried again at once.
 size_t reserve_workspace(size_t scratch_bytes, hipStream_t stream, bool in_capture = false);
-// What the staged attention kernels take of them at most: of partial results per workgroup, of tickets per group.
-constexpr size_t kStagedPartialBytes = size_t(36) << 10, kStagedTicketBytes = 8 * 128;
+// What the staged attention kernels take of them at most: of partial results per workgroup of a batch (in bf16) and of a
+// step alone (128 rows in fp32), of tickets per group.
+constexpr size_t kStagedPartialBytes = size_t(36) << 10, kStepPartialBytes = size_t(68) << 10, kStagedTicketBytes = 8 * 128;
 void free_workspaces();
 la_status select_workspace(int set);
 // Testing hooks of the attention launchers (la_debug_override).

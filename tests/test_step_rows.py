@@ -16,6 +16,7 @@ SHIM = """
 #include "la_batch_plan.h"
 extern "C" int rows128(int chunks, int tiles, int kv_heads, int many, int codes) { return la::step_rows128(chunks, tiles, kv_heads, many, codes); }
 extern "C" int cuts(int units, int chunks) { return la::step_cuts(units, chunks); }
+extern "C" int most(int groups) { return groups ? la::kMaxStepGroups : la::kMaxStepWorkgroups; }
 """
 
 
@@ -45,7 +46,7 @@ def test_the_rule(lib):
     for units in range(1, 400, 7):
         for chunks in range(1, 300, 13):
             x = lib.cuts(units, chunks)
-            assert 1 <= x <= max(1, chunks // 2) and x <= 64 and (x == 1 or units * x <= 256)
+            assert 1 <= x <= max(1, chunks // 2) and x <= 64 and (x == 1 or (units * x <= lib.most(0) == 256 and units <= lib.most(1)))
 
 
 SHAPES = [(2100, 30, 5, 34, 32, 32),      # 160 units of 64 rows, one range each; 96 of 128 in two: fp32 partial results
