@@ -1,19 +1,14 @@
 """Steps alone whose keys are cut into ranges, with any number of row blocks: the ranges of a row block on one XCD (the
 mapping of csrc/la_batch_plan.h, on the CPU), and on the GPU no group computed again and none further off."""
-import ctypes
-import os
-import subprocess
-
 import numpy as np
 import pytest
 import torch
 
 from oracle import la_oracle as orc
-from paper_2402_02057_amd import binding, buildlib, workloads as wl
+from paper_2402_02057_amd import binding, workloads as wl
+from step_cases import codes_inputs, error, every_tile_differs, inputs, label, new_like, planner
 
-TOL = 2e-2
 SHIM = """
-#include "la_batch_plan.h"
 extern "C" int per_xcd(int units) { return la::step_units_per_xcd(units); }
 extern "C" int cuts(int units, int chunks) { return la::step_cuts(units, chunks); }
 extern "C" int even(int units, int chunks) { return la::step_cuts_even(units, chunks); }
@@ -27,10 +22,7 @@ extern "C" int ranges(int units, int chunks, int rows, int head_dim, int fp32)
 
 
 def test_the_ranges_of_a_row_block_are_on_one_xcd(tmp_path):
-    (tmp_path / "shim.cpp").write_text(SHIM)
-    subprocess.run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-Wall", "-Werror", "-fPIC", "-shared", "-I", buildlib.CSRC,
-                    str(tmp_path / "shim.cpp"), "-o", str(tmp_path / "shim.so")], check=True)
-    lib = ctypes.CDLL(str(tmp_path / "shim.so"))
+    lib = planner(tmp_path, SHIM)
     for units in list(range(1, 130)) + [255, 256, 257, 1000]:
         for chunks in (1, 2, 3, 7, 30, 129, 1000):
             x, most = lib.cuts(units, chunks), lib.per_xcd(units)
@@ -57,6 +49,16 @@ def test_the_ranges_of_a_row_block_are_on_one_xcd(tmp_path):
     assert lib.rows128(66, 31, 4) and lib.rows128(514, 31, 2)              # cut 8 times; to 33 chunks
     assert lib.ranges(8, 66, 64, 128, 0) == -11 and lib.ranges(8, 18, 64, 128, 0) == 9 and lib.ranges(8, 258, 64, 128, 0) == 32
 
+    def fewer(units, rows, d):                          # numbers of chunks at which a step that always had bf16 takes fewer in fp32
+        return [c for c in range(1, 1000) if lib.ranges(units, c, rows, d, 0) < 0]
+    for units in (1, 3, 8):
+        assert fewer(units, 64, 128) == [53, 57, 59, 61, 63] + list(range(65, 73))
+        assert fewer(units, 32, 128) == [59, 63] + list(range(65, 71))
+        assert fewer(units, 64, 64) == fewer(units, 32, 64) == \
+            list(range(33, 50, 2)) + list(range(51, 91)) + list(range(97, 111)) + list(range(129, 133))
+    for units in range(9, 130):
+        assert fewer(units, 64, 128) == fewer(units, 32, 128) == [] and fewer(units, 64, 64) == ([33] if units <= 16 else [])
+
 
 SHAPES = [(700, 5, 4, 5, 4, 4, 128),       # 4 row blocks of 32 rows, 5 ranges each
           (2500, 20, 5, 20, 4, 4, 128),    # 12 of 64 rows, 16
@@ -65,30 +67,18 @@ SHAPES = [(700, 5, 4, 5, 4, 4, 128),       # 4 row blocks of 32 rows, 5 ranges e
           (2500, 20, 5, 20, 4, 4, 64),
           (300, 15, 5, 15, 50, 50, 128)]   # 100, 2
 FEWER = [(4096, 15, 5, 15, 4, 4, 128),     # 8 row blocks: 11 ranges in fp32, 32 in bf16 before
-         (3900, 3, 4, 1, 32, 8, 128),
+         (3580, 3, 4, 1, 32, 8, 128),      # 8 of 64 rows, 57 chunks: 10 in fp32, 28 in bf16 before
          (4096, 15, 5, 15, 4, 4, 64),
          (4096, 15, 5, 15, 8, 1, 128),     # 16 of 64 rows, 8 of 128 before
          (4096, 16, 5, 15, 16, 2, 128)]
 
 
-def new_like(q):
-    return torch.full_like(q, float("nan"))
-
-
-def error(out, want):
-    got = out.float().cpu().numpy().astype(np.float64)
-    assert np.isfinite(got).all() and np.abs(got - want).max() <= TOL
-    return float(np.linalg.norm(got - want) / np.linalg.norm(want))
-
-
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "P%d-W%d-%d/%d-d%d" % (s[0], s[1], s[4], s[5], s[6]))
+@pytest.mark.parametrize("shape", SHAPES, ids=label)
 def test_every_entry_point_agrees_and_none_is_further_off(shape, override):
     print("case", shape, flush=True)
     P, W, N, G, H, KV, d = shape
-    T, rng = 1 + (W + G) * (N - 1), np.random.default_rng(P)
-    x = {k: wl.f32_to_bf16_bits(rng.standard_normal(size=s, dtype=np.float32))
-         for k, s in dict(q=(T, H, d), k_cache=(KV, P, d), v_cache=(KV, P, d), step_k=(T, KV, d), step_v=(T, KV, d)).items()}
+    T, x = 1 + (W + G) * (N - 1), inputs(shape, P)
     dev = {k: binding.bf16_tensor(v) for k, v in x.items()}
     q, cache, args = dev["q"], (dev["k_cache"], dev["v_cache"]), (dev["step_k"], dev["step_v"], P, W, N, G, H, KV, d)
     override("attn_rowtile", "0")
@@ -113,42 +103,87 @@ def test_every_entry_point_agrees_and_none_is_further_off(shape, override):
     assert torch.equal(out, binding.la_step_attention_rows(q, *cache, dev["step_k"], dev["step_v"], ids, *args[2:], new_like(q)))
     cos = torch.ones(P + W + N, d // 2, device="cuda")
     assert torch.equal(out, binding.la_step_attention_rope(q, *cache, dev["step_k"], dev["step_v"], cos, torch.zeros_like(cos), *args[2:], new_like(q)))
-    # groups spread over XCDs are computed again, over all keys and without partial results: that is no nearer
+    # groups spread over XCDs are computed again, over all keys and without partial results: none here is, and that is no nearer
     override("force_recompute", "1")
-    assert err <= error(binding.la_step_attention(q, *cache, *args, new_like(q)), want)
+    again = binding.la_step_attention(q, *cache, *args, new_like(q))
+    assert every_tile_differs(out, again, KV) and err <= error(again, want)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", FEWER, ids=lambda s: "P%d-W%d-%d/%d-d%d" % (s[0], s[1], s[4], s[5], s[6]))
+@pytest.mark.parametrize("shape", FEWER, ids=label)
 def test_fewer_ranges_are_no_further_off_than_all(shape, override):
     print("case", shape, flush=True)
     P, W, N, G, H, KV, d = shape
-    T, rng = 1 + (W + G) * (N - 1), np.random.default_rng(P)
-    x = [wl.f32_to_bf16_bits(rng.standard_normal(size=s, dtype=np.float32)) for s in ((T, H, d), (KV, P, d), (KV, P, d), (T, KV, d), (T, KV, d))]
+    x = list(inputs(shape, P).values())
     dev = [binding.bf16_tensor(v) for v in x]
     want = orc.step_attention(*x, P, W, N, G, H, KV, d)
     out = binding.la_step_attention(*dev, P, W, N, G, H, KV, d, new_like(dev[0]))
     assert torch.equal(out, binding.la_step_attention_noalloc(*dev, P, W, N, G, H, KV, d, new_like(dev[0])))
-    override("attn_plan", "4,2,0,4,64" if T * H // KV > 480 else "2,4,0,4,64" if d == 128 else "2,2,0,4,64")
-    assert error(out, want) <= error(binding.la_step_attention(*dev, P, W, N, G, H, KV, d, new_like(dev[0])), want)
+    rows = len(x[0]) * H // KV
+    override("attn_plan", "4,2,0,4,64" if rows > 480 else "1,2,0,4,64" if rows <= 32 else "2,4,0,4,64" if d == 128 else "2,2,0,4,64")
+    before = binding.la_step_attention(*dev, P, W, N, G, H, KV, d, new_like(dev[0]))
+    assert every_tile_differs(out, before, KV) and error(out, want) <= error(before, want)
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape", SHAPES[:5:2], ids=lambda s: "P%d-W%d-%d/%d-d%d" % (s[0], s[1], s[4], s[5], s[6]))
+@pytest.mark.parametrize("shape", SHAPES[:5:2], ids=label)
 def test_quantised_cache(shape, override):
     print("case", shape, flush=True)
-    P, W, N, G, H, KV, d = shape
-    T, gen = 1 + (W + G) * (N - 1), torch.Generator(device="cuda").manual_seed(P)
-
-    def codes(*s):
-        return torch.randn(s, device="cuda", generator=gen).mul_(112).clamp_(-448, 448).to(torch.float8_e4m3fn).view(torch.uint8)
-    q = torch.randn(T, H, d, device="cuda", generator=gen).bfloat16()
-    kc, vc, sk, sv = codes(KV, P, d), codes(KV, P, d), codes(T, KV, d), codes(T, KV, d)
-    scale = torch.full((2, KV), 4 / 448, device="cuda") * (0.75 + 0.5 * torch.rand(2, KV, device="cuda", generator=gen))
-    want = orc.step_attention_fp8kv(binding.bf16_bits(q), *(t.cpu().numpy() for t in (kc, vc, sk, sv)), scale[0].cpu().numpy(),
-                                    scale[1].cpu().numpy(), P, W, N, G, H, KV, d)
-    errors = []
+    q, codes, scale = codes_inputs(shape, shape[0])
+    want = orc.step_attention_fp8kv(binding.bf16_bits(q), *(t.cpu().numpy() for t in codes), scale[0].cpu().numpy(),
+                                    scale[1].cpu().numpy(), *shape)
+    outs = []
     for again in (None, "1"):
         override("force_recompute", again)
-        errors.append(error(binding.la_step_attention_fp8kv(q, kc, vc, sk, sv, scale[0], scale[1], P, W, N, G, H, KV, d, new_like(q)), want))
-    assert errors[0] <= errors[1]
+        outs.append(binding.la_step_attention_fp8kv(q, *codes, scale[0], scale[1], *shape, new_like(q)))
+    assert every_tile_differs(*outs, shape[5]) and error(outs[0], want) <= error(outs[1], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape", SHAPES + FEWER[:3], ids=label)
+def test_true_subsets_of_the_rows(shape, override):
+    """Some of the rows, in another order: none is computed again over all keys."""
+    print("case", shape, flush=True)
+    P, W, N, G, H, KV, d = shape
+    x, rng = inputs(shape, P), np.random.default_rng(P + 1)
+    T = len(x["q"])
+    ids = np.concatenate([[0], 1 + rng.permutation(T - 1)[:T * 3 // 4]])
+    q, sk, sv = (binding.bf16_tensor(x[k][ids]) for k in ("q", "step_k", "step_v"))
+    kc, vc, on_gpu = binding.bf16_tensor(x["k_cache"]), binding.bf16_tensor(x["v_cache"]), torch.from_numpy(ids.astype(np.int32)).cuda()
+    want = orc.step_attention_rows(x["q"][ids], x["k_cache"], x["v_cache"], x["step_k"][ids], x["step_v"][ids], ids, P, W, N, G, H, KV, d)
+
+    def run():
+        return binding.la_step_attention_rows(q, kc, vc, sk, sv, on_gpu, P, W, N, G, H, KV, d, new_like(q))
+    out = run()
+    error(out, want)
+    override("force_recompute", "1")
+    assert every_tile_differs(out, run(), KV)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("interleaved", [False, True])
+@pytest.mark.parametrize("shape", SHAPES + FEWER[:3], ids=label)
+def test_rotations(shape, interleaved, override):
+    """Query rows and step keys rotated inside the attention have the bits of both rotated in memory first."""
+    print("case", shape, flush=True)
+    P, W, N, G, H, KV, d = shape
+    x = inputs(shape, P)
+    dev = {k: binding.bf16_tensor(v) for k, v in x.items()}
+    cos, sin = wl.rope_tables(P + W + N, d)
+    tables = torch.from_numpy(cos).cuda(), torch.from_numpy(sin).cuda()
+    sizes = P, W, N, G, H, KV, d
+    override("attn_rowtile", "0")
+    q2, k2 = dev["q"].clone(), dev["step_k"].clone()
+    binding.la_step_rope(q2, k2, *tables, *sizes, interleaved)
+    two = binding.la_step_attention(q2, dev["k_cache"], dev["v_cache"], k2, dev["step_v"], *sizes, new_like(q2))
+
+    def run():
+        return binding.la_step_attention_rope(dev["q"], dev["k_cache"], dev["v_cache"], dev["step_k"], dev["step_v"], *tables, *sizes,
+                                              new_like(q2), interleaved, rotate_keys=True)
+    out = run()
+    assert torch.equal(out, two)
+    rq, rk = orc.step_rope(orc.bf16_to_f64(x["q"]), orc.bf16_to_f64(x["step_k"]), cos, sin, P, W, N, G, interleaved)
+    error(out, orc.step_attention(wl.f32_to_bf16_bits(rq.astype(np.float32)), x["k_cache"], x["v_cache"],
+                                  wl.f32_to_bf16_bits(rk.astype(np.float32)), x["step_v"], *sizes))
+    override("force_recompute", "1")
+    assert every_tile_differs(out, run(), KV)
