@@ -27,9 +27,9 @@
 // (row, key block) from integer ranges in registers; no mask tensor exists anywhere.
 //
 // Split combine, in the same launch, wave by wave.  With XS > 1 each wave stores the slice(s)
-// of the unnormalised accumulator it owns after the key-split merge, rounded to bf16, and
-// (max, sum) per row, waits for the stores to be acknowledged by the L2, and takes a ticket of
-// its own; the wave that arrives last in its group merges all XS partials in index order (so
+// of the unnormalised accumulator it owns after the key-split merge, rounded to bf16 or in
+// fp32 (make_plan says which steps), and (max, sum) per row, waits for the stores to be
+// acknowledged by the L2, and takes a ticket of its own; the wave that arrives last in its group merges all XS partials in index order (so
 // results do not depend on arrival order), normalises and writes bf16.  The L2 of one XCD is
 // coherent for all its compute units, but the eight L2s are not coherent with each other
 // inside a kernel, and an agent-scope fence (L2 write-back + invalidate) costs tens of
@@ -38,9 +38,9 @@
 // from the hardware register: if all ids agree the partials are read straight from the shared
 // L2; if not, the last wave ignores the partials and its workgroup recomputes its rows over
 // all chunks from the read-only inputs and writes them directly.  The two paths agree to the
-// bf16 rounding of the partials, not bit for bit (the recomputed accumulator is never rounded),
-// so a result can differ in the last place with where the workgroups happened to run; both are
-// within the tolerance of the step.  Tickets return to zero, so no memset is needed between
+// rounding of partials and probabilities, not bit for bit (the recomputed accumulator is never
+// rounded, and a range has a maximum of its own), so a result can differ in the last place with
+// where the workgroups happened to run; both are within the tolerance of the step.  Tickets return to zero, so no memset is needed between
 // calls.
 //
 // Variants of the same kernel (template parameters): a paged cache (block table), a subset of
@@ -103,7 +103,7 @@ struct AttnParams {
     int rope_block;        // LDS bytes reserved per table (rope_rows * head_dim * 2 rounded up to 1 KB)
     int rope_flags;  // bit 0: pairing of the rotation, 0 (x[i], x[i + d/2]), 1 (x[2i], x[2i + 1]);
                      // bit 1: the step keys are rotated in the kernel as well
-    void* partials;     // XS > 1: per workgroup and wave, fragment-layout bf16 slices and fp32 (m, l)
+    void* partials;     // XS > 1: per workgroup and wave, fragment-layout slices (bf16 or fp32) and fp32 (m, l)
     unsigned* tickets;  // XS > 1: one counter (kTicketStride words apart) per (KV head, row block, wave), zero between calls
     int P, W, N, G, T;
     long long cache_rows;  // rows between the caches of consecutive KV heads (>= P; paged: the page size)
@@ -1252,7 +1252,7 @@ struct Plan {
     size_t partial_bytes_per_wg;
 };
 
-// Bytes of one workgroup's partial (Cfg::PART_WG_BYTES): per wave its slices as bf16 and (m, l).
+// Bytes of one workgroup's partial (Cfg::PART_WG_BYTES): per wave its slices, `bytes` a value, and (m, l).
 size_t partial_wg_bytes(int D, int RT, int KS, int bytes = 2)
 {
     const int DB = D / 32, SPW = KS > 1 ? DB / KS : DB;
@@ -1716,8 +1716,8 @@ la_status launch_step_attention_batch(const BatchSeq* seqs, int n_seqs, int page
     for (int first = 0; first < n_seqs; first += kMaxBatch) {
         const int n = n_seqs - first < kMaxBatch ? n_seqs - first : kMaxBatch;
         // Nothing to share a launch with: the one-step path and its own decomposition, at every length.  (The pipelined
-        // kernel beside it, us: 64/8 heads, 57 rows 14.2 and 27.2 on 2048 keys, 31.2 and 33.7 on 8192, 53.0 and 47.8 on
-        // 16384; 32/8 heads, 121 rows 14.0 and 27.3, 33.5 and 34.8, 54.4 and 49.0.  One-step calls do not reserve
+        // kernel beside it, us: 64/8 heads, 57 rows 12.9 and 27.2 on 2048 keys, 30.9 and 33.7 on 8192, 52.0 and 47.8 on
+        // 16384; 32/8 heads, 121 rows 12.7 and 27.3, 32.3 and 34.8, 52.5 and 49.0.  One-step calls do not reserve
         // its partial results.)
         if (n == 1) {
             const BatchSeq& d = seqs[order[first]];

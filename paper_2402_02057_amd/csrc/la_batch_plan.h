@@ -431,8 +431,11 @@ inline bool step_cuts_even(int units, int chunks)
 // takes 0.55 to 0.80 (64 rows of 128 dimensions in pairs of chunks, one tile, 64 dimensions; 13 to 361 rows on 1024 to
 // 16384 keys).  Fewer ranges in bf16 would be further from 64 bits (4/4 heads, 121 rows on 4096 keys: 2.98e-3 with 32 ranges,
 // 3.11e-3 with 12), in fp32 they are nearer (2.64e-3): so fewer are taken where the results are fp32 anyway or that is half a
-// microsecond ahead in fp32 too, which is from 45 to 80 chunks where 32 ranges fit.  4/4 heads 14.8 -> 13.6 us, 8/1, 57 rows
-// 15.3 -> 12.0, 32/8, 13 rows 15.1 -> 13.8, 4/4 with 64 dimensions 11.0 -> 10.1, 4/4, 31 rows (fp32 before) 16.7 -> 13.2.
+// microsecond ahead in fp32 too.  Where 32 ranges fit (8 row blocks at most) that is at 65 to 72 chunks and at 53, 57, 59, 61 and 63
+// (an odd number leaves the most ranges three chunks, walked as four) with 64 rows of 128 dimensions, at 65 to 70, 59 and 63 with one
+// tile, and with 64 dimensions at 51 to 90, 97 to 110, 129 to 132 and odd numbers from 33 to 49; where 16 fit, at 33 with 64
+// dimensions alone.  4/4 heads 14.8 -> 13.6 us, 8/1, 57 rows 15.3 -> 12.0, 32/8, 13 rows 15.1 -> 13.8 (all on 4096 keys), 4/4
+// with 64 dimensions 11.0 -> 10.1, 4/4, 31 rows (fp32 before) 16.7 -> 13.2.
 struct StepRanges {
     int x;
     bool fp32;

@@ -82,7 +82,7 @@ def test_two_calls_second_smaller():
 
 def test_refuses_what_does_not_fit(override):
     """A decomposition whose partials exceed the fixed block is refused before anything is launched
-    (the library's own choice never needs more than 5 MiB; a 64-way split forced by hand does).
+    (the library's own choice always fits; a 64-way split forced by hand does not).
     The buffers are real and of the right size all the same."""
     torch.cuda.set_device(0)
     override("attn_plan", "2,4,64,4,64")
