@@ -475,6 +475,9 @@ la_status la_step_attention_noalloc(const void* q, const void* k_cache, const vo
  *                                            applies) / off; NULL = the library's choice
  *   "batch_plan"       (LA_BATCH_PLAN)       32-row tiles per workgroup of a batched launch: "2" or "4"
  *                                            (staged kernel), "8" (pipelined kernel, where it applies)
+ *   "exchange_looks"   (no variable)         how often a wave of a step alone that is to add up the ranges of
+ *                                            its rows looks whether they are done before it leaves that
+ *                                            to the last of them ("0": always the last); NULL = the library's
  *   "force_recompute"  (LA_FORCE_RECOMPUTE)  "1": treat every split group as spread over several
  *                                            XCDs, so that the recompute path runs
  * Returns LA_EINVAL for an unknown key or a malformed plan.

@@ -29,7 +29,7 @@
 // Split combine, in the same launch, wave by wave.  With XS > 1 each wave stores the slice(s)
 // of the unnormalised accumulator it owns after the key-split merge, rounded to bf16 or in
 // fp32 (make_plan says which steps), and (max, sum) per row, waits for the stores to be
-// acknowledged by the L2, and takes a ticket of its own; the wave that arrives last in its group merges all XS partials in index order (so
+// acknowledged by the L2, and takes a ticket of its own; one wave of its group merges all XS partials in index order (so
 // results do not depend on arrival order), normalises and writes bf16.  The L2 of one XCD is
 // coherent for all its compute units, but the eight L2s are not coherent with each other
 // inside a kernel, and an agent-scope fence (L2 write-back + invalidate) costs tens of
@@ -49,6 +49,7 @@
 // way in (rotary embedding).
 #include <stdlib.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 #include <string>
@@ -70,6 +71,12 @@ namespace {
 // Tickets of different waves sit in different 128-byte lines: atomics on one line are served one
 // after the other by the L2 (eight counters side by side cost a microsecond at the 7B shape).
 constexpr int kTicketStride = 32;  // in 4-byte words
+// A ticket: arrivals so far (bits 0 .. 6), whether the wave that was to add them up has left (bit 7), the
+// sum of the arrivals' XCD ids (8 .. 17) and of their squares (18 .. 31).
+constexpr unsigned kTicketLeft = 1u << 7, kTicketArrivals = kTicketLeft - 1u;
+// How often that wave looks before it leaves: some 10 us, several times what the ranges of a step alone lie
+// apart where they run side by side.
+constexpr int kExchangeLooks = 32;
 
 struct AttnParams {
     const __bf16* q;
@@ -127,7 +134,8 @@ struct AttnParams {
     float inv_XS, inv_row_blocks, inv_group, inv_W, inv_n1;
     int chunks_lo, chunks_rem;  // n_chunks = XS * chunks_lo + chunks_rem
     int pre;              // chunks requested before the loop starts (1 .. stages)
-    int force_recompute;  // testing: treat every group as spread over several XCDs
+    short force_recompute;  // testing: treat every group as spread over several XCDs
+    unsigned short looks;   // XS > 1: how often the wave that adds up looks whether the others have arrived (0: the last one adds up)
 };
 
 // Row-subset variant: the pairwise rule of Sec. 3.3 (the closed-form words above assume consecutive step
@@ -972,9 +980,19 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 
         // ---- split combine, wave by wave (no workgroup barrier): a wave stores its slices with its
         //      rows' (m, l), waits for the L2 of this XCD to acknowledge the stores and takes a ticket
-        //      of its own; the wave that arrives last in its group merges the XS partials of these
-        //      slices in index order (so results do not depend on arrival order)
+        //      of its own; one wave of its group merges the XS partials of these slices in index order (so
+        //      results do not depend on arrival order).
+        //      Which one: wave w of range w % XS, so that every compute unit of the group reads a share of the partial
+        //      results.  Left to the wave that arrives last, one compute unit, whose waves end together, reads all of
+        //      them, at about 100 GB/s: XS * 18 KB of 64 rows, twice that of 128 (40/40 heads, 81 rows on 2048
+        //      keys 17.5 -> 17.1 us, with 128 rows and 6 ranges 18.5 -> 16.9; 64/8, 57 rows on 4096 with 128 rows and 8
+        //      ranges 19.4 -> 17.7; 4/4, 121 rows on 4096 13.8 -> 12.5).  Smaller shares (halves of a slice, twice the
+        //      waves that wait) gain from 16 ranges on and cost 0.6 us with four.
+        //      It looks at its ticket until the others have arrived, `looks` times at most: the ranges of a step alone
+        //      run side by side, but nothing promises it.  Then it sets a bit in the ticket and leaves, and
+        //      the last one to arrive, who finds it set, merges.
         if (wave_active) {
+            const bool adds_up = wave - __builtin_amdgcn_readfirstlane(div_small(wave, p.inv_XS)) * p.XS == xs;
             unsigned char* const group_base = reinterpret_cast<unsigned char*>(p.partials) +
                                               (size_t)unit * p.XS * C::PART_WG_BYTES + (size_t)wave * C::PART_WAVE_BYTES;
             {
@@ -994,85 +1012,99 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
             }
             __builtin_amdgcn_s_waitcnt(0);
             LA_STAMP(5);
-            unsigned role = 0;  // 0 not last, 1 last and co-located, 2 last but spread over several XCDs
+            unsigned role = 0;  // 0 another wave merges, 1 this one, 2 this one, but the group is spread over several XCDs
             if (lane == 0) {
                 // One atomic carries the arrival count and, to tell whether every member of the group
                 // ran on the same XCD (and so shares one L2), the sum and the sum of squares of the
                 // members' XCD ids: XS * sum(x^2) == (sum x)^2 holds iff all ids are equal.
                 const unsigned x = xcc_id();
                 const unsigned mine = 1u | (x << 8) | ((x * x) << 18);
-                const unsigned total = atomicAdd(my_ticket, mine) + mine;
-                const unsigned cnt = total & 0xffu, sum = (total >> 8) & 0x3ffu, sq = total >> 18;
-                if (cnt == (unsigned)p.XS) {
-                    *my_ticket = 0u;  // everyone has arrived; clean for the next call
+                unsigned total = atomicAdd(my_ticket, mine) + mine;
+                auto all_in = [&] { return (total & kTicketArrivals) == (unsigned)p.XS; };
+                bool merge = all_in();
+                if (p.looks) {
+                    if (merge) {
+                        merge = adds_up || (total & kTicketLeft);
+                    } else if (adds_up) {
+                        for (int i = p.looks; i > 0 && !all_in(); --i) total = __hip_atomic_load(my_ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        if (!all_in()) total = atomicAdd(my_ticket, kTicketLeft);
+                        merge = all_in();
+                    }
+                }
+                if (merge) {
+                    const unsigned sum = (total >> 8) & 0x3ffu, sq = total >> 18;
+                    *my_ticket = 0u;  // nobody looks at it any more; clean for the next call
                     role = (sq * (unsigned)p.XS == sum * sum && !p.force_recompute) ? 1u : 2u;
                 }
             }
             role = __builtin_amdgcn_readfirstlane(role);
             LA_STAMP(6);
             if (role == 1) {
-                // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2 (fp32: two)
-                constexpr int MB = 8 / PB;
-                float m_acc = kNegInf, l_acc = 0.0f;
-                float acc[C::SPW][16];
+                // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2 (in fp32 one slice at a
+                //      time, for the registers; two splits a trip took 0.6 to 1.2 us longer with 11 ranges)
+                constexpr int MB = 4, US = PB == 2 ? C::SPW : 1;
+                for (int u0 = 0; u0 < C::SPW; u0 += US) {
+                    float m_acc = kNegInf, l_acc = 0.0f;
+                    float acc[US][16];
 #pragma unroll
-                for (int u = 0; u < C::SPW; ++u)
+                    for (int u = 0; u < US; ++u)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
-                for (int s0 = 0; s0 < p.XS; s0 += MB) {
-                    f32x2 ml[MB];
-                    Part v[MB][C::SPW][PB];
+                        for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
+                    for (int s0 = 0; s0 < p.XS; s0 += MB) {
+                        f32x2 ml[MB];
+                        Part v[MB][US][PB];
 #pragma unroll
-                    for (int w = 0; w < MB; ++w) {
-                        const int s2 = min(s0 + w, p.XS - 1);
-                        const unsigned char* src = group_base + (size_t)s2 * C::PART_WG_BYTES;
-                        ml[w] = *reinterpret_cast<const f32x2*>(src + C::PART_ACC_BYTES + lane * 8);
+                        for (int w = 0; w < MB; ++w) {
+                            const int s2 = min(s0 + w, p.XS - 1);
+                            const unsigned char* src = group_base + (size_t)s2 * C::PART_WG_BYTES;
+                            ml[w] = *reinterpret_cast<const f32x2*>(src + C::PART_ACC_BYTES + lane * 8);
 #pragma unroll
-                        for (int u = 0; u < C::SPW; ++u)
+                            for (int u = 0; u < US; ++u)
 #pragma unroll
-                            for (int i = 0; i < PB; ++i)
-                                v[w][u][i] = *reinterpret_cast<const Part*>(src + ((u * PB + i) * 64 + lane) * 16);
+                                for (int i = 0; i < PB; ++i)
+                                    v[w][u][i] = *reinterpret_cast<const Part*>(src + (((u0 + u) * PB + i) * 64 + lane) * 16);
+                        }
+                        LA_STAMP(18);
+                        // batch maximum, then one weight per split: acc = acc * a0 + sum_w v_w * a_w
+                        float mb = m_acc;
+#pragma unroll
+                        for (int w = 0; w < MB; ++w)
+                            if (s0 + w < p.XS) mb = fmaxf(mb, ml[w][0]);
+                        const float m_use = (mb == kNegInf) ? 0.0f : mb;
+                        const float a0 = fast_exp2((m_acc - m_use) * sl2);
+                        l_acc *= a0;
+                        if (s0 > 0) {
+#pragma unroll
+                            for (int u = 0; u < US; ++u)
+#pragma unroll
+                                for (int i = 0; i < 16; ++i) acc[u][i] *= a0;
+                        }
+                        m_acc = mb;
+#pragma unroll
+                        for (int w = 0; w < MB; ++w) {
+                            const float aw = s0 + w < p.XS ? fast_exp2((ml[w][0] - m_use) * sl2) : 0.0f;
+                            l_acc = __builtin_fmaf(ml[w][1], aw, l_acc);
+#pragma unroll
+                            for (int u = 0; u < US; ++u)
+#pragma unroll
+                                for (int i = 0; i < PB; ++i)
+#pragma unroll
+                                    for (int e = 0; e < PE; ++e)
+                                        acc[u][i * PE + e] = __builtin_fmaf((float)v[w][u][i][e], aw, acc[u][i * PE + e]);
+                        }
                     }
-                    LA_STAMP(18);
-                    // batch maximum, then one weight per split: acc = acc * a0 + sum_w v_w * a_w
-                    float mb = m_acc;
+                    const float inv = out_scale / l_acc;
 #pragma unroll
-                    for (int w = 0; w < MB; ++w)
-                        if (s0 + w < p.XS) mb = fmaxf(mb, ml[w][0]);
-                    const float m_use = (mb == kNegInf) ? 0.0f : mb;
-                    const float a0 = fast_exp2((m_acc - m_use) * sl2);
-                    l_acc *= a0;
-                    if (s0 > 0) {
+                    for (int u = 0; u < US; ++u) {
+                        f32x16 vals;
 #pragma unroll
-                        for (int u = 0; u < C::SPW; ++u)
-#pragma unroll
-                            for (int i = 0; i < 16; ++i) acc[u][i] *= a0;
+                        for (int i = 0; i < 16; ++i) vals[i] = acc[u][i];
+                        store_slice<C>(p, row_base, kvh, db0 + u0 + u, l32, hi, vals, inv);
                     }
-                    m_acc = mb;
-#pragma unroll
-                    for (int w = 0; w < MB; ++w) {
-                        const float aw = s0 + w < p.XS ? fast_exp2((ml[w][0] - m_use) * sl2) : 0.0f;
-                        l_acc = __builtin_fmaf(ml[w][1], aw, l_acc);
-#pragma unroll
-                        for (int u = 0; u < C::SPW; ++u)
-#pragma unroll
-                            for (int i = 0; i < PB; ++i)
-#pragma unroll
-                                for (int e = 0; e < PE; ++e)
-                                    acc[u][i * PE + e] = __builtin_fmaf((float)v[w][u][i][e], aw, acc[u][i * PE + e]);
-                    }
-                }
-                const float inv = out_scale / l_acc;
-#pragma unroll
-                for (int u = 0; u < C::SPW; ++u) {
-                    f32x16 vals;
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) vals[i] = acc[u][i];
-                    store_slice<C>(p, row_base, kvh, db0 + u, l32, hi, vals, inv);
                 }
                 LA_STAMP(7);
             }
-            // ---- a wave that arrived last in a group spread over several XCDs, whose L2s are not
+            // ---- a wave that merges for a group spread over several XCDs, whose L2s are not
             //      coherent with each other inside a kernel, cannot trust the partials: the whole
             //      workgroup then recomputes its rows over every chunk from the read-only inputs (which
             //      are always coherent), and the waves that asked for it write their slices directly
@@ -1190,6 +1222,7 @@ struct Overrides {
     int plan[6] = {0, 0, 0, 0, 0, 0};  // RT, KS, XS, NS, KC, PRE (XS = 0, PRE = 0: heuristic)
     int batch_rows = 0;                // form of a batched launch (LaunchPlan::rows; 0: heuristic)
     int rowtile = -1;                  // 1 / 0: the kernel without partials forced on / off (-1: heuristic)
+    int exchange_looks = -1;           // AttnParams::looks of a step alone (-1: kExchangeLooks)
     bool force_recompute = false;
 };
 std::mutex g_config_mutex;  // the overrides, and the once-per-device kernel attributes
@@ -1463,6 +1496,7 @@ la_status build_params(AttnParams& prm, const Overrides& ov, const Plan& pl, con
     if (pl.PRE == 0 && cpi == 2 && prm.chunks_lo <= 6) prm.pre = cpi;
     // testing hook: exercise the path taken when a split group is not on one XCD
     prm.force_recompute = ov.force_recompute ? 1 : 0;
+    prm.looks = 0;  // (workgroups of a batch that take turns on the compute units do not wait for each other)
     return LA_OK;
 }
 
@@ -1526,6 +1560,7 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
     if (st != LA_OK) return st;
     const long long total = prm.total_wg;
     if (pl.XS > 1) prm.wg_per_xcd = step_units_per_xcd(kv_heads * pl.n_row_blocks) * pl.XS;
+    if (pl.XS > 1) prm.looks = (unsigned short)(ov.exchange_looks >= 0 ? ov.exchange_looks : kExchangeLooks);
     const bool quantised = k_scale != nullptr;
     if (quantised) {
         // 8-bit keys and values: rows of head_dim bytes (cache_rows counts rows, so it stands)
@@ -1819,6 +1854,8 @@ la_status set_override(const char* key, const char* value)
         g_overrides.batch_rows = parse_batch_form(value);
     } else if (k == "attn_rowtile") {
         g_overrides.rowtile = (value && (value[0] == '0' || value[0] == '1')) ? value[0] - '0' : -1;
+    } else if (k == "exchange_looks") {
+        g_overrides.exchange_looks = value && value[0] >= '0' && value[0] <= '9' ? std::min(atoi(value), 65535) : -1;
     } else if (k == "force_recompute") {
         g_overrides.force_recompute = value && value[0] == '1';
     } else {
