@@ -77,13 +77,41 @@ constexpr unsigned kTicketLeft = 1u << 7, kTicketArrivals = kTicketLeft - 1u;
 // How often that wave looks before it leaves: some 10 us, several times what the ranges of a step alone lie
 // apart where they run side by side.
 constexpr int kExchangeLooks = 32;
+// Bytes of a row block's results up to which the last wave to arrive adds up all the same: one compute unit reads them in
+// half a microsecond, which is what the waiting wave takes to see that they are there.  8-bit cache, 40/40 heads, 25 rows on
+// 445 keys (36 KB) 7.29 us, 7.43 if a wave waits; 64 dimensions, 32/8 heads, 121 rows on 223 (30 KB) 6.78 and 6.84.  40/40, 81
+// rows on 2048 (54 KB) 17.70 and 17.24, 8-bit 13.99 and 13.72.
+constexpr int kExchangeAlone = 48 * 1024;
+constexpr unsigned kForceRecompute = 1u << 16;  // of AttnParams::looks
 
-struct AttnParams {
+// What leads to the first requests: read at once, into scalar registers (`warmed_arguments`).
+struct AttnHead {
     const __bf16* q;
     const __bf16* k_cache;
     const __bf16* v_cache;
     const __bf16* step_k;
     const __bf16* step_v;
+    long long cache_rows;  // rows between the caches of consecutive KV heads (>= P; paged: the page size)
+    int total_wg;         // kv_heads * n_row_blocks * XS
+    int wg_per_xcd;       // ceil(total_wg / 8), or more where that keeps the ranges of a row block on one XCD
+    // Integer division costs dozens of instructions, and a wave issues about one instruction
+    // every four cycles: quotients by these small divisors are taken with a float reciprocal
+    // (exact while the dividend stays below 2^21, which the host checks).
+    float inv_XS, inv_row_blocks, inv_group;
+    int XS;
+    int n_row_blocks;
+    int chunks_lo, chunks_rem;  // n_chunks = XS * chunks_lo + chunks_rem
+    int pre;              // chunks requested before the loop starts (1 .. stages)
+    int n_prefix_chunks;  // ceil(P / KC)
+    int P, T;
+    int heads, kv_heads, group;
+    int R;                // T * group query rows per KV head
+    int n_chunks;         // prefix chunks + step chunks
+    float scale_log2;     // log2(e) / sqrt(head_dim)
+    int W;
+};
+
+struct AttnParams : AttnHead {
     __bf16* out;
     // Two pointers whose meaning depends on the kernel variant (the variants exclude each other, and
     // the structure has to stay small: it travels as a kernel argument, sixteen at a time in a batch):
@@ -112,30 +140,17 @@ struct AttnParams {
                      // bit 1: the step keys are rotated in the kernel as well
     void* partials;     // XS > 1: per workgroup and wave, fragment-layout slices (bf16 or fp32) and fp32 (m, l)
     unsigned* tickets;  // XS > 1: one counter (kTicketStride words apart) per (KV head, row block, wave), zero between calls
-    int P, W, N, G, T;
-    long long cache_rows;  // rows between the caches of consecutive KV heads (>= P; paged: the page size)
+    int N, G;
     long long page_bytes;  // bytes of one page (all KV heads)
     int page_chunks;       // chunks per page
     int n_pages;           // table entries are clamped to 0 .. n_pages-1
     int table_last;        // last valid index of block_table
     float inv_page_chunks;
-    int heads, kv_heads, group;
-    int R;                // T * group query rows per KV head
-    int n_prefix_chunks;  // ceil(P / KC)
-    int n_chunks;         // prefix chunks + step chunks
-    int n_row_blocks;
-    int XS;
-    int total_wg;         // kv_heads * n_row_blocks * XS
-    int wg_per_xcd;       // ceil(total_wg / 8), or more where that keeps the ranges of a row block on one XCD
-    float scale_log2;     // log2(e) / sqrt(head_dim)
-    // Integer division costs dozens of instructions, and a wave issues about one instruction
-    // every four cycles: quotients by these small divisors are taken with a float reciprocal
-    // (exact while the dividend stays below 2^21, which the host checks).
-    float inv_XS, inv_row_blocks, inv_group, inv_W, inv_n1;
-    int chunks_lo, chunks_rem;  // n_chunks = XS * chunks_lo + chunks_rem
-    int pre;              // chunks requested before the loop starts (1 .. stages)
-    short force_recompute;  // testing: treat every group as spread over several XCDs
-    unsigned short looks;   // XS > 1: how often the wave that adds up looks whether the others have arrived (0: the last one adds up)
+    float inv_W, inv_n1;
+    // XS > 1: how often the wave that adds up looks whether the others have arrived (0: the last one adds up), and
+    // kForceRecompute (testing: treat every group as spread over several XCDs).  A whole word: halves come through a
+    // vector load, which takes a trip to memory.
+    unsigned looks;
 };
 
 // Row-subset variant: the pairwise rule of Sec. 3.3 (the closed-form words above assume consecutive step
@@ -357,7 +372,7 @@ __device__ __forceinline__ void merge_key_splits(unsigned char* area, int rt, in
 // runs on (its id modulo 8) and `slot` its index among the step's workgroups on that XCD.
 // PB: see Cfg.
 template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false, int PB = 2>
-__device__ __forceinline__ void step_attention_body(const AttnParams& p, const int xcd, const int slot)
+__device__ __forceinline__ void step_attention_body(const AttnParams& p, const AttnHead& head, const int xcd, const int slot)
 {
     using C = Cfg<D, RT, KS, KC, NSTAGE, KVB, PB>;
     static_assert(KVB == 2 || (KVB == 1 && !PAGED && !ROWSET), "the quantised cache is packed and takes whole steps");
@@ -371,14 +386,14 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     // Consecutive workgroup ids go round-robin over the 8 XCDs (each with its own L2); put
     // the workgroups that stream the same KV head on one XCD.
     LA_STAMP(0);
-    int logical = xcd * p.wg_per_xcd + slot;
-    if (logical >= p.total_wg) return;
+    int logical = xcd * head.wg_per_xcd + slot;
+    if (logical >= head.total_wg) return;
     // (the float arithmetic runs on the vector unit: tell the compiler the results are uniform,
     // or every loop and branch that depends on them is compiled as divergent control flow)
-    const int unit = __builtin_amdgcn_readfirstlane(div_small(logical, p.inv_XS));  // (kvh, rb) pair
-    const int xs = logical - unit * p.XS;
-    const int kvh = __builtin_amdgcn_readfirstlane(div_small(unit, p.inv_row_blocks));
-    const int rb = unit - kvh * p.n_row_blocks;
+    const int unit = __builtin_amdgcn_readfirstlane(div_small(logical, head.inv_XS));  // (kvh, rb) pair
+    const int xs = logical - unit * head.XS;
+    const int kvh = __builtin_amdgcn_readfirstlane(div_small(unit, head.inv_row_blocks));
+    const int rb = unit - kvh * head.n_row_blocks;
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -390,12 +405,12 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 
     const unsigned lds_base = lds_address(lds);
     const int row_base = rb * C::ROWS + rt * 32;  // first row of this wave (in R space)
-    const bool wave_active = row_base < p.R;     // else: only helps loading
+    const bool wave_active = row_base < head.R;     // else: only helps loading
 
     // ---- chunk range of this split
-    int c_begin = xs * p.chunks_lo + min(xs, p.chunks_rem);
-    int c_end = c_begin + p.chunks_lo + (xs < p.chunks_rem ? 1 : 0);
-    bool direct = p.XS == 1;  // this pass covers every key of the rows: write `out` directly
+    int c_begin = xs * head.chunks_lo + min(xs, head.chunks_rem);
+    int c_end = c_begin + head.chunks_lo + (xs < head.chunks_rem ? 1 : 0);
+    bool direct = head.XS == 1;  // this pass covers every key of the rows: write `out` directly
 
     // ---- load addressing.  A wave-load moves 1 KB: RPW = 64 / NCH consecutive rows of 16-byte
     // pieces.  The LDS side is linear; the swizzle is applied on the global side.  Wave-load j
@@ -413,12 +428,12 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     }
 
     // This KV head's part of the four key/value tensors (wave-uniform).
-    const unsigned char* const kc_head = reinterpret_cast<const unsigned char*>(p.k_cache) + (size_t)kvh * (size_t)p.cache_rows * C::RBYTES;
-    const unsigned char* const vc_head = reinterpret_cast<const unsigned char*>(p.v_cache) + (size_t)kvh * (size_t)p.cache_rows * C::RBYTES;
-    const unsigned char* const sk_head = reinterpret_cast<const unsigned char*>(p.step_k) + (size_t)kvh * C::RBYTES;
-    const unsigned char* const sv_head = reinterpret_cast<const unsigned char*>(p.step_v) + (size_t)kvh * C::RBYTES;
-    const unsigned step_stride = (unsigned)(p.kv_heads * C::RBYTES);  // step keys are strided by kv_heads
-    const int n_prefix_chunks = p.n_prefix_chunks, n_P = p.P, n_T = p.T;
+    const unsigned char* const kc_head = reinterpret_cast<const unsigned char*>(head.k_cache) + (size_t)kvh * (size_t)head.cache_rows * C::RBYTES;
+    const unsigned char* const vc_head = reinterpret_cast<const unsigned char*>(head.v_cache) + (size_t)kvh * (size_t)head.cache_rows * C::RBYTES;
+    const unsigned char* const sk_head = reinterpret_cast<const unsigned char*>(head.step_k) + (size_t)kvh * C::RBYTES;
+    const unsigned char* const sv_head = reinterpret_cast<const unsigned char*>(head.step_v) + (size_t)kvh * C::RBYTES;
+    const unsigned step_stride = (unsigned)(head.kv_heads * C::RBYTES);  // step keys are strided by kv_heads
+    const int n_prefix_chunks = head.n_prefix_chunks, n_P = head.P, n_T = head.T;
 
     // ---- the stream of chunks to request, as running wave-uniform state: every scalar
     //      instruction in the loop is paid by all waves of the workgroup, so nothing is
@@ -545,11 +560,11 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
             const int wl = wave + i * C::NW;
             const int row = wl * (64 / C::QNCH) + lane / C::QNCH;
             const int lc = (lane % C::QNCH) ^ swizzle<D>(row);
-            const int rr = min(rb * C::ROWS + row, p.R - 1);
-            const int t = div_small(rr, p.inv_group), hh = rr - t * p.group;
+            const int rr = min(rb * C::ROWS + row, head.R - 1);
+            const int t = div_small(rr, head.inv_group), hh = rr - t * head.group;
             // (the host checks that q spans less than 2^31 bytes)
-            const unsigned off = (unsigned)(((t * p.heads + kvh * p.group + hh) * D + lc * 8) * 2);
-            dma16_base(p.q, off, lds_base + C::Q_OFFSET + wl * 1024);
+            const unsigned off = (unsigned)(((t * head.heads + kvh * head.group + hh) * D + lc * 8) * 2);
+            dma16_base(head.q, off, lds_base + C::Q_OFFSET + wl * 1024);
         }
         if constexpr (ROWSET) {  // the row ids travel with Q (entries past the end repeat the last one)
             static_assert(C::ROWSET_MAX % (C::NW * 64) == 0, "whole rounds of wave-loads");
@@ -566,7 +581,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     // factor the scores are multiplied with anyway; the value scale is applied to the finished rows.
     // (Read as constants, so that they come through the scalar cache and their wait is not a wait
     // for the loads requested below.)
-    float sl2 = p.scale_log2, out_scale = 1.0f;
+    float sl2 = head.scale_log2, out_scale = 1.0f;
     if constexpr (KVB == 1) {
         typedef const float __attribute__((address_space(4)))* const_f32;
         sl2 *= ((const_f32)(unsigned long long)p.k_scale)[kvh];
@@ -579,7 +594,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
     int issued = 0;               // chunks of this pass requested so far
     seek(c_begin);
     auto issue_first = [&](bool with_q) {
-        const int upfront = min(n_my, p.pre);
+        const int upfront = min(n_my, head.pre);
         // (paged cache: Q does not depend on the block table, so it goes first and the wait for
         // the table's first entries overlaps its issue)
         // (rotating variant: Q and the tables first as well: they are rotated in LDS while the first
@@ -982,17 +997,16 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
         //      rows' (m, l), waits for the L2 of this XCD to acknowledge the stores and takes a ticket
         //      of its own; one wave of its group merges the XS partials of these slices in index order (so
         //      results do not depend on arrival order).
-        //      Which one: wave w of range w % XS, so that every compute unit of the group reads a share of the partial
+        //      Which one, beyond `kExchangeAlone`: wave w of range w % XS, so that every compute unit of the group reads a share of the partial
         //      results.  Left to the wave that arrives last, one compute unit, whose waves end together, reads all of
         //      them, at about 100 GB/s: XS * 18 KB of 64 rows, twice that of 128 (40/40 heads, 81 rows on 2048
-        //      keys 17.5 -> 17.1 us, with 128 rows and 6 ranges 18.5 -> 16.9; 64/8, 57 rows on 4096 with 128 rows and 8
-        //      ranges 19.4 -> 17.7; 4/4, 121 rows on 4096 13.8 -> 12.5).  Smaller shares (halves of a slice, twice the
+        //      keys 17.6 -> 17.2 us, with 128 rows and 6 ranges 18.5 -> 16.9; 64/8, 57 rows on 4096 with 128 rows and 8
+        //      ranges 19.4 -> 17.7; 8/8, 57 rows on 4096 13.7 -> 12.0).  Smaller shares (halves of a slice, twice the
         //      waves that wait) gain from 16 ranges on and cost 0.6 us with four.
         //      It looks at its ticket until the others have arrived, `looks` times at most: the ranges of a step alone
         //      run side by side, but nothing promises it.  Then it sets a bit in the ticket and leaves, and
         //      the last one to arrive, who finds it set, merges.
         if (wave_active) {
-            const bool adds_up = wave - __builtin_amdgcn_readfirstlane(div_small(wave, p.inv_XS)) * p.XS == xs;
             unsigned char* const group_base = reinterpret_cast<unsigned char*>(p.partials) +
                                               (size_t)unit * p.XS * C::PART_WG_BYTES + (size_t)wave * C::PART_WAVE_BYTES;
             {
@@ -1010,39 +1024,47 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                     }
                 *reinterpret_cast<f32x2*>(dst + C::PART_ACC_BYTES + lane * 8) = f32x2{m_run, l_run};
             }
+            // (in registers before the ticket is taken: left to the compiler, they are loaded and computed when it is back)
+            const bool adds_up = wave - __builtin_amdgcn_readfirstlane(div_small(wave, p.inv_XS)) * p.XS == xs;
+            unsigned forced = p.looks & kForceRecompute, looks = p.looks & (kForceRecompute - 1u);
+            unsigned needed = looks && !adds_up ? kTicketLeft : 0u;   // of a ticket whose last arrival merges
+            looks = adds_up ? looks : 0u;
+            asm volatile("" : "+s"(forced), "+s"(looks), "+s"(needed));
             __builtin_amdgcn_s_waitcnt(0);
             LA_STAMP(5);
-            unsigned role = 0;  // 0 another wave merges, 1 this one, 2 this one, but the group is spread over several XCDs
-            if (lane == 0) {
-                // One atomic carries the arrival count and, to tell whether every member of the group
-                // ran on the same XCD (and so shares one L2), the sum and the sum of squares of the
-                // members' XCD ids: XS * sum(x^2) == (sum x)^2 holds iff all ids are equal.
-                const unsigned x = xcc_id();
-                const unsigned mine = 1u | (x << 8) | ((x * x) << 18);
-                unsigned total = atomicAdd(my_ticket, mine) + mine;
-                auto all_in = [&] { return (total & kTicketArrivals) == (unsigned)p.XS; };
-                bool merge = all_in();
-                if (p.looks) {
-                    if (merge) {
-                        merge = adds_up || (total & kTicketLeft);
-                    } else if (adds_up) {
-                        for (int i = p.looks; i > 0 && !all_in(); --i) total = __hip_atomic_load(my_ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        if (!all_in()) total = atomicAdd(my_ticket, kTicketLeft);
-                        merge = all_in();
-                    }
-                }
-                if (merge) {
-                    const unsigned sum = (total >> 8) & 0x3ffu, sq = total >> 18;
-                    *my_ticket = 0u;  // nobody looks at it any more; clean for the next call
-                    role = (sq * (unsigned)p.XS == sum * sum && !p.force_recompute) ? 1u : 2u;
-                }
+            // One atomic carries the arrival count and, to tell whether every member of the group
+            // ran on the same XCD (and so shares one L2), the sum and the sum of squares of the
+            // members' XCD ids: XS * sum(x^2) == (sum x)^2 holds iff all ids are equal.
+            unsigned total = 0u;
+            auto arrive = [&](unsigned v) {
+                if (lane == 0) total = atomicAdd(my_ticket, v) + v;
+                total = __builtin_amdgcn_readfirstlane(total);
+            };
+            auto all_in = [&] { return (total & kTicketArrivals) == (unsigned)p.XS; };
+            const unsigned x = xcc_id();
+            arrive(1u | (x << 8) | ((x * x) << 18));
+            bool merge = all_in() && (total & needed) == needed;
+            if (__builtin_expect(!all_in() && looks, 0)) {
+                for (; looks > 0 && !all_in(); --looks)
+                    total = __builtin_amdgcn_readfirstlane(__hip_atomic_load(my_ticket, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+                if (__builtin_expect(!all_in(), 0)) arrive(kTicketLeft);
+                merge = all_in();
             }
-            role = __builtin_amdgcn_readfirstlane(role);
+            // 0 another wave merges, 1 this one, 2 this one, but the group is spread over several XCDs
+            unsigned role = 0;
+            if (merge) {
+                const unsigned sum = (total >> 8) & 0x3ffu, sq = total >> 18;
+                if (lane == 0) *my_ticket = 0u;  // nobody looks at it any more; clean for the next call
+                role = (sq * (unsigned)p.XS == sum * sum && !forced) ? 1u : 2u;
+            }
             LA_STAMP(6);
             if (role == 1) {
                 // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2 (in fp32 one slice at a
-                //      time, for the registers; two splits a trip took 0.6 to 1.2 us longer with 11 ranges)
-                constexpr int MB = 4, US = PB == 2 ? C::SPW : 1;
+                //      time, for the registers; two splits a trip took 0.6 to 1.2 us longer with 11 ranges), the last one
+                //      or two in a trip of their own: places past the last range read it again, and a compute unit takes
+                //      in 64 bytes a clock (32/32 heads, pages, 121 rows on 777 keys, two ranges: 10.9 -> 10.6 us).
+                constexpr int US = PB == 2 ? C::SPW : 1;
+#pragma unroll
                 for (int u0 = 0; u0 < C::SPW; u0 += US) {
                     float m_acc = kNegInf, l_acc = 0.0f;
                     float acc[US][16];
@@ -1050,7 +1072,8 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                     for (int u = 0; u < US; ++u)
 #pragma unroll
                         for (int i = 0; i < 16; ++i) acc[u][i] = 0.0f;
-                    for (int s0 = 0; s0 < p.XS; s0 += MB) {
+                    auto trip = [&](auto splits, int s0) {
+                        constexpr int MB = decltype(splits)::value;
                         f32x2 ml[MB];
                         Part v[MB][US][PB];
 #pragma unroll
@@ -1092,7 +1115,10 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
                                     for (int e = 0; e < PE; ++e)
                                         acc[u][i * PE + e] = __builtin_fmaf((float)v[w][u][i][e], aw, acc[u][i * PE + e]);
                         }
-                    }
+                    };
+                    int s0 = 0;
+                    for (; __builtin_expect(p.XS - s0 > 2, 0); s0 += 4) trip(std::integral_constant<int, 4>{}, s0);
+                    if (s0 < p.XS) trip(std::integral_constant<int, 2>{}, s0);
                     const float inv = out_scale / l_acc;
 #pragma unroll
                     for (int u = 0; u < US; ++u) {
@@ -1112,7 +1138,7 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
         }
         __syncthreads();
         store_mask = (unsigned)__builtin_amdgcn_readfirstlane((int)*s_recompute);
-        if (store_mask == 0u) return;
+        if (__builtin_expect(store_mask == 0u, 1)) return;
         __syncthreads();  // everyone has read the mask before the next pass clears it
         c_begin = 0;
         c_end = p.n_chunks;
@@ -1130,8 +1156,9 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const i
 template <int D, int RT, int KS, int KC, int NSTAGE, bool PAGED = false, bool ROWSET = false, int KVB = 2, bool ROPE = false, int PB = 2>
 __global__ __launch_bounds__(RT* KS * 64) void step_attention_kernel(const AttnParams)
 {
-    const AttnParams& p = warmed_arguments<AttnParams>();
-    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE, PB>(p, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3));
+    AttnHead head;
+    const AttnParams& p = warmed_arguments<AttnParams>(head);
+    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED, ROWSET, KVB, ROPE, PB>(p, head, (int)(blockIdx.x & 7), (int)(blockIdx.x >> 3));
 }
 
 #include "la_attention_wide.h"
@@ -1158,8 +1185,9 @@ __global__ __launch_bounds__(RT* KS * 64) void step_attention_batch_kernel(const
 #pragma unroll
     for (int k = 1; k < kMaxBatch; ++k)
         if (k < sl.n && slot >= sl.slot0[k]) i = k;
-    const AttnParams& p = warmed_arguments<AttnParams>((unsigned)i * (unsigned)sizeof(AttnParams));
-    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED>(p, (int)(blockIdx.x & 7), slot - sl.slot0[i]);
+    AttnHead head;
+    const AttnParams& p = warmed_arguments<AttnParams>(head, (unsigned)i * (unsigned)sizeof(AttnParams));
+    step_attention_body<D, RT, KS, KC, NSTAGE, PAGED>(p, head, (int)(blockIdx.x & 7), slot - sl.slot0[i]);
 }
 
 // (two waves per SIMD are all there will be: the compiler need not save registers for more)
@@ -1495,8 +1523,8 @@ la_status build_params(AttnParams& prm, const Overrides& ov, const Plan& pl, con
     // amortises that (11.8 against 12.1 us in alternating runs; no difference from 11 chunks on).
     if (pl.PRE == 0 && cpi == 2 && prm.chunks_lo <= 6) prm.pre = cpi;
     // testing hook: exercise the path taken when a split group is not on one XCD
-    prm.force_recompute = ov.force_recompute ? 1 : 0;
-    prm.looks = 0;  // (workgroups of a batch that take turns on the compute units do not wait for each other)
+    // (no looks: workgroups of a batch that take turns on the compute units do not wait for each other)
+    prm.looks = ov.force_recompute ? kForceRecompute : 0;
     return LA_OK;
 }
 
@@ -1560,7 +1588,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
     if (st != LA_OK) return st;
     const long long total = prm.total_wg;
     if (pl.XS > 1) prm.wg_per_xcd = step_units_per_xcd(kv_heads * pl.n_row_blocks) * pl.XS;
-    if (pl.XS > 1) prm.looks = (unsigned short)(ov.exchange_looks >= 0 ? ov.exchange_looks : kExchangeLooks);
+    const int looks = pl.XS * (long long)pl.partial_bytes_per_wg > kExchangeAlone ? kExchangeLooks : 0;
+    if (pl.XS > 1) prm.looks |= (unsigned)(ov.exchange_looks >= 0 ? ov.exchange_looks : looks);
     const bool quantised = k_scale != nullptr;
     if (quantised) {
         // 8-bit keys and values: rows of head_dim bytes (cache_rows counts rows, so it stands)
