@@ -197,15 +197,19 @@ __device__ __forceinline__ void wait_young(int y)
 // otherwise make every later LDS read wait for ALL of them, including the chunks being
 // prefetched.  Completion is tracked by hand: s_waitcnt vmcnt(n) + workgroup barrier.
 // The address is a wave-uniform 64-bit base in scalar registers plus a 32-bit per-lane byte
-// offset: no 64-bit vector arithmetic per load.
+// offset: no 64-bit vector arithmetic per load.  The load uses a copy of the base: a scalar register that the vector
+// unit wrote (a readfirstlane, or a readlane that restores a spilled one) may be read by a vector memory instruction five
+// wait states later at the earliest, which the compiler does not look after in inline assembly; scalar instructions
+// wait by themselves, and one has to stand between the write of M0 and the load anyway.
 __device__ __forceinline__ void dma16_base(const void* base, unsigned lane_off, unsigned lds_base)
 {
     // the base is the same in every lane; say so, or the operand may be given vector registers
     const unsigned long long b = reinterpret_cast<unsigned long long>(base);
     const unsigned long long lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
     const unsigned long long hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :
+    unsigned long long at;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+                 : "=&s"(at)
                  : "v"(lane_off), "s"((hi << 32) | lo), "s"(lds_base)
                  : "memory");
 }
@@ -217,8 +221,9 @@ __device__ __forceinline__ void dma4_base(const void* base, unsigned lane_off, u
     const unsigned long long b = reinterpret_cast<unsigned long long>(base);
     const unsigned long long lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)b);
     const unsigned long long hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(b >> 32));
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
-                 :
+    unsigned long long at;
+    asm volatile("s_mov_b32 m0, %3\n\ts_mov_b64 %0, %2\n\tglobal_load_lds_dword %1, %0"
+                 : "=&s"(at)
                  : "v"(lane_off), "s"((hi << 32) | lo), "s"(lds_base)
                  : "memory");
 }

@@ -135,7 +135,8 @@ __device__ __forceinline__ void wide_attention_body(const AttnParams& p, const i
     const size_t page_bytes = PAGED ? (size_t)p.page_bytes : 0;
     auto load_entries = [&](int first) {
         pg_base = first;
-        asm volatile("global_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)"
+        // (five wait states, in case the pointer was written by the vector unit just now: see `dma16_base`)
+        asm volatile("s_nop 4\n\tglobal_load_dword %0, %1, %2\n\ts_waitcnt vmcnt(0)"
                      : "=&v"(pg_ents)
                      : "v"((unsigned)min(first + lane, p.table_last) * 4u), "s"(p.block_table)
                      : "memory");
