@@ -1058,6 +1058,34 @@ __device__ __forceinline__ void step_attention_body(const AttnParams& p, const A
                 role = (sq * (unsigned)p.XS == sum * sum && !forced) ? 1u : 2u;
             }
             LA_STAMP(6);
+            if constexpr (PB == 4 && C::SPW > 1) {
+                if (role == 1 && p.XS == 2) {
+                    // ---- two ranges in fp32: all slices in one trip, which would be one each below (8-bit cache, 20/20
+                    //      heads, 29 rows on 194 keys 7.85 -> 7.5 us)
+                    f32x2 ml[2];
+                    Part v[2][C::SPW][PB];
+#pragma unroll
+                    for (int w = 0; w < 2; ++w) {
+                        const unsigned char* src = group_base + w * C::PART_WG_BYTES;
+                        ml[w] = *reinterpret_cast<const f32x2*>(src + C::PART_ACC_BYTES + lane * 8);
+#pragma unroll
+                        for (int u = 0; u < C::SPW; ++u)
+#pragma unroll
+                            for (int i = 0; i < PB; ++i) v[w][u][i] = *reinterpret_cast<const Part*>(src + ((u * PB + i) * 64 + lane) * 16);
+                    }
+                    const float m = fmaxf(ml[0][0], ml[1][0]), m_use = m == kNegInf ? 0.0f : m;
+                    const float a0 = fast_exp2((ml[0][0] - m_use) * sl2), a1 = fast_exp2((ml[1][0] - m_use) * sl2);
+                    const float inv = out_scale / __builtin_fmaf(ml[1][1], a1, ml[0][1] * a0);
+#pragma unroll
+                    for (int u = 0; u < C::SPW; ++u) {
+                        f32x16 vals;
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) vals[i] = __builtin_fmaf(v[1][u][i / PE][i % PE], a1, v[0][u][i / PE][i % PE] * a0);
+                        store_slice<C>(p, row_base, kvh, db0 + u, l32, hi, vals, inv);
+                    }
+                    role = 0;
+                }
+            }
             if (role == 1) {
                 // ---- all partials sit in the L2 this XCD shares: four splits per trip to the L2 (in fp32 one slice at a
                 //      time, for the registers; two splits a trip took 0.6 to 1.2 us longer with 11 ranges), the last one

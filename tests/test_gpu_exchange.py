@@ -11,7 +11,8 @@ pytestmark = pytest.mark.gpu
 # P, W, N, G, heads, KV heads, head_dim and the decomposition (None: the library's): 2 to 8 and 32 ranges, more and fewer
 # than the eight, four or two waves of a workgroup; one and two slices a wave; a row block of one tile; fp32 results
 CASES = [((1024, 15, 5, 15, 32, 32, 128), None), ((2048, 10, 5, 10, 40, 40, 128), "2,4,3,4,64"), ((700, 9, 4, 5, 8, 8, 128), "2,4,2,4,64"),
-         ((700, 9, 4, 5, 8, 8, 128), "2,4,5,4,64"), ((700, 9, 4, 5, 8, 8, 128), "1,2,6,4,64"), ((900, 9, 4, 5, 8, 8, 64), "2,2,7,4,64"),
+         ((700, 9, 4, 5, 8, 8, 128), "2,4,5,4,64"), ((700, 9, 4, 5, 8, 8, 128), "1,2,6,4,64"), ((194, 7, 3, 7, 20, 20, 128), None), ((2100, 30, 5, 34, 32, 32, 128), None),
+         ((900, 9, 4, 5, 8, 8, 64), "2,2,7,4,64"),
          ((2100, 10, 5, 10, 40, 40, 128), "4,2,6,4,64"), ((4096, 7, 5, 7, 64, 8, 128), "4,2,8,4,64"), ((4096, 15, 5, 15, 4, 4, 128), "2,4,32,4,64"),
          ((4096, 15, 5, 15, 4, 4, 128), None), ((4096, 3, 4, 2, 4, 4, 128), None), ((4096, 15, 5, 15, 4, 4, 64), None), ((3000, 3, 4, 2, 8, 8, 64), None)]
 
