@@ -1615,6 +1615,8 @@ la_status launch_step_attention(const void* q, const void* k_cache, const void* 
                                       T, step_k, step_v, P, W, N, G, heads, kv_heads, head_dim, out);
     if (st != LA_OK) return st;
     const long long total = prm.total_wg;
+    if (pl.PRE == 0 && pl.KS <= pl.KC / 32)
+        prm.pre = std::min(step_chunks_ahead(pl.RT * 32, head_dim, pl.n_row_blocks, (pl.n_chunks + pl.XS - 1) / pl.XS), pl.NS);
     if (pl.XS > 1) prm.wg_per_xcd = step_units_per_xcd(kv_heads * pl.n_row_blocks) * pl.XS;
     const int looks = pl.XS * (long long)pl.partial_bytes_per_wg > kExchangeAlone ? kExchangeLooks : 0;
     if (pl.XS > 1) prm.looks |= (unsigned)(ov.exchange_looks >= 0 ? ov.exchange_looks : looks);

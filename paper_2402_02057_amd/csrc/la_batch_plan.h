@@ -458,28 +458,32 @@ inline StepRanges step_ranges(int units, int chunks, int rows, int head_dim, boo
 
 namespace batch_plan {
 
-// When the staged kernel ends a step, in 10 ns, from 150 drawn steps of 400 to 16384 keys, 9 to 361 rows, 32/32, 40/40,
-// 64/8 and 32/8 heads: a round of workgroups takes 4.4 us and 0.70 a chunk with 64 rows, 5.3 and 1.15 with 128 (8-bit
-// cache: 0.62 and 1.18), a range to exchange 0.7, and 1.1 where few KV heads make the stream from HBM short.
+// When the staged kernel ends a step, in 10 ns, from 200 drawn steps of 300 to 16384 keys, 9 to 361 rows, 4 to 64 heads in groups
+// of 1 to 8, measured in both forms: a round of workgroups takes 3.9 us and 0.78 a chunk with 64 rows, 4.9 and 1.13 with 128
+// (8-bit cache: 0.66 and 1.20), or what the chunks that its workgroups do not share take from HBM if that is more (7.2 and 5.6
+// ns a chunk and workgroup; 8-bit cache half), and a range to exchange 0.13 and 0.24.
 inline long long staged_step_end(bool rows128, int chunks, int tiles, int kv_heads, bool codes)
 {
-    const int units = kv_heads * (rows128 ? (tiles + 3) / 4 : (tiles + 1) / 2), x = step_cuts(units, chunks);
-    const long long rounds = ((long long)units * x + 255) / 256, range = (chunks + x - 1) / x;
-    return 150 + rounds * (rows128 ? 530 + (codes ? 118 : 115) * range : 440 + (codes ? 62 : 70) * range) + (kv_heads < 32 ? 110 : 70) * x;
+    const int blocks = rows128 ? (tiles + 3) / 4 : (tiles + 1) / 2, units = kv_heads * blocks, x = step_cuts(units, chunks);
+    const long long wgs = (long long)units * x, rounds = (wgs + 255) / 256, range = (chunks + x - 1) / x;
+    const long long apart = (wgs < 256 ? wgs : 256) / blocks, stream = range * apart * (rows128 ? 56 : 72) / (codes ? 200 : 100);
+    const long long walk = range * (rows128 ? (codes ? 120 : 113) : codes ? 66 : 78);
+    return 150 + rounds * ((rows128 ? 490 : 390) + (walk > stream ? walk : stream)) + (rows128 ? 24 : 13) * x;
 }
 
 }  // namespace batch_plan
 
-// Whether a step alone takes 128-row workgroups of the staged kernel (head_dim 128) instead of 64-row ones: where its times
-// end it half a microsecond sooner.  80 drawn steps (bf16 packed and paged, 8-bit) on that side of the line take 0.63 to
-// 1.02 of the time they take with 64 rows, 0.86 in the geometric mean: 32/32 heads, 161 rows on 6117 keys 47.9 -> 40.2 us,
-// 40/40, 241 rows on 13347 keys 163 -> 103, 64/8, 133 rows on 3449 keys 43.3 -> 31.9.  Errors against 64 bits are 3 to 10 %
-// smaller.
-// A step with one range has no partial results: 128 rows then have to be 2 us ahead, which is what
-// the noalloc entry point takes to clear its tickets.  many_rows: a step that has always had 128 rows, which round fewer
+// Whether a step alone takes 128-row workgroups of the staged kernel (head_dim 128) instead of 64-row ones, which pull twice the
+// chunks into LDS: where its times end it 0.75 us sooner.  Of 200 drawn steps (bf16 packed and paged, 8-bit) 40 are on that side of
+// the line and take 0.88 of the time they take with 64 rows in the geometric mean, 1.01 at worst; the better form for each would
+// be 0.1 % ahead of the rule over all 200.  32/32 heads, 105 rows on 4829 keys 26.8 -> 24.2 us, 161 rows on 1687 19.1 -> 17.0, 64/8,
+// 101 rows on 2535 21.3 -> 19.0, 40/40, 241 rows on 2845 43.2 -> 28.5.  (Near the line, left with 64 rows: 64/8, 57 rows on 4096
+// keys 18.2 and 17.7, 40/40, 81 rows on 2048 17.1 and 16.9.)
+// Errors against 64 bits are 3 to 10 % smaller.
+// A step with one range has no partial results: 128 rows then have to be 4.4 us ahead: fp32
+// partial results take 1 to 4, and the noalloc entry point 2 to clear its tickets.  many_rows: a step that has always had 128 rows, which round fewer
 // sums between key-split waves, goes back to 64 only with fp32 results and where 128 rows would be cut 16 times or more, to 20
-// chunks at most (8/1 heads, 121 rows on 4096 keys 21.2 -> 13.2 us, on 32768 48.3 -> 40.4; 16/2 on 8192 28.0 -> 23.1, on 16384
-// 37.2 -> 33.9; 3.05e-3 -> 2.70e-3.  Beyond: 16/2 on 32768, 33 chunks: 55.2 -> 55.6; cut 8 times, 32/4: 19.8 -> 18.9, 50.9 -> 53.7).  codes: the 8-bit cache.
+// chunks at most (8/1 heads, 121 rows on 4096 keys 15.6 -> 11.7 us, on 16384 24.9 -> 21.5; 3.05e-3 -> 2.70e-3).  codes: the 8-bit cache.
 inline bool step_rows128(int chunks, int tiles, int kv_heads, bool many_rows, bool codes)
 {
     using namespace batch_plan;
@@ -488,8 +492,24 @@ inline bool step_rows128(int chunks, int tiles, int kv_heads, bool many_rows, bo
         return x < 16 || chunks > 20 * x;
     }
     const bool cut64 = step_cuts(kv_heads * ((tiles + 1) / 2), chunks) > 1, cut128 = step_cuts(kv_heads * ((tiles + 3) / 4), chunks) > 1;
-    return staged_step_end(true, chunks, tiles, kv_heads, codes) + (cut128 && !cut64 ? 250 : 50) <
+    return staged_step_end(true, chunks, tiles, kv_heads, codes) + (cut128 && !cut64 ? 440 : 75) <
            staged_step_end(false, chunks, tiles, kv_heads, codes);
+}
+
+// Chunks that a step alone requests before its loop, where an iteration takes one (rows: of a workgroup; blocks: row blocks
+// of a KV head; range: chunks of the longest range).  Each request up front holds the first chunk back: 32/32 heads, 121 rows on
+// 1024, 3 chunks 12.4 us with one, 12.7 with two.  From four chunks on two are ahead: 40/40, 81 rows on 2048, 6 chunks 17.7 and
+// 16.9, 32/4, 151 rows on 3917, 11 chunks 22.7 and 21.6, 40/40, 241 rows on 2845, 17 chunks 32.5 and 28.3.  A full ring (four)
+// is behind (29.8 for the last; 32/32, 121 rows on 16000, 32 chunks 55.5 and 57.4) until row blocks share 32 chunks or more
+// (64/64, 181 rows on 6064, 49 chunks 69.8 and 68.2; 64/8, 121 on 16384, 65 chunks 82.9 and 81.9).  One tile: two (32/32, 25
+// rows on 3000: 18.4, 15.9, 16.4, 17.1 with one to four).  64 dimensions, whose chunks are half as large, gain from a third
+// from 16 on (32/8, 121 rows on 8000: 28.7 and 28.0).
+inline int step_chunks_ahead(int rows, int head_dim, int blocks, int range)
+{
+    if (head_dim == 64) return range > 16 ? 3 : 2;
+    if (rows != 128) return 2;
+    if (blocks > 1 && range >= 32) return 4;
+    return range < 4 ? 1 : 2;
 }
 
 }  // namespace la

@@ -10,6 +10,7 @@ from step_cases import codes_inputs, error, every_tile_differs, inputs, label, n
 SHIM = """
 extern "C" int rows128(int chunks, int tiles, int kv_heads, int many, int codes) { return la::step_rows128(chunks, tiles, kv_heads, many, codes); }
 extern "C" int cuts(int units, int chunks) { return la::step_cuts(units, chunks); }
+extern "C" int ahead(int rows, int head_dim, int blocks, int range) { return la::step_chunks_ahead(rows, head_dim, blocks, range); }
 extern "C" int most(int groups) { return groups ? la::kMaxStepGroups : la::kMaxStepWorkgroups; }
 """
 
@@ -37,6 +38,12 @@ def test_the_rule(lib):
         for chunks in range(1, 300, 13):
             x = lib.cuts(units, chunks)
             assert 1 <= x <= max(1, chunks // 2) and x <= 64 and (x == 1 or (units * x <= lib.most(0) == 256 and units <= lib.most(1)))
+
+
+def test_chunks_requested_ahead(lib):
+    for rows, d, blocks, chunks, want in ((128, 128, 1, 3, 1), (128, 128, 1, 4, 2), (128, 128, 1, 200, 2), (128, 128, 2, 3, 1), (128, 128, 2, 4, 2),
+                                          (128, 128, 2, 31, 2), (128, 128, 2, 32, 4), (32, 128, 1, 1, 2), (32, 128, 1, 200, 2), (64, 64, 3, 16, 2), (64, 64, 3, 17, 3)):
+        assert lib.ahead(rows, d, blocks, chunks) == want, (rows, d, blocks, chunks)
 
 
 SHAPES = [(2100, 30, 5, 34, 32, 32, 128), # 160 units of 64 rows, one range each; 96 of 128 in two: fp32 partial results
