@@ -426,10 +426,11 @@ inline bool step_cuts_even(int units, int chunks)
     return x > 1 && (units * x + kXcds - 1) / kXcds % x == 0;
 }
 
-// In how many ranges, and whether they exchange fp32.  One workgroup per compute unit is not always best: the last one of a
-// group reads all its ranges' results, 0.16 to 0.20 us a range in bf16 and 0.18 to 0.31 in fp32, where a chunk of a range
+// In how many ranges, and whether they exchange fp32.  One workgroup per compute unit is not always best: a range to add up
+// costs 0.16 to 0.20 us in bf16 and 0.18 to 0.31 in fp32 where the last workgroup of a group reads all of them, and a chunk of a range
 // takes 0.55 to 0.80 (64 rows of 128 dimensions in pairs of chunks, one tile, 64 dimensions; 13 to 361 rows on 1024 to
-// 16384 keys).  Fewer ranges in bf16 would be further from 64 bits (4/4 heads, 121 rows on 4096 keys: 2.98e-3 with 32 ranges,
+// 16384 keys).  Since waves of all workgroups read them the choice is within 1 to 2 % of the best one (72 steps measured with every
+// number of ranges; the best weights for these are within 0.8 to 1.3 %), so the line stays.  Fewer ranges in bf16 would be further from 64 bits (4/4 heads, 121 rows on 4096 keys: 2.98e-3 with 32 ranges,
 // 3.11e-3 with 12), in fp32 they are nearer (2.64e-3): so fewer are taken where the results are fp32 anyway or that is half a
 // microsecond ahead in fp32 too.  Where 32 ranges fit (8 row blocks at most) that is at 65 to 72 chunks and at 53, 57, 59, 61 and 63
 // (an odd number leaves the most ranges three chunks, walked as four) with 64 rows of 128 dimensions, at 65 to 70, 59 and 63 with one
